@@ -131,6 +131,69 @@ VL_HD Fq fq_neg(const Fq& a) { return fq_is_zero(a) ? a : fq_sub(fq_zero(), a); 
 VL_HD Fq fq_dbl(const Fq& a) { return fq_add(a, a); }
 
 #if defined(__HIP_DEVICE_COMPILE__)
+// multiply-adds into a 96-bit column sum: v_mad_u64_u32 into a 64-bit pair,
+// its carry-out into a top word; fr_macn / fr_macns carry one step of N
+// independent products
+__device__ __forceinline__ void fr_mac96(uint64_t& acc, uint32_t& top, uint32_t x, uint32_t y) {
+  uint64_t c, dummy;
+  asm("v_mad_u64_u32 %0, %1, %2, %3, %0" : "+v"(acc), "=s"(c) : "v"(x), "v"(y));
+  asm("v_addc_co_u32 %0, %1, %0, 0, %2" : "+v"(top), "=s"(dummy) : "s"(c));
+}
+
+__device__ __forceinline__ void fr_mac96s(uint64_t& acc, uint32_t& top, uint32_t x, uint32_t ys) {
+  uint64_t c, dummy;
+  asm("v_mad_u64_u32 %0, %1, %2, %3, %0" : "+v"(acc), "=s"(c) : "v"(x), "s"(ys));
+  asm("v_addc_co_u32 %0, %1, %0, 0, %2" : "+v"(top), "=s"(dummy) : "s"(c));
+}
+
+template <int N>
+__device__ __forceinline__ void fr_macn(uint64_t (&acc)[N], uint32_t (&top)[N], const uint32_t (&x)[N], const uint32_t (&y)[N]) {
+  if constexpr (N == 2) {
+    uint64_t c0, c1;
+    asm("v_mad_u64_u32 %0, %4, %6, %7, %0\n\t"
+        "v_mad_u64_u32 %1, %5, %8, %9, %1\n\t"
+        "v_addc_co_u32 %2, %4, %2, 0, %4\n\t"
+        "v_addc_co_u32 %3, %5, %3, 0, %5"
+        : "+v"(acc[0]), "+v"(acc[1]), "+v"(top[0]), "+v"(top[1]), "=&s"(c0), "=&s"(c1)
+        : "v"(x[0]), "v"(y[0]), "v"(x[1]), "v"(y[1]));
+  } else {
+    uint64_t c0, c1, c2;
+    asm("v_mad_u64_u32 %0, %6, %9, %10, %0\n\t"
+        "v_mad_u64_u32 %1, %7, %11, %12, %1\n\t"
+        "v_mad_u64_u32 %2, %8, %13, %14, %2\n\t"
+        "v_addc_co_u32 %3, %6, %3, 0, %6\n\t"
+        "v_addc_co_u32 %4, %7, %4, 0, %7\n\t"
+        "v_addc_co_u32 %5, %8, %5, 0, %8"
+        : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(top[0]), "+v"(top[1]), "+v"(top[2]),
+          "=&s"(c0), "=&s"(c1), "=&s"(c2)
+        : "v"(x[0]), "v"(y[0]), "v"(x[1]), "v"(y[1]), "v"(x[2]), "v"(y[2]));
+  }
+}
+
+template <int N>
+__device__ __forceinline__ void fr_macns(uint64_t (&acc)[N], uint32_t (&top)[N], const uint32_t (&x)[N], uint32_t ys) {
+  if constexpr (N == 2) {
+    uint64_t c0, c1;
+    asm("v_mad_u64_u32 %0, %4, %6, %8, %0\n\t"
+        "v_mad_u64_u32 %1, %5, %7, %8, %1\n\t"
+        "v_addc_co_u32 %2, %4, %2, 0, %4\n\t"
+        "v_addc_co_u32 %3, %5, %3, 0, %5"
+        : "+v"(acc[0]), "+v"(acc[1]), "+v"(top[0]), "+v"(top[1]), "=&s"(c0), "=&s"(c1)
+        : "v"(x[0]), "v"(x[1]), "s"(ys));
+  } else {
+    uint64_t c0, c1, c2;
+    asm("v_mad_u64_u32 %0, %6, %9, %12, %0\n\t"
+        "v_mad_u64_u32 %1, %7, %10, %12, %1\n\t"
+        "v_mad_u64_u32 %2, %8, %11, %12, %2\n\t"
+        "v_addc_co_u32 %3, %6, %3, 0, %6\n\t"
+        "v_addc_co_u32 %4, %7, %4, 0, %7\n\t"
+        "v_addc_co_u32 %5, %8, %5, 0, %8"
+        : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(top[0]), "+v"(top[1]), "+v"(top[2]),
+          "=&s"(c0), "=&s"(c1), "=&s"(c2)
+        : "v"(x[0]), "v"(x[1]), "v"(x[2]), "s"(ys));
+  }
+}
+
 // Montgomery product a b R^-1 mod q by product scanning (see fr_mul): column
 // k collects a_i b_{k-i} and m_i q_{k-i}; for k < 12 the digit m_k =
 // t0 (-q^-1) mod 2^32 is chosen so that m_k q_0 clears the column's low word,
