@@ -29,6 +29,7 @@
 #include <type_traits>
 
 #include "fr.hpp"
+#include "modinv.hpp"
 #include "sha256.hpp"
 
 namespace vl {
@@ -131,176 +132,173 @@ VL_HD Fq fq_neg(const Fq& a) { return fq_is_zero(a) ? a : fq_sub(fq_zero(), a); 
 VL_HD Fq fq_dbl(const Fq& a) { return fq_add(a, a); }
 
 #if defined(__HIP_DEVICE_COMPILE__)
-// multiply-adds into a 96-bit column sum: v_mad_u64_u32 into a 64-bit pair,
-// its carry-out into a top word; fr_macn / fr_macns carry one step of N
-// independent products
-__device__ __forceinline__ void fr_mac96(uint64_t& acc, uint32_t& top, uint32_t x, uint32_t y) {
-  uint64_t c, dummy;
-  asm("v_mad_u64_u32 %0, %1, %2, %3, %0" : "+v"(acc), "=s"(c) : "v"(x), "v"(y));
-  asm("v_addc_co_u32 %0, %1, %0, 0, %2" : "+v"(top), "=s"(dummy) : "s"(c));
-}
+// ---- lazily reduced elements (device) --------------------------------------
+// An Fl is 14 limbs of 28 bits with value sum l_i 2^(28 i), not unique mod q:
+// sums and differences work limb by limb with no carries (a difference adds a
+// multiple of q whose every limb exceeds the subtrahend's), and a product's
+// columns are 64-bit sums of up to 14 limb products and 14 reduction terms,
+// one v_mad_u64_u32 each.  With limbs below A 2^28 and B 2^28 a column stays
+// below (14 A B + 14) 2^56 plus a carry below 2^36, so A B <= 16 is safe; two
+// products may share one reduction while the sum of their A B stays <= 16.
+// The reduction divides by R' = 2^392.  Values below a q and b q give a result
+// below (a b 2^-11 + 1) q, so with a b <= 2^11 results are below 2q; their
+// limbs are below 2^28.
+constexpr uint32_t kM28 = 0x0fffffffu;
+constexpr uint32_t kQInv28 = kQInv32 & kM28;             // -q^-1 mod 2^28
+struct Fl {
+  uint32_t l[14];
+};
 
-__device__ __forceinline__ void fr_mac96s(uint64_t& acc, uint32_t& top, uint32_t x, uint32_t ys) {
-  uint64_t c, dummy;
-  asm("v_mad_u64_u32 %0, %1, %2, %3, %0" : "+v"(acc), "=s"(c) : "v"(x), "s"(ys));
-  asm("v_addc_co_u32 %0, %1, %0, 0, %2" : "+v"(top), "=s"(dummy) : "s"(c));
+constexpr __host__ __device__ uint32_t q_limb28(int i) {
+  constexpr uint32_t Q[14] = {0xfffaaabu, 0xfefffffu, 0x3ffffb9u, 0xfffeb15u, 0x6241eabu, 0xa0f6b0fu, 0xf6730d2u,
+                              0xf38512bu, 0x4774b84u, 0x4bacd76u, 0xba7b643u, 0xe69a4b1u, 0x1ea397fu, 0x001a011u};
+  return Q[i];
 }
-
-template <int N>
-__device__ __forceinline__ void fr_macn(uint64_t (&acc)[N], uint32_t (&top)[N], const uint32_t (&x)[N], const uint32_t (&y)[N]) {
-  if constexpr (N == 2) {
-    uint64_t c0, c1;
-    asm("v_mad_u64_u32 %0, %4, %6, %7, %0\n\t"
-        "v_mad_u64_u32 %1, %5, %8, %9, %1\n\t"
-        "v_addc_co_u32 %2, %4, %2, 0, %4\n\t"
-        "v_addc_co_u32 %3, %5, %3, 0, %5"
-        : "+v"(acc[0]), "+v"(acc[1]), "+v"(top[0]), "+v"(top[1]), "=&s"(c0), "=&s"(c1)
-        : "v"(x[0]), "v"(y[0]), "v"(x[1]), "v"(y[1]));
-  } else {
-    uint64_t c0, c1, c2;
-    asm("v_mad_u64_u32 %0, %6, %9, %10, %0\n\t"
-        "v_mad_u64_u32 %1, %7, %11, %12, %1\n\t"
-        "v_mad_u64_u32 %2, %8, %13, %14, %2\n\t"
-        "v_addc_co_u32 %3, %6, %3, 0, %6\n\t"
-        "v_addc_co_u32 %4, %7, %4, 0, %7\n\t"
-        "v_addc_co_u32 %5, %8, %5, 0, %8"
-        : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(top[0]), "+v"(top[1]), "+v"(top[2]),
-          "=&s"(c0), "=&s"(c1), "=&s"(c2)
-        : "v"(x[0]), "v"(y[0]), "v"(x[1]), "v"(y[1]), "v"(x[2]), "v"(y[2]));
+// limb i of K q written with every limb but the top raised by T 2^28 (taken
+// back from the next limb): limbs in [T 2^28 - T, (T + 1) 2^28)
+template <int K, int T>
+constexpr __host__ __device__ Fl make_kq() {
+  Fl r{};
+  uint64_t c = 0;
+  for (int i = 0; i < 14; ++i) {
+    c += (uint64_t)K * q_limb28(i);
+    r.l[i] = i < 13 ? (uint32_t)(c & kM28) + ((uint32_t)T << 28) : (uint32_t)c;
+    if (i > 0) r.l[i] -= T;
+    c >>= 28;
   }
+  return r;
+}
+template <int K, int T>
+__device__ __forceinline__ constexpr uint32_t kq_limb(int i) {
+  constexpr Fl k = make_kq<K, T>();
+  return k.l[i];
 }
 
-template <int N>
-__device__ __forceinline__ void fr_macns(uint64_t (&acc)[N], uint32_t (&top)[N], const uint32_t (&x)[N], uint32_t ys) {
-  if constexpr (N == 2) {
-    uint64_t c0, c1;
-    asm("v_mad_u64_u32 %0, %4, %6, %8, %0\n\t"
-        "v_mad_u64_u32 %1, %5, %7, %8, %1\n\t"
-        "v_addc_co_u32 %2, %4, %2, 0, %4\n\t"
-        "v_addc_co_u32 %3, %5, %3, 0, %5"
-        : "+v"(acc[0]), "+v"(acc[1]), "+v"(top[0]), "+v"(top[1]), "=&s"(c0), "=&s"(c1)
-        : "v"(x[0]), "v"(x[1]), "s"(ys));
-  } else {
-    uint64_t c0, c1, c2;
-    asm("v_mad_u64_u32 %0, %6, %9, %12, %0\n\t"
-        "v_mad_u64_u32 %1, %7, %10, %12, %1\n\t"
-        "v_mad_u64_u32 %2, %8, %11, %12, %2\n\t"
-        "v_addc_co_u32 %3, %6, %3, 0, %6\n\t"
-        "v_addc_co_u32 %4, %7, %4, 0, %7\n\t"
-        "v_addc_co_u32 %5, %8, %5, 0, %8"
-        : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(top[0]), "+v"(top[1]), "+v"(top[2]),
-          "=&s"(c0), "=&s"(c1), "=&s"(c2)
-        : "v"(x[0]), "v"(x[1]), "v"(x[2]), "s"(ys));
-  }
-}
-
-// Montgomery product a b R^-1 mod q by product scanning (see fr_mul): column
-// k collects a_i b_{k-i} and m_i q_{k-i}; for k < 12 the digit m_k =
-// t0 (-q^-1) mod 2^32 is chosen so that m_k q_0 clears the column's low word,
-// for k >= 12 the low word is result word k - 12.  A column sum of at most
-// 24 products stays below 2^69, held as a 64-bit pair plus a top word.
-// compile-time loop: f(std::integral_constant<int, I>) for I = B .. E - 1
-// (the product's 23 x 24 multiply-adds exceed the unroller's budget, and a
-// partly rolled loop would index the limbs dynamically)
-template <int B, int E, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (B < E) {
-    f(std::integral_constant<int, B>{});
-    static_for<B + 1, E>(f);
-  }
-}
-
-__device__ __forceinline__ Fq fq_mul_dev(const Fq& a, const Fq& b) {
-  uint32_t m[12], u[12];
-  uint64_t acc = 0;
-  uint32_t top = 0;
-  static_for<0, 23>([&](auto K) {
-    constexpr int k = decltype(K)::value;
-    static_for<0, 12>([&](auto I) {
-      constexpr int i = decltype(I)::value;
-      constexpr int j = k - i;
-      if constexpr (j >= 0 && j < 12) fr_mac96(acc, top, a.w[i], b.w[j]);
-    });
-    static_for<0, 12>([&](auto I) {
-      constexpr int i = decltype(I)::value;
-      constexpr int j = k - i;
-      if constexpr (i < k && j >= 1 && j < 12) fr_mac96s(acc, top, m[i], q_limb(j));
-    });
-    if constexpr (k < 12) {
-      const uint32_t mk = (uint32_t)acc * kQInv32;
-      m[k] = mk;
-      fr_mac96s(acc, top, mk, q_limb(0));   // the column's low word becomes 0
+// the 28-bit limbs of w << UP for a 384-bit w (UP <= 8)
+template <int UP>
+__device__ __forceinline__ Fl fl_split(const uint32_t (&w)[12]) {
+  Fl r;
+#pragma unroll
+  for (int i = 0; i < 14; ++i) {
+    const int bit = 28 * i - UP;
+    uint32_t v;
+    if (bit < 0) {
+      v = w[0] << -bit;
     } else {
-      u[k - 12] = (uint32_t)acc;
+      const int k = bit >> 5, sh = bit & 31;
+      v = k == 11 ? w[11] >> sh : (sh ? __builtin_amdgcn_alignbit(w[k + 1], w[k], sh) : w[k]);
     }
-    acc = (acc >> 32) | ((uint64_t)top << 32);
-    top = 0;
-  });
-  u[11] = (uint32_t)acc;                      // the result is below 2q < 2^384
+    r.l[i] = i < 13 ? v & kM28 : v;
+  }
+  return r;
+}
+// 12 words of a value below 2^384 with limbs below 2^28 (top limb any)
+__device__ __forceinline__ Fq fl_pack(const Fl& a) {
   Fq r;
 #pragma unroll
-  for (int j = 0; j < 12; ++j) r.w[j] = u[j];
-  return fq_reduce_once(r);
-}
-// N (2 or 3) independent products with their partial products interleaved
-// instruction by instruction (the multiply-adds of fr_macn / fr_macns carry
-// one step of every product), so that the products' dependency chains and
-// carry hazards overlap; the same results as N calls of fq_mul_dev.
-template <int N>
-__device__ __forceinline__ void fq_mul_dev_n(const Fq (&a)[N], const Fq (&b)[N], Fq (&r)[N]) {
-  uint32_t m[N][12], u[N][12];
-  uint64_t acc[N];
-  uint32_t top[N];
-#pragma unroll
-  for (int c = 0; c < N; ++c) { acc[c] = 0; top[c] = 0; }
-  static_for<0, 23>([&](auto K) {
-    constexpr int k = decltype(K)::value;
-    static_for<0, 12>([&](auto I) {
-      constexpr int i = decltype(I)::value;
-      constexpr int j = k - i;
-      if constexpr (j >= 0 && j < 12) {
-        uint32_t x[N], y[N];
-#pragma unroll
-        for (int c = 0; c < N; ++c) { x[c] = a[c].w[i]; y[c] = b[c].w[j]; }
-        fr_macn<N>(acc, top, x, y);
-      }
-    });
-    static_for<0, 12>([&](auto I) {
-      constexpr int i = decltype(I)::value;
-      constexpr int j = k - i;
-      if constexpr (i < k && j >= 1 && j < 12) {
-        uint32_t x[N];
-#pragma unroll
-        for (int c = 0; c < N; ++c) x[c] = m[c][i];
-        fr_macns<N>(acc, top, x, q_limb(j));
-      }
-    });
-    if constexpr (k < 12) {
-      uint32_t x[N];
-#pragma unroll
-      for (int c = 0; c < N; ++c) {
-        m[c][k] = (uint32_t)acc[c] * kQInv32;
-        x[c] = m[c][k];
-      }
-      fr_macns<N>(acc, top, x, q_limb(0));
-    } else {
-#pragma unroll
-      for (int c = 0; c < N; ++c) u[c][k - 12] = (uint32_t)acc[c];
-    }
-#pragma unroll
-    for (int c = 0; c < N; ++c) {
-      acc[c] = (acc[c] >> 32) | ((uint64_t)top[c] << 32);
-      top[c] = 0;
-    }
-  });
-#pragma unroll
-  for (int c = 0; c < N; ++c) {
-    u[c][11] = (uint32_t)acc[c];
-    Fq t;
-#pragma unroll
-    for (int j = 0; j < 12; ++j) t.w[j] = u[c][j];
-    r[c] = fq_reduce_once(t);
+  for (int k = 0; k < 12; ++k) {
+    const int bit = 32 * k, i = bit / 28, sh = bit - 28 * i;
+    uint32_t v = (a.l[i] >> sh) | (a.l[i + 1] << (28 - sh));
+    if (56 - sh < 32 && i + 2 < 14) v |= a.l[i + 2] << (56 - sh);
+    r.w[k] = v;
   }
+  return r;
+}
+
+__device__ __forceinline__ void fl_mac(uint64_t (&c)[28], const Fl& a, const Fl& b) {
+#pragma unroll
+  for (int i = 0; i < 14; ++i)
+#pragma unroll
+    for (int j = 0; j < 14; ++j) c[i + j] += (uint64_t)a.l[i] * b.l[j];
+}
+__device__ __forceinline__ void fl_zero_cols(uint64_t (&c)[28]) {
+#pragma unroll
+  for (int k = 0; k < 28; ++k) c[k] = 0;
+}
+// columns / 2^392 mod q
+__device__ __forceinline__ Fl fl_redc(uint64_t (&c)[28]) {
+#pragma unroll
+  for (int k = 0; k < 14; ++k) {
+    const uint32_t m = ((uint32_t)c[k] * kQInv28) & kM28;
+#pragma unroll
+    for (int j = 0; j < 14; ++j) c[k + j] += (uint64_t)m * q_limb28(j);
+    c[k + 1] += c[k] >> 28;
+  }
+  Fl r;
+  uint64_t t = c[14];
+#pragma unroll
+  for (int i = 0; i < 13; ++i) {
+    r.l[i] = (uint32_t)t & kM28;
+    t = (t >> 28) + c[15 + i];
+  }
+  r.l[13] = (uint32_t)t;
+  return r;
+}
+__device__ __forceinline__ Fl fl_mul(const Fl& a, const Fl& b) {
+  uint64_t c[28];
+  fl_zero_cols(c);
+  fl_mac(c, a, b);
+  return fl_redc(c);
+}
+// a^2: the 91 products of two different limbs once, with one limb doubled
+__device__ __forceinline__ Fl fl_sqr(const Fl& a) {
+  uint64_t c[28];
+  fl_zero_cols(c);
+#pragma unroll
+  for (int i = 0; i < 14; ++i) {
+    c[2 * i] += (uint64_t)a.l[i] * a.l[i];
+    const uint32_t d = 2 * a.l[i];
+#pragma unroll
+    for (int j = i + 1; j < 14; ++j) c[i + j] += (uint64_t)d * a.l[j];
+  }
+  return fl_redc(c);
+}
+// a b + d e
+__device__ __forceinline__ Fl fl_mul2_add(const Fl& a, const Fl& b, const Fl& d, const Fl& e) {
+  uint64_t c[28];
+  fl_zero_cols(c);
+  fl_mac(c, a, b);
+  fl_mac(c, d, e);
+  return fl_redc(c);
+}
+// a + K q - b: b's limbs at most T 2^28 - T and its value at most about K q
+template <int K, int T>
+__device__ __forceinline__ Fl fl_sub(const Fl& a, const Fl& b) {
+  Fl r;
+#pragma unroll
+  for (int i = 0; i < 14; ++i) r.l[i] = a.l[i] + (kq_limb<K, T>(i) - b.l[i]);
+  return r;
+}
+template <int K, int T>
+__device__ __forceinline__ Fl fl_neg(const Fl& b) {
+  Fl r;
+#pragma unroll
+  for (int i = 0; i < 14; ++i) r.l[i] = kq_limb<K, T>(i) - b.l[i];
+  return r;
+}
+// each limb's high bits moved to the next limb once: limbs below 2^28 + 16
+__device__ __forceinline__ Fl fl_carry1(const Fl& a) {
+  Fl r;
+  r.l[0] = a.l[0] & kM28;
+#pragma unroll
+  for (int i = 1; i < 13; ++i) r.l[i] = (a.l[i] & kM28) + (a.l[i - 1] >> 28);
+  r.l[13] = a.l[13] + (a.l[12] >> 28);
+  return r;
+}
+// whether a product (below 2q, limbs below 2^28) is 0 mod q: 0 or q itself
+__device__ __forceinline__ bool fl_is_zero(const Fl& a) {
+  uint32_t z = 0, e = 0;
+#pragma unroll
+  for (int i = 0; i < 14; ++i) {
+    z |= a.l[i];
+    e |= a.l[i] ^ q_limb28(i);
+  }
+  return z == 0 || e == 0;
+}
+
+// a b 2^-384 mod q (a, b < q): 2^8 a supplies the 392 - 384 bits
+__device__ __forceinline__ Fq fq_mul_dev(const Fq& a, const Fq& b) {
+  return fq_reduce_once(fl_pack(fl_mul(fl_split<8>(a.w), fl_split<0>(b.w))));
 }
 
 // one out-of-line copy for the code outside the commitment loop (setup,
@@ -381,70 +379,40 @@ struct ExpQp1Quarter {
   VL_HD uint32_t operator()(int i) const { return pick12(i, VL_FQ_QP1Q_LIMBS); }
 };
 
-// --- inversion: binary extended Euclid on canonical integers (Hankerson,
-// Menezes, Vanstone, Guide to Elliptic Curve Cryptography, Alg. 2.22) ------
-VL_HD bool fq_raw_is_one(const Fq& a) {
-  uint32_t d = a.w[0] ^ 1u;
-#pragma unroll
-  for (int i = 1; i < 12; ++i) d |= a.w[i];
-  return d == 0;
-}
-VL_HD Fq fq_raw_shr1(const Fq& a) {
-  Fq r;
-#pragma unroll
-  for (int j = 0; j < 11; ++j) r.w[j] = (a.w[j] >> 1) | (a.w[j + 1] << 31);
-  r.w[11] = a.w[11] >> 1;
-  return r;
-}
-// x / 2 mod q for x < q: x or x + q (< 2^382), shifted
-VL_HD Fq fq_half(const Fq& x) {
-  const uint32_t mask = 0u - (x.w[0] & 1u);
-  Fq t;
-  uint32_t c = 0;
-#pragma unroll
-  for (int j = 0; j < 12; ++j) t.w[j] = adc32(x.w[j], q_limb(j) & mask, c, c);
-  return fq_raw_shr1(t);
-}
-// a >= b as integers
-VL_HD bool fq_raw_geq(const Fq& a, const Fq& b) {
-  uint32_t borrow = 0;
-#pragma unroll
-  for (int i = 0; i < 12; ++i) (void)sbb32(a.w[i], b.w[i], borrow, borrow);
-  return borrow == 0;
-}
-VL_HD Fq fq_raw_sub(const Fq& a, const Fq& b) {
-  Fq d;
-  uint32_t borrow = 0;
-#pragma unroll
-  for (int i = 0; i < 12; ++i) d.w[i] = sbb32(a.w[i], b.w[i], borrow, borrow);
-  return d;
-}
-// The inverse of the Montgomery-form a (0 < a < q), in Montgomery form; 0 for
-// a = 0.  The loop keeps x1 a = u and x2 a = v (mod q) with u, v odd after
-// their shifts; every step shifts or subtracts, the bit lengths of u and v
-// (at most 2 x 381 together) drop by one per shift and a subtraction is
-// always followed by a shift, so at most 1524 steps run.  The integer
-// inverse of a R is a^-1 R^-1; one product with R^3 gives a^-1 R.
-VL_HD Fq fq_inv(const Fq& a) {
-  if (fq_is_zero(a)) return a;
-  Fq u = a, v = fq_q(), x1 = fq_raw_one(), x2 = fq_zero();
-  for (int step = 0; step < 1600; ++step) {
-    if (fq_raw_is_one(u) || fq_raw_is_one(v)) break;
-    if ((u.w[0] & 1u) == 0) {
-      u = fq_raw_shr1(u);
-      x1 = fq_half(x1);
-    } else if ((v.w[0] & 1u) == 0) {
-      v = fq_raw_shr1(v);
-      x2 = fq_half(x2);
-    } else if (fq_raw_geq(u, v)) {
-      u = fq_raw_sub(u, v);
-      x1 = fq_sub(x1, x2);
-    } else {
-      v = fq_raw_sub(v, u);
-      x2 = fq_sub(x2, x1);
+// --- inversion (modinv.hpp) -------------------------------------------------
+struct FqMod30 {
+  static constexpr int L = 13;
+  static constexpr int kBatches = 37;                    // (49 * 382 + 57) / 17 = 1104 divsteps
+  static constexpr uint32_t inv30 = 0x00030003u;         // q^-1 mod 2^30
+  VL_HD static uint32_t limb(int i) {
+    switch (i) {
+      case 0: return 0x3fffaaabu; case 1: return 0x27fbffffu; case 2: return 0x153ffffbu;
+      case 3: return 0x2affffacu; case 4: return 0x30f6241eu; case 5: return 0x034a83dau;
+      case 6: return 0x112bf673u; case 7: return 0x12e13ce1u; case 8: return 0x2cd76477u;
+      case 9: return 0x1ed90d2eu; case 10: return 0x29a4b1bau; case 11: return 0x3a8e5ff9u;
+      default: return 0x001a0111u;
     }
   }
-  return fq_mul(fq_raw_is_one(u) ? x1 : x2, fq_R3());
+};
+// the inverse mod q of the integer a < 2q, below 4q (0 for a = 0)
+VL_HD Fq fq_inv_raw(const Fq& a) {
+  int32_t x[13], d[13];
+  words_to_30<12, 13>(a.w, x);
+  modinv30<FqMod30>(x, d);
+  add_2m30<FqMod30>(d);
+  Fq r;
+  limbs30_to_words<12, 13>(d, r.w);
+  return r;
+}
+// The inverse of the Montgomery-form a, in Montgomery form; 0 for a = 0.  The
+// integer inverse of a R is a^-1 R^-1 (reduced below q first); one product
+// with R^3 gives a^-1 R.
+VL_HD Fq fq_inv(const Fq& a) {
+  if (fq_is_zero(a)) return a;
+  Fq d = fq_inv_raw(a);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) d = fq_reduce_once(d);
+  return fq_mul(d, fq_R3());
 }
 
 // canonical little-endian bytes <-> limbs

@@ -29,8 +29,9 @@ constexpr uint64_t kPointBytes = 96;
 constexpr uint64_t kTablePoints = 128;
 constexpr uint32_t kMaxGens = 1u << 20;
 constexpr uint32_t kMaxRows = 1u << 24;
-constexpr uint64_t kTargetTasks = 4096;   // waves that fill the GPU a few times over
-constexpr uint32_t kMinSlice = 256;       // columns per task (4 per lane) at the least
+constexpr uint64_t kTargetLanes = 131072;  // two waves on each of the GPU's 1024 SIMDs
+constexpr uint32_t kMinSlice = 4;          // columns per lane at the least
+constexpr uint64_t kPartialBytes = 192;    // one slice's sum
 
 vl_status check_setup(uint32_t m, uint32_t W) {
   if (m == 0 || m > kMaxGens) return fail(VL_ERR_SHAPE, "hyrax: m must be in 1 .. 2^20");
@@ -42,18 +43,37 @@ struct Split {
   uint32_t n_split, chunk;
 };
 
-Split plan_split(uint32_t R, uint32_t m, uint32_t split) {
-  uint64_t n = split;
-  if (n == 0) {
-    n = (kTargetTasks + R - 1) / R;
-    n = std::min<uint64_t>(n, (m + kMinSlice - 1) / kMinSlice);
-  }
-  n = std::max<uint64_t>(1, std::min<uint64_t>(n, (m + 63) / 64));
-  const uint64_t chunk = align_up((m + n - 1) / n, 64);
+// the slices' sums and, for more than kHyraxMaxFinal of them, the runs' sums
+uint64_t partial_bytes(uint32_t R, const Split& s) {
+  const uint64_t runs = s.n_split > kHyraxMaxFinal ? (s.n_split + kHyraxRun - 1) / kHyraxRun : 0;
+  return align_up((uint64_t)R * (s.n_split + runs) * kPartialBytes, 256);
+}
+
+// split given: that many slices of a multiple of 64 columns.  Otherwise
+// enough slices of at least kMinSlice columns to fill the GPU with one lane
+// per (row, slice), as far as `room` bytes of workspace hold them.
+Split plan_split(uint32_t R, uint32_t m, uint32_t split, uint64_t room = UINT64_MAX) {
   Split s;
-  s.chunk = (uint32_t)chunk;
-  s.n_split = (uint32_t)((m + chunk - 1) / chunk);
-  return s;
+  if (split) {
+    const uint64_t n = std::min<uint64_t>(split, (m + 63) / 64);
+    s.chunk = (uint32_t)align_up((m + n - 1) / n, 64);
+    s.n_split = (uint32_t)((m + s.chunk - 1) / s.chunk);
+    return s;
+  }
+  uint64_t n = std::min<uint64_t>((kTargetLanes + R - 1) / R, (m + kMinSlice - 1) / kMinSlice);
+  for (;; n = n * 7 / 8) {
+    n = std::max<uint64_t>(n, 1);
+    s.chunk = (uint32_t)((m + n - 1) / n);
+    s.n_split = (uint32_t)((m + s.chunk - 1) / s.chunk);
+    if (n == 1 || partial_bytes(R, s) <= room) return s;
+  }
+}
+
+// the least workspace a call is accepted with: slices of 256 columns, as
+// many as make 4096 row slices (or the split asked for)
+uint64_t least_bytes(uint32_t R, uint32_t m, uint32_t split) {
+  const uint64_t n = split ? split : std::min<uint64_t>((4096 + R - 1) / R, (m + 255) / 256);
+  return align_up(R * kPartialBytes * plan_split(R, m, (uint32_t)n).n_split, 256);
 }
 
 // ---- host G1 helpers ------------------------------------------------------
@@ -183,8 +203,7 @@ vl_status vl_hyrax_setup(uint32_t m, uint32_t windows, void* table, uint64_t tab
 
 uint64_t vl_hyrax_commit_workspace_size(uint32_t R, uint32_t m, uint32_t split) {
   if (R == 0 || m == 0 || R > kMaxRows || m > kMaxGens) return 0;
-  const Split s = plan_split(R, m, split);
-  return align_up((uint64_t)R * s.n_split * 48 * 4, 256);
+  return partial_bytes(R, plan_split(R, m, split));
 }
 
 vl_status vl_hyrax_commit(const void* M, int32_t dtype, uint32_t R, uint32_t m, uint64_t ld, const void* table,
@@ -204,14 +223,14 @@ vl_status vl_hyrax_commit(const void* M, int32_t dtype, uint32_t R, uint32_t m, 
   if ((uintptr_t)table % 16 || (uintptr_t)commits % 4)
     return fail(VL_ERR_INVALID_ARG, "hyrax commit: table must be 16-byte, commits 4-byte aligned");
   if (split > (m + 63) / 64) return fail(VL_ERR_INVALID_ARG, "hyrax commit: split exceeds ceil(m / 64)");
-  const uint64_t need = vl_hyrax_commit_workspace_size(R, m, split);
+  const uint64_t need = least_bytes(R, m, split);
   if (!workspace || workspace_bytes < need)
     return fail(VL_ERR_WORKSPACE, "hyrax commit: workspace of %llu bytes, %llu needed",
                 (unsigned long long)workspace_bytes, (unsigned long long)need);
-  const Split s = plan_split(R, m, split);
+  const Split s = plan_split(R, m, split, workspace_bytes);
   hipError_t e = launch_hyrax_commit(M, dtype, ld, R, m, windows, reinterpret_cast<const uint32_t*>(table), s.n_split,
                                      s.chunk, reinterpret_cast<uint32_t*>(workspace),
-                                     reinterpret_cast<uint32_t*>(commits), reinterpret_cast<hipStream_t>(stream));
+                                     partial_bytes(R, s) <= workspace_bytes, reinterpret_cast<uint32_t*>(commits), reinterpret_cast<hipStream_t>(stream));
   if (e != hipSuccess) return fail(VL_ERR_HIP, "hyrax commit: %s", hipGetErrorString(e));
   return VL_OK;
 }
