@@ -784,13 +784,16 @@ BlobLayout blob_layout(const Plan& P) {
   }
   L.lookups = o;
   o = align_up(o + P.lookups.size() * sizeof(LookupJob), 64);
-  for (int lo = 0; lo < 2; ++lo) {
-    L.lk_wide[lo].resize(P.lk_wide[lo].size());
-    for (size_t k = 0; k < P.lk_wide[lo].size(); ++k) {
-      L.lk_wide[lo][k] = o;
-      o = align_up(o + P.lk_wide[lo][k].size() * sizeof(LookupSweep), 64);
+  L.lookup_u = o;
+  o = align_up(o + P.lookup_u.size() * 4, 64);
+  for (int kd = 0; kd < LK_KINDS; ++kd) {
+    L.lk_wide[kd].resize(P.lk_wide[kd].size());
+    for (size_t k = 0; k < P.lk_wide[kd].size(); ++k) {
+      L.lk_wide[kd][k] = o;
+      o += P.lk_wide[kd][k].size() * sizeof(LookupSweep);
     }
   }
+  o = align_up(o, 64);
   L.total = align_up(o, 256);
   return L;
 }
@@ -830,13 +833,17 @@ void fill_blob(Plan& P, const BlobLayout& L, uint8_t* dblob) {
   if (!P.bmms.empty()) memcpy(P.blob.data() + L.bmms, P.bmms.data(), P.bmms.size() * sizeof(BmmJob));
   for (size_t k = 0; k < P.bmm_wide.size(); ++k)
     memcpy(P.blob.data() + L.bmm_wide[k], P.bmm_wide[k].data(), P.bmm_wide[k].size() * sizeof(BmmSweep));
-  if (!P.lookups.empty())
+  if (!P.lookups.empty()) {
+    for (LookupJob& j : P.lookups)
+      j.u = reinterpret_cast<const uint32_t*>(dblob + L.lookup_u) + reinterpret_cast<uint64_t>(j.u);
     memcpy(P.blob.data() + L.lookups, P.lookups.data(), P.lookups.size() * sizeof(LookupJob));
-  for (int lo = 0; lo < 2; ++lo)
-    for (size_t k = 0; k < P.lk_wide[lo].size(); ++k)
-      if (!P.lk_wide[lo][k].empty())
-        memcpy(P.blob.data() + L.lk_wide[lo][k], P.lk_wide[lo][k].data(),
-               P.lk_wide[lo][k].size() * sizeof(LookupSweep));
+    if (!P.lookup_u.empty()) memcpy(P.blob.data() + L.lookup_u, P.lookup_u.data(), P.lookup_u.size() * 4);
+  }
+  for (int kd = 0; kd < LK_KINDS; ++kd)
+    for (size_t k = 0; k < P.lk_wide[kd].size(); ++k)
+      if (!P.lk_wide[kd][k].empty())
+        memcpy(P.blob.data() + L.lk_wide[kd][k], P.lk_wide[kd][k].data(),
+               P.lk_wide[kd][k].size() * sizeof(LookupSweep));
   memcpy(P.blob.data() + L.eq, P.eq.data(), P.eq.size() * sizeof(EqJob));
   // wide rounds' io slots: zeros in the blob, so every call starts its counts
   // and status afresh
@@ -938,8 +945,7 @@ bool plan_forks(const Plan& P) {
   return false;
 }
 
-// whether a plan holds lookups alone (then its eq tables are first read by
-// the lookup sweeps, and the table kernels may use the internal streams)
+// whether a plan holds lookups alone
 static bool lookups_only(const Plan& P) {
   if (P.lookups.empty() || !P.bmms.empty() || !P.evals.empty() || !P.reduces.empty()) return false;
   for (const Segment& G : P.seg) {
@@ -954,43 +960,29 @@ hipError_t enqueue_plan(const Plan& P, const BlobLayout& L, uint8_t* dblob, hipS
                         hipStream_t s2, StageEvents* ev, const void* blob_src_dev, hipStream_t s3) {
   thread_local std::map<int, ForkEvents> forks;   // per host thread and device
   const size_t nseg = P.seg.size();
-  const bool two = s2 != s;
+  // a plan of lookups alone uses s2 for its counts only
+  const bool lk_side = s2 != s && !ev && lookups_only(P);
+  const bool two = s2 != s && !lookups_only(P);
   const bool side = s3 && s3 != s && !ev && P.fork;
-  const bool eq_side = s3 && s3 != s && !ev && P.eq_fork && lookups_only(P);
-  const bool inv_side = two && !ev && lookups_only(P);
   int dev = 0;
-  if (two || side || eq_side) {
+  if (two || side || lk_side) {
     const hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
   }
   ForkEvents& fork = forks[dev];
-  if (two || side || eq_side) {
+  if (two || side || lk_side) {
     // [0, nseg): rounds forks; nseg, nseg + 1: rounds start and join;
     // nseg + 2 + 2k, nseg + 3 + 2k: segment k's contraction fork and join;
-    // 3 nseg + 2 + k: the end of segment k's wide rounds; 4 nseg + 2,
-    // 4 nseg + 3: the eq fork and join; 4 nseg + 4, 4 nseg + 5: the fork and
-    // join of the lookups' table inversions
-    const hipError_t e = fork.need(4 * nseg + 6);
+    // 3 nseg + 2 + k: the end of segment k's wide rounds; from 4 nseg + 2 on,
+    // lookups: the fork, the tables' end, the counts' end
+    const hipError_t e = fork.need(4 * nseg + 5);
     if (e != hipSuccess) return e;
   }
   VL_STAGE(ev, VL_STAGE_UPLOAD, s,
            blob_src_dev ? launch_copy_in(dblob, blob_src_dev, L.total, s)
                         : upload_blob(dblob, P.blob.data(), L.total, s));
-  if (eq_side) {
-    // lookups: the eq tables are first read by the sweeps, after the
-    // multiplicities, the table inverses and the entries' terms; the eq
-    // kernel (bound by its field products) runs beside those (bound by
-    // atomics, one inversion chain per thread, and memory)
-    hipError_t e = hipEventRecord(fork.ev[4 * nseg + 2], s);
-    if (e == hipSuccess) e = hipStreamWaitEvent(s3, fork.ev[4 * nseg + 2], 0);
-    if (e == hipSuccess)
-      e = launch_eq(reinterpret_cast<const EqJob*>(dblob + L.eq), (uint32_t)P.eq.size(), P.eq_threads, s3);
-    if (e == hipSuccess) e = hipEventRecord(fork.ev[4 * nseg + 3], s3);
-    if (e != hipSuccess) return e;
-  } else {
-    VL_STAGE(ev, VL_STAGE_EQ, s,
-             launch_eq(reinterpret_cast<const EqJob*>(dblob + L.eq), (uint32_t)P.eq.size(), P.eq_threads, s));
-  }
+  VL_STAGE(ev, VL_STAGE_EQ, s,
+           launch_eq(reinterpret_cast<const EqJob*>(dblob + L.eq), (uint32_t)P.eq.size(), P.eq_threads, s));
   if (two) {
     // the rounds stream starts after everything queued before this call
     hipError_t e = hipEventRecord(fork.ev[nseg], s);
@@ -1112,40 +1104,52 @@ hipError_t enqueue_plan(const Plan& P, const BlobLayout& L, uint8_t* dblob, hipS
   if (!P.lookups.empty()) {
     const LookupJob* lj = reinterpret_cast<const LookupJob*>(dblob + L.lookups);
     const uint32_t nl = (uint32_t)P.lookups.size();
-    for (const auto& z : P.lookup_zero) VL_STAGE(ev, VL_STAGE_FINISH, s, launch_zero_words(z.first, z.second, s));
-    if (inv_side) {
-      // the table inversions (one chain of field products per thread, a few
-      // dozen blocks) read no count: they run on the rounds stream beside
-      // the count kernel, joined before the multiplicities
-      hipError_t e = hipEventRecord(fork.ev[4 * nseg + 4], s);
-      if (e == hipSuccess) e = hipStreamWaitEvent(s2, fork.ev[4 * nseg + 4], 0);
-      if (e == hipSuccess) e = launch_lookup_inv(lj, nl, P.lk_tab_blocks, s2);
-      if (e == hipSuccess) e = hipEventRecord(fork.ev[4 * nseg + 5], s2);
-      if (e == hipSuccess) e = launch_lookup_hist(lj, nl, P.lk_hist_blocks, s);
-      if (e == hipSuccess) e = hipStreamWaitEvent(s, fork.ev[4 * nseg + 5], 0);
+    auto sweep = [&](int kd, size_t k) -> hipError_t {
+      if (k >= P.lk_wide[kd].size() || P.lk_wide[kd][k].empty()) return hipSuccess;
+      return launch_lookup_sweep(lj, reinterpret_cast<const LookupSweep*>(dblob + L.lk_wide[kd][k]),
+                                 (uint32_t)P.lk_wide[kd][k].size(), P.lk_wide_blocks[kd][k], (uint32_t)k,
+                                 (LookupSweepKind)kd, s);
+    };
+    // The tables (an inversion per thread is one chain of instructions) and
+    // the first sweep on the caller's stream; the counts, the multiplicities
+    // and the start beside them on the rounds stream.
+    hipStream_t sc = lk_side ? s2 : s;
+    hipEvent_t* fe = lk_side ? &fork.ev[4 * nseg + 2] : nullptr;
+    if (lk_side) {
+      const hipError_t e = hipEventRecord(fe[0], s);
       if (e != hipSuccess) return e;
-    } else {
-      VL_STAGE(ev, VL_STAGE_FINISH, s, launch_lookup_hist(lj, nl, P.lk_hist_blocks, s));
-      VL_STAGE(ev, VL_STAGE_FINISH, s, launch_lookup_inv(lj, nl, P.lk_tab_blocks, s));
     }
-    VL_STAGE(ev, VL_STAGE_FINISH, s, launch_lookup_mult(lj, nl, P.lk_mult_blocks, s));
+    VL_STAGE(ev, VL_STAGE_FINISH, s, launch_lookup_tables(lj, nl, P.lk_tab_blocks, s));
+    if (lk_side) {
+      hipError_t e = hipEventRecord(fe[1], s);
+      if (e == hipSuccess) e = hipStreamWaitEvent(s2, fe[0], 0);
+      if (e != hipSuccess) return e;
+    }
+    for (const auto& z : P.lookup_zero) VL_STAGE(ev, VL_STAGE_FINISH, sc, launch_zero_words(z.first, z.second, sc));
+    VL_STAGE(ev, VL_STAGE_FINISH, sc, launch_lookup_hist(lj, nl, P.lk_hist_blocks, P.lk_hist_lds, sc));
     VL_STAGE(ev, VL_STAGE_FINISH, s, launch_lookup_prep(lj, nl, P.lk_prep_blocks, s));
-    if (eq_side) {
-      const hipError_t e = hipStreamWaitEvent(s, fork.ev[4 * nseg + 3], 0);
+    VL_STAGE(ev, VL_STAGE_PASS1, s, sweep(LK_FIRST, 0));
+    if (lk_side) {
+      const hipError_t e = hipStreamWaitEvent(s2, fe[1], 0);
       if (e != hipSuccess) return e;
     }
-    VL_STAGE(ev, VL_STAGE_PASS1, s, launch_lookup_start(lj, nl, s));
-    const size_t nk = std::max(P.lk_wide[0].size(), P.lk_wide[1].size());
-    for (size_t k = 0; k < nk; ++k) {
-      for (int lo = 0; lo < 2; ++lo) {
-        if (k >= P.lk_wide[lo].size() || P.lk_wide[lo][k].empty()) continue;
-        const LookupSweep* lst = reinterpret_cast<const LookupSweep*>(dblob + L.lk_wide[lo][k]);
-        const uint32_t nw = (uint32_t)P.lk_wide[lo][k].size();
-        VL_STAGE(ev, VL_STAGE_PASS1, s,
-                 launch_lookup_sweep(lj, lst, nw, P.lk_wide_blocks[lo][k], (uint32_t)k, lo == 1, s));
-        VL_STAGE(ev, VL_STAGE_ROUNDS, s, launch_lookup_chal(lj, lst, nw, (uint32_t)k, s));
-      }
+    VL_STAGE(ev, VL_STAGE_FINISH, sc, launch_lookup_mult(lj, nl, P.lk_mult_blocks, sc));
+    VL_STAGE(ev, VL_STAGE_PASS1, sc, launch_lookup_start(lj, nl, sc));
+    if (lk_side) {
+      hipError_t e = hipEventRecord(fe[2], s2);
+      if (e == hipSuccess) e = hipStreamWaitEvent(s, fe[2], 0);
+      if (e != hipSuccess) return e;
     }
+    size_t nk = 0;
+    for (const auto& w : P.lk_wide) nk = std::max(nk, w.size());
+    for (size_t k = 0; k < nk; ++k)
+      for (int kd = 0; kd < LK_KINDS; ++kd) {
+        if (k >= P.lk_wide[kd].size() || P.lk_wide[kd][k].empty()) continue;
+        if (kd != LK_FIRST) VL_STAGE(ev, VL_STAGE_PASS1, s, sweep(kd, k));
+        VL_STAGE(ev, VL_STAGE_ROUNDS, s,
+                 launch_lookup_step(lj, reinterpret_cast<const LookupSweep*>(dblob + L.lk_wide[kd][k]),
+                                    (uint32_t)P.lk_wide[kd][k].size(), (uint32_t)k, s));
+      }
     VL_STAGE(ev, VL_STAGE_ROUNDS, s, launch_lookup_rounds(lj, nl, s));
   }
   return hipSuccess;

@@ -205,20 +205,43 @@ struct BmmSweep {
 // One lookup argument (vl_lookup_prove, Protocol 1 with the sum of
 // eq. (lookup-sumcheck)): every entry (x_i[, y_i]) of a secret tensor is a
 // row (t0 + j[, tb_j]) of a table of N = 2^nL rows.  S is padded to
-// 2^(nH + nL) entries with the table's first row.  Tables (SoL, Montgomery):
-// over the padded entries A = 1/(beta + S), Sb = S + beta, E = eq(u, .);
-// over the table rows B = 1/(beta + T), Tb = T + beta, M = multiplicities,
-// EL = eq(u_L, .).  Rounds bind the high index bits first (only A, Sb, E
-// depend on them; the table rows' terms add a constant K per round), then
-// the low bits (all seven tables).  As for batched products, the first
-// `wide` rounds run as GPU-wide sweeps and a one-wave transcript step.
-constexpr uint32_t kLookupInvChunk = 16;       // table rows per thread in the batch inversion
-constexpr uint32_t kLookupSweepPairs = 256;    // pairs per sweep block (one per thread)
-constexpr uint32_t kLookupWidePairs = 512;
+// D' = 2^(nH + nL) entries with the table's first row.  Tables (Montgomery):
+// over the rows the records {B = 1/(beta + T), T + beta} and M' = c2 m; over
+// the padded entries A = 1/(beta + S) and Sb = S + beta, which are the
+// entries' rows' records: with nH >= 2 and wide rounds the first two rounds
+// look them up (gather) and store them folded, from half the entries on.
+// Rounds bind the high index bits first (only A and Sb depend on them; the
+// rows' terms add a constant per round), then the low bits.  The first `wide`
+// rounds run as GPU-wide sweeps and a one-block transcript step.
+// rounds with at least this many pairs run wide: a wide round of 256 pairs
+// takes about 30 us, in one workgroup 45; one of 128 about 27 there
+constexpr uint32_t kLookupWidePairs = 256;
+constexpr uint32_t kLookupTailVars = 9;       // log2 of the entries the one-workgroup rounds start from, at most
+constexpr uint32_t kLookupLowPairs = 64;       // pairs per block of a low round's sweep
+constexpr uint32_t kLkTerms = 9;               // terms of a low round's pair: three products at three points
+constexpr uint32_t kLookupPartWords = 72;      // a sweep block's nine sums
 constexpr uint32_t kLookupMaxWide = 32;
-constexpr uint32_t kLookupParts = 14;          // sweep partial elements per block
-// io words: [0] status, [8, 16) state, [16, 24) pending r, [24, 32) K
-constexpr uint32_t kLkIoState = 8, kLkIoR = 16, kLkIoK = 24, kLkIoWords = 32;
+constexpr uint32_t kLookupLdsVars = 16;        // tables of up to 2^16 rows are counted in LDS
+// variables of the low factor of an eq suffix: its table's entries (2^11)
+// stay in L1 while a sweep block passes over them
+constexpr uint32_t kLookupLoVars = 11;
+inline __host__ __device__ uint32_t lk_nlo(uint32_t n) {
+  return n == 0 ? 0 : (n - 1 < kLookupLoVars ? n - 1 : kLookupLoVars);
+}
+// pairs per block of a high round's sweep with h pairs: as many as the low
+// eq factor covers, down to one per thread to keep two blocks per CU
+inline __host__ __device__ uint64_t lk_span(uint64_t h) {
+  uint64_t s = 1ull << kLookupLoVars;
+  while (s > 256 && h / s < 512) s >>= 1;
+  return s;
+}
+inline __host__ __device__ uint32_t lk_round_blocks(uint32_t n, uint32_t nH, uint32_t rd) {
+  const uint64_t h = 1ull << (n - 1 - rd), s = rd >= nH ? kLookupLowPairs : lk_span(h);
+  return (uint32_t)((h + s - 1) / s);
+}
+// io words: [0] status, [8, 16) state, [16, 24) pending r, [24, 32) the next
+// high round's constant, [32, 56) the running scalars
+constexpr uint32_t kLkIoState = 8, kLkIoR = 16, kLkIoK = 24, kLkIoScale = 32, kLkIoWords = 56;
 struct LookupJob {
   uint32_t st[8];             // transcript state after gamma, beta, alpha, u
   uint32_t gamma[8], beta[8], alpha[8], c1[8], c2[8];   // Montgomery (c1 = alpha^2 N / D', c2 = N / D')
@@ -228,32 +251,35 @@ struct LookupJob {
   const int32_t* tb;          // table's second column or null
   int32_t dtype, dtype_y;
   int32_t t0;
-  uint32_t pad_;
+  uint32_t gather;            // 1: rounds 0 and 1 look A and Sb up
   uint64_t D;
   uint32_t nH, nL;
   uint32_t wide;
-  uint32_t hist_begin;        // block prefixes: histogram launch (D entries),
-  uint32_t prep_begin;        // preparation launch (padded entries),
-  uint32_t tab_begin;         // inversion launch (chunks of table rows)
+  uint32_t hist_begin;        // block prefixes: histogram launch,
+  uint32_t prep_begin;        // preparation launch (padded entries; none with gather),
+  uint32_t tab_begin;         // table launch: inv_blocks of row chunks, then the eq entries
   uint32_t mult_begin;        // multiplicity launch (one table row per thread)
+  uint32_t inv_blocks;
   uint32_t nkparts;           // multiplicity-launch blocks (partials of sum_j B_j m_j)
-  uint32_t pad2_;
-  uint32_t* cnt;              // N counts, zeroed by the plan
-  uint32_t* A;                // ld 2^(nH + nL)
+  uint32_t hist_chunk, hist_blocks;   // entries per histogram block, blocks
+  uint32_t inv_chunk;         // table rows per thread of the table launch
+  const uint32_t* u;          // the point u, Montgomery (8 words each)
+  uint32_t* hist;             // counts: N / 2 words per block (16-bit), or N words zeroed by the plan
+  uint32_t* A;                // ld D' (D' / 2 with gather)
   uint32_t* S;
-  uint32_t* E;
-  uint32_t* B;                // ld 2^nL
-  uint32_t* T;
-  uint32_t* M;
-  uint32_t* EL;
+  uint32_t* W;                // eq of u's last m <= lk_nlo variables, at 8 (2^m - 1) words
+  uint32_t* EH;               // eq of the last m of the other variables
+  uint32_t* rec;              // row records {B, T + beta}, 16 words each
+  uint32_t* M;                // ld N
   uint32_t* kpart;
-  uint32_t* part;             // sweep partials, kLookupParts elements per block
+  uint32_t* part;             // sweep partials
   uint32_t* io;
   int32_t* flag;              // set when an entry is not in the table
   uint8_t* proof;
   uint8_t* digest;
   int32_t* status;
 };
+enum LookupSweepKind { LK_FIRST, LK_SECOND, LK_FOLD, LK_PLAIN, LK_LOW, LK_KINDS };
 struct LookupSweep {
   uint32_t job;
   uint32_t block_begin;
@@ -285,14 +311,15 @@ hipError_t launch_bmm_chal(const BmmJob* jobs_dev, const BmmSweep* list_dev, uin
                            hipStream_t s);
 hipError_t launch_bmm_rounds(const BmmJob* jobs_dev, uint32_t n_jobs, hipStream_t s);
 // lookup arguments (lookup.hip)
-hipError_t launch_lookup_hist(const LookupJob* jobs_dev, uint32_t n_jobs, uint32_t n_blocks, hipStream_t s);
-hipError_t launch_lookup_inv(const LookupJob* jobs_dev, uint32_t n_jobs, uint32_t n_blocks, hipStream_t s);
+hipError_t launch_lookup_hist(const LookupJob* jobs_dev, uint32_t n_jobs, uint32_t n_blocks, uint32_t lds_bytes,
+                              hipStream_t s);
+hipError_t launch_lookup_tables(const LookupJob* jobs_dev, uint32_t n_jobs, uint32_t n_blocks, hipStream_t s);
 hipError_t launch_lookup_mult(const LookupJob* jobs_dev, uint32_t n_jobs, uint32_t n_blocks, hipStream_t s);
 hipError_t launch_lookup_prep(const LookupJob* jobs_dev, uint32_t n_jobs, uint32_t n_blocks, hipStream_t s);
 hipError_t launch_lookup_start(const LookupJob* jobs_dev, uint32_t n_jobs, hipStream_t s);
 hipError_t launch_lookup_sweep(const LookupJob* jobs_dev, const LookupSweep* list_dev, uint32_t n_list,
-                               uint32_t n_blocks, uint32_t round, bool low, hipStream_t s);
-hipError_t launch_lookup_chal(const LookupJob* jobs_dev, const LookupSweep* list_dev, uint32_t n_list,
+                               uint32_t n_blocks, uint32_t round, LookupSweepKind kind, hipStream_t s);
+hipError_t launch_lookup_step(const LookupJob* jobs_dev, const LookupSweep* list_dev, uint32_t n_list,
                               uint32_t round, hipStream_t s);
 hipError_t launch_lookup_rounds(const LookupJob* jobs_dev, uint32_t n_jobs, hipStream_t s);
 // Hyrax: generators and fixed-base tables of windows W for m generators;

@@ -11,6 +11,7 @@
 // inverses and the rounds (lookup.hip).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstring>
 #include <vector>
 
@@ -119,51 +120,74 @@ void plan_lookup(Builder& B, const vl_lookup& L, const LookupChallenges& ch, uin
   j.D = L.D;
   j.nH = nH;
   j.nL = nL;
-  j.cnt = B.dev<uint32_t>(B.take(4 * N));
-  B.P.lookup_zero.push_back({j.cnt, N});
-  j.A = B.dev<uint32_t>(B.take(32 * Dp));
-  j.S = B.dev<uint32_t>(B.take(32 * Dp));
-  j.E = B.dev<uint32_t>(B.take(32 * Dp));
-  j.B = B.dev<uint32_t>(B.take(32 * N));
-  j.T = B.dev<uint32_t>(B.take(32 * N));
+  uint32_t wide = 0;
+  while (wide < n && wide < kLookupMaxWide && (Dp >> (wide + 1)) >= kLookupWidePairs) ++wide;
+  if (wide < 2) wide = 0;   // then the one-workgroup rounds hold at most 2^kLookupTailVars entries anyway
+  j.wide = wide;
+  j.gather = wide && nH >= 2 ? 1 : 0;
+  // counts: up to 2^16 rows in LDS, 8192 to 32768 entries a block (a 16-bit
+  // counter holds them all), enough blocks for every CU before longer ones
+  if (nL <= kLookupLdsVars) {
+    j.hist_chunk = (uint32_t)std::min<uint64_t>(32768, std::max<uint64_t>(8192, (L.D + 255) / 256));
+    j.hist_blocks = (uint32_t)((L.D + j.hist_chunk - 1) / j.hist_chunk);
+    j.hist = B.dev<uint32_t>(B.take(4 * ((N + 1) / 2) * j.hist_blocks));
+    B.P.lk_hist_lds = std::max<uint32_t>(B.P.lk_hist_lds, (uint32_t)(4 * ((N + 1) / 2)));
+  } else {
+    j.hist_chunk = 1024;
+    j.hist_blocks = (uint32_t)((L.D + 1023) / 1024);
+    j.hist = B.dev<uint32_t>(B.take(4 * N));
+    B.P.lookup_zero.push_back({j.hist, N});
+  }
+  const uint64_t len = j.gather ? Dp / 2 : Dp;
+  j.A = B.dev<uint32_t>(B.take(32 * len));
+  j.S = B.dev<uint32_t>(B.take(32 * len));
+  const uint32_t nlo = lk_nlo(n);
+  const uint64_t eq_lo = (2ull << nlo) - 1, eq_hi = (1ull << (n - nlo)) - 1;   // entries of all suffix tables
+  j.W = B.dev<uint32_t>(B.take(32 * (eq_lo + eq_hi)));
+  j.EH = j.W + 8 * eq_lo;
+  j.rec = B.dev<uint32_t>(B.take(64 * N));
   j.M = B.dev<uint32_t>(B.take(32 * N));
-  j.EL = B.dev<uint32_t>(B.take(32 * N));
-  // E' = alpha eq(u, .) and EL' = c1 eq(u_L, .): the constant factors of
-  // their terms built into the tables (neither is sent)
-  B.eq_job(ch.u, j.E, nullptr, 0, false, false, &am);
-  B.eq_job(std::vector<Fr>(ch.u.begin() + nH, ch.u.end()), j.EL, nullptr, 0, false, false, &c1);
-  const uint64_t chunks = (N + kLookupInvChunk - 1) / kLookupInvChunk;
   j.nkparts = (uint32_t)((N + 255) / 256);
-  j.kpart = B.dev<uint32_t>(B.take(128ull * j.nkparts));
+  j.kpart = B.dev<uint32_t>(B.take(32ull * j.nkparts));
   j.io = B.dev<uint32_t>(B.take(4 * kLkIoWords));
   j.flag = flag;
   j.proof = proof_dev;
   j.digest = digest_dev;
   j.status = status_dev;
+  // the point u, in the blob (patched to an address by fill_blob)
+  j.u = reinterpret_cast<const uint32_t*>((uint64_t)B.P.lookup_u.size());
+  for (const Fr& x : ch.u) {
+    const Fr xm = fr_to_mont(x);
+    B.P.lookup_u.insert(B.P.lookup_u.end(), xm.w, xm.w + 8);
+  }
+  j.inv_chunk = (uint32_t)std::max<uint64_t>(1, N >> 16);
+  const uint64_t chunks = N / j.inv_chunk;
   j.hist_begin = B.P.lk_hist_blocks;
-  B.P.lk_hist_blocks += (uint32_t)((L.D + 255) / 256);
+  B.P.lk_hist_blocks += j.hist_blocks;
   j.prep_begin = B.P.lk_prep_blocks;
-  B.P.lk_prep_blocks += (uint32_t)((Dp + 255) / 256);
+  if (!j.gather) B.P.lk_prep_blocks += (uint32_t)((Dp + 255) / 256);
   j.tab_begin = B.P.lk_tab_blocks;
-  B.P.lk_tab_blocks += (uint32_t)((chunks + 255) / 256);
+  j.inv_blocks = (uint32_t)((chunks + 255) / 256);
+  B.P.lk_tab_blocks += j.inv_blocks + (uint32_t)((eq_lo + eq_hi + 255) / 256);
   j.mult_begin = B.P.lk_mult_blocks;
   B.P.lk_mult_blocks += j.nkparts;
-  uint32_t wide = 0;
-  while (wide < n && wide < kLookupMaxWide && (Dp >> (wide + 1)) >= kLookupWidePairs) ++wide;
-  j.wide = wide;
-  if (wide) j.part = B.dev<uint32_t>(B.take(((Dp / 2 + kLookupSweepPairs - 1) / kLookupSweepPairs) * 128));
+  if (wide) {
+    uint32_t nb = 0;
+    for (uint32_t k = 0; k < wide; ++k) nb = std::max(nb, lk_round_blocks(n, nH, k));
+    j.part = B.dev<uint32_t>(B.take(4ull * kLookupPartWords * nb));
+  }
   const uint32_t idx = (uint32_t)B.P.lookups.size();
   B.P.lookups.push_back(j);
-  for (int lo = 0; lo < 2; ++lo)
-    if (B.P.lk_wide[lo].size() < wide) {
-      B.P.lk_wide[lo].resize(wide);
-      B.P.lk_wide_blocks[lo].resize(wide, 0);
-    }
   for (uint32_t k = 0; k < wide; ++k) {
-    const uint64_t h = Dp >> (k + 1);
-    const int lo = k >= nH ? 1 : 0;
-    B.P.lk_wide[lo][k].push_back(LookupSweep{idx, B.P.lk_wide_blocks[lo][k]});
-    B.P.lk_wide_blocks[lo][k] += (uint32_t)((h + kLookupSweepPairs - 1) / kLookupSweepPairs);
+    const int kd = k >= nH ? LK_LOW : (j.gather && k < 2 ? (k ? LK_SECOND : LK_FIRST) : (k ? LK_FOLD : LK_PLAIN));
+    auto& lists = B.P.lk_wide[kd];
+    auto& blocks = B.P.lk_wide_blocks[kd];
+    if (lists.size() <= k) {
+      lists.resize(k + 1);
+      blocks.resize(k + 1, 0);
+    }
+    lists[k].push_back(LookupSweep{idx, blocks[k]});
+    blocks[k] += lk_round_blocks(n, nH, k);
   }
 }
 
@@ -208,20 +232,15 @@ vl_status lookup_run(const vl_lookup* ls, uint64_t n, uint64_t seed, uint8_t* ws
                 (unsigned long long)align_up(P.data_end, 256));
   const BlobLayout BL = blob_layout(P);
   fill_blob(P, BL, ws);
-  // the eq tables on the internal side stream and the table inversions on
-  // the internal rounds stream, beside the count kernel
-  hipStream_t s2 = nullptr, s3 = nullptr;
+  // the counts on the internal rounds stream beside the tables
+  hipStream_t s2 = nullptr;
   hipError_t e = rounds_stream_for(s, &s2);
-  if (e == hipSuccess) e = side_stream_for(s, &s3);
   if (e != hipSuccess) return fail(VL_ERR_HIP, "internal streams: %s", hipGetErrorString(e));
-  P.eq_fork = true;
-  e = enqueue_plan(P, BL, ws, s, s2, nullptr, nullptr, s3);
+  e = enqueue_plan(P, BL, ws, s, s2);
   const hipError_t e2 = hipStreamSynchronize(s);
-  // both are joined into s unless the enqueue failed
-  const hipError_t e3 = hipStreamSynchronize(s2), e4 = hipStreamSynchronize(s3);
+  const hipError_t e3 = hipStreamSynchronize(s2);   // joined into s unless the enqueue failed
   if (e == hipSuccess) e = e2;
   if (e == hipSuccess) e = e3;
-  if (e == hipSuccess) e = e4;
   if (e != hipSuccess) return fail(VL_ERR_HIP, "lookup prove: %s", hipGetErrorString(e));
   const int32_t* st = reinterpret_cast<const int32_t*>(oh + st_off);
   for (uint64_t k = 0; k < n; ++k) {

@@ -44,9 +44,9 @@ VL_HD void divsteps30(int32_t& delta, uint32_t f, uint32_t g, int32_t (&t)[4]) {
       const uint32_t sf = ((f ^ c) + c1) & odd;           // g odd: f, or -f in a swapping step
       const uint32_t su = ((u ^ c) + c1) & odd;
       const uint32_t sv = ((v ^ c) + c1) & odd;
-      f = c ? g : f;
-      u = c ? q : u;
-      v = c ? r : v;
+      f = (g & c) | (f & ~c);
+      u = (q & c) | (u & ~c);
+      v = (r & c) | (v & ~c);
       g = (g + sf) >> 1;
       q += su;
       r += sv;

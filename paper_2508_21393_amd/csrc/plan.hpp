@@ -73,7 +73,6 @@ struct Plan {
   std::vector<uint8_t> blob;      // host image of [err flags][eq jobs][points][segments]
   bool persistent = false;        // rounds launched before the contractions
   bool fork = false;              // contraction kinds may use a side stream
-  bool eq_fork = false;           // eq tables on a side stream beside the lookups' table kernels
   uint64_t data_end = 0;          // workspace bytes used
   std::vector<EqJob> eq;
   uint32_t eq_threads = 0;
@@ -91,13 +90,15 @@ struct Plan {
   std::vector<BmmJob> bmms;
   std::vector<std::vector<BmmSweep>> bmm_wide;
   std::vector<uint32_t> bmm_wide_blocks;
-  // lookup arguments: count buffers to zero, the entry-wise and table
-  // launches, wide rounds, the one-workgroup rounds
+  // lookup arguments: count buffers to zero, the points u, the entry-wise and
+  // table launches, wide rounds, the one-workgroup rounds
   std::vector<LookupJob> lookups;
   std::vector<std::pair<uint32_t*, uint64_t>> lookup_zero;
+  std::vector<uint32_t> lookup_u;   // all jobs' points; LookupJob::u holds the word offset until fill_blob
   uint32_t lk_hist_blocks = 0, lk_prep_blocks = 0, lk_tab_blocks = 0, lk_mult_blocks = 0;
-  std::vector<std::vector<LookupSweep>> lk_wide[2];   // per round: jobs binding a high [0] / low [1] bit
-  std::vector<uint32_t> lk_wide_blocks[2];
+  uint32_t lk_hist_lds = 0;
+  std::vector<std::vector<LookupSweep>> lk_wide[LK_KINDS];   // per sweep kind and round
+  std::vector<uint32_t> lk_wide_blocks[LK_KINDS];
 };
 
 struct SegLayout {
@@ -106,9 +107,9 @@ struct SegLayout {
 };
 
 struct BlobLayout {
-  uint64_t err, eq, points, mat_io, evals, reduces, bmms, lookups, total;
+  uint64_t err, eq, points, mat_io, evals, reduces, bmms, lookups, lookup_u, total;
   std::vector<SegLayout> seg;
-  std::vector<uint64_t> bmm_wide, lk_wide[2];
+  std::vector<uint64_t> bmm_wide, lk_wide[LK_KINDS];
 };
 
 // Builds jobs; device addresses are base + workspace offset (base 0 = sizing).
@@ -168,10 +169,8 @@ struct StageEvents {
 // blob_src_dev: device-side address of a pinned host buffer the blob is
 // copied from (graph capture), else the blob goes through the staging ring.
 // s3: a side stream for the contraction kinds of a segment (forked after the
-// eq tables, joined before the finish pass; see fork_contractions) and, with
-// P.eq_fork, for the eq tables of a lookup plan (joined before the first
-// kernel that reads them), or null; unused when ev is given, so that stage
-// times are each kernel's own.
+// eq tables, joined before the finish pass; see fork_contractions), or null;
+// unused when ev is given, so that stage times are each kernel's own.
 hipError_t enqueue_plan(const Plan& P, const BlobLayout& L, uint8_t* dblob, hipStream_t s,
                         hipStream_t s2, StageEvents* ev = nullptr, const void* blob_src_dev = nullptr,
                         hipStream_t s3 = nullptr);

@@ -22,6 +22,150 @@ __device__ __forceinline__ void wave_sum(Fr (&v)[K], uint32_t width) {
   }
 }
 
+// Sums of K elements per thread over a workgroup of NW waves, for K values
+// that end up in lanes 0 .. K - 1 of wave 0 (lane k: the sum of value k,
+// reduced; other lanes hold nothing of use).  Every element is cut into ten
+// 26-bit limbs, whose sums over 64 lanes stay below 2^32, so a wave adds them
+// with one DPP add per limb and level and no carries (wave_sum takes 8 lane
+// shuffles and a field addition per element and level: 4100 cycles for three
+// values on one wave, this about 900); lane k of wave 0 then adds the waves'
+// limbs, carries once and reduces once.  lds: K * 10 * NW words.
+//
+// ten sums side by side (a DPP operand needs two instructions between its
+// write and its read: the other limbs')
+#define VL_DPP_LEVEL(ctrl, rows, bc)                                                                        \
+  _Pragma("unroll") for (int i = 0; i < 10; ++i)                                                            \
+      x[i] += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x[i], ctrl, rows, 0xf, bc);
+__device__ __forceinline__ void row_add10(uint32_t (&x)[10]) {   // a row's sums, in its lane 15
+  VL_DPP_LEVEL(0x111, 0xf, true)    // row_shr:1, 2, 4, 8
+  VL_DPP_LEVEL(0x112, 0xf, true)
+  VL_DPP_LEVEL(0x114, 0xf, true)
+  VL_DPP_LEVEL(0x118, 0xf, true)
+}
+__device__ __forceinline__ void wave_add10(uint32_t (&x)[10]) {   // the wave's sums, in lane 63
+  row_add10(x);
+  VL_DPP_LEVEL(0x142, 0xa, false)   // row_bcast:15, row_bcast:31
+  VL_DPP_LEVEL(0x143, 0xc, false)
+}
+#undef VL_DPP_LEVEL
+// limb sums t_i (i < 10, weight 2^(26 i), signed, total in [0, 2^272)) mod p
+__device__ __forceinline__ Fr fr_of_limb_sums(const uint64_t (&t)[10]) {
+  uint32_t l[11];
+  int64_t c = 0;
+#pragma unroll
+  for (int i = 0; i < 10; ++i) {
+    c += (int64_t)t[i];
+    l[i] = (uint32_t)c & 0x3ffffffu;
+    c >>= 26;
+  }
+  l[10] = (uint32_t)c;
+  uint32_t w[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    const int bit = 32 * k, i = bit / 26, sh = bit - 26 * i;
+    uint32_t v = l[i] >> sh;
+    if (i + 1 < 11) v |= l[i + 1] << (26 - sh);
+    if (i + 2 < 11 && 52 - sh < 32) v |= l[i + 2] << (52 - sh);
+    w[k] = v;
+  }
+  // p / 2^240 is between 29677 and 29678: the quotient by the top words is
+  // exact or one too small
+  const uint32_t q = ((w[8] << 16) | (w[7] >> 16)) / 29678u;
+  Fr r;
+  uint64_t m = 0;
+  uint32_t borrow = 0;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    m += (uint64_t)q * p_limb(k);
+    r.w[k] = sbb32(w[k], (uint32_t)m, borrow, borrow);
+    m >>= 32;
+  }
+  return fr_reduce_once(r);
+}
+// Value sums of a workgroup whose rows of 16 lanes each hold one value: acc
+// holds ten 64-bit limb sums per value (zeroed and read between barriers).
+// acc_add adds the row's 16 elements to value k (the same in the row's lanes)
+// if the row takes part.
+__device__ __forceinline__ void acc_add(unsigned long long* acc, uint32_t k, const Fr& v, bool take = true) {
+  uint32_t x[10];
+#pragma unroll
+  for (int i = 0; i < 10; ++i) {
+    const int bit = 26 * i, j = bit >> 5, sh = bit & 31;
+    x[i] = (sh == 0 ? v.w[j] : (j < 7 ? __builtin_amdgcn_alignbit(v.w[j + 1], v.w[j], sh) : v.w[7] >> sh)) & 0x3ffffffu;
+  }
+  row_add10(x);
+  if (take && (threadIdx.x & 15u) == 15u)
+#pragma unroll
+    for (int i = 0; i < 10; ++i) atomicAdd(acc + 10 * k + i, (unsigned long long)x[i]);
+}
+// The value at X = k (0 .. 3, per lane) of the quadratic with sums[base],
+// [base + 1] its values at 0 and 1 and [base + 2] its leading coefficient:
+// q(2) = 2 q1 - q0 + 2 q2, q(3) = 3 q1 - 2 q0 + 6 q2, formed on the limb sums
+// (up to 2^13 elements each; 2^14 p keeps the total positive).
+__device__ __forceinline__ Fr acc_point(const unsigned long long* acc, uint32_t base, uint32_t k) {
+  const int64_t c0 = k == 0 ? 1 : (k == 1 ? 0 : (k == 2 ? -1 : -2));
+  const int64_t c1 = k == 0 ? 0 : (k == 1 ? 1 : (k == 2 ? 2 : 3));
+  const int64_t c2 = k < 2 ? 0 : (k == 2 ? 2 : 6);
+  uint64_t t[10];
+#pragma unroll
+  for (int i = 0; i < 10; ++i) {
+    constexpr uint32_t P[9] = {VL_P_LIMBS, 0u};
+    const int bit = 26 * i, j = bit >> 5, sh = bit & 31;
+    const uint64_t pl = ((((uint64_t)P[j + 1 < 9 ? j + 1 : 8] << 32) | P[j]) >> sh) & 0x3ffffffu;
+    t[i] = (uint64_t)(c0 * (int64_t)acc[10 * base + i] + c1 * (int64_t)acc[10 * base + 10 + i] +
+                      c2 * (int64_t)acc[10 * base + 20 + i]) + (pl << 14);
+  }
+  return fr_of_limb_sums(t);
+}
+// x in vector registers: the compiler computes products of wave-uniform
+// values on the scalar unit, four instructions per partial product
+__device__ __forceinline__ Fr fr_vgpr(Fr x) {
+#pragma unroll
+  for (int j = 0; j < 8; ++j) asm("" : "+v"(x.w[j]));
+  return x;
+}
+// x of lane + N within rows of 16 lanes (zero past the row)
+template <int N>
+__device__ __forceinline__ Fr fr_row_shl(const Fr& x) {
+  Fr r;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) r.w[j] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x.w[j], 0x100 + N, 0xf, 0xf, true);
+  return r;
+}
+
+template <int K, int NW>
+__device__ __forceinline__ Fr block_sum_lanes(const Fr (&v)[K], uint32_t* lds) {
+  const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    uint32_t x[10];
+#pragma unroll
+    for (int i = 0; i < 10; ++i) {
+      const int bit = 26 * i, j = bit >> 5, sh = bit & 31;
+      x[i] = (sh == 0 ? v[k].w[j] : (j < 7 ? __builtin_amdgcn_alignbit(v[k].w[j + 1], v[k].w[j], sh) : v[k].w[7] >> sh)) &
+             0x3ffffffu;
+    }
+    wave_add10(x);
+    if (lane == 63)
+#pragma unroll
+      for (int i = 0; i < 10; ++i) lds[(k * 10 + i) * NW + wave] = x[i];
+  }
+  __syncthreads();
+  Fr r = fr_zero();
+  if (wave == 0) {
+    const uint32_t k = lane < K ? lane : K - 1;
+    uint64_t t[10];
+#pragma unroll
+    for (int i = 0; i < 10; ++i) {
+      t[i] = 0;
+#pragma unroll
+      for (int q = 0; q < NW; ++q) t[i] += lds[(k * 10 + i) * NW + q];
+    }
+    r = fr_of_limb_sums(t);
+  }
+  return r;
+}
+
 // rounds workgroup: 8 waves, two per SIMD, so that the global sweeps have a
 // second wave to issue from while one waits on its loads or its multiply
 // chains.  At up to 256 VGPRs per wave one such workgroup fills its CU's
@@ -159,6 +303,169 @@ __device__ __forceinline__ void absorb_round_lanes_k(Transcript& tr, const Fr (&
   }
 #pragma unroll
   for (int i = 0; i < 8; ++i) tr.h[i] = h[i];
+}
+
+// LDS words of one workgroup's transcript: the state, a message's values (up
+// to five), the message words and the challenge.
+struct RoundLds {
+  uint32_t st[8];
+  uint32_t v[40];
+  uint32_t w[64];
+  uint32_t r[8];
+};
+__device__ __forceinline__ uint32_t rotv(uint32_t x, int n) { return __builtin_amdgcn_alignbit(x, x, n); }
+__device__ __forceinline__ uint32_t xor3v(uint32_t a, uint32_t b, uint32_t c) { return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96); }
+__device__ __forceinline__ uint32_t sha_s0(uint32_t x) { return xor3v(rotv(x, 7), rotv(x, 18), x >> 3); }
+__device__ __forceinline__ uint32_t sha_s1(uint32_t x) { return xor3v(rotv(x, 17), rotv(x, 19), x >> 10); }
+// one SHA-256 round on s = {a .. h}; wk: message word plus constant
+__device__ __forceinline__ void sha_round(uint32_t (&s)[8], uint32_t wk) {
+  const uint32_t t1 = (s[7] + wk + __builtin_amdgcn_bitop3_b32(s[4], s[5], s[6], 0xca)) +
+                      xor3v(rotv(s[4], 6), rotv(s[4], 11), rotv(s[4], 25));
+  const uint32_t a = t1 + xor3v(rotv(s[0], 2), rotv(s[0], 13), rotv(s[0], 22)) +
+                     __builtin_amdgcn_bitop3_b32(s[0], s[1], s[2], 0xe8);
+  s[7] = s[6]; s[6] = s[5]; s[5] = s[4]; s[4] = s[3] + t1;
+  s[3] = s[2]; s[2] = s[1]; s[1] = s[0]; s[0] = a;
+}
+#define VL_SHA_IV {0x6a09e667u, 0xbb67ae85u, 0x3c6ef372u, 0xa54ff53au, 0x510e527fu, 0x9b05688cu, 0x1f83d9abu, 0x5be0cd19u}
+
+// Word `lane` of the padded message state || five-letter label || K values,
+// written to T.w by each lane (NB blocks, NB <= 4): the label's first four
+// letters are word 8, its last one the top byte of word 9, so word i >= 9
+// holds the last byte of value word i - 10 and the first three of i - 9.
+template <int K>
+__device__ __forceinline__ void tr_message(RoundLds& T, uint32_t label4, uint32_t label1) {
+  constexpr int N = 32 + 5 + 32 * K, NB = (N + 9 + 63) / 64;
+  static_assert(NB <= 4, "one lane per message word");
+  auto word = [&](int d) -> uint32_t { return d < 8 * K ? T.v[d < 0 ? 0 : d] : (d == 8 * K ? 0x80u : 0u); };
+  const int i = (int)(threadIdx.x & 63u);
+  const uint32_t lo = word(i - 9), hi = i >= 10 ? word(i - 10) : label1 << 24;
+  uint32_t m = (hi & 0xff000000u) | ((lo & 0xffu) << 16) | (lo & 0xff00u) | ((lo >> 16) & 0xffu);
+  if (i < 8) m = T.st[i & 7];
+  if (i == 8) m = label4;
+  if (i == 16 * NB - 1) m = N * 8;
+  if (i < 16 * NB) T.w[i] = m;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
+// absorb("final", x_0 .. x_{K-1}) by all 64 lanes of one wave, the K <= 5
+// canonical values in T.v: one block after the other (once per proof, so small
+// code counts: it is fetched for one pass)
+template <int K>
+__device__ __forceinline__ void tr_final(RoundLds& T) {
+  constexpr int NB = (32 + 5 + 32 * K + 9 + 63) / 64;
+  tr_message<K>(T, 0x66696e61u, 0x6cu);   // "fina", "l"
+  uint32_t h[8] = VL_SHA_IV;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) asm("" : "+v"(h[i]));
+  const uint32_t* KK = sha256_k();
+#pragma unroll 1
+  for (int b = 0; b < NB; ++b) {
+    uint32_t z[16], s[8];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      z[i] = T.w[16 * b + i];
+      asm("" : "+v"(z[i]));
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s[i] = h[i];
+#pragma unroll 1
+    for (int it = 0; it < 4; ++it) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        sha_round(s, z[i] + KK[16 * it + i]);
+        z[i] = z[i] + sha_s0(z[(i + 1) & 15]) + z[(i + 9) & 15] + sha_s1(z[(i + 14) & 15]);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) h[i] += s[i];
+  }
+  if ((threadIdx.x & 63u) == 0)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) T.st[i] = h[i];
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+// the state as 32 digest bytes, by one lane
+__device__ __forceinline__ void tr_put_digest(const RoundLds& T, uint8_t* out) {
+#pragma unroll 1
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) out[4 * i + q] = (uint8_t)(T.st[i] >> (24 - 8 * q));
+}
+
+// absorb("round", g(0..K-1)) and squeeze("r") by all 64 lanes of one wave, K =
+// 3 or 4: T.v holds the canonical values (8 K words), T.st the state; leaves
+// the new state in T.st and the challenge, in Montgomery form, in T.r.  The
+// same digests as tr_absorb_frs and tr_squeeze_fixed.
+// Bound by the issue of one wave's instructions, 4 cycles each (14 a hash
+// round and 10 a schedule word), so lanes share what they can: lane i builds
+// message word i; lane b < 3 holds block b's schedule and its chaining value
+// moves from lane to lane; lane c squeezes with counter c, so that a rejected
+// candidate (one in ten) costs nothing.  About 24,500 cycles.
+template <int K>
+__device__ __forceinline__ void tr_round(RoundLds& T) {
+  const uint32_t lane = threadIdx.x & 63u;
+  tr_message<K>(T, 0x726f756eu, 0x64u);   // "roun", "d"
+  const uint32_t blk = min(lane, 2u);
+  const uint32_t* KK = sha256_k();
+  uint32_t w[64];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) w[i] = T.w[16 * blk + i];
+#pragma unroll
+  for (int i = 16; i < 64; ++i) w[i] = w[i - 16] + sha_s0(w[i - 15]) + w[i - 7] + sha_s1(w[i - 2]);
+#pragma unroll
+  for (int i = 0; i < 64; ++i) w[i] += KK[i];
+  uint32_t h[8] = VL_SHA_IV;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) asm("" : "+v"(h[i]));   // vector registers from the start
+#pragma unroll 1
+  for (int b = 0; b < 3; ++b) {
+    uint32_t s[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s[i] = h[i];
+#pragma unroll
+    for (int i = 0; i < 64; ++i) sha_round(s, w[i]);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      h[i] += s[i];
+      // to the next block's lane (row_shr:1); after the last block lane 2
+      // holds the digest, and lane 3 gets it
+      h[i] = (uint32_t)__builtin_amdgcn_update_dpp((int)h[i], (int)h[i], 0x111, 0xf, 0xf, false);
+    }
+  }
+  uint32_t d[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) d[i] = (uint32_t)__builtin_amdgcn_readlane((int)h[i], 3);
+  uint64_t ok = 0;
+  uint32_t g[8];
+  Fr x;
+#pragma unroll 1
+  for (uint32_t base = 0; ok == 0; base += 64) {
+    const uint32_t c = base + lane;
+    uint32_t z[16] = {d[0], d[1], d[2], d[3], d[4], d[5], d[6], d[7], 0x72000000u | ((c & 0xffu) << 16) | (c & 0xff00u),
+                      0x00800000u, 0, 0, 0, 0, 0, 37 * 8};   // "r", the counter (below 2^16), padding
+    uint32_t s[8] = VL_SHA_IV;
+#pragma unroll
+    for (int i = 0; i < 64; ++i) {
+      if (i >= 16) z[i & 15] = z[i & 15] + sha_s0(z[(i + 1) & 15]) + z[(i + 9) & 15] + sha_s1(z[(i + 14) & 15]);
+      sha_round(s, z[i & 15] + KK[i]);
+    }
+    constexpr uint32_t iv[8] = VL_SHA_IV;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      g[i] = s[i] + iv[i];
+      x.w[i] = __builtin_amdgcn_perm(g[i], g[i], 0x00010203u);
+    }
+    x.w[7] &= 0x7fffffffu;
+    ok = __ballot(fr_lt_p(x));
+  }
+  const Fr xm = fr_to_mont(x);
+  if (lane == (uint32_t)__builtin_ctzll(ok))
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      T.st[i] = g[i];
+      T.r[i] = xm.w[i];
+    }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 }
 
 // One round's messages and challenge by wave 0 (all 64 lanes active; gc
