@@ -90,6 +90,7 @@ void plan_bmm(Builder& B, const vl_bmm& b, const BmmChallenges& ch, uint8_t* pro
   uint32_t* packU = B.dev<uint32_t>(B.take((uint64_t)b.D0 * 32));
   uint32_t* packV = B.dev<uint32_t>(B.take((uint64_t)b.D2 * 32));
   uint32_t* E = B.dev<uint32_t>(B.take(8 * Hp * 4));
+  const uint64_t rho_eq = B.P.eq.size();
   B.eq_job(ch.rho, E, nullptr, 0, false, false);            // eq(rho, .), Montgomery
   B.eq_job(ch.u, nullptr, packU, b.D0, true, false);        // e R^2 digits: a lands in Montgomery form
   B.eq_job(ch.v, nullptr, packV, b.D2, false, false);       // e R digits: b and t land canonical
@@ -136,8 +137,9 @@ void plan_bmm(Builder& B, const vl_bmm& b, const BmmChallenges& ch, uint8_t* pro
   }
 
   memcpy(j.st, ch.tr.h, 32);
-  j.nh = nh;
-  j.n1 = n1;
+  j.nh = (uint8_t)nh;
+  j.n1 = (uint8_t)n1;
+  j.rho = reinterpret_cast<const uint32_t*>(rho_eq);
   j.E = E;
   j.a = ta;
   j.b = tb;
@@ -150,7 +152,7 @@ void plan_bmm(Builder& B, const vl_bmm& b, const BmmChallenges& ch, uint8_t* pro
   const uint32_t nv = nh + n1;
   uint32_t wide = 0;
   while (wide < nv && wide < kBmmMaxWide && (N >> (wide + 1)) >= kBmmWidePairs) ++wide;
-  j.wide = wide;
+  j.wide = (uint8_t)wide;
   if (wide) j.part = B.dev<uint32_t>(B.take(((N / 2 + kBmmSweepPairs - 1) / kBmmSweepPairs) * 32 * 4));
   const uint32_t idx = (uint32_t)B.P.bmms.size();
   B.P.bmms.push_back(j);

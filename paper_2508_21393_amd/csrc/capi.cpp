@@ -830,6 +830,7 @@ void fill_blob(Plan& P, const BlobLayout& L, uint8_t* dblob) {
   if (!P.evals.empty()) memcpy(P.blob.data() + L.evals, P.evals.data(), P.evals.size() * sizeof(EvalJob));
   if (!P.reduces.empty())
     memcpy(P.blob.data() + L.reduces, P.reduces.data(), P.reduces.size() * sizeof(ReduceJob));
+  for (BmmJob& j : P.bmms) j.rho = P.eq[reinterpret_cast<uint64_t>(j.rho)].point;
   if (!P.bmms.empty()) memcpy(P.blob.data() + L.bmms, P.bmms.data(), P.bmms.size() * sizeof(BmmJob));
   for (size_t k = 0; k < P.bmm_wide.size(); ++k)
     memcpy(P.blob.data() + L.bmm_wide[k], P.bmm_wide[k].data(), P.bmm_wide[k].size() * sizeof(BmmSweep));
@@ -1097,7 +1098,7 @@ hipError_t enqueue_plan(const Plan& P, const BlobLayout& L, uint8_t* dblob, hipS
       const BmmSweep* lst = reinterpret_cast<const BmmSweep*>(dblob + L.bmm_wide[k]);
       const uint32_t nl = (uint32_t)P.bmm_wide[k].size();
       VL_STAGE(ev, VL_STAGE_PASS1, s, launch_bmm_sweep(bj, lst, nl, P.bmm_wide_blocks[k], (uint32_t)k, s));
-      VL_STAGE(ev, VL_STAGE_ROUNDS, s, launch_bmm_chal(bj, lst, nl, (uint32_t)k, s));
+      VL_STAGE(ev, VL_STAGE_ROUNDS, s, launch_bmm_step(bj, lst, nl, (uint32_t)k, s));
     }
     VL_STAGE(ev, VL_STAGE_ROUNDS, s, launch_bmm_rounds(bj, nb, s));
   }

@@ -166,25 +166,29 @@ constexpr uint32_t reduce_io_words(uint32_t n_rows) { return kReduceIoR + 8 * n_
 // one sumcheck over (head, inner) variables of
 //     sum_{h, w} eq(rho, h) a[h, w] b[h, w],  a[h, w] = A~(h, u, w),
 //     b[h, w] = B~(h, w, v),
-// head variables first (rounds of degree 3, eq(rho, .) folded along), then
-// the inner ones (degree 2, scaled by the folded eq value).  Tables: E =
-// eq(rho, .) (2^nh entries, Montgomery), a (Montgomery) and b (canonical)
-// over 2^(nh + n1) entries, head index most significant, so every round
-// value is canonical.  The first `wide` rounds run as GPU-wide sweeps
-// (bmm_sweep_kernel, one launch per round) each followed by a one-wave
-// transcript step (bmm_chal_kernel); the rest run in one workgroup
-// (bmm_rounds_kernel).  io holds the state handed between the launches.
-constexpr uint32_t kBmmSweepPairs = 256;     // pairs per sweep block (one per thread)
+// head variables first (rounds of degree 3, weighted with the eq table of
+// rho's suffix), then the inner ones (degree 2, times the head rounds'
+// scalar).  Tables: E = eq(rho, .) (2^nh entries, Montgomery, replaced by the
+// suffixes' tables), a (Montgomery) and b (canonical) over 2^(nh + n1)
+// entries, head index most significant, so every round value is canonical.
+// The first `wide` rounds run as GPU-wide sweeps (bmm_sweep_kernel, one launch
+// per round) each followed by a transcript step (bmm_step_kernel); the rest
+// run in one workgroup (bmm_rounds_kernel).  io holds the state handed between
+// the launches.
+constexpr uint32_t kBmmSweepPairs = 256;     // pairs per sweep block (three threads each)
 constexpr uint32_t kBmmWidePairs = 1024;     // rounds with at least this many pairs run wide
 constexpr uint32_t kBmmMaxWide = 24;
 // io words: [0] status (VL_OK while running), [8, 16) transcript state,
-// [16, 24) pending challenge r (Montgomery), [24, 32) the claim c (canonical)
-constexpr uint32_t kBmmIoState = 8, kBmmIoR = 16, kBmmIoC = 24, kBmmIoWords = 32;
+// [16, 24) pending challenge r (Montgomery), [24, 32) the claim c (canonical),
+// [32, 40) the running scalar
+constexpr uint32_t kBmmIoState = 8, kBmmIoR = 16, kBmmIoC = 24, kBmmIoScale = 32, kBmmIoWords = 40;
 struct BmmJob {
   uint32_t st[8];             // transcript state after squeezing rho, u, v
-  uint32_t nh, n1;            // head and inner variables
-  uint32_t wide;              // rounds done by the sweep/chal launches
+  uint8_t nh, n1;             // head and inner variables
+  uint8_t wide;               // rounds done by the sweep/step launches
+  uint8_t pad_;
   uint32_t c_nparts;
+  const uint32_t* rho;        // Montgomery (the point of E's eq job; its index until fill_blob)
   const uint32_t* c_part;     // pass-1 partials of the claim's dot product
   uint32_t* E;                // ld 2^nh
   uint32_t* a;                // ld 2^(nh + n1)
@@ -307,7 +311,7 @@ hipError_t launch_zero_words(uint32_t* p, uint64_t n_words, hipStream_t s);
 hipError_t launch_bmm_start(const BmmJob* jobs_dev, uint32_t n_jobs, hipStream_t s);
 hipError_t launch_bmm_sweep(const BmmJob* jobs_dev, const BmmSweep* list_dev, uint32_t n_list, uint32_t n_blocks,
                             uint32_t round, hipStream_t s);
-hipError_t launch_bmm_chal(const BmmJob* jobs_dev, const BmmSweep* list_dev, uint32_t n_list, uint32_t round,
+hipError_t launch_bmm_step(const BmmJob* jobs_dev, const BmmSweep* list_dev, uint32_t n_list, uint32_t round,
                            hipStream_t s);
 hipError_t launch_bmm_rounds(const BmmJob* jobs_dev, uint32_t n_jobs, hipStream_t s);
 // lookup arguments (lookup.hip)

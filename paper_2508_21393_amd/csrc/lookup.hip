@@ -119,18 +119,6 @@ __device__ __forceinline__ int32_t lk_io_status(const LookupJob& J) {
   return *reinterpret_cast<volatile const int32_t*>(J.io);
 }
 
-__device__ __forceinline__ Fr ld_rec(const uint32_t* p) {   // 8 words, 16-byte aligned
-  const u32x4 a = reinterpret_cast<const u32x4*>(p)[0], b = reinterpret_cast<const u32x4*>(p)[1];
-  return fr_from_limbs(a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w);
-}
-__device__ __forceinline__ void st_rec(uint32_t* p, const Fr& v) {
-  reinterpret_cast<u32x4*>(p)[0] = u32x4{v.w[0], v.w[1], v.w[2], v.w[3]};
-  reinterpret_cast<u32x4*>(p)[1] = u32x4{v.w[4], v.w[5], v.w[6], v.w[7]};
-}
-__device__ __forceinline__ Fr lk_fold(const Fr& r, const Fr& x0, const Fr& x1) {
-  return fr_add(x0, fr_mul(r, fr_sub(x1, x0)));
-}
-
 // eq of u's last m variables at t (m <= lk_nlo(n))
 __device__ __forceinline__ Fr lk_weight(const LookupJob& J, uint32_t m, uint64_t t) {
   return load_sol(J.W + 8 * ((1ull << m) - 1), 1ull << m, t);
@@ -168,8 +156,8 @@ __device__ __forceinline__ LkTerm lk_term(const Fr (&ex)[2], const Fr (&ey)[2], 
   o.X = ex[0];
   o.Y = ey[0];
   if (fold) {
-    o.X = lk_fold(r, ex[0], ex[1]);
-    o.Y = lk_fold(r, ey[0], ey[1]);
+    o.X = fr_fold(r, ex[0], ex[1]);
+    o.Y = fr_fold(r, ey[0], ey[1]);
   }
   o.val = fr_mul(fr_mul(o.X, o.Y), w);
   return o;
@@ -184,23 +172,9 @@ struct LkState {
   Fr sc, sce;
   Fr kc;       // the next high round's constant 2^(nH - rd - 1) K
 };
-// u of round rd and its eq1: om + X slope at X = k of the lane
-__device__ __forceinline__ Fr lk_e(const LookupJob& J, uint32_t rd, uint32_t lane, Fr& om, Fr& slope) {
-  const Fr u = fr_vgpr(lds_or_global_fr(J.u + 8 * rd));
-  om = fr_sub(fr_R(), u);
-  slope = fr_sub(u, om);
-  Fr e = om;
-#pragma unroll
-  for (uint32_t k = 0; k < 3; ++k) {
-    const Fr n = fr_add(e, slope);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) e.w[j] = (lane & 3u) > k ? n.w[j] : e.w[j];
-  }
-  return e;
-}
 __device__ __forceinline__ void lk_set_sce(const LookupJob& J, uint32_t rd, LkState& s, uint32_t lane) {
   Fr om, slope;
-  const Fr e = lk_e(J, rd, lane, om, slope), m = fr_mul(s.sc, e);
+  const Fr e = fr_eq1(fr_vgpr(lds_or_global_fr(J.u + 8 * rd)), lane & 3u, om, slope), m = fr_mul(s.sc, e);
 #pragma unroll
   for (int j = 0; j < 8; ++j) s.sce.w[j] = lane < 8 ? m.w[j] : s.sc.w[j];
 }
@@ -239,13 +213,13 @@ __device__ __forceinline__ bool lk_step(const LookupJob& J, uint32_t rd, const u
     lds_put(T.v + 8 * lane, gm);
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  tr_round<4>(T);
+  tr_round(T, 4);
   return true;
 }
 // the running scalars and the constant for round rd + 1, after r is known
 __device__ __forceinline__ void lk_advance(const LookupJob& J, uint32_t rd, LkState& s, const RoundLds& T, uint32_t lane) {
   Fr om, slope;
-  lk_e(J, rd, lane, om, slope);
+  fr_eq1(fr_vgpr(lds_or_global_fr(J.u + 8 * rd)), 0, om, slope);
   const Fr f = fr_add(om, fr_mul(slope, fr_vgpr(lds_get(T.r)))), m = fr_mul(s.sc, f);
   const bool use = lane < 4 || (lane < 8 && rd >= J.nH);
 #pragma unroll
@@ -514,20 +488,20 @@ __global__ void __launch_bounds__(256) lookup_sweep_kernel(const LookupJob* __re
     Fr a0, a1, s0, s1;
     if (MODE == kSecond) {
       const uint32_t *p0 = lk_row(J, t), *p1 = lk_row(J, t + h), *p2 = lk_row(J, t + 2 * h), *p3 = lk_row(J, t + 3 * h);
-      a0 = lk_fold(r, ld_rec(p0), ld_rec(p2));
-      a1 = lk_fold(r, ld_rec(p1), ld_rec(p3));
-      s0 = lk_fold(r, ld_rec(p0 + 8), ld_rec(p2 + 8));
-      s1 = lk_fold(r, ld_rec(p1 + 8), ld_rec(p3 + 8));
+      a0 = fr_fold(r, ld_rec(p0), ld_rec(p2));
+      a1 = fr_fold(r, ld_rec(p1), ld_rec(p3));
+      s0 = fr_fold(r, ld_rec(p0 + 8), ld_rec(p2 + 8));
+      s1 = fr_fold(r, ld_rec(p1 + 8), ld_rec(p3 + 8));
     } else {
       a0 = load_sol(J.A, ld, t);
       a1 = load_sol(J.A, ld, t + h);
       s0 = load_sol(J.S, ld, t);
       s1 = load_sol(J.S, ld, t + h);
       if (MODE == kFold) {
-        a0 = lk_fold(r, a0, load_sol(J.A, ld, t + 2 * h));
-        a1 = lk_fold(r, a1, load_sol(J.A, ld, t + 3 * h));
-        s0 = lk_fold(r, s0, load_sol(J.S, ld, t + 2 * h));
-        s1 = lk_fold(r, s1, load_sol(J.S, ld, t + 3 * h));
+        a0 = fr_fold(r, a0, load_sol(J.A, ld, t + 2 * h));
+        a1 = fr_fold(r, a1, load_sol(J.A, ld, t + 3 * h));
+        s0 = fr_fold(r, s0, load_sol(J.S, ld, t + 2 * h));
+        s1 = fr_fold(r, s1, load_sol(J.S, ld, t + 3 * h));
       }
     }
     if (MODE != kPlain) {
@@ -765,7 +739,7 @@ __global__ void __launch_bounds__(64 * kTailWaves) lookup_rounds_kernel(const Lo
   const uint32_t k = min(lane, 4u);
   const bool folds = pending && (k < 2 || n - 1 >= J.nH);
   Fr mine = get(k, 0);
-  if (folds) mine = lk_fold(r, mine, get(k, 1));
+  if (folds) mine = fr_fold(r, mine, get(k, 1));
   Fr v[5];
 #pragma unroll
   for (int q = 0; q < 5; ++q) v[q] = readlane_fr(mine, q);
@@ -790,7 +764,7 @@ __global__ void __launch_bounds__(64 * kTailWaves) lookup_rounds_kernel(const Lo
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   if (J.digest) {
-    tr_final<5>(T);
+    tr_absorb_lanes(T, kLblFinal4, kLblFinal1, 5);
     if (lane == 0) tr_put_digest(T, J.digest);
   }
   if (lane == 0) *J.status = VL_OK;

@@ -117,6 +117,46 @@ __device__ __forceinline__ Fr acc_point(const unsigned long long* acc, uint32_t 
   }
   return fr_of_limb_sums(t);
 }
+// the same for a line with sums[base], [base + 1] its values at 0 and 1, at X =
+// k <= 2
+__device__ __forceinline__ Fr acc_line(const unsigned long long* acc, uint32_t base, uint32_t k) {
+  const int64_t c0 = 1 - (int64_t)k, c1 = (int64_t)k;
+  uint64_t t[10];
+#pragma unroll
+  for (int i = 0; i < 10; ++i) {
+    constexpr uint32_t P[9] = {VL_P_LIMBS, 0u};
+    const int bit = 26 * i, j = bit >> 5, sh = bit & 31;
+    const uint64_t pl = ((((uint64_t)P[j + 1 < 9 ? j + 1 : 8] << 32) | P[j]) >> sh) & 0x3ffffffu;
+    t[i] = (uint64_t)(c0 * (int64_t)acc[10 * base + i] + c1 * (int64_t)acc[10 * base + 10 + i]) + (pl << 14);
+  }
+  return fr_of_limb_sums(t);
+}
+// 8 words, 16-byte aligned
+__device__ __forceinline__ Fr ld_rec(const uint32_t* p) {
+  const u32x4 a = reinterpret_cast<const u32x4*>(p)[0], b = reinterpret_cast<const u32x4*>(p)[1];
+  return fr_from_limbs(a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w);
+}
+__device__ __forceinline__ void st_rec(uint32_t* p, const Fr& v) {
+  reinterpret_cast<u32x4*>(p)[0] = u32x4{v.w[0], v.w[1], v.w[2], v.w[3]};
+  reinterpret_cast<u32x4*>(p)[1] = u32x4{v.w[4], v.w[5], v.w[6], v.w[7]};
+}
+// e folded by r with e': e + r (e' - e)
+__device__ __forceinline__ Fr fr_fold(const Fr& r, const Fr& x0, const Fr& x1) {
+  return fr_add(x0, fr_mul(r, fr_sub(x1, x0)));
+}
+// eq1(u, X) = (1 - u) + X (2 u - 1) as om + X slope, and its value at X = k (per lane, k <= 3)
+__device__ __forceinline__ Fr fr_eq1(const Fr& u, uint32_t k, Fr& om, Fr& slope) {
+  om = fr_sub(fr_R(), u);
+  slope = fr_sub(u, om);
+  Fr e = om;
+#pragma unroll
+  for (uint32_t q = 0; q < 3; ++q) {
+    const Fr n = fr_add(e, slope);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) e.w[j] = k > q ? n.w[j] : e.w[j];
+  }
+  return e;
+}
 // x in vector registers: the compiler computes products of wave-uniform
 // values on the scalar unit, four instructions per partial product
 __device__ __forceinline__ Fr fr_vgpr(Fr x) {
@@ -329,13 +369,12 @@ __device__ __forceinline__ void sha_round(uint32_t (&s)[8], uint32_t wk) {
 #define VL_SHA_IV {0x6a09e667u, 0xbb67ae85u, 0x3c6ef372u, 0xa54ff53au, 0x510e527fu, 0x9b05688cu, 0x1f83d9abu, 0x5be0cd19u}
 
 // Word `lane` of the padded message state || five-letter label || K values,
-// written to T.w by each lane (NB blocks, NB <= 4): the label's first four
-// letters are word 8, its last one the top byte of word 9, so word i >= 9
+// written to T.w by each lane (K <= 5: at most four blocks): the label's first
+// four letters are word 8, its last one the top byte of word 9, so word i >= 9
 // holds the last byte of value word i - 10 and the first three of i - 9.
-template <int K>
-__device__ __forceinline__ void tr_message(RoundLds& T, uint32_t label4, uint32_t label1) {
-  constexpr int N = 32 + 5 + 32 * K, NB = (N + 9 + 63) / 64;
-  static_assert(NB <= 4, "one lane per message word");
+// Returns the number of blocks.
+__device__ __forceinline__ uint32_t tr_message(RoundLds& T, uint32_t label4, uint32_t label1, int K) {
+  const int N = 32 + 5 + 32 * K, NB = (N + 9 + 63) / 64;
   auto word = [&](int d) -> uint32_t { return d < 8 * K ? T.v[d < 0 ? 0 : d] : (d == 8 * K ? 0x80u : 0u); };
   const int i = (int)(threadIdx.x & 63u);
   const uint32_t lo = word(i - 9), hi = i >= 10 ? word(i - 10) : label1 << 24;
@@ -343,23 +382,24 @@ __device__ __forceinline__ void tr_message(RoundLds& T, uint32_t label4, uint32_
   if (i < 8) m = T.st[i & 7];
   if (i == 8) m = label4;
   if (i == 16 * NB - 1) m = N * 8;
-  if (i < 16 * NB) T.w[i] = m;
+  T.w[i] = m;
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  return (uint32_t)NB;
 }
 
-// absorb("final", x_0 .. x_{K-1}) by all 64 lanes of one wave, the K <= 5
-// canonical values in T.v: one block after the other (once per proof, so small
-// code counts: it is fetched for one pass)
-template <int K>
-__device__ __forceinline__ void tr_final(RoundLds& T) {
-  constexpr int NB = (32 + 5 + 32 * K + 9 + 63) / 64;
-  tr_message<K>(T, 0x66696e61u, 0x6cu);   // "fina", "l"
+// absorb(label, x_0 .. x_{K-1}) for a five-letter label by all 64 lanes of one
+// wave, the K <= 5 canonical values in T.v: one block after the other (once or
+// twice per proof, so small code counts: it is fetched for one pass)
+constexpr uint32_t kLblFinal4 = 0x66696e61u, kLblFinal1 = 0x6cu;   // "fina", "l"
+constexpr uint32_t kLblClaim4 = 0x636c6169u, kLblClaim1 = 0x6du;   // "clai", "m"
+__device__ __forceinline__ void tr_absorb_lanes(RoundLds& T, uint32_t label4, uint32_t label1, int K) {
+  const uint32_t NB = tr_message(T, label4, label1, K);
   uint32_t h[8] = VL_SHA_IV;
 #pragma unroll
   for (int i = 0; i < 8; ++i) asm("" : "+v"(h[i]));
   const uint32_t* KK = sha256_k();
 #pragma unroll 1
-  for (int b = 0; b < NB; ++b) {
+  for (uint32_t b = 0; b < NB; ++b) {
     uint32_t z[16], s[8];
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
@@ -401,10 +441,9 @@ __device__ __forceinline__ void tr_put_digest(const RoundLds& T, uint8_t* out) {
 // message word i; lane b < 3 holds block b's schedule and its chaining value
 // moves from lane to lane; lane c squeezes with counter c, so that a rejected
 // candidate (one in ten) costs nothing.  About 24,500 cycles.
-template <int K>
-__device__ __forceinline__ void tr_round(RoundLds& T) {
+__device__ __forceinline__ void tr_round(RoundLds& T, int K) {
   const uint32_t lane = threadIdx.x & 63u;
-  tr_message<K>(T, 0x726f756eu, 0x64u);   // "roun", "d"
+  tr_message(T, 0x726f756eu, 0x64u, K);   // "roun", "d": three blocks
   const uint32_t blk = min(lane, 2u);
   const uint32_t* KK = sha256_k();
   uint32_t w[64];
