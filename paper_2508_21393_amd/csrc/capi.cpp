@@ -775,6 +775,12 @@ BlobLayout blob_layout(const Plan& P) {
   o = align_up(o + P.evals.size() * sizeof(EvalJob), 64);
   L.reduces = o;
   o = align_up(o + P.reduces.size() * sizeof(ReduceJob), 64);
+  L.red_wide.resize(P.red_wide.size());
+  for (size_t k = 0; k < P.red_wide.size(); ++k) {
+    L.red_wide[k] = o;
+    o += P.red_wide[k].size() * sizeof(MatSweep);
+  }
+  o = align_up(o, 64);
   L.bmms = o;
   o = align_up(o + P.bmms.size() * sizeof(BmmJob), 64);
   L.bmm_wide.resize(P.bmm_wide.size());
@@ -814,22 +820,33 @@ uint64_t blob_bound(const vl_group* groups, uint64_t n) {
                   256);
 }
 
-// fills the blob (descriptor pointers patched to the workspace copy)
-void fill_blob(Plan& P, const BlobLayout& L, uint8_t* dblob) {
-  P.blob.assign(L.total, 0);
+// the eq jobs' points at their places in the blob (or where an earlier kernel
+// writes them)
+void set_eq_points(Plan& P, const BlobLayout& L, uint8_t* dblob) {
   uint64_t po = L.points;
   for (size_t i = 0; i < P.eq.size(); ++i) {
-    if (P.point_dev[i]) {   // written on the device by an earlier kernel
+    if (P.point_dev[i]) {
       P.eq[i].point = P.point_dev[i];
       continue;
     }
     P.eq[i].point = reinterpret_cast<const uint32_t*>(dblob + po);
-    memcpy(P.blob.data() + po, P.points[i].data(), P.points[i].size() * 4);
     po = align_up(po + P.points[i].size() * 4, 64);
   }
+}
+
+// fills the blob (descriptor pointers patched to the workspace copy)
+void fill_blob(Plan& P, const BlobLayout& L, uint8_t* dblob) {
+  P.blob.assign(L.total, 0);
+  set_eq_points(P, L, dblob);
+  for (size_t i = 0; i < P.eq.size(); ++i)
+    if (!P.point_dev[i] && !P.points[i].empty())
+      memcpy(P.blob.data() + (reinterpret_cast<const uint8_t*>(P.eq[i].point) - dblob), P.points[i].data(),
+             P.points[i].size() * 4);
   if (!P.evals.empty()) memcpy(P.blob.data() + L.evals, P.evals.data(), P.evals.size() * sizeof(EvalJob));
   if (!P.reduces.empty())
     memcpy(P.blob.data() + L.reduces, P.reduces.data(), P.reduces.size() * sizeof(ReduceJob));
+  for (size_t k = 0; k < P.red_wide.size(); ++k)
+    memcpy(P.blob.data() + L.red_wide[k], P.red_wide[k].data(), P.red_wide[k].size() * sizeof(MatSweep));
   for (BmmJob& j : P.bmms) j.rho = P.eq[reinterpret_cast<uint64_t>(j.rho)].point;
   if (!P.bmms.empty()) memcpy(P.blob.data() + L.bmms, P.bmms.data(), P.bmms.size() * sizeof(BmmJob));
   for (size_t k = 0; k < P.bmm_wide.size(); ++k)
@@ -1087,9 +1104,16 @@ hipError_t enqueue_plan(const Plan& P, const BlobLayout& L, uint8_t* dblob, hipS
   if (!P.evals.empty())
     VL_STAGE(ev, VL_STAGE_ROUNDS, s,
              launch_eval(reinterpret_cast<const EvalJob*>(dblob + L.evals), (uint32_t)P.evals.size(), s));
-  if (!P.reduces.empty())
-    VL_STAGE(ev, VL_STAGE_ROUNDS, s,
-             launch_reduce(reinterpret_cast<const ReduceJob*>(dblob + L.reduces), (uint32_t)P.reduces.size(), s));
+  if (!P.reduces.empty()) {
+    const ReduceJob* rj = reinterpret_cast<const ReduceJob*>(dblob + L.reduces);
+    for (size_t k = 0; k < P.red_wide.size(); ++k) {
+      const MatSweep* lst = reinterpret_cast<const MatSweep*>(dblob + L.red_wide[k]);
+      const uint32_t nl = (uint32_t)P.red_wide[k].size();
+      VL_STAGE(ev, VL_STAGE_ROUNDS, s, launch_reduce_sweep(rj, lst, nl, P.red_wide_blocks[k], (uint32_t)k, s));
+      VL_STAGE(ev, VL_STAGE_ROUNDS, s, launch_reduce_step(rj, lst, nl, (uint32_t)k, s));
+    }
+    VL_STAGE(ev, VL_STAGE_ROUNDS, s, launch_reduce(rj, (uint32_t)P.reduces.size(), s));
+  }
   if (!P.bmms.empty()) {
     const BmmJob* bj = reinterpret_cast<const BmmJob*>(dblob + L.bmms);
     const uint32_t nb = (uint32_t)P.bmms.size();

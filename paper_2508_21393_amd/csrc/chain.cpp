@@ -473,7 +473,23 @@ static vl_status chain_run(const vl_lora_layer& L, uint64_t seed, uint8_t* ws, u
   struct RedBufs {
     uint32_t* io;
     uint32_t* ey[kMaxClaims];
+    size_t ex_job[kMaxClaims], ey_job[kMaxClaims];   // plan A's eq jobs: their points
   } rbufs[kTensors];
+  // wide rounds of the reduce job just added; returns the partials' bytes
+  auto wide_rounds = [](Plan& P, ReduceJob& rj) -> uint64_t {
+    const uint32_t idx = (uint32_t)P.reduces.size();
+    rj.wide = 0;
+    while (rj.wide < rj.n && (1u << (rj.n - 1 - rj.wide)) >= kRedWidePairs) ++rj.wide;
+    if (P.red_wide.size() < rj.wide) {
+      P.red_wide.resize(rj.wide);
+      P.red_wide_blocks.resize(rj.wide, 0);
+    }
+    for (uint32_t k = 0; k < rj.wide; ++k) {
+      P.red_wide[k].push_back(MatSweep{idx, P.red_wide_blocks[k]});
+      P.red_wide_blocks[k] += (1u << (rj.n - 1 - k)) / kRedSweepPairs;
+    }
+    return rj.wide ? 4ull * kRedPartWords * ((1u << (rj.n - 1)) / kRedSweepPairs) : 0;
+  };
   Plan PA;
   const uint64_t s4a = build_plan(PA, T, ws, [&](Builder& B) {
     B.P.n_err = kTensors;
@@ -495,18 +511,22 @@ static vl_status chain_run(const vl_lora_layer& L, uint64_t seed, uint8_t* ws, u
         const Claim& c = claims[j][k];
         const Fr rm = fr_to_mont(rho[j][k]);
         memcpy(rj.coef[k], rm.w, 32);
-        rj.a[k] = B.dev<uint32_t>(B.take(8 * LR * 4));
+        rj.w[k] = B.dev<uint32_t>(B.take(8 * LR * 4));
         rj.b[k] = B.dev<uint32_t>(B.take(8 * LR * 4));
         uint32_t* packY = B.dev<uint32_t>(B.take((uint64_t)m.cols * 32));
         rbufs[j].ey[k] = B.dev<uint32_t>(B.take(8 * LC * 4));
-        B.eq_job(c.x, rj.a[k], nullptr, 0, false, false);              // eq(x_k, .), Montgomery
+        rbufs[j].ex_job[k] = B.P.eq.size();
+        B.eq_job(c.x, rj.w[k], nullptr, 0, false, false);              // eq(x_k, .), Montgomery
+        rbufs[j].ey_job[k] = B.P.eq.size();
         B.eq_job(c.y, rbufs[j].ey[k], packY, m.cols, false, true);     // eq(y_k, .): canonical + e R digits
         B.contract(m.p, m.dtype, digits_for(m.dtype), m.cols, false, m.rows, m.cols, packY, rj.b[k], LR, LR, err);
       }
       rj.proof = od ? od + roff[j] : nullptr;
+      wide_rounds(B.P, rj);
       B.P.reduces.push_back(rj);
     }
   });
+  uint32_t* packs[kTensors];
   Plan PB;
   const uint64_t s4b = build_plan(PB, T, ws + (sizing ? 0 : align_up(s4a, 256)), [&](Builder& B) {
     B.P.n_err = kTensors;
@@ -523,13 +543,15 @@ static vl_status chain_run(const vl_lora_layer& L, uint64_t seed, uint8_t* ws, u
       rj.io = rbufs[j].io;
       uint32_t* packR = B.dev<uint32_t>(B.take((uint64_t)m.rows * 32));
       rj.a[0] = B.dev<uint32_t>(B.take(8 * LC * 4));
-      rj.bsum = B.dev<uint32_t>(B.take(8 * LC * 4));
-      for (uint32_t k = 0; k < K; ++k) rj.b[k] = rbufs[j].ey[k];
+      for (uint32_t k = 0; k < K; ++k) rj.w[k] = rbufs[j].ey[k];
       B.eq_job_dev(nR, rbufs[j].io ? rbufs[j].io + kReduceIoR : nullptr, nullptr, packR, m.rows, true, false);
       B.contract(m.p, m.dtype, digits_for(m.dtype), m.cols, true, m.cols, m.rows, packR, rj.a[0], LC, LC, err);
       rj.proof = od ? od + roff[j] + 32ull * (3ull * nR + K) : nullptr;
       rj.digest = od ? od + dg_off + 32 * (kGroups + j) : nullptr;
       rj.status = status_d ? status_d + 12 + j : nullptr;
+      const uint64_t pb = wide_rounds(B.P, rj);
+      if (pb) rj.part = B.dev<uint32_t>(B.take(pb));
+      packs[j] = packR;
       B.P.reduces.push_back(rj);
     }
   });
@@ -545,8 +567,19 @@ static vl_status chain_run(const vl_lora_layer& L, uint64_t seed, uint8_t* ws, u
       return fail(VL_ERR_WORKSPACE, "workspace of %llu bytes, %llu needed", (unsigned long long)ws_bytes,
                   (unsigned long long)align_up(s4, 256));
     const BlobLayout LA = blob_layout(PA), LB = blob_layout(PB);
-    fill_blob(PA, LA, ws);
+    // phase 1's sweep partials (at most kRedPartWords words per 256 rows, of
+    // the at least 512 there are) go where plan B's eq job later writes the
+    // digits of eq(r, .) (8 words a row)
+    for (int j = 0; j < kTensors; ++j) PA.reduces[j].part = packs[j];
+    // the points are the eq jobs'; fill_blob gives them their addresses
     uint8_t* wsb = ws + align_up(s4a, 256);
+    set_eq_points(PA, LA, ws);
+    for (int j = 0; j < kTensors; ++j)
+      for (uint32_t k = 0; k < PA.reduces[j].K; ++k) {
+        PA.reduces[j].pt[k] = PA.eq[rbufs[j].ex_job[k]].point;
+        PB.reduces[j].pt[k] = PA.eq[rbufs[j].ey_job[k]].point;
+      }
+    fill_blob(PA, LA, ws);
     fill_blob(PB, LB, wsb);
     hipError_t e = enqueue_plan(PA, LA, ws, s, s, nullptr);
     if (e == hipSuccess) e = enqueue_plan(PB, LB, wsb, s, s, nullptr);

@@ -132,35 +132,47 @@ struct EvalJob {
 };
 
 // One phase of a claim reduction (several claims M~(x_k, y_k) = v_k on one
-// matrix turned into one), run by one workgroup:
+// matrix turned into one):
 //  phase 1: a sumcheck over the row variables of
 //           sum_k rho_k sum_i eq(x_k, i) t_k(i),  t_k(i) = sum_j M[i][j] eq(y_k, j),
-//           tables a[k] = eq(x_k, .) (Montgomery) and b[k] = t_k (canonical);
-//           then the values t_k(r) are sent and absorbed, sigma_1..sigma_K
-//           squeezed; r (Montgomery), sigma and the state go to io
+//           weights w[k] = eq(x_k, .) (Montgomery), tables b[k] = t_k
+//           (canonical); then the values t_k(r) are sent and absorbed,
+//           sigma_1..sigma_K squeezed; r (Montgomery), sigma and the state go
+//           to io
 //  phase 2: a sumcheck over the column variables of
 //           sum_j M~(r, j) sum_k sigma_k eq(y_k, j),
-//           a[0] = M~(r, .) (Montgomery), b[k] = eq(y_k, .) (canonical), their
-//           sigma-combination built into bsum; then M~(r, s) is sent
-constexpr int kMaxClaims = 4;
+//           weights w[k] = eq(y_k, .) (canonical), table a[0] = M~(r, .)
+//           (Montgomery); then M~(r, s) is sent
+// The first `wide` rounds run as GPU-wide sweeps and a one-workgroup step.
+constexpr int kMaxClaims = 3;
+constexpr uint32_t kMaxReduceClaims = kMaxClaims;
+constexpr uint32_t kRedSweepPairs = 128;     // pairs per sweep block (two threads per claim each)
+// rounds with at least this many pairs run wide: a sweep and a step take about
+// 28 us, 512 pairs of three claims in one workgroup about 40
+constexpr uint32_t kRedWidePairs = 512;
+constexpr uint32_t kRedPartWords = 16 * kMaxReduceClaims;
 struct ReduceJob {
   uint32_t st[8];             // phase 1: transcript state after the rho squeezes
   uint32_t coef[kMaxClaims][8];   // phase 1: rho_k, Montgomery
   uint32_t phase;             // 1 or 2
   uint32_t K;                 // claims
   uint32_t n;                 // rounds (row or column variables)
-  uint32_t pad_;
+  uint32_t wide;
   uint64_t ld;                // table stride, 2^n
-  uint32_t* a[kMaxClaims];
+  uint32_t* a[1];
   uint32_t* b[kMaxClaims];
-  uint32_t* bsum;             // phase 2: sum_k sigma_k b[k] (2^n entries)
-  uint32_t* io;               // [state: 8][sigma: kMaxClaims x 8][r: n_rows x 8] words
+  uint32_t* w[kMaxClaims];
+  const uint32_t* pt[kMaxClaims];   // the points x_k or y_k, Montgomery (their eq jobs')
+  uint32_t* part;             // sweep partials, 2 K elements per block
+  uint32_t* io;               // [state: 8][running scalars, then sigma: kMaxClaims x 8][r: n_rows x 8] words
   uint8_t* proof;             // this phase's proof bytes
   uint8_t* digest;            // phase 2: final state of the reduction's branch
   int32_t* status;            // phase 2: VL_OK when done
 };
+// phase 2 keeps the pending challenge of its wide rounds in the first r slot
+// (phase 1's r has been read by then)
 constexpr uint32_t kReduceIoSigma = 8, kReduceIoR = 8 + 8 * kMaxClaims;
-constexpr uint32_t reduce_io_words(uint32_t n_rows) { return kReduceIoR + 8 * n_rows; }
+constexpr uint32_t reduce_io_words(uint32_t n_rows) { return kReduceIoR + 8 * (n_rows ? n_rows : 1); }
 
 // One per-head batched product (vl_bmm_prove): C_h = A_h B_h for h < H as
 // one sumcheck over (head, inner) variables of
@@ -292,6 +304,10 @@ struct LookupSweep {
 // host launchers (kernels.hip)
 hipError_t launch_eval(const EvalJob* jobs_dev, uint32_t n_jobs, hipStream_t s);
 hipError_t launch_reduce(const ReduceJob* jobs_dev, uint32_t n_jobs, hipStream_t s);
+hipError_t launch_reduce_sweep(const ReduceJob* jobs_dev, const MatSweep* list_dev, uint32_t n_list, uint32_t n_blocks,
+                               uint32_t round, hipStream_t s);
+hipError_t launch_reduce_step(const ReduceJob* jobs_dev, const MatSweep* list_dev, uint32_t n_list, uint32_t round,
+                              hipStream_t s);
 hipError_t launch_eq(const EqJob* jobs_dev, uint32_t n_jobs, uint32_t n_threads, hipStream_t s);
 hipError_t launch_contract(int kind, const ContractJob* jobs_dev, uint32_t n_jobs, uint32_t n_tasks,
                            hipStream_t s);

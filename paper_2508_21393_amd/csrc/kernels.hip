@@ -857,146 +857,280 @@ __global__ void __launch_bounds__(256) eval_kernel(const EvalJob* __restrict__ j
   }
 }
 
-// absorb(label, x_0 .. x_{K-1}) for a run-time K <= kMaxClaims
+// absorb(label, x_0 .. x_{K-1}) for a run-time K <= kMaxReduceClaims
 template <int LN>
 __device__ __forceinline__ void absorb_k(Transcript& tr, const char (&label)[LN], const Fr* xs, uint32_t K) {
   switch (K) {
     case 1: { const Fr a[1] = {xs[0]}; tr_absorb_frs(tr, label, a); break; }
     case 2: { const Fr a[2] = {xs[0], xs[1]}; tr_absorb_frs(tr, label, a); break; }
-    case 3: { const Fr a[3] = {xs[0], xs[1], xs[2]}; tr_absorb_frs(tr, label, a); break; }
-    default: { const Fr a[4] = {xs[0], xs[1], xs[2], xs[3]}; tr_absorb_frs(tr, label, a); break; }
+    default: { const Fr a[3] = {xs[0], xs[1], xs[2]}; tr_absorb_frs(tr, label, a); break; }
   }
 }
 
-// One workgroup per reduction phase (ReduceJob).  Both phases are sumchecks
-// of sum_t sum_k a_k[t] b_k[t] over tables in global memory: the a tables in
-// Montgomery form, the b tables canonical, so every product and round value
-// is canonical (as in the rounds kernel).  Round i > 0 folds the tables by
-// the previous challenge in the same sweep that sums the round's pairs (each
-// thread reads and writes only its own entries).  Wave 0 runs the
-// transcript: it writes g(0), g(1), g(2), absorbs them and squeezes r.
-__global__ void __launch_bounds__(kRoundsBlock) reduce_kernel(const ReduceJob* __restrict__ jobs) {
-  const ReduceJob& J = jobs[blockIdx.x];
-  __shared__ uint32_t red[3 * 8 * (kRoundsBlock / kWave)];
-  __shared__ uint32_t bcast[8];
-  const uint32_t tid = threadIdx.x, NT = blockDim.x;
-  const uint32_t wave = tid >> 6, lane = tid & 63u;
-  const uint32_t K = J.phase == 1 ? J.K : 1;
-  const uint64_t ld = J.ld, len = 1ull << J.n;
-  uint32_t* A[kMaxClaims];
-  uint32_t* Bt[kMaxClaims];
-  for (uint32_t k = 0; k < kMaxClaims; ++k) {
-    A[k] = J.a[k];
-    Bt[k] = J.b[k];
-  }
-  Transcript tr;
+// Claim reductions (ReduceJob).  Both phases are sumchecks of
+//     sum_k s_k sum_t eq(p_k, t) B_k(t),
+// B_k = t_k in phase 1 and the one table M~(r, .) in phase 2.  The challenges
+// enter eq(p_k, .) only through a running scalar (see lookup.hip), so a round
+// sums the line sum_t eq(p_k's suffix, t) B_k(X, t) by its values at 0 and 1, and
+//     g(X) = sum_k sc_k eq1(p_{k,rd}, X) (line_k at X).
+// One of the tables and its weights is in Montgomery form and the other
+// canonical, so every round value is canonical.  A table W_k starts as
+// eq(p_k, .); the weights of a round are the sums of W_k's two halves
+// (eq1(p, 0) + eq1(p, 1) = 1), written over its lower half.
+
+// Term (k, pt) of pair t: the fold by r of the entries e (and e' 2 h further
+// on) and its product with the weight w0 + w1; two products a term.
+struct RedTerm {
+  Fr B, w, val;
+};
+__device__ __forceinline__ RedTerm red_term(const Fr (&e)[2], bool fold, const Fr& r, const Fr& w0, const Fr& w1) {
+  RedTerm o;
+  o.B = fold ? fr_fold(r, e[0], e[1]) : e[0];
+  o.w = fr_add(w0, w1);
+  o.val = fr_mul(o.B, o.w);
+  return o;
+}
+// Wave 0's state: lane 4 k + x has claim k's running scalar and that times
+// eq1(p_{k,rd}, x).
+struct RedState {
+  Fr sc, sce;
+};
+__device__ __forceinline__ uint32_t red_claim(const ReduceJob& J, uint32_t lane) { return min(lane >> 2, J.K - 1); }
+__device__ __forceinline__ void red_set_sce(const ReduceJob& J, uint32_t rd, RedState& s, uint32_t lane) {
+  if (rd >= J.n) return;
+  Fr om, slope;
+  s.sce = fr_mul(s.sc, fr_eq1(lds_or_global_fr(J.pt[red_claim(J, lane)] + 8 * rd), lane & 3u, om, slope));
+  if (lane >= 4 * J.K) s.sce = fr_zero();
+}
+__device__ __forceinline__ void red_load_state(const ReduceJob& J, uint32_t rd, RedState& s, RoundLds& T, uint32_t lane) {
+  const uint32_t k = red_claim(J, lane);
+  if (J.phase == 1 && rd == 0) {
 #pragma unroll
-  for (int i = 0; i < 8; ++i) tr.h[i] = J.phase == 1 ? J.st[i] : J.io[i];
-  if (J.phase == 1) {
-    // scale the eq(x_k, .) tables by rho_k: the round sums then need no
-    // per-claim coefficient, and folding keeps the scale
-    for (uint32_t k = 0; k < K; ++k) {
-      const Fr rho = lds_or_global_fr(J.coef[k]);
-      for (uint64_t t = tid; t < len; t += NT) store_sol(A[k], ld, t, fr_mul(rho, load_sol(A[k], ld, t)));
-    }
+    for (int j = 0; j < 8; ++j) s.sc.w[j] = J.coef[k][j];
   } else {
-    // b = sum_k sigma_k eq(y_k, .), canonical
-    Fr sig[kMaxClaims];
-    for (uint32_t k = 0; k < J.K; ++k) sig[k] = lds_or_global_fr(J.io + kReduceIoSigma + 8 * k);
-    for (uint64_t t = tid; t < len; t += NT) {
-      Fr acc = fr_zero();
-      for (uint32_t k = 0; k < J.K; ++k) acc = fr_add(acc, fr_mul(sig[k], load_sol(J.b[k], ld, t)));
-      store_sol(J.bsum, ld, t, acc);
-    }
-    Bt[0] = J.bsum;
+    s.sc = lds_or_global_fr(J.io + kReduceIoSigma + 8 * k);
   }
-  __threadfence_block();
+  if (lane < 8) {
+    T.st[lane] = J.phase == 1 && rd == 0 ? J.st[lane] : J.io[lane];
+    T.r[lane] = rd ? J.io[kReduceIoR + 8 * (J.phase == 1 ? rd - 1 : 0) + lane] : 0u;
+  }
+  red_set_sce(J, rd, s, lane);
+}
+__device__ __forceinline__ void red_advance(const ReduceJob& J, uint32_t rd, RedState& s, const RoundLds& T, uint32_t lane) {
+  Fr om, slope;
+  fr_eq1(lds_or_global_fr(J.pt[red_claim(J, lane)] + 8 * rd), 0, om, slope);
+  s.sc = fr_mul(s.sc, fr_add(om, fr_mul(slope, fr_vgpr(lds_get(T.r)))));
+  red_set_sce(J, rd + 1, s, lane);
+}
+// Round rd by wave 0: acc holds the limb sums of the lines at 0 and 1 of every
+// claim.  Lanes 0 .. 2 write g(0), g(1), g(2); absorbed, r squeezed into T.
+__device__ __forceinline__ void red_step(const ReduceJob& J, uint32_t rd, const unsigned long long* acc,
+                                         const RedState& s, RoundLds& T, uint32_t lane) {
+  Fr v = fr_mul(acc_line(acc, 2 * red_claim(J, lane), min(lane & 3u, 2u)), s.sce);
+  v = fr_add(fr_add(v, fr_row_shl<4>(v)), fr_add(fr_row_shl<8>(v), fr_row_shl<12>(v)));
+  if (lane < 3) {
+    put_canon(J.proof + 96ull * rd + 32 * lane, v);
+    lds_put(T.v + 8 * lane, v);
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  tr_round(T, 3);
+}
+
+// One wide round: the listed jobs, kRedSweepPairs pairs per block; the
+// waves take the terms (claim, point) of the pairs in turn.  Tables fold in
+// place: every wave reads its terms' entries before any wave writes.
+__global__ void __launch_bounds__(2 * kRedSweepPairs * kMaxReduceClaims) reduce_sweep_kernel(
+    const ReduceJob* __restrict__ jobs, const MatSweep* __restrict__ list, uint32_t n_list, uint32_t n_blocks,
+    uint32_t rd) {
+  __shared__ unsigned long long acc[20 * kMaxReduceClaims + 10];
+  const uint32_t blk = blockIdx.x;
+  if (blk >= n_blocks) return;
+  uint32_t lo = 0, hi = n_list;
+  while (hi - lo > 1) {
+    const uint32_t mid = (lo + hi) >> 1;
+    if (list[mid].block_begin <= blk) lo = mid; else hi = mid;
+  }
+  const MatSweep& S = list[lo];
+  const ReduceJob& J = jobs[S.job];
+  const uint32_t tid = threadIdx.x, term = tid / kRedSweepPairs, k = term >> 1, pt = term & 1u;
+  const uint64_t ld = J.ld, h = 1ull << (J.n - 1 - rd);   // a multiple of kRedSweepPairs
+  const uint64_t t = (uint64_t)(blk - S.block_begin) * kRedSweepPairs + tid % kRedSweepPairs;
+  const uint64_t i0 = pt ? t + h : t;
+  const bool fold = rd > 0, mine = k < J.K;
+  Fr e[2], w0 = fr_zero(), w1 = fr_zero(), r = fr_zero();
+  e[0] = e[1] = fr_zero();
+  uint32_t* tab = nullptr;
+  if (mine) {
+    tab = J.phase == 1 ? J.b[k] : J.a[0];
+    e[0] = load_sol(tab, ld, i0);
+    if (fold) {
+      e[1] = load_sol(tab, ld, i0 + 2 * h);
+      r = lds_or_global_fr(J.io + kReduceIoR + 8 * (J.phase == 1 ? rd - 1 : 0));
+    }
+    w0 = load_sol(J.w[k], ld, t);
+    w1 = load_sol(J.w[k], ld, t + h);
+  }
+  if (tid < 20 * kMaxReduceClaims + 10) acc[tid] = 0;
+  __syncthreads();   // everything read (and acc zeroed)
+  if (mine) {
+    const RedTerm o = red_term(e, fold, r, w0, w1);
+    if (fold && (J.phase == 1 || k == 0)) store_sol(tab, ld, i0, o.B);
+    if (pt == 0) store_sol(J.w[k], ld, t, o.w);
+    acc_add(acc, term, o.val);
+  }
   __syncthreads();
-  uint8_t* out = J.proof;
-  bool pending = false;
-  Fr r = fr_zero();
-  for (uint32_t rd = 0; rd < J.n; ++rd) {
-    const uint32_t h = 1u << (J.n - 1 - rd);
-    Fr g[3];
-    g[0] = g[1] = g[2] = fr_zero();
-    for (uint32_t t = tid; t < h; t += NT) {
-      for (uint32_t k = 0; k < K; ++k) {
-        Fr a0 = load_sol(A[k], ld, t), a1 = load_sol(A[k], ld, t + h);
-        Fr b0 = load_sol(Bt[k], ld, t), b1 = load_sol(Bt[k], ld, t + h);
-        if (pending) {
-          // entries t, t + h of the folded table come from t, t + 2h and
-          // t + h, t + 3h of the table as it stands (half-size 2h)
-          const Fr rr2[2] = {r, r};
-          const Fr da[2] = {fr_sub(load_sol(A[k], ld, t + 2 * h), a0), fr_sub(load_sol(A[k], ld, t + 3 * h), a1)};
-          const Fr db[2] = {fr_sub(load_sol(Bt[k], ld, t + 2 * h), b0), fr_sub(load_sol(Bt[k], ld, t + 3 * h), b1)};
-          Fr fa[2], fb[2];
-          fr_mul_n<2>(rr2, da, fa);
-          fr_mul_n<2>(rr2, db, fb);
-          a0 = fr_add(a0, fa[0]);
-          a1 = fr_add(a1, fa[1]);
-          b0 = fr_add(b0, fb[0]);
-          b1 = fr_add(b1, fb[1]);
-          store_sol(A[k], ld, t, a0);
-          store_sol(A[k], ld, t + h, a1);
-          store_sol(Bt[k], ld, t, b0);
-          store_sol(Bt[k], ld, t + h, b1);
-        }
-        const Fr x[3] = {a0, a1, at_two(a0, a1)}, y[3] = {b0, b1, at_two(b0, b1)};
-        Fr pr[3];
-        fr_mul_n<3>(x, y, pr);
+  if (tid < 64) {
+    const Fr v = acc_line(acc, min(tid, 2 * kMaxReduceClaims - 1), 0);
+    if (tid < 2 * J.K) st_rec(J.part + (uint64_t)(blk - S.block_begin) * kRedPartWords + 8 * tid, v);
+  }
+}
+
+// The transcript step after a wide round, one workgroup per job: wave q adds
+// the blocks' value q, wave 0 runs the round's step.
+__global__ void __launch_bounds__(128 * kMaxReduceClaims) reduce_step_kernel(const ReduceJob* __restrict__ jobs,
+                                                                            const MatSweep* __restrict__ list,
+                                                                            uint32_t rd) {
+  __shared__ unsigned long long acc[20 * kMaxReduceClaims + 10];
+  __shared__ RoundLds T;
+  const ReduceJob& J = jobs[list[blockIdx.x].job];
+  const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = tid & 63u;
+  const uint32_t nblocks = (1u << (J.n - 1 - rd)) / kRedSweepPairs;
+  if (tid < 20 * kMaxReduceClaims + 10) acc[tid] = 0;
+  RedState s;
+  if (wave == 0) red_load_state(J, rd, s, T, lane);
+  __syncthreads();
+  if (wave < 2 * J.K) {
+    Fr v = fr_zero();
+    for (uint32_t i = lane; i < nblocks; i += 64) v = fr_add(v, ld_rec(J.part + (uint64_t)kRedPartWords * i + 8 * wave));
+    acc_add(acc, wave, v);
+  }
+  __syncthreads();
+  if (wave != 0) return;
+  red_step(J, rd, acc, s, T, lane);
+  red_advance(J, rd, s, T, lane);
+  if (lane < 8) {
+    J.io[lane] = T.st[lane];
+    J.io[kReduceIoR + 8 * (J.phase == 1 ? rd : 0) + lane] = T.r[lane];
+  }
+  if ((lane & 3u) == 0 && lane < 4 * J.K)
 #pragma unroll
-        for (int q = 0; q < 3; ++q) g[q] = fr_add(g[q], pr[q]);
-      }
-    }
-    __threadfence_block();   // the folded entries, for the next sweep
-    block_sum_w0<3>(g, red);
+    for (int j = 0; j < 8; ++j) J.io[kReduceIoSigma + 2 * lane + j] = s.sc.w[j];
+}
+
+// The rounds left after the wide ones, one workgroup per job, and the phase's
+// end.  The tables come from global memory until their first fold (at most
+// 2 kRedWidePairs entries then), the weights until their first sums, and live
+// in LDS after that.  The rows of 16 lanes of waves 1 .. 11 take the terms of
+// 16 pairs at a time; wave 0 runs the transcript.  With all rounds in this
+// workgroup, both tables folded and three products a pair, the 7 tensors of
+// the FFN-up layer took 603 and 664 us in the two phases.
+constexpr uint32_t kRedTailWaves = 12;
+static_assert(20 * kMaxReduceClaims <= 64, "one wave zeroes the sums");
+__global__ void __launch_bounds__(64 * kRedTailWaves) reduce_kernel(const ReduceJob* __restrict__ jobs) {
+  const ReduceJob& J = jobs[blockIdx.x];
+  constexpr uint32_t kLen = kRedWidePairs;                                  // entries of the first table buffer
+  __shared__ uint32_t buf[kMaxReduceClaims][8 * (kLen + kLen / 2)];         // tables: two buffers each
+  __shared__ uint32_t wbuf[kMaxReduceClaims][8 * (kLen / 2 + kLen / 4)];    // weights: two buffers each
+  __shared__ unsigned long long acc[20 * kMaxReduceClaims + 10];
+  __shared__ RoundLds T;
+  const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = tid & 63u;
+  const uint32_t n = J.n, K = J.K, wide = J.wide, phase = J.phase, ntab = phase == 1 ? K : 1;
+  const uint64_t ld = J.ld;
+  bool pending = wide > 0;
+  int at = -1, wat = -1;   // the tables' and the weights' place: -1 global, else buffer 0 or 1
+  auto get = [&](uint32_t k, uint32_t i) {
+    if (at >= 0) return load_sol(buf[k] + (at ? 8 * kLen : 0), at ? kLen / 2 : kLen, i);
+    return load_sol(phase == 1 ? J.b[k] : J.a[0], ld, i);
+  };
+  RedState s;
+  if (wave == 0) red_load_state(J, wide, s, T, lane);
+  if (tid < 20 * kMaxReduceClaims + 10) acc[tid] = 0;
+  __syncthreads();
+#pragma unroll 1
+  for (uint32_t rd = wide; rd < n; ++rd) {
+    const uint32_t h = 1u << (n - 1 - rd);
     if (wave == 0) {
-      const Fr rr = round_challenge(tr, g, out, lane);
-      if (lane == 0) {
-        lds_put(bcast, rr);
-        if (J.phase == 1)
-#pragma unroll
-          for (int j = 0; j < 8; ++j) J.io[kReduceIoR + 8 * rd + j] = rr.w[j];   // Montgomery, for eq(r, .)
+      if (rd > wide) red_advance(J, rd - 1, s, T, lane);
+    } else {
+      const uint32_t chunks = (h + 15) / 16, units = 2 * K * chunks;
+      const Fr r = lds_get(T.r);
+#pragma unroll 1
+      for (uint32_t q0 = 4 * (wave - 1); q0 < units; q0 += 4 * (kRedTailWaves - 1)) {
+        const uint32_t q = q0 + (lane >> 4), term = q / chunks, k = term >> 1, pt = term & 1u;
+        const uint32_t t = (q % chunks) * 16 + (lane & 15u), tab = phase == 1 ? k : 0;
+        const bool take = q < units;
+        RedTerm o;
+        o.val = fr_zero();
+        if (take && t < h) {
+          const uint32_t i0 = pt ? t + h : t;
+          Fr e[2], w0, w1;
+          e[0] = get(tab, i0);
+          e[1] = fr_zero();
+          if (pending) e[1] = get(tab, i0 + 2 * h);
+          if (wat >= 0) {
+            const uint32_t* w = wbuf[k] + (wat ? 4 * kLen : 0);
+            w0 = load_sol(w, wat ? kLen / 4 : kLen / 2, t);
+            w1 = load_sol(w, wat ? kLen / 4 : kLen / 2, t + h);
+          } else {
+            w0 = load_sol(J.w[k], ld, t);
+            w1 = load_sol(J.w[k], ld, t + h);
+          }
+          o = red_term(e, pending, r, w0, w1);
+          if (pending && (phase == 1 || k == 0))
+            store_sol(buf[tab] + (at == 0 ? 8 * kLen : 0), at == 0 ? kLen / 2 : kLen, i0, o.B);
+          if (pt == 0)
+            store_sol(wbuf[k] + (wat == 0 ? 4 * kLen : 0), wat == 0 ? kLen / 4 : kLen / 2, t, o.w);
+        }
+        acc_add(acc, term, o.val, take);
       }
     }
-    out += 96;
-    __syncthreads();
-    r = lds_get(bcast);
+    if (pending) at = at == 0 ? 1 : 0;
+    wat = wat == 0 ? 1 : 0;
+    __syncthreads();   // the sums, the folded entries and the next weights
+    if (wave == 0) {
+      red_step(J, rd, acc, s, T, lane);
+      if (lane < 20 * kMaxReduceClaims) acc[lane] = 0;
+      if (phase == 1 && lane < 8) J.io[kReduceIoR + 8 * rd + lane] = T.r[lane];   // Montgomery, for eq(r, .)
+    }
+    __syncthreads();   // r and the zeroed sums
     pending = true;
   }
-  // the last challenge folds the remaining pair of each table
-  if (tid == 0) {
-    Fr fin[kMaxClaims];
-    for (uint32_t k = 0; k < K; ++k) {
-      if (J.phase == 1) {
-        const Fr b0 = load_sol(Bt[k], ld, 0);
-        fin[k] = pending ? fr_add(b0, fr_mul(r, fr_sub(load_sol(Bt[k], ld, 1), b0))) : b0;
-      } else {
-        const Fr a0 = load_sol(A[k], ld, 0);
-        fin[k] = fr_from_mont(pending ? fr_add(a0, fr_mul(r, fr_sub(load_sol(A[k], ld, 1), a0))) : a0);
-      }
-      put_canon(out + 32 * k, fin[k]);
-    }
-    if (J.phase == 1) {
-      // t_k(r) sent and absorbed; sigma_1..sigma_K squeezed for phase 2
+  const Fr r = lds_get(T.r);
+  if (wave != 0) return;
+  // lane k < ntab: the last challenge folds the remaining pair of table k
+  Fr mine = get(min(lane, ntab - 1), 0);
+  if (pending) mine = fr_fold(r, mine, get(min(lane, ntab - 1), 1));
+  if (phase == 2) mine = fr_from_mont(mine);
+  if (lane < ntab) {
+    put_canon(J.proof + 96ull * n + 32 * lane, mine);
+    lds_put(T.v + 8 * lane, mine);
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  if (phase == 1) {
+    // t_k(r) sent and absorbed ("rfinal"); sigma_1 .. sigma_K squeezed for phase 2
+    if (lane == 0) {
+      Transcript tr;
+      Fr fin[kMaxReduceClaims];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) tr.h[j] = T.st[j];
+#pragma unroll
+      for (uint32_t k = 0; k < kMaxReduceClaims; ++k) fin[k] = lds_get(T.v + 8 * k);
       absorb_k(tr, VL_LBL_RFINAL, fin, K);
+#pragma unroll 1
       for (uint32_t k = 0; k < K; ++k) {
         const Fr sg = fr_to_mont(tr_squeeze_fixed(tr, VL_LBL_SIGMA));
 #pragma unroll
         for (int j = 0; j < 8; ++j) J.io[kReduceIoSigma + 8 * k + j] = sg.w[j];
       }
 #pragma unroll
-      for (int i = 0; i < 8; ++i) J.io[i] = tr.h[i];
-    } else {
-      const Fr f1[1] = {fin[0]};
-      tr_absorb_frs(tr, VL_LBL_FINAL, f1);
-      if (J.digest) {
-        uint8_t d[32];
-        tr_to_bytes(tr, d);
-        for (int i = 0; i < 32; ++i) J.digest[i] = d[i];
-      }
-      if (J.status) *J.status = VL_OK;
+      for (int j = 0; j < 8; ++j) J.io[j] = tr.h[j];
     }
+    return;
+  }
+  tr_absorb_lanes(T, kLblFinal4, kLblFinal1, 1);
+  if (lane == 0) {
+    if (J.digest) tr_put_digest(T, J.digest);
+    if (J.status) *J.status = VL_OK;
   }
 }
 
@@ -1097,7 +1231,22 @@ hipError_t launch_eval(const EvalJob* jobs, uint32_t n_jobs, hipStream_t s) {
 
 hipError_t launch_reduce(const ReduceJob* jobs, uint32_t n_jobs, hipStream_t s) {
   if (n_jobs == 0) return hipSuccess;
-  hipLaunchKernelGGL(reduce_kernel, dim3(n_jobs), dim3(kRoundsBlock), 0, s, jobs);
+  hipLaunchKernelGGL(reduce_kernel, dim3(n_jobs), dim3(64 * kRedTailWaves), 0, s, jobs);
+  return hipGetLastError();
+}
+
+hipError_t launch_reduce_sweep(const ReduceJob* jobs, const MatSweep* list, uint32_t n_list, uint32_t n_blocks,
+                               uint32_t round, hipStream_t s) {
+  if (n_blocks == 0) return hipSuccess;
+  hipLaunchKernelGGL(reduce_sweep_kernel, dim3(n_blocks), dim3(2 * kRedSweepPairs * kMaxReduceClaims), 0, s, jobs, list,
+                     n_list, n_blocks, round);
+  return hipGetLastError();
+}
+
+hipError_t launch_reduce_step(const ReduceJob* jobs, const MatSweep* list, uint32_t n_list, uint32_t round,
+                              hipStream_t s) {
+  if (n_list == 0) return hipSuccess;
+  hipLaunchKernelGGL(reduce_step_kernel, dim3(n_list), dim3(128 * kMaxReduceClaims), 0, s, jobs, list, round);
   return hipGetLastError();
 }
 

@@ -85,6 +85,8 @@ struct Plan {
   // launched after every segment, in this order, on the caller's stream
   std::vector<EvalJob> evals;
   std::vector<ReduceJob> reduces;
+  std::vector<std::vector<MatSweep>> red_wide;   // per wide round: the jobs and their first blocks
+  std::vector<uint32_t> red_wide_blocks;
   // per-head batched products: start, wide rounds (per round, the jobs and
   // their first blocks), the one-workgroup rounds
   std::vector<BmmJob> bmms;
@@ -109,7 +111,7 @@ struct SegLayout {
 struct BlobLayout {
   uint64_t err, eq, points, mat_io, evals, reduces, bmms, lookups, lookup_u, total;
   std::vector<SegLayout> seg;
-  std::vector<uint64_t> bmm_wide, lk_wide[LK_KINDS];
+  std::vector<uint64_t> bmm_wide, red_wide, lk_wide[LK_KINDS];
 };
 
 // Builds jobs; device addresses are base + workspace offset (base 0 = sizing).
@@ -153,6 +155,7 @@ struct Builder {
 BlobLayout blob_layout(const Plan& P);
 uint64_t blob_bound(const vl_group* groups, uint64_t n);
 void fill_blob(Plan& P, const BlobLayout& L, uint8_t* dblob);
+void set_eq_points(Plan& P, const BlobLayout& L, uint8_t* dblob);
 // HIP events around every launch (blocking mode timing); one pair per
 // launch, summed per stage after the call's streams are synchronised.
 struct StageEvents {
