@@ -677,18 +677,15 @@ void Builder::group(const vl_group& g, const Challenges& ch, uint8_t* proof_dev,
                             : pass1(a, L1, b, L1, 1, true, rj.prods[k].g_nparts, ready);
     rj.ready_target += rj.prods[k].g_nparts;
   }
-  // wide rounds for product 0 while its half-table has >= kMatWidePairs pairs
-  // (from round 2, when that has >= kMatWideStart); not in persistent mode,
-  // whose rounds workgroups are resident before the contractions run
+  // wide rounds for product 0 while its half-table has >= kMatWidePairs pairs;
+  // not in persistent mode, whose rounds workgroups are resident before the
+  // contractions run
   const uint32_t n1w = rj.prods[0].n1;
-  if (!T.persistent && n1w >= 2 && (1ull << (n1w - 2)) >= kMatWideStart) {
+  if (!T.persistent && n1w >= 2 && (1ull << (n1w - 2)) >= kMatWidePairs) {
     uint32_t W = 1;
     while (W < kMatMaxWide && W + 1 < n1w && (1ull << (n1w - 1 - W)) >= kMatWidePairs) ++W;
-    const uint32_t nb1 = (uint32_t)(((1ull << (n1w - 2)) + kMatSweepPairs - 1) / kMatSweepPairs);
     rj.wide = W;
     rj.io = nullptr;   // a slot of the descriptor blob, set when the blob is filled
-    rj.wpart_stride = (uint64_t)nb1 * 24;
-    rj.wpart = dev<uint32_t>(take((uint64_t)nb1 * 96 * 2));
     Segment& G = S();
     const uint32_t idx = (uint32_t)G.rounds.size();
     P.n_wide += 1;
@@ -702,8 +699,7 @@ void Builder::group(const vl_group& g, const Challenges& ch, uint8_t* proof_dev,
       m.block_begin = G.wide_blocks[rd];
       G.wide[rd].push_back(m);
       if (rd > 0)
-        G.wide_blocks[rd] +=
-            (uint32_t)(((1ull << (n1w - 1 - rd)) + kMatSweepPairs - 1) / kMatSweepPairs);
+        G.wide_blocks[rd] += (uint32_t)((1ull << (n1w - 1 - rd)) / kMatSweepPairs);
     }
   }
   // persistent mode: one resident launch for every group (segment 0's list)

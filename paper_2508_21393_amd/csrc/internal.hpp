@@ -48,13 +48,14 @@ struct UploadArgs {
 // Round 1 of one product (or the claim's dot product: c = sum_i eqU[i] t[i]
 // after a contraction of C by columns, c = sum_j eqV[j] s[j] after one by rows)
 // as per-block partial sums, computed across the GPU before the rounds.
-constexpr uint32_t kPass1Pairs = 512;   // pairs (entries for the dot) per 256-thread block
+constexpr uint32_t kPass1Pairs = 512;   // pairs (entries for the dot) per block
+constexpr uint32_t kPass1Block = 768;
 struct Pass1Job {
   const uint32_t* a;          // SoL table (eqU or eqV for the claim)
   const uint32_t* b;          // SoL table (t or s for the claim)
   uint64_t a_ld, b_ld;
   uint32_t h;                 // pairs (t, t + h), or entries of the dot product
-  uint32_t dot;               // 1: sum_i a[i] b[i]; 0: the round-1 values g(0), g(1), g(2)
+  uint32_t dot;               // 1: sum_i a[i] b[i]; 0: the sums of round 1 (values at 0, 1, leading coefficient)
   uint32_t block_begin;       // prefix sum of blocks within a launch
   uint32_t pad_;
   uint32_t* out;              // 3 elements (24 words) per block
@@ -79,15 +80,14 @@ struct RoundsProd {
 // previous launch's partials; the rounds workgroup takes the last wide
 // round's step.  io (in the descriptor blob, so every call starts from
 // zeros): [0] status, [8..23] transcript state after round k in slot k & 1,
-// [24..39] r_k in slot k & 1 (Montgomery).  Sweep partials: two buffers of
-// wpart_stride words, round k's in buffer k & 1.
-constexpr uint32_t kMatSweepPairs = 256;
-// a product goes wide when its round 2 has kMatWideStart pairs or more (at
-// 1024 a sweep launch costs more than the round on one workgroup), and stays
-// wide while a round has kMatWidePairs or more
-constexpr uint32_t kMatWideStart = 2048;
-constexpr uint32_t kMatWidePairs = 1024;
-constexpr uint32_t kMatMaxWide = 16;          // n1 <= 20 needs at most 10
+// [24..39] r_k in slot k & 1 (Montgomery).  The partials lie in entries of the
+// a~ table that the round folds away (mat_part).
+constexpr uint32_t kMatSweepPairs = 128;
+// (a wide round of 512 pairs takes 20 us, in one workgroup about 23; one of
+// 256 there 17 to 19)
+constexpr uint32_t kMatWidePairs = 512;
+constexpr uint32_t kMatLds = 512;             // entries of the rounds workgroup's LDS tables
+constexpr uint32_t kMatMaxWide = 16;          // n1 <= 20 needs at most 11
 constexpr uint32_t kMatIoState = 8, kMatIoR = 24, kMatIoWords = 48;
 struct MatSweep {
   uint32_t job;               // index in the launch's RoundsJob array
@@ -114,8 +114,6 @@ struct RoundsJob {
   uint32_t spin_limit;        // polls of `ready` before giving up (VL_ERR_TIMEOUT)
   uint32_t wide;              // product 0's rounds summed by wide launches (0: none, else >= 2)
   uint32_t* io;               // wide rounds: status, transcript states, challenges
-  uint32_t* wpart;            // wide rounds: sweep partials, 3 elements per block, two buffers
-  uint64_t wpart_stride;      // words per partials buffer
   RoundsProd prods[VL_MAX_PRODS];
 };
 

@@ -123,209 +123,119 @@ __global__ void __launch_bounds__(256) pack_kernel(const uint32_t* __restrict__ 
 }
 
 // ---------------------------------------------------------------- rounds ----
-// absorb("round", g(0), g(1), g(2)) by the lanes of wave 0: the message
-// (the state, the label and the three canonical values, 133 bytes in three
-// SHA-256 blocks) has its three blocks' message schedules computed side by
-// side, lane b < 3 holding block b's, and every lane then runs the 3 x 64
-// compression rounds on those words (uniform values read with v_readlane).
-// The same digest as tr_absorb_frs; the state is taken from lane 0.
-__device__ __forceinline__ void absorb_round_lanes(Transcript& tr, const Fr (&gc)[3], uint32_t lane) {
-  constexpr int L = sizeof(VL_LBL_ROUND) - 1;
-  constexpr int N = 32 + L + 96;
-  constexpr int NB = (N + 9 + 63) / 64;
-  static_assert(NB == 3, "the round absorb is three blocks");
-  uint32_t st[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) st[i] = __builtin_amdgcn_readlane(tr.h[i], 0);
-  auto byte_at = [&](int k) -> uint32_t {
-    if (k < 32) return (st[k >> 2] >> (24 - 8 * (k & 3))) & 0xffu;
-    if (k < 32 + L) return (uint8_t)VL_LBL_ROUND[k - 32];
-    if (k < N) return fr_byte(gc[(k - 32 - L) >> 5], (k - 32 - L) & 31);
-    if (k == N) return 0x80u;
-    if (k >= NB * 64 - 8) return (uint32_t)(((uint64_t)N * 8) >> (8 * (NB * 64 - 1 - k))) & 0xffu;
-    return 0u;
-  };
-  const uint32_t blk = min(lane, 2u);
-  uint32_t w[64];
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    uint32_t v[NB];
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      uint32_t x = 0;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) x |= byte_at(64 * b + 4 * i + q) << (24 - 8 * q);
-      v[b] = x;
-    }
-    w[i] = blk == 0 ? v[0] : (blk == 1 ? v[1] : v[2]);
-  }
-#pragma unroll
-  for (int i = 16; i < 64; ++i) {
-    const uint32_t w15 = w[i - 15], w2 = w[i - 2];
-    const uint32_t s0 = xor3_u32(rotr32(w15, 7), rotr32(w15, 18), w15 >> 3);
-    const uint32_t s1 = xor3_u32(rotr32(w2, 17), rotr32(w2, 19), w2 >> 10);
-    w[i] = add3_u32(w[i - 16], s0, w[i - 7]) + s1;
-  }
-  const uint32_t* K = sha256_k();
-#pragma unroll
-  for (int i = 0; i < 64; ++i) w[i] += K[i];
-  // a fresh SHA-256 hash: the chaining value starts at the initial hash value
-  uint32_t h[8] = {0x6a09e667u, 0xbb67ae85u, 0x3c6ef372u, 0xa54ff53au,
-                   0x510e527fu, 0x9b05688cu, 0x1f83d9abu, 0x5be0cd19u};
+// A round of product p sums, over the pairs t < h, the quadratic
+//     (a_t + X (a_{t+h} - a_t)) (b_t + X (b_{t+h} - b_t))
+// by its values at 0 and 1 and its leading coefficient ("points" 0, 1, 2); the
+// messages g(0), g(1), g(2) follow from the three sums.  The a~ tables are in
+// Montgomery form and the b~ tables in canonical form, so every product, and
+// with it every sum and message, is canonical; folding by r in Montgomery form
+// keeps both forms.
+
+// LDS sums (ten limb sums each): the claim, three values per product for its
+// first round, and the three of the round at hand
+constexpr uint32_t kMatAccProd = 1, kMatAccRound = 1 + 3 * VL_MAX_PRODS;
+constexpr uint32_t kMatAccWords = 10 * (kMatAccRound + 3);
+
+// the product at point pt of a pair, from its table entries e[0] (point 2: the
+// difference of the pair's) and, to be folded by r, e[1]
+struct MatTerm {
+  Fr A, B, val;
+};
+__device__ __forceinline__ MatTerm mat_term(const Fr (&ea)[2], const Fr (&eb)[2], const Fr& r) {
+  MatTerm o;
+  o.A = fr_fold(r, ea[0], ea[1]);
+  o.B = fr_fold(r, eb[0], eb[1]);
+  o.val = fr_mul(o.A, o.B);
+  return o;
+}
+
+// sums of the pass-1 partials into acc (zeroed), by all nw waves of the
+// workgroup: value 0 the claim, kMatAccProd + 3 p + q value q of product p
+__device__ __forceinline__ void mat_sum_first(const RoundsJob& J, unsigned long long* acc, uint32_t nw) {
+  const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
 #pragma unroll 1
-  for (uint32_t b = 0; b < (uint32_t)NB; ++b) {
-    uint32_t a = h[0], bb = h[1], c = h[2], dd = h[3], e = h[4], f = h[5], g = h[6], hh = h[7];
-#pragma unroll
-    for (int i = 0; i < 64; ++i) {
-      const uint32_t wk = __builtin_amdgcn_readlane(w[i], b);
-      const uint32_t S1 = xor3_u32(rotr32(e, 6), rotr32(e, 11), rotr32(e, 25));
-      const uint32_t ch = bitsel(e, f, g);
-      const uint32_t t1 = add3_u32(hh, S1, ch) + wk;
-      const uint32_t S0 = xor3_u32(rotr32(a, 2), rotr32(a, 13), rotr32(a, 22));
-      const uint32_t mj = maj_u32(a, bb, c);
-      hh = g; g = f; f = e; e = dd + t1; dd = c; c = bb; bb = a; a = add3_u32(t1, S0, mj);
-    }
-    h[0] += a; h[1] += bb; h[2] += c; h[3] += dd; h[4] += e; h[5] += f; h[6] += g; h[7] += hh;
+  for (uint32_t v = wave; v < kMatAccProd + 3 * J.n_prods; v += nw) {
+    const uint32_t p = v ? (v - kMatAccProd) / 3 : 0, q = v ? (v - kMatAccProd) % 3 : 0;
+    const uint32_t* part = v ? J.prods[p].g_part + 8 * q : J.c_part;
+    const uint32_t n = v ? J.prods[p].g_nparts : J.c_nparts;
+    Fr x = fr_zero();
+    for (uint32_t i = lane; i < n; i += kWave) x = fr_add(x, ld_rec(part + 24ull * i));
+    acc_add(acc, v, x);
   }
-#pragma unroll
-  for (int i = 0; i < 8; ++i) tr.h[i] = h[i];
 }
-
-// One sumcheck round's messages and challenge, run by wave 0 (all its
-// lanes, g canonical and valid in lane 0): lane k < 3 writes g(k) to the
-// proof; the wave absorbs the three values (all 64 lanes must be active:
-// lanes 1 and 2 hold message schedules) and lane 0 squeezes r.  Returns r in
-// Montgomery form in every lane of wave 0.
-__device__ __forceinline__ Fr round_challenge(Transcript& tr, const Fr (&g)[3], uint8_t* out, uint32_t lane,
-                                              bool write = true) {
-  Fr gc[3];
-#pragma unroll
-  for (int k = 0; k < 3; ++k) gc[k] = readlane_fr(g[k], 0);
-  Fr mine;   // word by word: a select of whole values goes through scratch memory
-#pragma unroll
-  for (int j = 0; j < 8; ++j) mine.w[j] = lane == 0 ? gc[0].w[j] : (lane == 1 ? gc[1].w[j] : gc[2].w[j]);
-  if (write && lane < 3) put_canon(out + 32 * lane, mine);
-  Fr r = fr_zero();
-  absorb_round_lanes(tr, gc, lane);
-  if (lane == 0) r = fr_to_mont(tr_squeeze_fixed(tr, VL_LBL_R));
-  return readlane_fr(r, 0);
+// partials of wide round rd: block b's three sums lie in the entries of a~'s
+// first plane that this block, and no other, folds away in that round
+__device__ __forceinline__ uint32_t* mat_part(const RoundsJob& J, uint32_t rd, uint32_t b) {
+  return J.prods[0].a + (2ull << (J.prods[0].n1 - 1 - rd)) + (uint64_t)kMatSweepPairs * b;
 }
-
-// ------------------------------------------------------- wide rounds ------
-// The transcript step of wide round k of a group (its values from partial
-// sums, absorbed; r_k squeezed), computed by a 256-thread block.  Every block
-// of the launch that needs r_k computes the step itself from the same
-// partials, so no block waits for another and no fence is needed; only the
-// launch's first block of the group (write) stores the proof bytes and io.
-// Round 0 (k = 0): the range flag, c = C~(u, v) and every product's round-1
-// values from the pass-1 partials, the prover guard, the claim and the part
-// claims, as the rounds kernel does without wide rounds; a failure is
-// reported (by the writing block) and every block returns false.  Later
-// rounds: the partials of sweep k (buffer k & 1), the state after round
-// k - 1 (io slot (k - 1) & 1).  r_k is returned in every thread.
-__device__ bool mat_step_block(const RoundsJob& J, uint32_t k, bool write, Fr& r_out) {
-  __shared__ uint32_t red[4 * 8 * 4];
-  __shared__ uint32_t first[VL_MAX_PRODS][3][8];
-  __shared__ uint32_t bcast[8];
-  __shared__ int32_t verdict;
-  const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = tid & 63u;
-  uint8_t* out = J.proof + 32ull * J.n_prods + 96ull * k;
-  Transcript tr;
-  Fr g[4];
-  g[0] = g[1] = g[2] = g[3] = fr_zero();
-  if (k == 0) {
-    const int32_t bad = J.err && *(volatile const int32_t*)J.err;
-    if (bad) {
-      if (write && tid == 0) {
-        J.io[0] = (uint32_t)VL_ERR_RANGE;
-        *J.status = VL_ERR_RANGE;
-      }
-      return false;
+// sums of wide round rd >= 1 into acc's round values, by waves 0 .. 2
+__device__ __forceinline__ void mat_sum_wide(const RoundsJob& J, uint32_t rd, unsigned long long* acc) {
+  const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
+  if (wave >= 3) return;
+  const uint32_t nb = (1u << (J.prods[0].n1 - 1 - rd)) / kMatSweepPairs;
+  Fr x = fr_zero();
+  for (uint32_t i = lane; i < nb; i += kWave) x = fr_add(x, ld_rec(mat_part(J, rd, i) + 8 * wave));
+  acc_add(acc, kMatAccRound + wave, x);
+}
+// The statement, by wave 0: the prover guard (c equals the sum of every
+// product's g(0) + g(1)), then the claim and the part claims written (by one
+// workgroup) and absorbed.
+__device__ __forceinline__ bool mat_claim(const RoundsJob& J, const unsigned long long* acc, RoundLds& T, bool write) {
+  const uint32_t lane = threadIdx.x & 63u, n = J.n_prods;
+  if (lane < 8) T.st[lane] = J.st[lane];
+  // lane p < n: product p's sum; lane 8: c
+  const uint32_t v0 = lane < n ? kMatAccProd + 3 * lane : 0;
+  uint64_t t[10];
+#pragma unroll
+  for (int i = 0; i < 10; ++i) t[i] = acc[10 * v0 + i] + (lane < n ? acc[10 * v0 + 10 + i] : 0ull);
+  const Fr mine = fr_of_limb_sums(t);
+  Fr sum = mine;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) sum.w[j] = lane < n ? sum.w[j] : 0u;
+  sum = fr_add(sum, fr_row_shl<4>(sum));
+  sum = fr_add(sum, fr_row_shl<2>(sum));
+  sum = fr_add(sum, fr_row_shl<1>(sum));
+  if (!fr_eq(readlane_fr(sum, 0), readlane_fr(mine, 8))) return false;
+#pragma unroll 1
+  for (uint32_t p = 0; p < n; ++p) {   // c, then the sums of products 0 .. n - 2
+    if (lane == (p ? p - 1 : 8u)) {
+      if (write) put_canon(J.proof + 32 * p, mine);
+      lds_put(T.v, mine);
     }
-    Fr v[4];
-    v[0] = v[1] = v[2] = v[3] = fr_zero();
-    for (uint32_t i = tid; i < J.c_nparts; i += 256) v[0] = fr_add(v[0], lds_or_global_fr(J.c_part + 24ull * i));
-    block256_sum4(v, red);
-    const Fr c = v[0];   // valid in thread 0
-    __syncthreads();
-    Fr total = fr_zero();
-    for (uint32_t p = 0; p < J.n_prods; ++p) {
-      const RoundsProd& P = J.prods[p];
-      Fr gp[4];
-      gp[0] = gp[1] = gp[2] = gp[3] = fr_zero();
-      for (uint32_t i = tid; i < P.g_nparts; i += 256)
-#pragma unroll
-        for (int q = 0; q < 3; ++q) gp[q] = fr_add(gp[q], lds_or_global_fr(P.g_part + 24ull * i + 8 * q));
-      block256_sum4(gp, red);
-      if (tid == 0)
-#pragma unroll
-        for (int q = 0; q < 3; ++q) lds_put(first[p][q], gp[q]);
-      total = fr_add(total, fr_add(gp[0], gp[1]));
-      __syncthreads();
-    }
-    if (tid == 0) verdict = fr_eq(total, c) ? 1 : 0;
-    __syncthreads();
-    if (!verdict) {
-      if (write && tid == 0) {
-        J.io[0] = (uint32_t)VL_ERR_FALSE_STATEMENT;
-        *J.status = VL_ERR_FALSE_STATEMENT;
-      }
-      return false;
-    }
-    if (tid == 0) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) tr.h[i] = J.st[i];
-      const Fr cc[1] = {c};
-      if (write) put_canon(J.proof, cc[0]);
-      tr_absorb_frs(tr, VL_LBL_CLAIM, cc);
-      for (uint32_t p = 0; p + 1 < J.n_prods; ++p) {
-        const Fr sc[1] = {fr_add(lds_get(first[p][0]), lds_get(first[p][1]))};
-        if (write) put_canon(J.proof + 32 * (1 + p), sc[0]);
-        tr_absorb_frs(tr, VL_LBL_PART, sc);
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < 3; ++q) g[q] = lds_get(first[0][q]);
-  } else {
-    const uint32_t h = 1u << (J.prods[0].n1 - 1 - k);
-    const uint32_t nb = (h + kMatSweepPairs - 1) / kMatSweepPairs;
-    const uint32_t* part = J.wpart + (uint64_t)(k & 1) * J.wpart_stride;
-    for (uint32_t i = tid; i < nb; i += 256)
-#pragma unroll
-      for (int q = 0; q < 3; ++q) g[q] = fr_add(g[q], lds_or_global_fr(part + 24ull * i + 8 * q));
-    block256_sum4(g, red);   // valid in thread 0
-    if (tid == 0)
-#pragma unroll
-      for (int i = 0; i < 8; ++i) tr.h[i] = J.io[kMatIoState + 8 * ((k - 1) & 1) + i];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    tr_absorb_lanes(T, p ? kLblPart4 : kLblClaim4, p ? 0u : kLblClaim1, 1);
   }
-  if (wave == 0) {
-    const Fr g3[3] = {g[0], g[1], g[2]};
-    const Fr r = round_challenge(tr, g3, out, lane, write);
-    if (lane == 0) {
-      if (write)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          J.io[kMatIoState + 8 * (k & 1) + i] = tr.h[i];
-          J.io[kMatIoR + 8 * (k & 1) + i] = r.w[i];
-        }
-      lds_put(bcast, r);
-    }
-  }
-  __syncthreads();
-  r_out = lds_get(bcast);
   return true;
 }
+// A round's messages from the sums at value v0, and its challenge, by wave 0
+__device__ __forceinline__ void mat_round(const unsigned long long* acc, uint32_t v0, uint8_t* out, RoundLds& T,
+                                          bool write) {
+  const uint32_t lane = threadIdx.x & 63u;
+  const Fr g = acc_point(acc, v0, min(lane, 2u));
+  if (lane < 3) {
+    if (write) put_canon(out + 32 * lane, g);
+    lds_put(T.v + 8 * lane, g);
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  tr_round(T, 3);
+}
 
-// Wide round rd >= 1 of product 0 across the GPU: every block first takes
-// round rd - 1's transcript step (mat_step_block) for r_{rd-1}; then every
-// thread takes one pair t < h of round rd, folds the entries t, t + h,
-// t + 2h, t + 3h of the tables by r_{rd-1} into t and t + h (as the rounds
-// kernel's sweeps do; each thread reads and writes only its own entries)
-// and adds the pair's three products; a block writes its sums to the
-// partials buffer rd & 1.
-__global__ void __launch_bounds__(256) mat_sweep_kernel(const RoundsJob* __restrict__ jobs,
-                                                        const MatSweep* __restrict__ list, uint32_t n_list,
-                                                        uint32_t n_blocks, uint32_t rd) {
+// Wide round rd >= 1 of product 0 across the GPU, kMatSweepPairs pairs per
+// block.  Wave 0 of every block first takes round rd - 1's transcript step
+// (round 0: also the statement) from the previous launch's sums, so no block
+// waits for another and a round is one launch; only the job's first block
+// stores proof bytes and io.  Then each thread folds by r_{rd-1} and takes the
+// product at one point of a pair; the entries are loaded before the step.
+// Bound by the step (about 13 us of 20, 28 the first); with the sums by lane
+// shuffles, the squeeze and the statement on one lane it was 30 us, 43 the
+// first.  256 pairs per block: 22 us.
+__global__ void __launch_bounds__(3 * kMatSweepPairs) mat_sweep_kernel(const RoundsJob* __restrict__ jobs,
+                                                                       const MatSweep* __restrict__ list,
+                                                                       uint32_t n_list, uint32_t n_blocks,
+                                                                       uint32_t rd) {
+  __shared__ unsigned long long acc[kMatAccWords];
+  __shared__ RoundLds T;
+  __shared__ int32_t verdict;
   const uint32_t blk = blockIdx.x;
   if (blk >= n_blocks) return;
   uint32_t lo = 0, hi = n_list;
@@ -336,56 +246,79 @@ __global__ void __launch_bounds__(256) mat_sweep_kernel(const RoundsJob* __restr
   const MatSweep& S = list[lo];
   const RoundsJob& J = jobs[S.job];
   if (*reinterpret_cast<volatile const int32_t*>(J.io) != VL_OK) return;
-  Fr r;
-  if (!mat_step_block(J, rd - 1, blk == S.block_begin, r)) return;
-  const RoundsProd& P = J.prods[0];
-  uint32_t* a = P.a;
-  uint32_t* b = P.b;
-  const uint64_t ld = P.ld;
-  const uint32_t h = 1u << (P.n1 - 1 - rd);
-  const uint32_t t = (blk - S.block_begin) * kMatSweepPairs + threadIdx.x;
-  Fr g[4];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) g[k] = fr_zero();
-  if (t < h) {
-    const Fr a00 = load_sol(a, ld, t), a01 = load_sol(a, ld, t + 2 * h);
-    const Fr a10 = load_sol(a, ld, t + h), a11 = load_sol(a, ld, t + 3 * h);
-    const Fr b00 = load_sol(b, ld, t), b01 = load_sol(b, ld, t + 2 * h);
-    const Fr b10 = load_sol(b, ld, t + h), b11 = load_sol(b, ld, t + 3 * h);
-    const Fr rr2[2] = {r, r}, da[2] = {fr_sub(a01, a00), fr_sub(a11, a10)};
-    const Fr db[2] = {fr_sub(b01, b00), fr_sub(b11, b10)};
-    Fr fa[2], fb[2];
-    fr_mul_n<2>(rr2, da, fa);
-    fr_mul_n<2>(rr2, db, fb);
-    const Fr a0 = fr_add(a00, fa[0]), a1 = fr_add(a10, fa[1]);
-    const Fr b0 = fr_add(b00, fb[0]), b1 = fr_add(b10, fb[1]);
-    store_sol(a, ld, t, a0);
-    store_sol(a, ld, t + h, a1);
-    store_sol(b, ld, t, b0);
-    store_sol(b, ld, t + h, b1);
-    const Fr x[3] = {a0, a1, at_two(a0, a1)}, y[3] = {b0, b1, at_two(b0, b1)};
-    Fr pr[3];
-    fr_mul_n<3>(x, y, pr);
-#pragma unroll
-    for (int k = 0; k < 3; ++k) g[k] = pr[k];
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, pt = tid / kMatSweepPairs;
+  const bool write = blk == S.block_begin;
+  if (rd == 1 && J.err && *(volatile const int32_t*)J.err) {
+    if (write && tid == 0) {
+      J.io[0] = (uint32_t)VL_ERR_RANGE;
+      *J.status = VL_ERR_RANGE;
+    }
+    return;
   }
-  __shared__ uint32_t red[4 * 8 * 4];
-  block256_sum4(g, red);
-  if (threadIdx.x == 0) {
-    uint32_t* o = J.wpart + (uint64_t)(rd & 1) * J.wpart_stride + (uint64_t)(blk - S.block_begin) * 24;
+  const RoundsProd& P = J.prods[0];
+  const uint64_t ld = P.ld;
+  const uint32_t h = 1u << (P.n1 - 1 - rd);   // a multiple of kMatSweepPairs
+  const uint32_t t = (blk - S.block_begin) * kMatSweepPairs + tid % kMatSweepPairs;
+  const uint32_t i0 = pt == 1 ? t + h : t;
+  Fr ea[2], eb[2];
 #pragma unroll
-    for (int k = 0; k < 3; ++k)
-#pragma unroll
-      for (int j = 0; j < 8; ++j) o[k * 8 + j] = g[k].w[j];
+  for (int q = 0; q < 2; ++q) {
+    ea[q] = load_sol(P.a, ld, i0 + 2 * q * h);
+    eb[q] = load_sol(P.b, ld, i0 + 2 * q * h);
+    if (pt == 2) {
+      ea[q] = fr_sub(load_sol(P.a, ld, t + h + 2 * q * h), ea[q]);
+      eb[q] = fr_sub(load_sol(P.b, ld, t + h + 2 * q * h), eb[q]);
+    }
+  }
+  for (uint32_t i = tid; i < kMatAccWords; i += 3 * kMatSweepPairs) acc[i] = 0;
+  __syncthreads();
+  if (rd == 1) {
+    mat_sum_first(J, acc, 3 * kMatSweepPairs / kWave);
+  } else {
+    mat_sum_wide(J, rd - 1, acc);
+    if (tid < 8) T.st[tid] = J.io[kMatIoState + 8 * (rd & 1) + tid];
+  }
+  __syncthreads();
+  if (tid < 64) {
+    const bool ok = rd > 1 || mat_claim(J, acc, T, write);
+    if (lane == 0) verdict = ok ? 1 : 0;
+    if (ok) {
+      mat_round(acc, rd == 1 ? kMatAccProd : kMatAccRound, J.proof + 32ull * J.n_prods + 96ull * (rd - 1), T, write);
+      if (write && lane < 8) {
+        J.io[kMatIoState + 8 * ((rd - 1) & 1) + lane] = T.st[lane];
+        J.io[kMatIoR + 8 * ((rd - 1) & 1) + lane] = T.r[lane];
+      }
+      if (lane < 30) acc[10 * kMatAccRound + lane] = 0;
+    } else if (write && lane == 0) {
+      J.io[0] = (uint32_t)VL_ERR_FALSE_STATEMENT;
+      *J.status = VL_ERR_FALSE_STATEMENT;
+    }
+  }
+  __syncthreads();
+  if (!verdict) return;
+  const MatTerm o = mat_term(ea, eb, lds_get(T.r));
+  if (pt < 2) {
+    store_sol(P.a, ld, i0, o.A);
+    store_sol(P.b, ld, i0, o.B);
+  }
+  acc_add(acc, kMatAccRound + pt, o.val);
+  __syncthreads();
+  if (tid < 64) {
+    const Fr v = acc_value(acc, kMatAccRound + min(tid, 2u));
+    if (tid < 3) st_rec(mat_part(J, rd, blk - S.block_begin) + 8 * tid, v);
   }
 }
 
 // Pass 1: the claim's dot product and round 1 of every product as partial
-// sums, kPass1Pairs pairs per 256-thread block, spread over the whole GPU
-// (the rounds kernel of a group runs on one CU and only adds the partials).
-__global__ void __launch_bounds__(256) pass1_kernel(const Pass1Job* __restrict__ jobs, uint32_t n_jobs,
-                                                    uint32_t n_blocks) {
-  const uint32_t blk = blockIdx.x;
+// sums, kPass1Pairs pairs per block, spread over the whole GPU (the rounds
+// kernel of a group runs on one CU and only adds the partials).  A thread
+// takes one point of its pairs.  Bound by the loads' latency and one product's
+// chain; with all three products on a thread and sums by lane shuffles it was
+// 12.7 us for the 13B query forward at T 128, now 8.4.
+__global__ void __launch_bounds__(kPass1Block) pass1_kernel(const Pass1Job* __restrict__ jobs, uint32_t n_jobs,
+                                                            uint32_t n_blocks) {
+  __shared__ unsigned long long acc[30];
+  const uint32_t blk = blockIdx.x, tid = threadIdx.x, lane = tid & 63u;
   if (blk >= n_blocks) return;
   uint32_t lo = 0, hi = n_jobs;
   while (hi - lo > 1) {
@@ -393,80 +326,64 @@ __global__ void __launch_bounds__(256) pass1_kernel(const Pass1Job* __restrict__
     if (jobs[mid].block_begin <= blk) lo = mid; else hi = mid;
   }
   const Pass1Job& J = jobs[lo];
-  const uint32_t base = (blk - J.block_begin) * kPass1Pairs;
-  const uint32_t end = min(base + kPass1Pairs, J.h);
-  Fr g[3];
-  g[0] = g[1] = g[2] = fr_zero();
-  for (uint32_t t = base + threadIdx.x; t < end; t += 256) {
-    if (J.dot) {
-      g[0] = fr_add(g[0], fr_mul(load_sol(J.a, J.a_ld, t), load_sol(J.b, J.b_ld, t)));
-    } else {
-      const Fr a0 = load_sol(J.a, J.a_ld, t), a1 = load_sol(J.a, J.a_ld, t + J.h);
-      const Fr b0 = load_sol(J.b, J.b_ld, t), b1 = load_sol(J.b, J.b_ld, t + J.h);
-      const Fr x[3] = {a0, a1, at_two(a0, a1)}, y[3] = {b0, b1, at_two(b0, b1)};
-      Fr pr[3];
-      fr_mul_n<3>(x, y, pr);
-#pragma unroll
-      for (int k = 0; k < 3; ++k) g[k] = fr_add(g[k], pr[k]);
+  if (tid < 30) acc[tid] = 0;
+  const uint32_t base = (blk - J.block_begin) * kPass1Pairs, end = min(base + kPass1Pairs, J.h);
+  // a dot product's entries over all threads, a product's pairs over a third
+  const uint32_t step = J.dot ? kPass1Block : kPass1Block / 3, pt = J.dot ? 0 : tid / step;
+  Fr g = fr_zero();
+#pragma unroll 1
+  for (uint32_t t = base + tid % step; t < end; t += step) {
+    const uint32_t i0 = pt ? t + J.h : t;
+    Fr a = load_sol(J.a, J.a_ld, i0), b = load_sol(J.b, J.b_ld, i0);
+    if (pt == 2) {
+      a = fr_sub(a, load_sol(J.a, J.a_ld, t));
+      b = fr_sub(b, load_sol(J.b, J.b_ld, t));
     }
+    g = fr_add(g, fr_mul(a, b));
   }
-  __shared__ uint32_t red[3 * 8 * 4];
-  wave_sum<3>(g, kWave);
-  const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
-  if (lane == 0)
-#pragma unroll
-    for (int k = 0; k < 3; ++k)
-#pragma unroll
-      for (int j = 0; j < 8; ++j) red[(k * 8 + j) * 4 + wave] = g[k].w[j];
   __syncthreads();
-  if (wave == 0) {
+  acc_add(acc, pt, g);
+  __syncthreads();
+  if (tid >= 64) return;
+  const Fr v = acc_value(acc, min(lane, 2u));
+  Fr s[3];
 #pragma unroll
-    for (int k = 0; k < 3; ++k)
+  for (int k = 0; k < 3; ++k) s[k] = readlane_fr(v, k);
+  if (lane == 0) {
+    uint32_t* o = J.out + (uint64_t)(blk - J.block_begin) * 24;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) g[k].w[j] = lane < 4 ? red[(k * 8 + j) * 4 + lane] : 0u;
-    wave_sum<3>(g, 4);
-    if (lane == 0) {
-      uint32_t* o = J.out + (uint64_t)(blk - J.block_begin) * 24;
-#pragma unroll
-      for (int k = 0; k < 3; ++k)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) o[k * 8 + j] = g[k].w[j];
-      // persistent mode: count this block for the group's resident rounds
-      // workgroup (release: the partials, and everything the earlier
-      // kernels of the stream wrote, are visible to whoever sees the count)
-      if (J.ready) __hip_atomic_fetch_add(J.ready, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    for (int k = 0; k < 3; ++k) st_rec(o + 8 * k, s[k]);
+    // persistent mode: count this block for the group's resident rounds
+    // workgroup (release: the partials, and everything the earlier
+    // kernels of the stream wrote, are visible to whoever sees the count)
+    if (J.ready) __hip_atomic_fetch_add(J.ready, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
-// One workgroup per group.  Round 1 of every product comes from the pass-1
-// partials (its g(0) + g(1) is the product's sum, so the prover guard needs
-// no extra pass).  Every later round computes g(0), g(1) and g(2) from the
-// folded tables (g(0) + g(1) equals the previous round's g(r) by the folding
-// identity, for any tables).  The a~ tables are in Montgomery form and the
-// b~ tables in canonical form, so every product a * b, and with it every
-// round value, is canonical; folding by r in Montgomery form keeps both
-// forms.  While the half-table is
-// larger than a wave the tables live in global memory and the whole group
-// works; the last rounds (half-table <= 64) run in wave 0 alone with the
-// pairs in registers: lane t holds entries t and t + h, and folding moves
-// entry t + h/2 down by h/2 lanes.  The transcript lane's chain (hashing,
-// two field conversions) is the serial part of every round.
+// The rounds of a group, one workgroup each, apart from the wide ones: the
+// statement (without wide rounds), then product after product.  Round 0's sums
+// come from pass 1, the last wide round's from its blocks' partials.  Every
+// other round folds the tables by the challenge before and sums the new pairs
+// in one pass: entries t, t + h, t + 2 h, t + 3 h fold into t and t + h.  The
+// rows of 16 lanes of waves 1 .. 7 take the terms, wave 0 the transcript.
+// Tables of more than kMatLds entries fold in place in global memory, a pair's
+// points in one thread (the leading one first, which reads all four entries);
+// shorter ones are folded from one LDS buffer into the other and a pair's
+// points go to different rows.
+// A round is a serial chain: a fold, a product, the sum and the hash (about
+// 10 of 15 us).  With the sums by lane shuffles, the squeeze and claims on one
+// lane and 183 KB of code it took 18 us in a single product (134 us for the
+// 64 x 128 x 32 product, now 116) and 30 with 42 groups at once.
 __global__ void __launch_bounds__(kRoundsBlock) rounds_kernel(const RoundsJob* __restrict__ jobs) {
   const RoundsJob& J = jobs[blockIdx.x];
-  // the rounds are one serial chain per group (transcript hashing on a
-  // single lane); when they overlap contraction kernels on the same CUs,
-  // their waves go first
+  // the rounds are one serial chain per group; when they overlap contraction
+  // kernels on the same CUs, their waves go first
   __builtin_amdgcn_s_setprio(3);
-  __shared__ uint32_t red[3 * 8 * (kRoundsBlock / kWave)];
-  __shared__ uint32_t first[VL_MAX_PRODS][3][8];   // round-1 values per product
-  __shared__ uint32_t bcast[8];                    // the round's challenge
-  __shared__ uint32_t coef[2][3][3][8];            // register rounds: value k as c0 + c1 r + c2 r^2
-  __shared__ uint32_t rbuf[2][8];                  // register rounds: r_j by parity
-  __shared__ uint32_t finv[2][8];                  // the product's final a~, b~
+  __shared__ uint32_t buf[2][8 * (kMatLds + kMatLds / 2)];   // a, b: two buffers each
+  __shared__ unsigned long long acc[kMatAccWords];
+  __shared__ RoundLds T;
   __shared__ int32_t verdict;
-  const uint32_t tid = threadIdx.x, NT = blockDim.x;
-  const uint32_t wave = tid >> 6, lane = tid & 63u;
+  const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = tid & 63u;
 
   if (J.ready) {
     // persistent mode: wait until every pass-1 block of this group has
@@ -494,9 +411,10 @@ __global__ void __launch_bounds__(kRoundsBlock) rounds_kernel(const RoundsJob* _
       return;
     }
   }
-  if (J.wide) {
-    // the range flag, the claim, the prover guard and product 0's first
-    // J.wide rounds ran as wide launches, which left their status in io
+  const uint32_t wide = J.wide;
+  if (wide) {
+    // the range flag, the statement and product 0's first rounds were wide
+    // launches' work, which left their status in io
     const int32_t st = *reinterpret_cast<volatile const int32_t*>(J.io);
     if (st != VL_OK) {
       if (tid == 0) *J.status = st;
@@ -506,37 +424,20 @@ __global__ void __launch_bounds__(kRoundsBlock) rounds_kernel(const RoundsJob* _
     if (tid == 0) *J.status = VL_ERR_RANGE;
     return;
   }
-  // c = C~(u, v) from the pass-1 partials of its dot product (canonical:
-  // one factor in Montgomery form, the other canonical)
-  Fr c = fr_zero();
-  if (!J.wide) {
-    Fr v1[1];
-    v1[0] = fr_zero();
-    for (uint32_t i = tid; i < J.c_nparts; i += NT) v1[0] = fr_add(v1[0], lds_or_global_fr(J.c_part + 24ull * i));
-    block_sum_w0<1>(v1, red);
-    c = v1[0];          // valid in lane 0 of wave 0
-    __syncthreads();    // red is reused by the next sum
+  for (uint32_t i = tid; i < kMatAccWords; i += kRoundsBlock) acc[i] = 0;
+  __syncthreads();
+  mat_sum_first(J, acc, kRoundsBlock / kWave);
+  if (wide) {
+    mat_sum_wide(J, wide - 1, acc);
+    // the state after round wide - 2, the last step a wide launch took
+    if (tid < 8) T.st[tid] = J.io[kMatIoState + 8 * (wide & 1) + tid];
   }
-
-  // round 1 of every product from its partials; its g(0) + g(1) is
-  // sum_w a_p[w] b_p[w]
-  Fr total = fr_zero();
-  for (uint32_t p = 0; p < J.n_prods; ++p) {
-    const RoundsProd& P = J.prods[p];
-    Fr g[3];
-    g[0] = g[1] = g[2] = fr_zero();
-    for (uint32_t i = tid; i < P.g_nparts; i += NT)
-#pragma unroll
-      for (int k = 0; k < 3; ++k) g[k] = fr_add(g[k], lds_or_global_fr(P.g_part + 24ull * i + 8 * k));
-    block_sum_w0<3>(g, red);
-    if (tid == 0)
-#pragma unroll
-      for (int k = 0; k < 3; ++k) lds_put(first[p][k], g[k]);
-    total = fr_add(total, fr_add(g[0], g[1]));
-    __syncthreads();   // red is reused by the next sum
-  }
-  if (!J.wide) {
-    if (tid == 0) verdict = fr_eq(total, c) ? 1 : 0;
+  __syncthreads();
+  if (!wide) {
+    if (wave == 0) {
+      const bool ok = mat_claim(J, acc, T, true);
+      if (lane == 0) verdict = ok ? 1 : 0;
+    }
     __syncthreads();
     if (!verdict) {
       if (tid == 0) *J.status = VL_ERR_FALSE_STATEMENT;
@@ -544,285 +445,94 @@ __global__ void __launch_bounds__(kRoundsBlock) rounds_kernel(const RoundsJob* _
     }
   }
 
-  // the transcript lives in thread 0; every thread keeps the same proof cursor
-  Transcript tr;
-  uint8_t* out = J.proof;
-  if (J.wide) {
-    // the state after round wide - 2, the last step a wide launch took
-    if (tid == 0)
-#pragma unroll
-      for (int i = 0; i < 8; ++i) tr.h[i] = J.io[kMatIoState + 8 * ((J.wide - 2) & 1) + i];
-  } else if (tid == 0) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) tr.h[i] = J.st[i];
-    const Fr cc[1] = {c};
-    put_canon(out, cc[0]);
-    tr_absorb_frs(tr, VL_LBL_CLAIM, cc);
-    for (uint32_t p = 0; p + 1 < J.n_prods; ++p) {
-      const Fr sc[1] = {fr_add(lds_get(first[p][0]), lds_get(first[p][1]))};
-      put_canon(out + 32 * (1 + p), sc[0]);
-      tr_absorb_frs(tr, VL_LBL_PART, sc);
-    }
-  }
-  out += 32 * J.n_prods;
+  uint8_t* out = J.proof + 32ull * J.n_prods;
+#pragma unroll 1
   for (uint32_t p = 0; p < J.n_prods; ++p) {
     const RoundsProd& P = J.prods[p];
-    uint32_t* a = P.a;
-    uint32_t* b = P.b;
+    uint32_t *const ga = P.a, *const gb = P.b;
     const uint64_t ld = P.ld;
-    uint32_t rd = 0;
-    // rounds over tables in global memory, the whole workgroup.  Round 0's
-    // values come from pass 1; every later one folds the tables by the
-    // previous challenge and sums the new pairs in the same sweep: for
-    // t < h, entries t, t + h, t + 2h, t + 3h of the tables as they stand
-    // (half-size 2h) fold into entries t and t + h (half-size h), which are
-    // the round's pair.  Each thread reads and writes only its own entries.
-    bool pending = false;   // tables still to be folded by r
-    Fr r = fr_zero();
-    if (p == 0 && J.wide) {
-      // rounds 0 .. wide - 1 were summed by wide launches, which also took
-      // the transcript steps of rounds 0 .. wide - 2; take round wide - 1's
-      // step here (its values from the last sweep's partials), then resume
-      // with the tables still to be folded by its challenge
-      const uint32_t k = J.wide - 1;
-      const uint32_t hk = 1u << (P.n1 - 1 - k);
-      const uint32_t nb = (hk + kMatSweepPairs - 1) / kMatSweepPairs;
-      const uint32_t* part = J.wpart + (uint64_t)(k & 1) * J.wpart_stride;
-      Fr g[3];
-      g[0] = g[1] = g[2] = fr_zero();
-      for (uint32_t i = tid; i < nb; i += NT)
+    const uint32_t n1 = P.n1, rd0 = p == 0 && wide ? wide - 1 : 0;
+    int at = -1;   // the tables' place: -1 global, else the LDS buffer of kMatLds entries (0) or half of them (1)
+    auto get = [&](uint32_t k, uint32_t i) {
+      if (at >= 0) return load_sol(buf[k] + (at ? 8 * kMatLds : 0), at ? kMatLds / 2 : kMatLds, i);
+      return load_sol(k ? gb : ga, ld, i);
+    };
+#pragma unroll 1
+    for (uint32_t rd = rd0; rd < n1; ++rd) {
+      const uint32_t h = 1u << (n1 - 1 - rd);
+      if (rd > rd0) {
+        const bool lds = 2 * h <= kMatLds;   // the folded tables' place
+        if (wave) {
+          const Fr r = lds_get(T.r);
+          constexpr uint32_t kRows = 4 * (kRoundsBlock / kWave - 1), kPtRows = kRows / 3;
+          const uint32_t row = 4 * (wave - 1) + (lane >> 4), chunks = (h + 15) / 16;
+          const uint32_t first = lds ? row / 3 : row, step = lds ? kPtRows : kRows;
+          const bool on = !lds || first < kPtRows;
+#pragma unroll 1
+          for (uint32_t j = 0; j < (lds ? 1u : 3u); ++j) {
+            const uint32_t pt = lds ? row % 3 : (j == 0 ? 2 : j - 1);
+            Fr sum = fr_zero();
+#pragma unroll 1
+            for (uint32_t ch = first; on && ch < chunks; ch += step) {
+              const uint32_t t = ch * 16 + (lane & 15u), i0 = pt == 1 ? t + h : t;
+              if (t >= h) continue;
+              Fr ea[2], eb[2];
 #pragma unroll
-        for (int q = 0; q < 3; ++q) g[q] = fr_add(g[q], lds_or_global_fr(part + 24ull * i + 8 * q));
-      block_sum_w0<3>(g, red);
-      if (wave == 0) {
-        const Fr rr = round_challenge(tr, g, out + 96ull * k, lane);
-        if (lane == 0) lds_put(bcast, rr);
-      }
-      __syncthreads();
-      r = lds_get(bcast);
-      rd = J.wide;
-      pending = true;
-      out += 96ull * J.wide;
-    }
-    for (; rd < P.n1; ++rd) {
-      const uint32_t h = 1u << (P.n1 - 1 - rd);
-      if (h <= kWave) break;
-      Fr g[3];
-      if (rd == 0) {
-#pragma unroll
-        for (int k = 0; k < 3; ++k) g[k] = lds_get(first[p][k]);
-      } else {
-        g[0] = g[1] = g[2] = fr_zero();
-        for (uint32_t t = tid; t < h; t += NT) {
-          const Fr a00 = load_sol(a, ld, t), a01 = load_sol(a, ld, t + 2 * h);
-          const Fr a10 = load_sol(a, ld, t + h), a11 = load_sol(a, ld, t + 3 * h);
-          const Fr b00 = load_sol(b, ld, t), b01 = load_sol(b, ld, t + 2 * h);
-          const Fr b10 = load_sol(b, ld, t + h), b11 = load_sol(b, ld, t + 3 * h);
-          const Fr rr2[2] = {r, r}, da[2] = {fr_sub(a01, a00), fr_sub(a11, a10)};
-          const Fr db[2] = {fr_sub(b01, b00), fr_sub(b11, b10)};
-          Fr fa[2], fb[2];
-          fr_mul_n<2>(rr2, da, fa);
-          fr_mul_n<2>(rr2, db, fb);
-          const Fr a0 = fr_add(a00, fa[0]), a1 = fr_add(a10, fa[1]);
-          const Fr b0 = fr_add(b00, fb[0]), b1 = fr_add(b10, fb[1]);
-          store_sol(a, ld, t, a0);
-          store_sol(a, ld, t + h, a1);
-          store_sol(b, ld, t, b0);
-          store_sol(b, ld, t + h, b1);
-          const Fr x[3] = {a0, a1, at_two(a0, a1)}, y[3] = {b0, b1, at_two(b0, b1)};
-          Fr pr[3];
-          fr_mul_n<3>(x, y, pr);
-#pragma unroll
-          for (int k = 0; k < 3; ++k) g[k] = fr_add(g[k], pr[k]);
+              for (int q = 0; q < 2; ++q) {
+                ea[q] = get(0, i0 + 2 * q * h);
+                eb[q] = get(1, i0 + 2 * q * h);
+                if (pt == 2) {
+                  ea[q] = fr_sub(get(0, t + h + 2 * q * h), ea[q]);
+                  eb[q] = fr_sub(get(1, t + h + 2 * q * h), eb[q]);
+                }
+              }
+              const MatTerm o = mat_term(ea, eb, r);
+              if (pt < 2) {
+                if (lds) {
+                  const uint32_t off = at == 0 ? 8 * kMatLds : 0, len = at == 0 ? kMatLds / 2 : kMatLds;
+                  store_sol(buf[0] + off, len, i0, o.A);
+                  store_sol(buf[1] + off, len, i0, o.B);
+                } else {
+                  store_sol(ga, ld, i0, o.A);
+                  store_sol(gb, ld, i0, o.B);
+                }
+              }
+              sum = fr_add(sum, o.val);
+            }
+            acc_add(acc, kMatAccRound + pt, sum, on);
+          }
+          if (!lds) __threadfence_block();   // the folded entries, for the next round
         }
-        __threadfence_block();   // the folded entries, for the next sweep
-        block_sum_w0<3>(g, red);
+        if (lds) at = at == 0 ? 1 : 0;
+        __syncthreads();   // the sums and the folded entries
       }
       if (wave == 0) {
-        const Fr rr = round_challenge(tr, g, out, lane);
-        if (lane == 0) lds_put(bcast, rr);
+        mat_round(acc, rd == 0 ? kMatAccProd + 3 * p : kMatAccRound, out + 96ull * rd, T, true);
+        if (lane < 30) acc[10 * kMatAccRound + lane] = 0;
       }
-      out += 96;
-      __syncthreads();
-      // every thread reads r before its next sweep's block sum, whose
-      // barrier wave 0 passes before it writes bcast again
-      r = lds_get(bcast);
-      pending = true;
+      __syncthreads();   // r and the zeroed sums
     }
-    // The last rounds (half-table h <= 64), split over two waves so that the
-    // table work of a round overlaps the hashing of the one before:
-    //  - wave 1 holds the pairs in registers (lane t: entries t and t + h of
-    //    a and b; the last global challenge, if any, folded in as they are
-    //    loaded).  While wave 0 hashes round j it folds the tables by r_{j-1}
-    //    and writes the next round's three values as quadratics in the
-    //    challenge r_j it does not know yet: with the folded entries
-    //    x + r y, each value sum (x + r y)(x' + r y') has the coefficients
-    //    sum x x', sum (x y' + y x'), sum y y' (three products per pair);
-    //  - wave 0 evaluates round j's values from those coefficients at r_{j-1}
-    //    (exact: the same field elements as a direct sum), writes them to the
-    //    proof, absorbs them and squeezes r_j.
-    // One barrier per round hands r_j to wave 1 and the coefficients to wave
-    // 0 (both double-buffered by round parity); the other waves only take part
-    // in the barriers.
-    if (rd < P.n1) {
-      const uint32_t rd0 = rd;
-      uint32_t h = 1u << (P.n1 - 1 - rd0);
-      Fr A0 = fr_zero(), A1 = fr_zero(), B0 = fr_zero(), B1 = fr_zero();
-      if (wave >= 1 && wave <= 3) {
-        if (lane < h) {
-          A0 = load_sol(a, ld, lane);
-          A1 = load_sol(a, ld, lane + h);
-          B0 = load_sol(b, ld, lane);
-          B1 = load_sol(b, ld, lane + h);
-          if (pending) {
-            const Fr rr2[2] = {r, r};
-            const Fr da[2] = {fr_sub(load_sol(a, ld, lane + 2 * h), A0), fr_sub(load_sol(a, ld, lane + 3 * h), A1)};
-            const Fr db[2] = {fr_sub(load_sol(b, ld, lane + 2 * h), B0), fr_sub(load_sol(b, ld, lane + 3 * h), B1)};
-            Fr fa[2], fb[2];
-            fr_mul_n<2>(rr2, da, fa);
-            fr_mul_n<2>(rr2, db, fb);
-            A0 = fr_add(A0, fa[0]);
-            A1 = fr_add(A1, fa[1]);
-            B0 = fr_add(B0, fb[0]);
-            B1 = fr_add(B1, fb[1]);
-          }
-        }
-        // round rd0's values directly, as constant quadratics (wave 1)
-        if (wave == 1) {
-          Fr g[3];   // lanes >= h hold zeros
-          {
-            const Fr x[3] = {A0, A1, at_two(A0, A1)}, y[3] = {B0, B1, at_two(B0, B1)};
-            fr_mul_n<3>(x, y, g);
-          }
-          wave_sum<3>(g, h);
-          if (lane == 0)
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-              lds_put(coef[rd0 & 1][k][0], g[k]);
-              lds_put(coef[rd0 & 1][k][1], g[k]);   // c1 = [1] - [0] - [2] = 0
-              lds_put(coef[rd0 & 1][k][2], fr_zero());
-            }
-        }
-      }
-      __syncthreads();
-      for (uint32_t j = rd0; j < P.n1; ++j, h >>= 1) {
-        if (wave == 0) {
-          const Fr rp = j > rd0 ? lds_get(rbuf[(j - 1) & 1]) : fr_zero();
-          // g_k = c0 + r (c1 + r c2) with c1 = [1] - c0 - c2, lane k < 3
-          // evaluating value k (the three side by side), then gathered
-          const uint32_t kk = lane < 3 ? lane : 2u;
-          const Fr c0 = lds_get(coef[j & 1][kk][0]), c2 = lds_get(coef[j & 1][kk][2]);
-          const Fr c1 = fr_sub(fr_sub(lds_get(coef[j & 1][kk][1]), c0), c2);
-          const Fr mine = fr_add(c0, fr_mul(rp, fr_add(c1, fr_mul(rp, c2))));
-          Fr g[3];
-#pragma unroll
-          for (int k = 0; k < 3; ++k) g[k] = readlane_fr(mine, k);
-          const Fr rj = round_challenge(tr, g, out, lane);
-          if (lane == 0) lds_put(rbuf[j & 1], rj);
-        } else if (wave >= 1 && wave <= 3) {
-          if (j > rd0) {
-            // fold by r_{j-1}; entry t + h of the folded table comes from lane t + h
-            const Fr rp = lds_get(rbuf[(j - 1) & 1]);
-            const uint32_t hp = 2 * h;   // the previous round's half-size
-            const Fr rp2[2] = {rp, rp}, d[2] = {fr_sub(A1, A0), fr_sub(B1, B0)};
-            Fr f[2];
-            fr_mul_n<2>(rp2, d, f);
-            Fr na = fr_add(A0, f[0]);
-            Fr nb = fr_add(B0, f[1]);
-            if (lane >= hp) na = nb = fr_zero();
-            Fr ua, ub;
-#pragma unroll
-            for (int w = 0; w < 8; ++w) {
-              ua.w[w] = __shfl(na.w[w], (int)(lane + h), kWave);
-              ub.w[w] = __shfl(nb.w[w], (int)(lane + h), kWave);
-            }
-            const bool in = lane < h;
-            A0 = in ? na : fr_zero();
-            B0 = in ? nb : fr_zero();
-            A1 = in ? ua : fr_zero();
-            B1 = in ? ub : fr_zero();
-          }
-          if (j + 1 < P.n1) {
-            // round j + 1 as quadratics in r_j: lane t < h/2 pairs its
-            // folded entry x + r y (from entries t, t + h) with lane
-            // t + h/2's (entries t + h/2, t + h/2 + h)
-            const uint32_t hh = h >> 1;
-            Fr qa0, qa1, qb0, qb1;   // lane t + hh's pair
-#pragma unroll
-            for (int w = 0; w < 8; ++w) {
-              qa0.w[w] = __shfl(A0.w[w], (int)(lane + hh), kWave);
-              qa1.w[w] = __shfl(A1.w[w], (int)(lane + hh), kWave);
-              qb0.w[w] = __shfl(B0.w[w], (int)(lane + hh), kWave);
-              qb1.w[w] = __shfl(B1.w[w], (int)(lane + hh), kWave);
-            }
-            Fr xa[3], ya[3], xb[3], yb[3];
-            xa[0] = A0;  ya[0] = fr_sub(A1, A0);
-            xb[0] = B0;  yb[0] = fr_sub(B1, B0);
-            xa[1] = qa0; ya[1] = fr_sub(qa1, qa0);
-            xb[1] = qb0; yb[1] = fr_sub(qb1, qb0);
-            xa[2] = at_two(xa[0], xa[1]); ya[2] = at_two(ya[0], ya[1]);
-            xb[2] = at_two(xb[0], xb[1]); yb[2] = at_two(yb[0], yb[1]);
-            // Karatsuba's three products split over waves 1, 2, 3: the sums of
-            // x x' (term 0), (x + y)(x' + y') (term 1) and y y' (term 2);
-            // wave 0 forms c1 = [1] - [0] - [2]
-            const uint32_t role = wave - 1;
-            Fr ua[3], ub[3], pr[3];
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-              ua[k] = role == 0 ? xa[k] : (role == 2 ? ya[k] : fr_add(xa[k], ya[k]));
-              ub[k] = role == 0 ? xb[k] : (role == 2 ? yb[k] : fr_add(xb[k], yb[k]));
-            }
-            fr_mul_n<3>(ua, ub, pr);
-            if (lane >= hh)
-#pragma unroll
-              for (int k = 0; k < 3; ++k) pr[k] = fr_zero();
-            wave_sum<3>(pr, hh);
-            if (lane == 0)
-#pragma unroll
-              for (int k = 0; k < 3; ++k) lds_put(coef[(j + 1) & 1][k][role], pr[k]);
-          }
-        }
-        out += 96;
-        __syncthreads();
-      }
-      // the last challenge folds the single remaining pair into the finals
-      if (wave == 1 && lane == 0) {
-        const Fr rl = lds_get(rbuf[(P.n1 - 1) & 1]);
-        const Fr rl2[2] = {rl, rl}, d[2] = {fr_sub(A1, A0), fr_sub(B1, B0)};
-        Fr f[2];
-        fr_mul_n<2>(rl2, d, f);
-        lds_put(finv[0], fr_add(A0, f[0]));
-        lds_put(finv[1], fr_add(B0, f[1]));
-      }
-      __syncthreads();
-    }
+    // lane k < 2 of wave 0: the final value of table k, the last challenge
+    // folding the remaining pair; a~ out of Montgomery form
+    out += 96ull * n1;
     if (wave == 0) {
-      Fr fa, fb;   // the product's final a~ and b~ (lane 0)
-      if (P.n1 > 0) {
-        fa = lds_get(finv[0]);
-        fb = lds_get(finv[1]);
-      } else {   // no rounds (D1 = 1)
-        fa = load_sol(a, ld, 0);
-        fb = load_sol(b, ld, 0);
+      const uint32_t k = min(lane, 1u);
+      Fr mine = get(k, 0);
+      if (n1) mine = fr_fold(lds_get(T.r), mine, get(k, 1));
+      const Fr canon = fr_from_mont(mine);
+      if (k == 0) mine = canon;
+      if (lane < 2) {
+        put_canon(out + 32 * lane, mine);
+        lds_put(T.v + 8 * lane, mine);
       }
-      if (lane == 0) {
-        Fr fin[2];
-        fin[0] = fr_from_mont(fa);   // a~ tables are in Montgomery form,
-        fin[1] = fb;                 // b~ tables in canonical form
-        put_canon(out, fin[0]);
-        put_canon(out + 32, fin[1]);
-        tr_absorb_frs(tr, VL_LBL_FINAL, fin);
-      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      if (p + 1 < J.n_prods || J.digest) tr_absorb_lanes(T, kLblFinal4, kLblFinal1, 2);
     }
     out += 64;
-    __syncthreads();
+    __syncthreads();   // the buffers, before the next product's tables
   }
   if (tid == 0) {
-    if (J.digest) {
-      uint8_t d[32];
-      tr_to_bytes(tr, d);
-      for (int i = 0; i < 32; ++i) J.digest[i] = d[i];
-    }
+    if (J.digest) tr_put_digest(T, J.digest);
     *J.status = VL_OK;
   }
 }
@@ -1206,14 +916,15 @@ hipError_t launch_pack(const uint32_t* eq, uint64_t ld, uint64_t len, uint32_t* 
 
 hipError_t launch_pass1(const Pass1Job* jobs, uint32_t n_jobs, uint32_t n_blocks, hipStream_t s) {
   if (n_blocks == 0) return hipSuccess;
-  hipLaunchKernelGGL(pass1_kernel, dim3(n_blocks), dim3(256), 0, s, jobs, n_jobs, n_blocks);
+  hipLaunchKernelGGL(pass1_kernel, dim3(n_blocks), dim3(kPass1Block), 0, s, jobs, n_jobs, n_blocks);
   return hipGetLastError();
 }
 
 hipError_t launch_mat_sweep(const RoundsJob* jobs, const MatSweep* list, uint32_t n_list, uint32_t n_blocks,
                             uint32_t round, hipStream_t s) {
   if (!n_blocks) return hipSuccess;
-  hipLaunchKernelGGL(mat_sweep_kernel, dim3(n_blocks), dim3(256), 0, s, jobs, list, n_list, n_blocks, round);
+  hipLaunchKernelGGL(mat_sweep_kernel, dim3(n_blocks), dim3(3 * kMatSweepPairs), 0, s, jobs, list, n_list, n_blocks,
+                     round);
   return hipGetLastError();
 }
 
