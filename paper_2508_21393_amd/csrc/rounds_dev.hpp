@@ -269,15 +269,6 @@ __device__ __forceinline__ uint32_t rotv(uint32_t x, int n) { return __builtin_a
 __device__ __forceinline__ uint32_t xor3v(uint32_t a, uint32_t b, uint32_t c) { return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96); }
 __device__ __forceinline__ uint32_t sha_s0(uint32_t x) { return xor3v(rotv(x, 7), rotv(x, 18), x >> 3); }
 __device__ __forceinline__ uint32_t sha_s1(uint32_t x) { return xor3v(rotv(x, 17), rotv(x, 19), x >> 10); }
-// one SHA-256 round on s = {a .. h}; wk: message word plus constant
-__device__ __forceinline__ void sha_round(uint32_t (&s)[8], uint32_t wk) {
-  const uint32_t t1 = (s[7] + wk + __builtin_amdgcn_bitop3_b32(s[4], s[5], s[6], 0xca)) +
-                      xor3v(rotv(s[4], 6), rotv(s[4], 11), rotv(s[4], 25));
-  const uint32_t a = t1 + xor3v(rotv(s[0], 2), rotv(s[0], 13), rotv(s[0], 22)) +
-                     __builtin_amdgcn_bitop3_b32(s[0], s[1], s[2], 0xe8);
-  s[7] = s[6]; s[6] = s[5]; s[5] = s[4]; s[4] = s[3] + t1;
-  s[3] = s[2]; s[2] = s[1]; s[1] = s[0]; s[0] = a;
-}
 #define VL_SHA_IV {0x6a09e667u, 0xbb67ae85u, 0x3c6ef372u, 0xa54ff53au, 0x510e527fu, 0x9b05688cu, 0x1f83d9abu, 0x5be0cd19u}
 
 // Word `lane` of the padded message state || five-letter label || K values,
@@ -301,42 +292,126 @@ __device__ __forceinline__ uint32_t tr_message(RoundLds& T, uint32_t label4, uin
   return (uint32_t)NB;
 }
 
+// One SHA-256 hash on two lanes four apart: the one in the even bank of four
+// lanes has a, b, c, d and forms S0(a) + maj(a, b, c), the one in the odd bank
+// has e, f, g, h and forms t1 = S1(e) + ch(e, f, g) + h + wk.  The same
+// instructions serve both: rotations by per-lane amounts, and maj(a, b, c) is
+// the choice between b and c by ~(a ^ b).  Ten instructions a round instead of
+// 14; a wave issues one per four cycles and that bounds a transcript.
+struct ShaLane {
+  uint32_t odd;          // 1 in the lane of e .. h
+  uint32_t r1, r2, r3;   // rotations
+  uint32_t m;            // all ones in the lane of a .. d
+};
+__device__ __forceinline__ ShaLane sha_lane(uint32_t lane) {
+  ShaLane L;
+  L.odd = (lane >> 2) & 1u;
+  L.r1 = L.odd ? 6u : 2u;
+  L.r2 = L.odd ? 11u : 13u;
+  L.r3 = L.odd ? 25u : 22u;
+  L.m = L.odd ? 0u : ~0u;
+  return L;
+}
+// x of the lane four below in odd banks (old elsewhere), or four above in even ones
+__device__ __forceinline__ uint32_t sha_to_odd(uint32_t old, uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)x, 0x114, 0xf, 0xa, false);   // row_shr:4
+}
+__device__ __forceinline__ uint32_t sha_to_even(uint32_t old, uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)x, 0x104, 0xf, 0x5, false);   // row_shl:4
+}
+// one round: the new a or e replaces s3; u holds h + wk of this round in odd
+// lanes and zero in even ones, and leaves as that of the next (its word w).
+// An instruction's result is read across lanes three instructions later.
+#define VL_SHA_RND(s0, s1, s2, s3, w)                                            \
+  "v_alignbit_b32 %[x], %[" s0 "], %[" s0 "], %[r1]\n"                           \
+  "v_alignbit_b32 %[y], %[" s0 "], %[" s0 "], %[r2]\n"                           \
+  "v_alignbit_b32 %[z], %[" s0 "], %[" s0 "], %[r3]\n"                           \
+  "v_bitop3_b32 %[f], %[" s0 "], %[" s1 "], %[m] bitop3:0xd2\n"                  \
+  "v_bitop3_b32 %[x], %[x], %[y], %[z] bitop3:0x96\n"                            \
+  "v_bitop3_b32 %[f], %[f], %[" s1 "], %[" s2 "] bitop3:0xca\n"                  \
+  "v_add3_u32 %[t], %[x], %[f], %[u]\n"                                          \
+  "v_add_u32_dpp %[u], %[" s2 "], %[" w "] quad_perm:[0,1,2,3] row_mask:0xf bank_mask:0xa\n" \
+  "v_add_u32_dpp %[" s3 "], %[" s3 "], %[t] row_shr:4 row_mask:0xf bank_mask:0xa\n" \
+  "v_add_u32_dpp %[" s3 "], %[t], %[t] row_shl:4 row_mask:0xf bank_mask:0x5\n"
+__device__ __forceinline__ void sha_four(uint32_t (&s)[4], uint32_t& u, const ShaLane& L, uint32_t w1, uint32_t w2,
+                                         uint32_t w3, uint32_t w4) {
+  uint32_t x, y, z, f, t;
+  asm(VL_SHA_RND("a", "b", "c", "d", "w1") VL_SHA_RND("d", "a", "b", "c", "w2")
+      VL_SHA_RND("c", "d", "a", "b", "w3") VL_SHA_RND("b", "c", "d", "a", "w4")
+      : [a] "+v"(s[0]), [b] "+v"(s[1]), [c] "+v"(s[2]), [d] "+v"(s[3]), [u] "+v"(u), [x] "=&v"(x), [y] "=&v"(y),
+        [z] "=&v"(z), [f] "=&v"(f), [t] "=&v"(t)
+      : [r1] "v"(L.r1), [r2] "v"(L.r2), [r3] "v"(L.r3), [m] "v"(L.m), [w1] "v"(w1), [w2] "v"(w2), [w3] "v"(w3),
+        [w4] "v"(w4));
+}
+#undef VL_SHA_RND
+
+// words 2 k, 2 k + 1 of a schedule in the two lanes (p) and 2 k + 1, 2 k + 2 (q),
+// a ring of eight of each: the next pair, i = k mod 8, two words in twelve
+// instructions
+__device__ __forceinline__ void sha_next_pair(uint32_t (&p)[8], uint32_t (&q)[8], int i) {
+  p[i] = p[i] + sha_s0(q[i]) + q[(i + 4) & 7] + sha_s1(p[(i + 7) & 7]);
+  q[(i + 7) & 7] = sha_to_odd(q[(i + 7) & 7], p[i]);
+  q[i] = sha_to_even(0u, p[i]);   // its odd lanes: with the pair after
+}
+
 // absorb(label, x_0 .. x_{K-1}) for a label of four or five letters by all 64 lanes of one
-// wave, the K <= 5 canonical values in T.v: one block after the other (once or
-// twice per proof, so small code counts: it is fetched for one pass)
+// wave, the K <= 5 canonical values in T.v: one block after the other, every
+// lane pair the same (once or twice per proof, so small code counts: it is
+// fetched for one pass)
 constexpr uint32_t kLblFinal4 = 0x66696e61u, kLblFinal1 = 0x6cu;   // "fina", "l"
 constexpr uint32_t kLblPart4 = 0x70617274u;                        // "part"
 constexpr uint32_t kLblClaim4 = 0x636c6169u, kLblClaim1 = 0x6du;   // "clai", "m"
 __device__ __forceinline__ void tr_absorb_lanes(RoundLds& T, uint32_t label4, uint32_t label1, int K) {
+  const uint32_t lane = threadIdx.x & 63u;
   const uint32_t NB = tr_message(T, label4, label1, K);
-  uint32_t h[8] = VL_SHA_IV;
+  const ShaLane L = sha_lane(lane);
+  constexpr uint32_t iv[8] = VL_SHA_IV;
+  uint32_t h[4];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) asm("" : "+v"(h[i]));
+  for (int j = 0; j < 4; ++j) h[j] = L.odd ? iv[4 + j] : iv[j];
   const uint32_t* KK = sha256_k();
 #pragma unroll 1
   for (uint32_t b = 0; b < NB; ++b) {
-    uint32_t z[16], s[8];
+    uint32_t w0 = T.w[16 * b], p[8], q[8], s[4];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      z[i] = T.w[16 * b + i];
-      asm("" : "+v"(z[i]));
+    for (int k = 0; k < 8; ++k) {
+      p[k] = T.w[16 * b + 2 * k + L.odd];
+      q[k] = T.w[(16 * b + 2 * k + 1 + L.odd) & 63];   // (word 16 of the last one follows below)
     }
 #pragma unroll
-    for (int i = 0; i < 8; ++i) s[i] = h[i];
+    for (int j = 0; j < 4; ++j) s[j] = h[j];
+    uint32_t kk[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) kk[i] = KK[i];
 #pragma unroll 1
     for (int it = 0; it < 4; ++it) {
+      uint32_t w[16], u;
+      w[0] = w0;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        sha_round(s, z[i] + KK[16 * it + i]);
-        z[i] = z[i] + sha_s0(z[(i + 1) & 15]) + z[(i + 9) & 15] + sha_s1(z[(i + 14) & 15]);
+      for (int k = 0; k < 8; ++k) {
+        w[2 * k + 1] = p[k];
+        if (k < 7) w[2 * k + 2] = q[k];
+      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i) w[i] += kk[i];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) kk[i] = KK[(16 * it + 16 + i) & 63];   // on their way during the rounds
+      __builtin_amdgcn_sched_barrier(0);
+      u = L.odd ? s[3] + w[0] : 0u;
+#pragma unroll
+      for (int i = 0; i < 16; i += 4) sha_four(s, u, L, w[i + 1], w[i + 2], w[i + 3], w[(i + 4) & 15]);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        sha_next_pair(p, q, i);
+        if (i == 0) w0 = q[7];
       }
     }
 #pragma unroll
-    for (int i = 0; i < 8; ++i) h[i] += s[i];
+    for (int j = 0; j < 4; ++j) h[j] += s[j];
   }
-  if ((threadIdx.x & 63u) == 0)
+  if ((lane & ~4u) == 0)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) T.st[i] = h[i];
+    for (int j = 0; j < 4; ++j) T.st[lane + j] = h[j];
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 }
 // the state as 32 digest bytes, by one lane
@@ -351,75 +426,117 @@ __device__ __forceinline__ void tr_put_digest(const RoundLds& T, uint8_t* out) {
 // 3 or 4: T.v holds the canonical values (8 K words), T.st the state; leaves
 // the new state in T.st and the challenge, in Montgomery form, in T.r.  The
 // same digests as tr_absorb_frs and tr_squeeze_fixed.
-// Bound by the issue of one wave's instructions, 4 cycles each (14 a hash
-// round and 10 a schedule word), so lanes share what they can: lane i builds
-// message word i; lane b < 3 holds block b's schedule and its chaining value
-// moves from lane to lane; lane c squeezes with counter c, so that a rejected
-// candidate (one in ten) costs nothing.  About 24,500 cycles.
+// Bound by the issue of one wave's instructions, 4 cycles each, so lanes share
+// what they can: lane i builds message word i; the lane pair of block b < 3
+// makes its schedule and the chaining value moves from pair to pair; pair c
+// squeezes with counter c, so that a rejected candidate (one in ten) costs
+// nothing.  Both hashes pass through the same code.  7.9 us; 10.2
+// with a hash in one lane and the schedule word by word.
 __device__ __forceinline__ void tr_round(RoundLds& T, int K) {
   const uint32_t lane = threadIdx.x & 63u;
   tr_message(T, 0x726f756eu, 0x64u, K);   // "roun", "d": three blocks
-  const uint32_t blk = min(lane, 2u);
-  const uint32_t* KK = sha256_k();
-  uint32_t w[64];
+  const uint32_t blk = min(lane & 3u, 2u);
+  constexpr uint32_t KK[64] = {VL_SHA256_K};   // literals: scalar loads of them took longer
+  ShaLane L = sha_lane(lane);
+  asm("" : "+v"(L.r1), "+v"(L.r2), "+v"(L.r3), "+v"(L.m));
+  uint32_t w0 = T.w[16 * blk], p[8], q[8], h[4];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) w[i] = T.w[16 * blk + i];
-#pragma unroll
-  for (int i = 16; i < 64; ++i) w[i] = w[i - 16] + sha_s0(w[i - 15]) + w[i - 7] + sha_s1(w[i - 2]);
-#pragma unroll
-  for (int i = 0; i < 64; ++i) w[i] += KK[i];
-  uint32_t h[8] = VL_SHA_IV;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) asm("" : "+v"(h[i]));   // vector registers from the start
-#pragma unroll 1
-  for (int b = 0; b < 3; ++b) {
-    uint32_t s[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) s[i] = h[i];
-#pragma unroll
-    for (int i = 0; i < 64; ++i) sha_round(s, w[i]);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      h[i] += s[i];
-      // to the next block's lane (row_shr:1); after the last block lane 2
-      // holds the digest, and lane 3 gets it
-      h[i] = (uint32_t)__builtin_amdgcn_update_dpp((int)h[i], (int)h[i], 0x111, 0xf, 0xf, false);
-    }
+  for (int k = 0; k < 8; ++k) {
+    p[k] = T.w[16 * blk + 2 * k + L.odd];
+    q[k] = T.w[16 * blk + 2 * k + 1 + L.odd];   // (word 16 of the last one follows below)
   }
-  uint32_t d[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) d[i] = (uint32_t)__builtin_amdgcn_readlane((int)h[i], 3);
-  uint64_t ok = 0;
-  uint32_t g[8];
-  Fr x;
+  uint32_t base = 0;   // phase 0: absorb; then counters base ..
 #pragma unroll 1
-  for (uint32_t base = 0; ok == 0; base += 64) {
-    const uint32_t c = base + lane;
-    uint32_t z[16] = {d[0], d[1], d[2], d[3], d[4], d[5], d[6], d[7], 0x72000000u | ((c & 0xffu) << 16) | (c & 0xff00u),
-                      0x00800000u, 0, 0, 0, 0, 0, 37 * 8};   // "r", the counter (below 2^16), padding
-    uint32_t s[8] = VL_SHA_IV;
-#pragma unroll
-    for (int i = 0; i < 64; ++i) {
-      if (i >= 16) z[i & 15] = z[i & 15] + sha_s0(z[(i + 1) & 15]) + z[(i + 9) & 15] + sha_s1(z[(i + 14) & 15]);
-      sha_round(s, z[i & 15] + KK[i]);
-    }
+  for (uint32_t phase = 0;; ++phase) {
     constexpr uint32_t iv[8] = VL_SHA_IV;
+    uint32_t w[64];
+    w[0] = w0;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      g[i] = s[i] + iv[i];
-      x.w[i] = __builtin_amdgcn_perm(g[i], g[i], 0x00010203u);
+    for (int k = 0; k < 32; ++k) {
+      const int i = k & 7;
+      if (k >= 8) {
+        sha_next_pair(p, q, i);
+        w[2 * k] = q[(i + 7) & 7];
+      } else if (k > 0) {
+        w[2 * k] = q[k - 1];
+      }
+      w[2 * k + 1] = p[i];
     }
-    x.w[7] &= 0x7fffffffu;
-    ok = __ballot(fr_lt_p(x));
+#pragma unroll
+    for (int i = 0; i < 64; ++i) w[i] += KK[i];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      h[j] = L.odd ? iv[4 + j] : iv[j];
+      asm("" : "+v"(h[j]));
+    }
+#pragma unroll 1
+    for (uint32_t b = 0; b < (phase ? 1u : 3u); ++b) {
+      uint32_t s[4], u = L.odd ? h[3] + w[0] : 0u;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) s[j] = h[j];
+#pragma unroll
+      for (int i = 0; i < 64; i += 4) sha_four(s, u, L, w[i + 1], w[i + 2], w[i + 3], w[(i + 4) & 63]);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        h[j] += s[j];
+        // to the next block's pair (row_shr:1); after the last block lanes 2
+        // and 6 hold the digest, and 3 and 7 get it
+        if (!phase) h[j] = (uint32_t)__builtin_amdgcn_update_dpp((int)h[j], (int)h[j], 0x111, 0xf, 0xf, false);
+      }
+    }
+    uint32_t d[9];
+    if (phase == 0) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        d[j] = (uint32_t)__builtin_amdgcn_readlane((int)h[j], 3);
+        d[4 + j] = (uint32_t)__builtin_amdgcn_readlane((int)h[j], 7);
+      }
+      if (lane == 0)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) T.st[j] = d[j];
+    } else {
+      // the candidate's eight words to the odd lane
+      uint32_t g[8];
+      Fr x;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        g[j] = sha_to_odd(0u, h[j]);
+        g[4 + j] = h[j];
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j) x.w[j] = __builtin_amdgcn_perm(g[j], g[j], 0x00010203u);
+      x.w[7] &= 0x7fffffffu;
+      const uint64_t ok = __ballot(L.odd && fr_lt_p(x));
+      if (ok) {
+        const Fr xm = fr_to_mont(x);
+        if (lane == (uint32_t)__builtin_ctzll(ok))
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            T.st[j] = g[j];
+            T.r[j] = xm.w[j];
+          }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        return;
+      }
+      base += 32;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) d[j] = T.st[j];
+    }
+    // state || "r", the counter (below 2^16) || padding
+    const uint32_t c = base + (lane >> 4) * 8 + ((lane >> 3) & 1u) * 4 + (lane & 3u);
+    d[8] = 0x72000000u | ((c & 0xffu) << 16) | (c & 0xff00u);
+    w0 = d[0];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      p[k] = L.odd ? d[2 * k + 1] : d[2 * k];
+      q[k] = L.odd ? d[2 * k + 2] : d[2 * k + 1];
+    }
+    p[4] = L.odd ? 0x00800000u : d[8];
+    q[4] = L.odd ? 0u : 0x00800000u;
+    p[5] = p[6] = q[5] = q[6] = 0u;
+    p[7] = L.odd ? 37 * 8 : 0u;
+    q[7] = 37 * 8;
   }
-  const Fr xm = fr_to_mont(x);
-  if (lane == (uint32_t)__builtin_ctzll(ok))
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      T.st[i] = g[i];
-      T.r[i] = xm.w[i];
-    }
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 }
 
 }  // namespace vl
