@@ -544,6 +544,12 @@ void Builder::contract(const void* M, int dtype, int nd, uint64_t ld, bool rows,
   }
 }
 
+// the table's entries, or without one the packed ones (pack_len <= 2^nvars)
+static uint32_t eq_blocks_of(const EqJob& e) {
+  const uint64_t n = e.eq ? 1ull << e.nvars : std::max<uint64_t>(1, e.pack ? e.pack_len : 1);
+  return (uint32_t)((n + kEqBlock - 1) / kEqBlock);
+}
+
 void Builder::eq_job(const std::vector<Fr>& x, uint32_t* eq, uint32_t* pack, uint32_t pack_len, bool pack_r2,
                      bool eq_canon, const Fr* scale, const std::vector<uint32_t>* mont) {
   EqJob e{};
@@ -555,7 +561,7 @@ void Builder::eq_job(const std::vector<Fr>& x, uint32_t* eq, uint32_t* pack, uin
   e.pack_r2 = pack_r2 ? 1u : 0u;
   e.eq_canon = eq_canon ? 1u : 0u;
   e.pack_len = pack_len;
-  e.thread_begin = P.eq_threads;
+  e.block_begin = P.eq_blocks;
   e.eq = eq;
   e.eq_ld = 1ull << x.size();
   e.pack = pack;
@@ -571,10 +577,7 @@ void Builder::eq_job(const std::vector<Fr>& x, uint32_t* eq, uint32_t* pack, uin
     P.points.push_back(std::move(pts));
   }
   P.point_dev.push_back(nullptr);
-  // one thread per 4 entries (one for the whole table below 2 variables);
-  // pack_len <= 2^nvars
-  const uint32_t threads = std::max<uint32_t>(1, (uint32_t)((1ull << x.size()) / 4));
-  P.eq_threads += std::max(threads, (pack_len + 3) / 4);
+  P.eq_blocks += eq_blocks_of(e);
   P.eq.push_back(e);
 }
 
@@ -585,14 +588,13 @@ void Builder::eq_job_dev(uint32_t nvars, const uint32_t* point_dev, uint32_t* eq
   e.pack_r2 = pack_r2 ? 1u : 0u;
   e.eq_canon = eq_canon ? 1u : 0u;
   e.pack_len = pack_len;
-  e.thread_begin = P.eq_threads;
+  e.block_begin = P.eq_blocks;
   e.eq = eq;
   e.eq_ld = 1ull << nvars;
   e.pack = pack;
   P.points.push_back({});
   P.point_dev.push_back(point_dev);
-  const uint32_t threads = std::max<uint32_t>(1, (uint32_t)((1ull << nvars) / 4));
-  P.eq_threads += std::max(threads, (pack_len + 3) / 4);
+  P.eq_blocks += eq_blocks_of(e);
   P.eq.push_back(e);
 }
 
@@ -996,7 +998,7 @@ hipError_t enqueue_plan(const Plan& P, const BlobLayout& L, uint8_t* dblob, hipS
            blob_src_dev ? launch_copy_in(dblob, blob_src_dev, L.total, s)
                         : upload_blob(dblob, P.blob.data(), L.total, s));
   VL_STAGE(ev, VL_STAGE_EQ, s,
-           launch_eq(reinterpret_cast<const EqJob*>(dblob + L.eq), (uint32_t)P.eq.size(), P.eq_threads, s));
+           launch_eq(reinterpret_cast<const EqJob*>(dblob + L.eq), (uint32_t)P.eq.size(), P.eq_blocks, s));
   if (two) {
     // the rounds stream starts after everything queued before this call
     hipError_t e = hipEventRecord(fork.ev[nseg], s);
@@ -1642,9 +1644,8 @@ vl_status vl_eq_table(const vl_fr* point, uint32_t nvars, vl_fr_vec out, void* s
     Fr x;
     memcpy(x.w, point[i].w, 32);
     if (!fr_lt_p(x)) return fail(VL_ERR_INVALID_ARG, "point[%u] is not canonical", i);
-    const Fr xm = fr_to_mont(x), om = fr_sub(fr_R(), xm);
-    memcpy(a.pt[i][0], xm.w, 32);
-    memcpy(a.pt[i][1], om.w, 32);
+    const Fr xm = fr_to_mont(x);
+    memcpy(a.pt[i], xm.w, 32);
   }
   const hipError_t e = launch_eq_point(a, reinterpret_cast<hipStream_t>(stream));
   if (e != hipSuccess) return fail(VL_ERR_HIP, "eq_table: %s", hipGetErrorString(e));

@@ -279,14 +279,6 @@ VL_HD Fr fr_mul(const Fr& a, const Fr& b) {
 #endif
 }
 
-// r[c] = a[c] * b[c] * R^-1 for c < N (N = 2 or 3), independent products
-template <int N>
-VL_HD void fr_mul_n(const Fr (&a)[N], const Fr (&b)[N], Fr (&r)[N]) {
-  static_assert(N == 2 || N == 3, "two or three products");
-#pragma unroll
-  for (int c = 0; c < N; ++c) r[c] = fr_mul(a[c], b[c]);
-}
-
 VL_HD Fr fr_to_mont(const Fr& a) { return fr_mul(a, fr_R2()); }
 VL_HD Fr fr_from_mont(const Fr& a) { return fr_mul(a, fr_one_raw()); }
 

@@ -12,10 +12,11 @@ namespace vl {
 
 // An eq table to build: out[i] = prod_j (x_j or 1 - x_j), i < 2^nvars, plus
 // its "pack" form used by the integer contractions (see contract kernel).
+constexpr uint32_t kEqBlock = 256;
 struct EqJob {
   uint32_t nvars;
   uint32_t pack_len;          // entries to emit into pack (8 signed digits each)
-  uint32_t thread_begin;      // prefix sum of threads over jobs in a launch
+  uint32_t block_begin;       // prefix sum of blocks (kEqBlock entries each) over jobs in a launch
   uint32_t pack_r2;           // 1: pack holds e * R^2 (contractions land in Montgomery
                               // form); 0: e * R (they land in canonical form)
   uint32_t eq_canon;          // 1: eq holds canonical values, 0: Montgomery form
@@ -33,7 +34,7 @@ struct EqPointArgs {
   uint32_t pad_;
   uint32_t* out;
   uint64_t ld;
-  uint32_t pt[20][2][8];      // Montgomery (x_j, 1 - x_j)
+  uint32_t pt[20][8];         // Montgomery
 };
 
 // A slice of a host image copied to device memory by a kernel launch.
@@ -306,7 +307,7 @@ hipError_t launch_reduce_sweep(const ReduceJob* jobs_dev, const MatSweep* list_d
                                uint32_t round, hipStream_t s);
 hipError_t launch_reduce_step(const ReduceJob* jobs_dev, const MatSweep* list_dev, uint32_t n_list, uint32_t round,
                               hipStream_t s);
-hipError_t launch_eq(const EqJob* jobs_dev, uint32_t n_jobs, uint32_t n_threads, hipStream_t s);
+hipError_t launch_eq(const EqJob* jobs_dev, uint32_t n_jobs, uint32_t n_blocks, hipStream_t s);
 hipError_t launch_contract(int kind, const ContractJob* jobs_dev, uint32_t n_jobs, uint32_t n_tasks,
                            hipStream_t s);
 hipError_t launch_finish(const FinishJob* jobs_dev, uint32_t n_jobs, uint32_t n_blocks, hipStream_t s);

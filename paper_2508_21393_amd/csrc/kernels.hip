@@ -20,98 +20,106 @@
 namespace vl {
 
 // ---------------------------------------------------------------- eq -------
-__global__ void __launch_bounds__(256) eq_kernel(const EqJob* __restrict__ jobs, uint32_t n_jobs,
-                                                 uint32_t n_threads) {
-  const uint32_t tid = blockIdx.x * blockDim.x + threadIdx.x;
-  if (tid >= n_threads) return;
+// Entry i of an eq table is a product of n factors: x_j for bit 1 and 1 - x_j
+// for bit 0, b_1 the most significant bit.  A block has kEqBlock = 2^8
+// consecutive entries, one per thread: two tables of 16 products over the low
+// variables, four lanes multiplying an entry's factors as a tree, and the
+// block's product over the others (with the form's constant and the scale)
+// likewise; then two products an entry.  Bound by that chain of about seven
+// products: with n + 4 of them in sequence on a thread of four entries, and 41
+// KB of code, the single 64 x 128 x 32 product's tables took 15 us and the 7B
+// block's 36, now 5.4 and 23.
+struct EqLds {
+  uint32_t g[2][16][8];
+  uint32_t up[8];
+};
+// the form an entry is multiplied into: times R once more, as the factors are
+// (Montgomery), or out of Montgomery form
+enum EqForm { EQ_CANON = 0, EQ_MONT = 1, EQ_R2 = 2 };
+// Entry 256 blk + threadIdx.x (or a product without meaning past 2^n), in form
+// `form`, then taken `down` forms lower in `low`.
+template <typename P>
+__device__ __forceinline__ Fr eq_entry(const P& point, uint32_t n, uint32_t blk, const uint32_t* scale, uint32_t form,
+                                       uint32_t down, EqLds& T, Fr& low) {
+  const uint32_t tid = threadIdx.x;
+  const uint32_t nu = n > 8 ? n - 8 : 0;
+  if (tid < 192) {
+    // threads 4 e + k < 128: factor k of group entry e; 128 + m: the block's
+    // factor m
+    const bool grp = tid < 128;
+    const uint32_t e = (tid >> 2) & 15u, k = tid & 3u, m = tid - 128;
+    const uint32_t bit = grp ? 4 * (tid >> 6) + k : 8 + m;
+    const uint32_t set = grp ? (e >> k) & 1u : (m < 32 ? (blk >> m) & 1u : 0u);
+    Fr f = fr_R();
+    if (bit < n) {
+      const Fr x = point(n - 1 - bit);
+      f = set ? x : fr_sub(f, x);
+    } else if (!grp && m == nu && form != EQ_MONT) {
+      // a product with R^2 (R^3 / R) or with 1
+      f = fr_R2();
+      if (form == EQ_CANON)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) f.w[j] = j == 0 ? 1u : 0u;
+    } else if (!grp && m == nu + 1 && scale) {
+      f = lds_or_global_fr(scale);
+    }
+    const uint32_t width = grp ? 4u : nu + 2;
+#pragma unroll 1
+    for (uint32_t off = 1; off < width; off <<= 1) {
+      Fr o;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) o.w[j] = __shfl_xor(f.w[j], (int)off, kWave);
+      f = fr_mul(f, o);
+    }
+    if (grp ? k == 0 : m == 0) lds_put(grp ? T.g[tid >> 6][e] : T.up, f);
+  }
+  __syncthreads();
+  Fr e = lds_get(T.g[0][tid & 15u]), out = e;
+#pragma unroll 1
+  for (uint32_t q = 0; q < 2 + down; ++q) {
+    Fr f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) f.w[j] = j == 0 ? 1u : 0u;
+    if (q < 2) f = lds_get(q ? T.up : T.g[1][(tid >> 4) & 15u]);
+    e = fr_mul(e, f);
+    if (q < 2) out = e;
+  }
+  low = e;
+  return out;
+}
+
+__global__ void __launch_bounds__(kEqBlock) eq_kernel(const EqJob* __restrict__ jobs, uint32_t n_jobs,
+                                                      uint32_t n_blocks) {
+  __shared__ EqLds T;
+  const uint32_t blk = blockIdx.x;
+  if (blk >= n_blocks) return;
   uint32_t lo = 0, hi = n_jobs;
   while (hi - lo > 1) {
     const uint32_t mid = (lo + hi) >> 1;
-    if (jobs[mid].thread_begin <= tid) lo = mid; else hi = mid;
+    if (jobs[mid].block_begin <= blk) lo = mid; else hi = mid;
   }
   const EqJob& J = jobs[lo];
-  // thread t covers entries 4t .. 4t + 3 (the whole table when nvars < 2)
-  const uint32_t t = tid - J.thread_begin;
-  const uint32_t n = J.nvars;
-  const uint64_t len = 1ull << n;
-  auto point = [&](uint32_t j) {
-    Fr x;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) x.w[k] = J.point[j * 8 + k];
-    return x;
-  };
-  Fr e[4];
-  Fr sc = fr_R();
-  if (J.scaled)
-#pragma unroll
-    for (int k = 0; k < 8; ++k) sc.w[k] = J.scale[k];
-  if (n < 2) {
-    e[0] = n == 0 ? sc : fr_mul(sc, fr_sub(fr_R(), point(0)));
-    e[1] = n == 0 ? fr_zero() : fr_mul(sc, point(0));
-    e[2] = e[3] = fr_zero();
-  } else {
-    // factor j is x_j for bit 1 and 1 - x_j for bit 0 (b_1 the most
-    // significant bit): the first n - 2 come from t, shared by the four
-    // entries; the last two split the product into a tree of 2 + 4 products
-    Fr base = fr_R();
-    for (uint32_t j = 0; j + 2 < n; ++j) {
-      const Fr x = point(j);
-      const Fr f = ((t >> (n - 3 - j)) & 1u) ? x : fr_sub(fr_R(), x);
-      base = j == 0 ? f : fr_mul(base, f);
-    }
-    if (J.scaled) base = n > 2 ? fr_mul(base, sc) : sc;
-    const Fr xa = point(n - 2), xb = point(n - 1);
-    const Fr bb[2] = {base, base}, fa[2] = {fr_sub(fr_R(), xa), xa}, fb[2] = {fr_sub(fr_R(), xb), xb};
-    Fr h[2], q0[2], q1[2];
-    fr_mul_n<2>(bb, fa, h);
-    const Fr h0[2] = {h[0], h[0]}, h1[2] = {h[1], h[1]};
-    fr_mul_n<2>(h0, fb, q0);
-    fr_mul_n<2>(h1, fb, q1);
-    e[0] = q0[0];
-    e[1] = q0[1];
-    e[2] = q1[0];
-    e[3] = q1[1];
-  }
-  const uint64_t i0 = 4ull * t;
-#pragma unroll
-  for (uint32_t q = 0; q < 4; ++q) {
-    const uint64_t i = i0 + q;
-    if (J.eq && i < len) store_sol(J.eq, J.eq_ld, i, J.eq_canon ? fr_from_mont(e[q]) : e[q]);
-    // pack: e * R^2 (or e * R) mod p as signed digits, 8 words per entry
-    if (J.pack && i < J.pack_len) signed_digits(J.pack_r2 ? fr_to_mont(e[q]) : e[q], J.pack + i * 8);
-  }
+  const uint32_t b = blk - J.block_begin;
+  // the pack holds e R^2 or e R (level 2 or 1), the table e R or e (1 or 0)
+  const uint32_t eq_form = J.eq_canon ? EQ_CANON : EQ_MONT;
+  const uint32_t form = J.pack ? (J.pack_r2 ? EQ_R2 : EQ_MONT) : eq_form;
+  Fr low;
+  const uint32_t* pt = J.point;
+  const Fr e = eq_entry([&](uint32_t j) { return lds_or_global_fr(pt + 8 * j); }, J.nvars, b,
+                        J.scaled ? J.scale : nullptr, form, J.eq ? form - eq_form : 0u, T, low);
+  const uint64_t i = (uint64_t)b * kEqBlock + threadIdx.x;
+  if (J.eq && i < (1ull << J.nvars)) store_sol(J.eq, J.eq_ld, i, low);
+  if (J.pack && i < J.pack_len) signed_digits(e, J.pack + i * 8);
 }
 
 // eq table for a point passed by value (vl_eq_table): no device staging
-__global__ void __launch_bounds__(256) eq_point_kernel(EqPointArgs a) {
-  const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const uint32_t n = a.nvars;
-  const uint64_t len = 1ull << n;
-  if (2 * t >= len && !(n == 0 && t == 0)) return;
-  Fr e0, e1;
-  if (n == 0) {
-    e0 = fr_R();
-    e1 = fr_zero();
-  } else {
-    Fr base = fr_R();
-    for (uint32_t j = 0; j + 1 < n; ++j) {
-      const uint32_t bit = (uint32_t)(t >> (n - 2 - j)) & 1u;
-      Fr x;
-#pragma unroll
-      for (int k = 0; k < 8; ++k) x.w[k] = a.pt[j][bit ? 0 : 1][k];
-      base = fr_mul(base, x);
-    }
-    Fr xl, oml;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      xl.w[k] = a.pt[n - 1][0][k];
-      oml.w[k] = a.pt[n - 1][1][k];
-    }
-    e0 = fr_mul(base, oml);
-    e1 = fr_mul(base, xl);
-  }
-  if (2 * t < len) store_sol(a.out, a.ld, 2 * t, e0);
-  if (2 * t + 1 < len) store_sol(a.out, a.ld, 2 * t + 1, e1);
+__global__ void __launch_bounds__(kEqBlock) eq_point_kernel(EqPointArgs a) {
+  __shared__ EqLds T;
+  Fr low;
+  const Fr e = eq_entry([&](uint32_t j) { return lds_or_global_fr(a.pt[j]); }, a.nvars, blockIdx.x, nullptr, EQ_MONT, 0u,
+                        T, low);
+  const uint64_t i = (uint64_t)blockIdx.x * kEqBlock + threadIdx.x;
+  if (i < (1ull << a.nvars)) store_sol(a.out, a.ld, i, e);
 }
 
 // pack form of a caller-provided eq vector (vl_mle_partial_eval)
@@ -894,16 +902,14 @@ __global__ void __launch_bounds__(256) zero_kernel(uint32_t* __restrict__ p, uin
 
 // ---------------------------------------------------------------- launchers -
 
-hipError_t launch_eq(const EqJob* jobs, uint32_t n_jobs, uint32_t n_threads, hipStream_t s) {
-  if (n_threads == 0) return hipSuccess;
-  hipLaunchKernelGGL(eq_kernel, dim3(blocks_for(n_threads, 256)), dim3(256), 0, s, jobs, n_jobs,
-                     n_threads);
+hipError_t launch_eq(const EqJob* jobs, uint32_t n_jobs, uint32_t n_blocks, hipStream_t s) {
+  if (n_blocks == 0) return hipSuccess;
+  hipLaunchKernelGGL(eq_kernel, dim3(n_blocks), dim3(kEqBlock), 0, s, jobs, n_jobs, n_blocks);
   return hipGetLastError();
 }
 
 hipError_t launch_eq_point(const EqPointArgs& a, hipStream_t s) {
-  const uint64_t pairs = a.nvars ? (1ull << a.nvars) / 2 : 1;
-  hipLaunchKernelGGL(eq_point_kernel, dim3(blocks_for(pairs, 256)), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(eq_point_kernel, dim3(blocks_for(1ull << a.nvars, kEqBlock)), dim3(kEqBlock), 0, s, a);
   return hipGetLastError();
 }
 

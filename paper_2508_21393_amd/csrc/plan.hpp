@@ -75,7 +75,7 @@ struct Plan {
   bool fork = false;              // contraction kinds may use a side stream
   uint64_t data_end = 0;          // workspace bytes used
   std::vector<EqJob> eq;
-  uint32_t eq_threads = 0;
+  uint32_t eq_blocks = 0;
   std::vector<Segment> seg;
   std::vector<std::vector<uint32_t>> points;  // per eq job: (x_j, 1 - x_j) Montgomery
   std::vector<const uint32_t*> point_dev;     // per eq job: a point already in device memory, or null
