@@ -182,45 +182,6 @@ __device__ __forceinline__ void g1l_madd(G1l& p, const Fl& x, const Fl& y) {
   p.Y = fl_mul2_add(R, fl_sub<16, 2>(Q, p.X), fl_neg<4, 1>(p.Y), PPP);
 }
 
-// p + o (add-2008-s)
-__device__ __forceinline__ G1l g1l_add(const G1l& p, const G1l& o) {
-  if (fl_all_zero(p.ZZ)) return o;
-  if (fl_all_zero(o.ZZ)) return p;
-  const Fl U1 = fl_mul(p.X, o.ZZ);
-  const Fl P = fl_sub<4, 1>(fl_mul(o.X, p.ZZ), U1);
-  const Fl S1 = fl_mul(p.Y, o.ZZZ);
-  const Fl R = fl_sub<4, 1>(fl_mul(o.Y, p.ZZZ), S1);
-  const Fl PP = fl_sqr(P);
-  const Fl RR = fl_sqr(R);
-  if (__builtin_expect(fl_is_zero(PP), 0)) {
-    if (fl_is_zero(RR)) return g1l_dbl(p);
-    G1l z = p;
-    z.ZZ = fl_zero();
-    z.ZZZ = fl_zero();
-    return z;
-  }
-  const Fl PPP = fl_mul(P, PP);
-  const Fl Q = fl_mul(U1, PP);
-  G1l r;
-  r.ZZ = fl_mul(fl_mul(p.ZZ, o.ZZ), PP);
-  r.ZZZ = fl_mul(fl_mul(p.ZZZ, o.ZZZ), PPP);
-  r.X = x3_of(RR, PPP, Q);
-  r.Y = fl_mul2_add(R, fl_sub<16, 2>(Q, r.X), fl_neg<4, 1>(S1), PPP);
-  return r;
-}
-
-__device__ __forceinline__ G1l g1l_shfl_xor(const G1l& p, int mask) {
-  G1l r;
-#pragma unroll
-  for (int i = 0; i < 14; ++i) {
-    r.X.l[i] = __shfl_xor(p.X.l[i], mask);
-    r.Y.l[i] = __shfl_xor(p.Y.l[i], mask);
-    r.ZZ.l[i] = __shfl_xor(p.ZZ.l[i], mask);
-    r.ZZZ.l[i] = __shfl_xor(p.ZZZ.l[i], mask);
-  }
-  return r;
-}
-
 __device__ __forceinline__ void store_fl(uint32_t* dst, const Fl& a) {
   Fl t = a;     // all limbs below 2^28 for the packing
   uint32_t c = 0;
@@ -253,29 +214,100 @@ __device__ __forceinline__ void store_l(uint32_t* dst, const G1l& p) {
   store_fl(dst + 24, p.ZZ);
   store_fl(dst + 36, p.ZZZ);
 }
-__device__ __forceinline__ G1l load_l(const uint32_t* src) {
-  G1l p;
-  p.X = load_fl(src);
-  p.Y = load_fl(src + 12);
-  p.ZZ = load_fl(src + 24);
-  p.ZZZ = load_fl(src + 36);
-  return p;
-}
 __device__ __forceinline__ G1l g1l_infinity() {
   G1l p;
   p.X = p.Y = p.ZZ = p.ZZZ = fl_zero();
   return p;
 }
-// The sum of partials[(s0 + k) R + i] for lane-group member gl of G
-// (k = gl, gl + G, ... < n), then over the group's lanes (xor distances
-// stride G / 2 .. stride): every lane of the group ends with the sum.
-__device__ __forceinline__ G1l sum_slices(const uint32_t* partials, uint64_t R, uint64_t i, uint32_t s0, uint32_t n,
-                                          uint32_t gl, uint32_t G, uint32_t stride) {
-  G1l acc = g1l_infinity();
+// A point on four neighbouring lanes: lane q of the quad has X, Y, ZZ or ZZZ.
+template <int CTRL>   // the limbs of lane (CTRL >> 2 q) & 3 of the quad
+__device__ __forceinline__ Fl quad(const Fl& a) {
+  Fl r;
+#pragma unroll
+  for (int i = 0; i < 14; ++i) r.l[i] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a.l[i], CTRL, 0xf, 0xf, true);
+  return r;
+}
+__device__ __forceinline__ Fl fl_sel(bool c, const Fl& a, const Fl& b) {
+  Fl r;
+#pragma unroll
+  for (int i = 0; i < 14; ++i) r.l[i] = c ? a.l[i] : b.l[i];
+  return r;
+}
+// a + o (add-2008-s) on quads: four products deep, each of the 14 products of
+// the formulas in one of the lanes.  Bounds as in g1l_madd, but for Y: two
+// reduced products, below 4q, carried to limbs below 2^28.
+__device__ __forceinline__ Fl quad_add(const Fl& a, const Fl& o, uint32_t q) {
+  // a.X o.ZZ = U1, a.Y o.ZZZ = S1, a.ZZ o.X = U2, a.ZZZ o.Y = S2
+  const Fl m1 = fl_mul(a, quad<0x4e>(o));
+  const Fl d = fl_sub<4, 1>(quad<0x4e>(m1), m1);   // lane 0: P = U2 - U1, lane 1: R = S2 - S1
+  // P^2, R^2, ZZ ZZ, ZZZ ZZZ
+  const Fl m2 = fl_mul(fl_sel(q < 2, d, a), fl_sel(q < 2, d, o));
+  const Fl pp = quad<0x00>(m2);
+  // P PP = PPP, U1 PP = Q, ZZ ZZ PP
+  const Fl m3 = fl_mul(fl_sel(q == 0, d, fl_sel(q == 1, quad<0x00>(m1), m2)), pp);
+  const Fl ppp = quad<0x00>(m3), qq = quad<0x55>(m3);
+  const Fl x3 = x3_of(quad<0x55>(m2), ppp, qq);
+  // R (Q - X3), -S1 PPP, -, ZZZ ZZZ PPP
+  const Fl m4 = fl_mul(fl_sel(q == 0, quad<0x55>(d), fl_sel(q == 1, fl_neg<4, 1>(m1), m2)),
+                       fl_sel(q == 0, fl_sub<16, 2>(qq, x3), ppp));
+  const Fl y0 = quad<0x00>(m4), y1 = quad<0x55>(m4);
+  Fl r;
+  uint32_t c = 0;
+#pragma unroll
+  for (int i = 0; i < 14; ++i) {
+    const uint32_t t = y0.l[i] + y1.l[i] + c;
+    const uint32_t y = i < 13 ? t & kM28 : t;
+    c = t >> 28;
+    r.l[i] = q == 0 ? x3.l[i] : (q == 1 ? y : (q == 2 ? m3.l[i] : m4.l[i]));
+  }
+  // infinity on either side, equal and opposite points
+  uint32_t za = 0, zo = 0;
+#pragma unroll
+  for (int i = 0; i < 14; ++i) {
+    za |= a.l[i];
+    zo |= o.l[i];
+  }
+  za = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)za, 0xaa, 0xf, 0xf, true);
+  zo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)zo, 0xaa, 0xf, 0xf, true);
+  const bool same_x = za && zo && fl_is_zero(pp);
+  if (__builtin_expect(__ballot(same_x) != 0, 0)) {
+    G1l p;
+    p.X = quad<0x00>(a);
+    p.Y = quad<0x55>(a);
+    p.ZZ = quad<0xaa>(a);
+    p.ZZZ = quad<0xff>(a);
+    const bool equal = fl_is_zero(quad<0x55>(m2));
+    const G1l t = g1l_dbl(p);
+    const Fl v = fl_sel(q == 0, t.X, fl_sel(q == 1, t.Y, fl_sel(q == 2, t.ZZ, t.ZZZ)));
+#pragma unroll
+    for (int i = 0; i < 14; ++i) r.l[i] = same_x ? (equal ? v.l[i] : 0u) : r.l[i];
+  }
+  return fl_sel(zo == 0, a, fl_sel(za == 0, o, r));
+}
+// The sum of partials[(s0 + k) R + i] for quad gl of the G quads of a row
+// (k = gl, gl + G, ... < n), then over those quads (xor distances stride G / 2
+// .. stride of lanes): every quad of the row ends with the sum.
+__device__ __forceinline__ Fl sum_slices(const uint32_t* partials, uint64_t R, uint64_t i, uint32_t s0, uint32_t n,
+                                         uint32_t gl, uint32_t G, uint32_t stride) {
+  const uint32_t q = threadIdx.x & 3u, nl = (n + G - 1) / G;
+  auto load = [&](uint32_t k) {
+    return k < n ? load_fl(partials + ((uint64_t)(s0 + k) * R + i) * kZWords + 12 * q) : fl_zero();
+  };
+  Fl acc = load(gl);
+  uint32_t k = gl + G, off = (G >> 1) * stride;
 #pragma unroll 1
-  for (uint32_t k = gl; k < n; k += G) acc = g1l_add(acc, load_l(partials + ((uint64_t)(s0 + k) * R + i) * kZWords));
-#pragma unroll 1
-  for (uint32_t off = (G >> 1) * stride; off >= stride; off >>= 1) acc = g1l_add(acc, g1l_shfl_xor(acc, (int)off));
+  for (uint32_t it = 1; it < nl || off >= stride; ++it) {
+    Fl o;
+    if (it < nl) {
+      o = load(k);
+      k += G;
+    } else {
+#pragma unroll
+      for (int j = 0; j < 14; ++j) o.l[j] = __shfl_xor(acc.l[j], (int)off);
+      off >>= 1;
+    }
+    acc = quad_add(acc, o, q);
+  }
   return acc;
 }
 #endif
@@ -354,7 +386,7 @@ struct NonzeroTerms {
 // of 4 cycles a mixed addition (3542 of them multiply-adds), no LDS, no
 // cross-lane step.  With a wave per (row, slice), 32-bit limbs and carries
 // (about 7900 instructions an addition and a butterfly over the lanes) a
-// 4096 x 4096 int16 commitment took 4.82 ms, with this 3.33 ms.
+// 4096 x 4096 int16 commitment took 4.82 ms, with this 2.99 ms.
 template <typename T>
 __global__ void __launch_bounds__(256, 2) hyrax_commit_kernel(const T* __restrict__ M, uint64_t ld, uint32_t R,
                                                               uint32_t m, uint32_t W,
@@ -393,54 +425,53 @@ __global__ void __launch_bounds__(256, 2) hyrax_commit_kernel(const T* __restric
 #endif
 }
 
-// Runs of `run` slices of a row summed by one wave each: slice s' of out is
-// the sum of slices s' run .. s' run + run - 1.
+// Runs of `run` slices of a row summed by the 16 quads of one wave each: slice
+// s' of out is the sum of slices s' run .. s' run + run - 1.
 __global__ void __launch_bounds__(64) hyrax_sum_kernel(uint32_t R, uint32_t n_split, uint32_t run,
                                                        const uint32_t* __restrict__ partials, uint32_t* out) {
 #if defined(__HIP_DEVICE_COMPILE__)
   const uint32_t i = blockIdx.x % R, s = blockIdx.x / R;
   const uint32_t s0 = s * run;
-  const G1l acc = sum_slices(partials, R, i, s0, min(run, n_split - s0), threadIdx.x, 64, 1);
-  if (threadIdx.x == 0) store_l(out + ((uint64_t)s * R + i) * kZWords, acc);
+  const Fl acc = sum_slices(partials, R, i, s0, min(run, n_split - s0), threadIdx.x >> 2, 16, 4);
+  if (threadIdx.x < 4) store_fl(out + ((uint64_t)s * R + i) * kZWords + 12 * threadIdx.x, acc);
 #endif
 }
 
-// C_i = the sum of row i's slices by a group of G lanes (a power of two up to
-// 64; the lanes of a wave are G members of 64 / G rows), as 96 canonical bytes
-// (24 words).  Every lane inverts its row's ZZ ZZZ by division steps
-// (modinv.hpp), so rows share nothing.  A chain of additions, about 11 us
-// each, and one inversion, about 30 us: with 43 slices of a row added by one
-// lane and a binary Euclid of 0.4 ms, committing a 16 x 11008 matrix took
-// 2.26 ms, with the runs and groups of lanes 0.37 ms.
+// C_i = the sum of row i's slices by a group of G quads (a power of two up to
+// 16; a wave has 16 / G rows), as 96 canonical bytes (24 words).  Every lane
+// inverts its row's ZZ ZZZ by division steps (modinv.hpp), so rows share
+// nothing.  A chain of additions and one inversion of about 30 us.  An
+// addition on one lane is 14 products deep, 11 us alone and more where the
+// waves of a CU fetch its 60 KB of code at different places: the two kernels
+// took 264 us for a 16 x 11008 matrix and 359 for 4096 x 4096, with the
+// quads (four deep) 160 and 139.
 __global__ void __launch_bounds__(64) hyrax_final_kernel(uint32_t R, uint32_t n_split, uint32_t G,
                                                          const uint32_t* __restrict__ partials, uint32_t* commits) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  const uint32_t rows = 64 / G;
-  const uint64_t i = (uint64_t)blockIdx.x * rows + threadIdx.x % rows;
-  const uint32_t gl = threadIdx.x / rows;
-  const G1l acc = sum_slices(partials, R, min(i, (uint64_t)R - 1), 0, n_split, gl, G, rows);
-  if (i >= R || gl != 0) return;
-  uint32_t* out = commits + i * 24;
-  if (fl_all_zero(acc.ZZ)) {
-#pragma unroll
-    for (int k = 0; k < 24; ++k) out[k] = 0;
-    return;
-  }
+  const uint32_t rows = 16 / G, qd = threadIdx.x >> 2, q = threadIdx.x & 3u;
+  const uint64_t i = (uint64_t)blockIdx.x * rows + qd % rows;
+  const uint32_t gl = qd / rows;
+  const Fl acc = sum_slices(partials, R, min(i, (uint64_t)R - 1), 0, n_split, gl, G, 4 * rows);
+  // lane 0 x = 2^4 X / ZZ, lane 1 y = 2^6 Y / ZZZ (the other two like lane 1)
+  const Fl X = quad<0x54>(acc), Z = quad<0xaa>(acc), ZZZ = quad<0xff>(acc);
+  const bool inf = fl_all_zero(Z);
   // 1 / (ZZ ZZZ) in R' form: the inverse of the integer a R' is a^-1 / R', and
   // a product with R'^3 gives a^-1 R'
-  const Fq inv = fq_inv_raw(fl_pack(fl_mul(acc.ZZ, acc.ZZZ)));
+  const Fq inv = fq_inv_raw(fl_pack(fl_mul(Z, ZZZ)));
   constexpr uint32_t r3[12] = {0xd1f7b890u, 0x22294cc4u, 0x56c9f3afu, 0xc0ccb5bau, 0xd975ccb5u, 0x89a8c5c0u,
                                0x6c968b4cu, 0x922672eau, 0xa691de8cu, 0x7c835652u, 0xbbb98497u, 0x141ab424u};
-  const Fl t = fl_mul(fl_split<0>(inv.w), fl_split<0>(r3));
-  // x = 2^4 X / ZZ, y = 2^6 Y / ZZZ, out of Montgomery form
-  const Fl x = fl_mul(fl_mul(acc.X, fl_mul(t, acc.ZZZ)), fl_small(16));
-  const Fl y = fl_mul(fl_mul(acc.Y, fl_mul(t, acc.ZZ)), fl_small(64));
-  const Fq xc = fq_reduce_once(fl_pack(x)), yc = fq_reduce_once(fl_pack(y));
-#pragma unroll
-  for (int k = 0; k < 12; ++k) {
-    out[k] = xc.w[k];
-    out[12 + k] = yc.w[k];
+  Fl f = fl_split<0>(inv.w);
+#pragma unroll 1
+  for (uint32_t k = 0; k < 4; ++k) {   // one product's code, out of Montgomery form with the last
+    Fl g = fl_sel(k == 0, fl_split<0>(r3), fl_sel(k == 1, fl_sel(q == 0, ZZZ, Z), X));
+    if (k == 3) g = fl_small(q == 0 ? 16 : 64);
+    f = fl_mul(f, g);
   }
+  if (i >= R || gl != 0 || q >= 2) return;
+  const Fq c = fq_reduce_once(fl_pack(f));
+  uint32_t* out = commits + i * 24 + 12 * q;
+#pragma unroll
+  for (int k = 0; k < 12; ++k) out[k] = inf ? 0u : c.w[k];
 #endif
 }
 
@@ -475,7 +506,7 @@ hipError_t launch_hyrax_commit(const void* M, int dtype, uint64_t ld, uint32_t R
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  // Many slices are first summed in runs of 128 (two per lane of a wave);
+  // Many slices are first summed in runs of 128 (eight per quad of a wave);
   // the runs' sums go behind the slices (with_runs: there is room for them).
   if (with_runs && n_split > kHyraxMaxFinal) {
     const uint32_t runs = (n_split + kHyraxRun - 1) / kHyraxRun;
@@ -486,11 +517,11 @@ hipError_t launch_hyrax_commit(const void* M, int dtype, uint64_t ld, uint32_t R
     partials = sums;
     n_split = runs;
   }
-  // as many lanes per row as one wave on each SIMD gives: beyond that the
+  // as many quads per row as one wave on each SIMD gives: beyond that the
   // waves of a SIMD take turns at their inversions
   uint32_t G = 1;
-  while (G < 64 && 2 * G <= n_split && (uint64_t)R * 2 * G <= 65536) G *= 2;
-  hipLaunchKernelGGL(hyrax_final_kernel, dim3(blocks_for(R, 64 / G)), dim3(64), 0, s, R, n_split, G, partials, commits);
+  while (G < 16 && 2 * G <= n_split && (uint64_t)R * 8 * G <= 65536) G *= 2;
+  hipLaunchKernelGGL(hyrax_final_kernel, dim3(blocks_for(R, 16 / G)), dim3(64), 0, s, R, n_split, G, partials, commits);
   return hipGetLastError();
 }
 
