@@ -143,6 +143,10 @@ __global__ void __launch_bounds__(256) pack_kernel(const uint32_t* __restrict__ 
 // first round, and the three of the round at hand
 constexpr uint32_t kMatAccProd = 1, kMatAccRound = 1 + 3 * VL_MAX_PRODS;
 constexpr uint32_t kMatAccWords = 10 * (kMatAccRound + 3);
+// in the rounds kernel behind those, twice: the three values of the next round
+// with the tables folded by 0, by 1, and their leading coefficients in the
+// challenge
+constexpr uint32_t kMatAccNext = kMatAccRound + 3, kMatAccNextLen = 9;
 
 // the product at point pt of a pair, from its table entries e[0] (point 2: the
 // difference of the pair's) and, to be folded by r, e[1]
@@ -215,11 +219,15 @@ __device__ __forceinline__ bool mat_claim(const RoundsJob& J, const unsigned lon
   }
   return true;
 }
-// A round's messages from the sums at value v0, and its challenge, by wave 0
+// A round's messages from the sums at value v0, and its challenge, by wave 0.
+// next: the sums are kMatAccNextLen ones, quadratics in the challenge before,
+// T.r.
 __device__ __forceinline__ void mat_round(const unsigned long long* acc, uint32_t v0, uint8_t* out, RoundLds& T,
-                                          bool write) {
+                                          bool write, bool next = false) {
   const uint32_t lane = threadIdx.x & 63u;
-  const Fr g = acc_point(acc, v0, min(lane, 2u));
+  // lane 4 j + k: value k's j-th
+  Fr g = acc_point(acc, v0 + (next ? 3 * min(lane >> 2, 2u) : 0), min(lane & 3u, 2u));
+  if (next) g = fr_eval2(g, fr_row_shl<4>(g), fr_row_shl<8>(g), fr_vgpr(lds_get(T.r)));
   if (lane < 3) {
     if (write) put_canon(out + 32 * lane, g);
     lds_put(T.v + 8 * lane, g);
@@ -369,26 +377,32 @@ __global__ void __launch_bounds__(kPass1Block) pass1_kernel(const Pass1Job* __re
 }
 
 // The rounds of a group, one workgroup each, apart from the wide ones: the
-// statement (without wide rounds), then product after product.  Round 0's sums
-// come from pass 1, the last wide round's from its blocks' partials.  Every
-// other round folds the tables by the challenge before and sums the new pairs
-// in one pass: entries t, t + h, t + 2 h, t + 3 h fold into t and t + h.  The
-// rows of 16 lanes of waves 1 .. 7 take the terms, wave 0 the transcript.
+// statement (without wide rounds), then product after product.  The first
+// round's sums come from pass 1, or from the last wide round's blocks.  While
+// wave 0 hashes round rd, waves 1 .. 7 fold the tables by r_{rd-1} and sum
+// round rd + 1 as quadratics in the r_rd not known yet, three products per
+// value: of pair t < h they take the entries t, t + 2 h (the value at 0), t + h,
+// t + 3 h (at 1) and the differences (the leading coefficient) of the tables
+// of 4 h entries.  So a round is the hash and the quadratics at r, with one
+// barrier.  A row of 16 lanes takes one of the three values of 16 pairs.
 // Tables of more than kMatLds entries fold in place in global memory, a pair's
-// points in one thread (the leading one first, which reads all four entries);
+// values in one thread (the leading one first, which reads all entries);
 // shorter ones are folded from one LDS buffer into the other and a pair's
-// points go to different rows.
-// A round is a serial chain: a fold, a product, the sum and the hash (about
-// 10 of 15 us).  With the sums by lane shuffles, the squeeze and claims on one
-// lane and 183 KB of code it took 18 us in a single product (134 us for the
-// 64 x 128 x 32 product, now 116) and 30 with 42 groups at once.
+// values go to different rows.
+// Bound by the hash (7.9 of about 10.7 us a round).  With the sums after
+// the hash a round took 13 us, before that, with sums by lane shuffles, the
+// squeeze and claims on one lane and 183 KB of code, 18, and 30 with 42 groups
+// at once; the 64 x 128 x 32 product's rounds 134 us, now 97.
 __global__ void __launch_bounds__(kRoundsBlock) rounds_kernel(const RoundsJob* __restrict__ jobs) {
   const RoundsJob& J = jobs[blockIdx.x];
   // the rounds are one serial chain per group; when they overlap contraction
-  // kernels on the same CUs, their waves go first
-  __builtin_amdgcn_s_setprio(3);
+  // kernels on the same CUs, their waves go first, and before them the
+  // transcript's, which shares its SIMD with another
+  if (threadIdx.x < kWave) __builtin_amdgcn_s_setprio(3); else __builtin_amdgcn_s_setprio(2);
   __shared__ uint32_t buf[2][8 * (kMatLds + kMatLds / 2)];   // a, b: two buffers each
-  __shared__ unsigned long long acc[kMatAccWords];
+  constexpr uint32_t kAcc = 10 * (kMatAccNext + 2 * kMatAccNextLen);
+  __shared__ unsigned long long acc[kAcc];
+  __shared__ uint32_t rbuf[2][8], fin[2][2][8];              // r_rd by parity; the last pairs
   __shared__ RoundLds T;
   __shared__ int32_t verdict;
   const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = tid & 63u;
@@ -432,7 +446,7 @@ __global__ void __launch_bounds__(kRoundsBlock) rounds_kernel(const RoundsJob* _
     if (tid == 0) *J.status = VL_ERR_RANGE;
     return;
   }
-  for (uint32_t i = tid; i < kMatAccWords; i += kRoundsBlock) acc[i] = 0;
+  for (uint32_t i = tid; i < kAcc; i += kRoundsBlock) acc[i] = 0;
   __syncthreads();
   mat_sum_first(J, acc, kRoundsBlock / kWave);
   if (wide) {
@@ -467,66 +481,83 @@ __global__ void __launch_bounds__(kRoundsBlock) rounds_kernel(const RoundsJob* _
     };
 #pragma unroll 1
     for (uint32_t rd = rd0; rd < n1; ++rd) {
-      const uint32_t h = 1u << (n1 - 1 - rd);
-      if (rd > rd0) {
-        const bool lds = 2 * h <= kMatLds;   // the folded tables' place
-        if (wave) {
-          const Fr r = lds_get(T.r);
-          constexpr uint32_t kRows = 4 * (kRoundsBlock / kWave - 1), kPtRows = kRows / 3;
-          const uint32_t row = 4 * (wave - 1) + (lane >> 4), chunks = (h + 15) / 16;
-          const uint32_t first = lds ? row / 3 : row, step = lds ? kPtRows : kRows;
-          const bool on = !lds || first < kPtRows;
+      unsigned long long* const cur = acc + 10 * (kMatAccNext + kMatAccNextLen * (rd & 1));
+      unsigned long long* const nxt = acc + 10 * (kMatAccNext + kMatAccNextLen * (~rd & 1));
+      const bool fold = rd > rd0;
+      // the last round's tables are one pair each, in fin
+      const bool lds = fold && rd + 1 < n1 && (2u << (n1 - 1 - rd)) <= kMatLds;
+      if (wave == 0) {
+        if (fold) {
+          mat_round(cur, 0, out + 96ull * rd, T, true, true);
+        } else {
+          mat_round(acc, rd == 0 ? kMatAccProd + 3 * p : kMatAccRound, out + 96ull * rd, T, true);
+        }
+#pragma unroll
+        for (uint32_t i = lane; i < 10 * kMatAccNextLen; i += kWave) cur[i] = 0;
+        if (lane < 8) rbuf[rd & 1][lane] = T.r[lane];
+      } else if (rd + 1 < n1) {
+        const uint32_t h = 1u << (n1 - 2 - rd);   // pairs of round rd + 1
+        const Fr r = lds_get(rbuf[~rd & 1]);
+        const bool split = lds || at >= 0 || !fold;   // a pair's values on different rows
+        constexpr uint32_t kRows = 4 * (kRoundsBlock / kWave - 1), kPtRows = kRows / 3;
+        const uint32_t row = 4 * (wave - 1) + (lane >> 4), chunks = (h + 15) / 16;
+        const uint32_t first = split ? row / 3 : row, step = split ? kPtRows : kRows;
+        const bool on = !split || first < kPtRows;
 #pragma unroll 1
-          for (uint32_t j = 0; j < (lds ? 1u : 3u); ++j) {
-            const uint32_t pt = lds ? row % 3 : (j == 0 ? 2 : j - 1);
-            Fr sum = fr_zero();
+        for (uint32_t j = 0; j < (split ? 1u : 3u); ++j) {
+          const uint32_t pt = split ? row % 3 : (j == 0 ? 2 : j - 1);
+          Fr sum[3];
+          sum[0] = sum[1] = sum[2] = fr_zero();
 #pragma unroll 1
-            for (uint32_t ch = first; on && ch < chunks; ch += step) {
-              const uint32_t t = ch * 16 + (lane & 15u), i0 = pt == 1 ? t + h : t;
-              if (t >= h) continue;
-              Fr ea[2], eb[2];
+          for (uint32_t ch = first; on && ch < chunks; ch += step) {
+            const uint32_t t = ch * 16 + (lane & 15u), i0 = pt == 1 ? t + h : t;
+            if (t >= h) continue;
+            // entries i0 and i0 + 2 h of the tables of round rd (point 2: the
+            // differences of the pair's)
+            Fr e[2][2];
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
 #pragma unroll
               for (int q = 0; q < 2; ++q) {
-                ea[q] = get(0, i0 + 2 * q * h);
-                eb[q] = get(1, i0 + 2 * q * h);
-                if (pt == 2) {
-                  ea[q] = fr_sub(get(0, t + h + 2 * q * h), ea[q]);
-                  eb[q] = fr_sub(get(1, t + h + 2 * q * h), eb[q]);
-                }
+                auto entry = [&](uint32_t off) {
+                  Fr x = get(k, i0 + off);
+                  if (pt == 2) x = fr_sub(get(k, t + h + off), x);
+                  return x;
+                };
+                e[k][q] = entry(2 * q * h);
+                if (fold) e[k][q] = fr_fold(r, e[k][q], entry(2 * q * h + 4 * h));
               }
-              const MatTerm o = mat_term(ea, eb, r);
-              if (pt < 2) {
-                if (lds) {
-                  const uint32_t off = at == 0 ? 8 * kMatLds : 0, len = at == 0 ? kMatLds / 2 : kMatLds;
-                  store_sol(buf[0] + off, len, i0, o.A);
-                  store_sol(buf[1] + off, len, i0, o.B);
-                } else {
-                  store_sol(ga, ld, i0, o.A);
-                  store_sol(gb, ld, i0, o.B);
-                }
+            if (fold && pt < 2) {
+              const uint32_t off = at == 0 ? 8 * kMatLds : 0, len = at == 0 ? kMatLds / 2 : kMatLds;
+#pragma unroll
+              for (int q = 0; q < 2; ++q) {
+                store_sol(lds ? buf[0] + off : ga, lds ? len : ld, i0 + 2 * q * h, e[0][q]);
+                store_sol(lds ? buf[1] + off : gb, lds ? len : ld, i0 + 2 * q * h, e[1][q]);
               }
-              sum = fr_add(sum, o.val);
             }
-            acc_add(acc, kMatAccRound + pt, sum, on);
+            sum[0] = fr_add(sum[0], fr_mul(e[0][0], e[1][0]));
+            sum[1] = fr_add(sum[1], fr_mul(e[0][1], e[1][1]));
+            sum[2] = fr_add(sum[2], fr_mul(fr_sub(e[0][1], e[0][0]), fr_sub(e[1][1], e[1][0])));
           }
-          if (!lds) __threadfence_block();   // the folded entries, for the next round
+#pragma unroll
+          for (uint32_t q = 0; q < 3; ++q) acc_add(nxt, 3 * q + pt, sum[q], on);
         }
-        if (lds) at = at == 0 ? 1 : 0;
-        __syncthreads();   // the sums and the folded entries
+        if (!lds) __threadfence_block();   // the folded entries, for the next round
+      } else if (fold && tid < kWave + 4) {   // the last pair of each table
+        const uint32_t k = (lane >> 1) & 1u, i = lane & 1u;
+        lds_put(fin[k][i], fr_fold(lds_get(rbuf[~rd & 1]), get(k, i), get(k, i + 2)));
       }
-      if (wave == 0) {
-        mat_round(acc, rd == 0 ? kMatAccProd + 3 * p : kMatAccRound, out + 96ull * rd, T, true);
-        if (lane < 30) acc[10 * kMatAccRound + lane] = 0;
-      }
-      __syncthreads();   // r and the zeroed sums
+      if (lds) at = at == 0 ? 1 : 0;
+      __syncthreads();   // r_rd, round rd + 1's sums, the folded entries
     }
     // lane k < 2 of wave 0: the final value of table k, the last challenge
     // folding the remaining pair; a~ out of Montgomery form
     out += 96ull * n1;
     if (wave == 0) {
       const uint32_t k = min(lane, 1u);
-      Fr mine = get(k, 0);
-      if (n1) mine = fr_fold(lds_get(T.r), mine, get(k, 1));
+      const bool two = n1 > rd0 + 1;
+      Fr mine = two ? lds_get(fin[k][0]) : get(k, 0);
+      if (n1) mine = fr_fold(lds_get(T.r), mine, two ? lds_get(fin[k][1]) : get(k, 1));
       const Fr canon = fr_from_mont(mine);
       if (k == 0) mine = canon;
       if (lane < 2) {

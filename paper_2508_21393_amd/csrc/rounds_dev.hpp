@@ -151,6 +151,10 @@ __device__ __forceinline__ void st_rec(uint32_t* p, const Fr& v) {
 __device__ __forceinline__ Fr fr_fold(const Fr& r, const Fr& x0, const Fr& x1) {
   return fr_add(x0, fr_mul(r, fr_sub(x1, x0)));
 }
+// the quadratic with values v0, v1 at 0 and 1 and leading coefficient v2, at r
+__device__ __forceinline__ Fr fr_eval2(const Fr& v0, const Fr& v1, const Fr& v2, const Fr& r) {
+  return fr_add(v0, fr_mul(r, fr_add(fr_sub(fr_sub(v1, v0), v2), fr_mul(r, v2))));
+}
 // eq1(u, X) = (1 - u) + X (2 u - 1) as om + X slope, and its value at X = k (per lane, k <= 3)
 __device__ __forceinline__ Fr fr_eq1(const Fr& u, uint32_t k, Fr& om, Fr& slope) {
   om = fr_sub(fr_R(), u);
