@@ -384,22 +384,25 @@ __global__ void __launch_bounds__(kPass1Block) pass1_kernel(const Pass1Job* __re
 // value: of pair t < h they take the entries t, t + 2 h (the value at 0), t + h,
 // t + 3 h (at 1) and the differences (the leading coefficient) of the tables
 // of 4 h entries.  So a round is the hash and the quadratics at r, with one
-// barrier.  A row of 16 lanes takes one of the three values of 16 pairs.
+// barrier.  A row of 16 lanes takes one of the three values of 16 pairs, a wave
+// the same value of four rows.
 // Tables of more than kMatLds entries fold in place in global memory, a pair's
 // values in one thread (the leading one first, which reads all entries);
 // shorter ones are folded from one LDS buffer into the other and a pair's
-// values go to different rows.
+// values go to different waves.
 // Bound by the hash (7.9 of about 10.7 us a round).  With the sums after
 // the hash a round took 13 us, before that, with sums by lane shuffles, the
 // squeeze and claims on one lane and 183 KB of code, 18, and 30 with 42 groups
-// at once; the 64 x 128 x 32 product's rounds 134 us, now 97.
+// at once; the 64 x 128 x 32 product's rounds 134 us, now 88.  The LDS tables
+// hold whole elements (16-byte accesses), and there is one copy of the hash's
+// code: a kernel's first pass over code costs as much as several rounds.
 __global__ void __launch_bounds__(kRoundsBlock) rounds_kernel(const RoundsJob* __restrict__ jobs) {
   const RoundsJob& J = jobs[blockIdx.x];
   // the rounds are one serial chain per group; when they overlap contraction
   // kernels on the same CUs, their waves go first, and before them the
   // transcript's, which shares its SIMD with another
   if (threadIdx.x < kWave) __builtin_amdgcn_s_setprio(3); else __builtin_amdgcn_s_setprio(2);
-  __shared__ uint32_t buf[2][8 * (kMatLds + kMatLds / 2)];   // a, b: two buffers each
+  __shared__ alignas(16) uint32_t buf[2][8 * (kMatLds + kMatLds / 2)];   // a, b: two buffers each
   constexpr uint32_t kAcc = 10 * (kMatAccNext + 2 * kMatAccNextLen);
   __shared__ unsigned long long acc[kAcc];
   __shared__ uint32_t rbuf[2][8], fin[2][2][8];              // r_rd by parity; the last pairs
@@ -476,7 +479,7 @@ __global__ void __launch_bounds__(kRoundsBlock) rounds_kernel(const RoundsJob* _
     const uint32_t n1 = P.n1, rd0 = p == 0 && wide ? wide - 1 : 0;
     int at = -1;   // the tables' place: -1 global, else the LDS buffer of kMatLds entries (0) or half of them (1)
     auto get = [&](uint32_t k, uint32_t i) {
-      if (at >= 0) return load_sol(buf[k] + (at ? 8 * kMatLds : 0), at ? kMatLds / 2 : kMatLds, i);
+      if (at >= 0) return ld_rec(buf[k] + (at ? 8 * kMatLds : 0) + 8 * i);
       return load_sol(k ? gb : ga, ld, i);
     };
 #pragma unroll 1
@@ -487,29 +490,27 @@ __global__ void __launch_bounds__(kRoundsBlock) rounds_kernel(const RoundsJob* _
       // the last round's tables are one pair each, in fin
       const bool lds = fold && rd + 1 < n1 && (2u << (n1 - 1 - rd)) <= kMatLds;
       if (wave == 0) {
-        if (fold) {
-          mat_round(cur, 0, out + 96ull * rd, T, true, true);
-        } else {
-          mat_round(acc, rd == 0 ? kMatAccProd + 3 * p : kMatAccRound, out + 96ull * rd, T, true);
-        }
+        // (one call: its code is large)
+        mat_round(fold ? cur : acc, fold ? 0 : (rd == 0 ? kMatAccProd + 3 * p : kMatAccRound), out + 96ull * rd, T, true,
+                  fold);
 #pragma unroll
         for (uint32_t i = lane; i < 10 * kMatAccNextLen; i += kWave) cur[i] = 0;
         if (lane < 8) rbuf[rd & 1][lane] = T.r[lane];
       } else if (rd + 1 < n1) {
         const uint32_t h = 1u << (n1 - 2 - rd);   // pairs of round rd + 1
         const Fr r = lds_get(rbuf[~rd & 1]);
-        const bool split = lds || at >= 0 || !fold;   // a pair's values on different rows
-        constexpr uint32_t kRows = 4 * (kRoundsBlock / kWave - 1), kPtRows = kRows / 3;
-        const uint32_t row = 4 * (wave - 1) + (lane >> 4), chunks = (h + 15) / 16;
-        const uint32_t first = split ? row / 3 : row, step = split ? kPtRows : kRows;
-        const bool on = !split || first < kPtRows;
+        const bool split = lds || !fold;   // a pair's values on different waves
+        constexpr uint32_t kWaves = kRoundsBlock / kWave - 1, kPtWaves = kWaves / 3;
+        const uint32_t chunks = (h + 15) / 16;
+        const uint32_t first = 4 * (split ? (wave - 1) / 3 : wave - 1), step = 4 * (split ? kPtWaves : kWaves);
+        const bool on = (!split || wave <= 3 * kPtWaves) && first < chunks;
 #pragma unroll 1
-        for (uint32_t j = 0; j < (split ? 1u : 3u); ++j) {
-          const uint32_t pt = split ? row % 3 : (j == 0 ? 2 : j - 1);
+        for (uint32_t j = 0; on && j < (split ? 1u : 3u); ++j) {
+          const uint32_t pt = split ? (wave - 1) % 3 : (j == 0 ? 2 : j - 1);
           Fr sum[3];
           sum[0] = sum[1] = sum[2] = fr_zero();
 #pragma unroll 1
-          for (uint32_t ch = first; on && ch < chunks; ch += step) {
+          for (uint32_t ch = first + (lane >> 4); ch < chunks; ch += step) {
             const uint32_t t = ch * 16 + (lane & 15u), i0 = pt == 1 ? t + h : t;
             if (t >= h) continue;
             // entries i0 and i0 + 2 h of the tables of round rd (point 2: the
@@ -528,11 +529,17 @@ __global__ void __launch_bounds__(kRoundsBlock) rounds_kernel(const RoundsJob* _
                 if (fold) e[k][q] = fr_fold(r, e[k][q], entry(2 * q * h + 4 * h));
               }
             if (fold && pt < 2) {
-              const uint32_t off = at == 0 ? 8 * kMatLds : 0, len = at == 0 ? kMatLds / 2 : kMatLds;
+              const uint32_t off = at == 0 ? 8 * kMatLds : 0;
 #pragma unroll
               for (int q = 0; q < 2; ++q) {
-                store_sol(lds ? buf[0] + off : ga, lds ? len : ld, i0 + 2 * q * h, e[0][q]);
-                store_sol(lds ? buf[1] + off : gb, lds ? len : ld, i0 + 2 * q * h, e[1][q]);
+                const uint32_t i = i0 + 2 * q * h;
+                if (lds) {
+                  st_rec(buf[0] + off + 8 * i, e[0][q]);
+                  st_rec(buf[1] + off + 8 * i, e[1][q]);
+                } else {
+                  store_sol(ga, ld, i, e[0][q]);
+                  store_sol(gb, ld, i, e[1][q]);
+                }
               }
             }
             sum[0] = fr_add(sum[0], fr_mul(e[0][0], e[1][0]));
@@ -540,7 +547,7 @@ __global__ void __launch_bounds__(kRoundsBlock) rounds_kernel(const RoundsJob* _
             sum[2] = fr_add(sum[2], fr_mul(fr_sub(e[0][1], e[0][0]), fr_sub(e[1][1], e[1][0])));
           }
 #pragma unroll
-          for (uint32_t q = 0; q < 3; ++q) acc_add(nxt, 3 * q + pt, sum[q], on);
+          for (uint32_t q = 0; q < 3; ++q) acc_add(nxt, 3 * q + pt, sum[q]);
         }
         if (!lds) __threadfence_block();   // the folded entries, for the next round
       } else if (fold && tid < kWave + 4) {   // the last pair of each table
