@@ -153,7 +153,9 @@ void plan_bmm(Builder& B, const vl_bmm& b, const BmmChallenges& ch, uint8_t* pro
   uint32_t wide = 0;
   while (wide < nv && wide < kBmmMaxWide && (N >> (wide + 1)) >= kBmmWidePairs) ++wide;
   j.wide = (uint8_t)wide;
-  if (wide) j.part = B.dev<uint32_t>(B.take(((N / 2 + kBmmSweepPairs - 1) / kBmmSweepPairs) * 32 * 4));
+  // the first round's sums: over the claim's eq table, which pass 1 has used up
+  const uint64_t part = N / 2 / kBmmSweepPairs * 24 * 4;
+  if (wide) j.part = part <= align_up(8 * Hp * Lc * 4, 256) ? eqc : B.dev<uint32_t>(B.take(part));
   const uint32_t idx = (uint32_t)B.P.bmms.size();
   B.P.bmms.push_back(j);
   if (B.P.bmm_wide.size() < wide) {

@@ -551,12 +551,8 @@ static uint32_t eq_blocks_of(const EqJob& e) {
 }
 
 void Builder::eq_job(const std::vector<Fr>& x, uint32_t* eq, uint32_t* pack, uint32_t pack_len, bool pack_r2,
-                     bool eq_canon, const Fr* scale, const std::vector<uint32_t>* mont) {
+                     bool eq_canon, const std::vector<uint32_t>* mont) {
   EqJob e{};
-  if (scale) {
-    e.scaled = 1;
-    memcpy(e.scale, scale->w, 32);
-  }
   e.nvars = (uint32_t)x.size();
   e.pack_r2 = pack_r2 ? 1u : 0u;
   e.eq_canon = eq_canon ? 1u : 0u;
@@ -638,15 +634,15 @@ void Builder::group(const vl_group& g, const Challenges& ch, uint8_t* proof_dev,
   if (by_rows) {
     uint32_t* eqV = dev<uint32_t>(take(8 * L2 * 4));
     uint32_t* svec = dev<uint32_t>(take(8 * L2 * 4));
-    eq_job(u, nullptr, packU, D0, true, false, nullptr, &ch.um);
-    eq_job(v, eqV, packV, D2, false, true, nullptr, &ch.vm);
+    eq_job(u, nullptr, packU, D0, true, false, &ch.um);
+    eq_job(v, eqV, packV, D2, false, true, &ch.vm);
     contract(g.C, g.dtype_c, ndc, g.ldc, true, D2, D0, packU, svec, L2, L2, err);
     rj.c_part = pass1(eqV, L2, svec, L2, (uint32_t)L2, true, rj.c_nparts, ready);
   } else {
     uint32_t* eqU = dev<uint32_t>(take(8 * L0 * 4));
     uint32_t* tvec = dev<uint32_t>(take(8 * L0 * 4));
-    eq_job(u, eqU, packU, D0, true, false, nullptr, &ch.um);
-    eq_job(v, nullptr, packV, D2, false, false, nullptr, &ch.vm);
+    eq_job(u, eqU, packU, D0, true, false, &ch.um);
+    eq_job(v, nullptr, packV, D2, false, false, &ch.vm);
     contract(g.C, g.dtype_c, ndc, g.ldc, false, D0, D2, packV, tvec, L0, L0, err);
     rj.c_part = pass1(eqU, L0, tvec, L0, (uint32_t)L0, true, rj.c_nparts, ready);
   }
@@ -784,8 +780,9 @@ BlobLayout blob_layout(const Plan& P) {
   L.bmm_wide.resize(P.bmm_wide.size());
   for (size_t k = 0; k < P.bmm_wide.size(); ++k) {
     L.bmm_wide[k] = o;
-    o = align_up(o + P.bmm_wide[k].size() * sizeof(BmmSweep), 64);
+    o += P.bmm_wide[k].size() * sizeof(BmmSweep);
   }
+  o = align_up(o, 64);
   L.lookups = o;
   o = align_up(o + P.lookups.size() * sizeof(LookupJob), 64);
   L.lookup_u = o;
@@ -1119,8 +1116,11 @@ hipError_t enqueue_plan(const Plan& P, const BlobLayout& L, uint8_t* dblob, hipS
     for (size_t k = 0; k < P.bmm_wide.size(); ++k) {
       const BmmSweep* lst = reinterpret_cast<const BmmSweep*>(dblob + L.bmm_wide[k]);
       const uint32_t nl = (uint32_t)P.bmm_wide[k].size();
-      VL_STAGE(ev, VL_STAGE_PASS1, s, launch_bmm_sweep(bj, lst, nl, P.bmm_wide_blocks[k], (uint32_t)k, s));
-      VL_STAGE(ev, VL_STAGE_ROUNDS, s, launch_bmm_step(bj, lst, nl, (uint32_t)k, s));
+      // round k - 1's step, for the jobs that stay wide
+      const bool merge = k > 0 && P.bmm_wide_blocks[k] <= kBmmMergeBlocks;
+      if (k > 0 && !merge) VL_STAGE(ev, VL_STAGE_ROUNDS, s, launch_bmm_step(bj, lst, nl, (uint32_t)k - 1, s));
+      VL_STAGE(ev, merge ? VL_STAGE_ROUNDS : VL_STAGE_PASS1, s,
+               launch_bmm_sweep(bj, lst, nl, P.bmm_wide_blocks[k], (uint32_t)k, merge, s));
     }
     VL_STAGE(ev, VL_STAGE_ROUNDS, s, launch_bmm_rounds(bj, nb, s));
   }

@@ -20,12 +20,11 @@ struct EqJob {
   uint32_t pack_r2;           // 1: pack holds e * R^2 (contractions land in Montgomery
                               // form); 0: e * R (they land in canonical form)
   uint32_t eq_canon;          // 1: eq holds canonical values, 0: Montgomery form
-  uint32_t scaled;            // 1: every entry multiplied by scale
+  uint32_t pad_;
   const uint32_t* point;      // device: nvars Montgomery elements x_j (8 words each)
   uint32_t* eq;               // SoL output, may be null
   uint64_t eq_ld;
   uint32_t* pack;             // pack_len * 8 words, may be null
-  uint32_t scale[8];          // Montgomery
 };
 
 // eq table of a point passed by value (at most 20 variables)
@@ -183,16 +182,23 @@ constexpr uint32_t reduce_io_words(uint32_t n_rows) { return kReduceIoR + 8 * (n
 // suffixes' tables), a (Montgomery) and b (canonical) over 2^(nh + n1)
 // entries, head index most significant, so every round value is canonical.
 // The first `wide` rounds run as GPU-wide sweeps (bmm_sweep_kernel, one launch
-// per round) each followed by a transcript step (bmm_step_kernel); the rest
-// run in one workgroup (bmm_rounds_kernel).  io holds the state handed between
-// the launches.
+// per round); a round's transcript step is taken by the next sweep's blocks, by
+// a launch of its own (bmm_step_kernel) before sweeps of more than
+// kBmmMergeBlocks blocks, and for the last of them by the workgroup that runs
+// the rest (bmm_rounds_kernel).  io holds the state handed between the
+// launches.
 constexpr uint32_t kBmmSweepPairs = 256;     // pairs per sweep block (three threads each)
-constexpr uint32_t kBmmWidePairs = 1024;     // rounds with at least this many pairs run wide
+// rounds with at least this many pairs run wide (one of 512 or 256 takes 22 us,
+// in one workgroup 28)
+constexpr uint32_t kBmmWidePairs = 256;
+constexpr uint32_t kBmmMergeBlocks = 256;
+constexpr uint32_t kBmmLds = 1024;           // entries of the rounds workgroup's LDS tables
+constexpr uint32_t kBmmAhead = 128;          // rounds with at most this many are summed ahead in the rounds workgroup
 constexpr uint32_t kBmmMaxWide = 24;
-// io words: [0] status (VL_OK while running), [8, 16) transcript state,
-// [16, 24) pending challenge r (Montgomery), [24, 32) the claim c (canonical),
-// [32, 40) the running scalar
-constexpr uint32_t kBmmIoState = 8, kBmmIoR = 16, kBmmIoC = 24, kBmmIoScale = 32, kBmmIoWords = 40;
+// io words: [0] status (VL_OK while running), [8, 16) the claim c (canonical),
+// [16, 40) and [40, 64) what round rd leaves for the next, by parity: the
+// transcript state, the challenge r and the running scalar (Montgomery)
+constexpr uint32_t kBmmIoC = 8, kBmmIoSlot = 16, kBmmSlotR = 8, kBmmSlotScale = 16, kBmmIoWords = 64;
 struct BmmJob {
   uint32_t st[8];             // transcript state after squeezing rho, u, v
   uint8_t nh, n1;             // head and inner variables
@@ -204,7 +210,7 @@ struct BmmJob {
   uint32_t* E;                // ld 2^nh
   uint32_t* a;                // ld 2^(nh + n1)
   uint32_t* b;
-  uint32_t* part;             // sweep partials: 4 elements (32 words) per block
+  uint32_t* part;             // round 0's sums: 3 elements per block
   uint32_t* io;
   uint8_t* proof;             // device-writable proof bytes
   uint8_t* digest;            // 32 bytes or null
@@ -325,7 +331,7 @@ hipError_t launch_zero_words(uint32_t* p, uint64_t n_words, hipStream_t s);
 // batched products (bmm.hip)
 hipError_t launch_bmm_start(const BmmJob* jobs_dev, uint32_t n_jobs, hipStream_t s);
 hipError_t launch_bmm_sweep(const BmmJob* jobs_dev, const BmmSweep* list_dev, uint32_t n_list, uint32_t n_blocks,
-                            uint32_t round, hipStream_t s);
+                            uint32_t round, bool step, hipStream_t s);
 hipError_t launch_bmm_step(const BmmJob* jobs_dev, const BmmSweep* list_dev, uint32_t n_list, uint32_t round,
                            hipStream_t s);
 hipError_t launch_bmm_rounds(const BmmJob* jobs_dev, uint32_t n_jobs, hipStream_t s);

@@ -24,7 +24,7 @@ namespace vl {
 // for bit 0, b_1 the most significant bit.  A block has kEqBlock = 2^8
 // consecutive entries, one per thread: two tables of 16 products over the low
 // variables, four lanes multiplying an entry's factors as a tree, and the
-// block's product over the others (with the form's constant and the scale)
+// block's product over the others (with the form's constant)
 // likewise; then two products an entry.  Bound by that chain of about seven
 // products: with n + 4 of them in sequence on a thread of four entries, and 41
 // KB of code, the single 64 x 128 x 32 product's tables took 15 us and the 7B
@@ -39,8 +39,8 @@ enum EqForm { EQ_CANON = 0, EQ_MONT = 1, EQ_R2 = 2 };
 // Entry 256 blk + threadIdx.x (or a product without meaning past 2^n), in form
 // `form`, then taken `down` forms lower in `low`.
 template <typename P>
-__device__ __forceinline__ Fr eq_entry(const P& point, uint32_t n, uint32_t blk, const uint32_t* scale, uint32_t form,
-                                       uint32_t down, EqLds& T, Fr& low) {
+__device__ __forceinline__ Fr eq_entry(const P& point, uint32_t n, uint32_t blk, uint32_t form, uint32_t down,
+                                       EqLds& T, Fr& low) {
   const uint32_t tid = threadIdx.x;
   const uint32_t nu = n > 8 ? n - 8 : 0;
   if (tid < 192) {
@@ -60,10 +60,8 @@ __device__ __forceinline__ Fr eq_entry(const P& point, uint32_t n, uint32_t blk,
       if (form == EQ_CANON)
 #pragma unroll
         for (int j = 0; j < 8; ++j) f.w[j] = j == 0 ? 1u : 0u;
-    } else if (!grp && m == nu + 1 && scale) {
-      f = lds_or_global_fr(scale);
     }
-    const uint32_t width = grp ? 4u : nu + 2;
+    const uint32_t width = grp ? 4u : nu + 1;
 #pragma unroll 1
     for (uint32_t off = 1; off < width; off <<= 1) {
       Fr o;
@@ -105,8 +103,8 @@ __global__ void __launch_bounds__(kEqBlock) eq_kernel(const EqJob* __restrict__ 
   const uint32_t form = J.pack ? (J.pack_r2 ? EQ_R2 : EQ_MONT) : eq_form;
   Fr low;
   const uint32_t* pt = J.point;
-  const Fr e = eq_entry([&](uint32_t j) { return lds_or_global_fr(pt + 8 * j); }, J.nvars, b,
-                        J.scaled ? J.scale : nullptr, form, J.eq ? form - eq_form : 0u, T, low);
+  const Fr e = eq_entry([&](uint32_t j) { return lds_or_global_fr(pt + 8 * j); }, J.nvars, b, form,
+                        J.eq ? form - eq_form : 0u, T, low);
   const uint64_t i = (uint64_t)b * kEqBlock + threadIdx.x;
   if (J.eq && i < (1ull << J.nvars)) store_sol(J.eq, J.eq_ld, i, low);
   if (J.pack && i < J.pack_len) signed_digits(e, J.pack + i * 8);
@@ -116,7 +114,7 @@ __global__ void __launch_bounds__(kEqBlock) eq_kernel(const EqJob* __restrict__ 
 __global__ void __launch_bounds__(kEqBlock) eq_point_kernel(EqPointArgs a) {
   __shared__ EqLds T;
   Fr low;
-  const Fr e = eq_entry([&](uint32_t j) { return lds_or_global_fr(a.pt[j]); }, a.nvars, blockIdx.x, nullptr, EQ_MONT, 0u,
+  const Fr e = eq_entry([&](uint32_t j) { return lds_or_global_fr(a.pt[j]); }, a.nvars, blockIdx.x, EQ_MONT, 0u,
                         T, low);
   const uint64_t i = (uint64_t)blockIdx.x * kEqBlock + threadIdx.x;
   if (i < (1ull << a.nvars)) store_sol(a.out, a.ld, i, e);

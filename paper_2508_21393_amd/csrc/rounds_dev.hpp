@@ -151,6 +151,12 @@ __device__ __forceinline__ void st_rec(uint32_t* p, const Fr& v) {
 __device__ __forceinline__ Fr fr_fold(const Fr& r, const Fr& x0, const Fr& x1) {
   return fr_add(x0, fr_mul(r, fr_sub(x1, x0)));
 }
+__device__ __forceinline__ Fr fr_pick(bool c, const Fr& a, const Fr& b) {
+  Fr r;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) r.w[j] = c ? a.w[j] : b.w[j];
+  return r;
+}
 // the quadratic with values v0, v1 at 0 and 1 and leading coefficient v2, at r
 __device__ __forceinline__ Fr fr_eval2(const Fr& v0, const Fr& v1, const Fr& v2, const Fr& r) {
   return fr_add(v0, fr_mul(r, fr_add(fr_sub(fr_sub(v1, v0), v2), fr_mul(r, v2))));

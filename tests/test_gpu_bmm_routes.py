@@ -1,5 +1,6 @@
 """Batched products whose rounds change route: all in one workgroup (up to
-2^10 entries), one or more GPU-wide rounds, head rounds that end inside the
+2^8 entries), one or more GPU-wide rounds, with the steps inside the sweeps or
+launches of their own (2^19 entries), head rounds that end inside the
 wide part or inside the workgroup, no head rounds, no inner rounds, no rounds;
 byte for byte against the oracle."""
 import pytest
@@ -12,7 +13,7 @@ from gpu_util import to_dev
 pytestmark = pytest.mark.gpu
 
 SHAPES = [(1, 1, 1, 1), (2, 1, 1, 1), (1, 3, 2, 2), (8, 2, 64, 2), (16, 3, 64, 2), (32, 2, 64, 3), (3, 2, 700, 2),
-          (1000, 1, 2, 1), (1025, 2, 1, 1), (1, 2, 2049, 2), (5, 2, 1000, 3)]
+          (1000, 1, 2, 1), (1025, 2, 1, 1), (1, 2, 2049, 2), (5, 2, 1000, 3), (300, 1, 700, 1)]
 
 
 @pytest.mark.parametrize("shape", SHAPES)
