@@ -1127,11 +1127,11 @@ hipError_t enqueue_plan(const Plan& P, const BlobLayout& L, uint8_t* dblob, hipS
   if (!P.lookups.empty()) {
     const LookupJob* lj = reinterpret_cast<const LookupJob*>(dblob + L.lookups);
     const uint32_t nl = (uint32_t)P.lookups.size();
-    auto sweep = [&](int kd, size_t k) -> hipError_t {
+    auto sweep = [&](int kd, size_t k, bool step) -> hipError_t {
       if (k >= P.lk_wide[kd].size() || P.lk_wide[kd][k].empty()) return hipSuccess;
       return launch_lookup_sweep(lj, reinterpret_cast<const LookupSweep*>(dblob + L.lk_wide[kd][k]),
                                  (uint32_t)P.lk_wide[kd][k].size(), P.lk_wide_blocks[kd][k], (uint32_t)k,
-                                 (LookupSweepKind)kd, s);
+                                 (LookupSweepKind)kd, step, s);
     };
     // The tables (an inversion per thread is one chain of instructions) and
     // the first sweep on the caller's stream; the counts, the multiplicities
@@ -1151,7 +1151,7 @@ hipError_t enqueue_plan(const Plan& P, const BlobLayout& L, uint8_t* dblob, hipS
     for (const auto& z : P.lookup_zero) VL_STAGE(ev, VL_STAGE_FINISH, sc, launch_zero_words(z.first, z.second, sc));
     VL_STAGE(ev, VL_STAGE_FINISH, sc, launch_lookup_hist(lj, nl, P.lk_hist_blocks, P.lk_hist_lds, sc));
     VL_STAGE(ev, VL_STAGE_FINISH, s, launch_lookup_prep(lj, nl, P.lk_prep_blocks, s));
-    VL_STAGE(ev, VL_STAGE_PASS1, s, sweep(LK_FIRST, 0));
+    VL_STAGE(ev, VL_STAGE_PASS1, s, sweep(LK_FIRST, 0, false));
     if (lk_side) {
       const hipError_t e = hipStreamWaitEvent(s2, fe[1], 0);
       if (e != hipSuccess) return e;
@@ -1165,13 +1165,23 @@ hipError_t enqueue_plan(const Plan& P, const BlobLayout& L, uint8_t* dblob, hipS
     }
     size_t nk = 0;
     for (const auto& w : P.lk_wide) nk = std::max(nk, w.size());
+    auto jobs_at = [&](int kd, size_t k) { return k < P.lk_wide[kd].size() ? P.lk_wide[kd][k].size() : 0; };
+    // whether round k's low sweep takes round k - 1's step: for all of that
+    // round's jobs or none
+    auto merged = [&](size_t k) {
+      size_t before = 0;
+      for (int kd = 0; kd < LK_KINDS; ++kd) before += k ? jobs_at(kd, k - 1) : 0;
+      return k > 0 && jobs_at(LK_LOW, k) == before && before && P.lk_wide_blocks[LK_LOW][k] <= kLookupMergeBlocks;
+    };
     for (size_t k = 0; k < nk; ++k)
       for (int kd = 0; kd < LK_KINDS; ++kd) {
-        if (k >= P.lk_wide[kd].size() || P.lk_wide[kd][k].empty()) continue;
-        if (kd != LK_FIRST) VL_STAGE(ev, VL_STAGE_PASS1, s, sweep(kd, k));
-        VL_STAGE(ev, VL_STAGE_ROUNDS, s,
-                 launch_lookup_step(lj, reinterpret_cast<const LookupSweep*>(dblob + L.lk_wide[kd][k]),
-                                    (uint32_t)P.lk_wide[kd][k].size(), (uint32_t)k, s));
+        if (jobs_at(kd, k) == 0) continue;
+        const bool step = kd == LK_LOW && merged(k);
+        if (kd != LK_FIRST) VL_STAGE(ev, step ? VL_STAGE_ROUNDS : VL_STAGE_PASS1, s, sweep(kd, k, step));
+        if (!merged(k + 1))
+          VL_STAGE(ev, VL_STAGE_ROUNDS, s,
+                   launch_lookup_step(lj, reinterpret_cast<const LookupSweep*>(dblob + L.lk_wide[kd][k]),
+                                      (uint32_t)P.lk_wide[kd][k].size(), (uint32_t)k, s));
       }
     VL_STAGE(ev, VL_STAGE_ROUNDS, s, launch_lookup_rounds(lj, nl, s));
   }

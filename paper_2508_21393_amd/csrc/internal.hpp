@@ -260,9 +260,14 @@ inline __host__ __device__ uint32_t lk_round_blocks(uint32_t n, uint32_t nH, uin
   const uint64_t h = 1ull << (n - 1 - rd), s = rd >= nH ? kLookupLowPairs : lk_span(h);
   return (uint32_t)((h + s - 1) / s);
 }
-// io words: [0] status, [8, 16) state, [16, 24) pending r, [24, 32) the next
-// high round's constant, [32, 56) the running scalars
-constexpr uint32_t kLkIoState = 8, kLkIoR = 16, kLkIoK = 24, kLkIoScale = 32, kLkIoWords = 56;
+// low rounds whose sweep has at most this many blocks take the step of the round
+// before (where every job of that round goes on with one)
+constexpr uint32_t kLookupMergeBlocks = 256;
+// io words: [0] status, then two slots of what round rd leaves for the next, by
+// parity: [0, 8) state, [8, 16) r, [16, 24) the next high round's constant,
+// [24, 48) the running scalars
+constexpr uint32_t kLkIoSlot = 8, kLkSlotR = 8, kLkSlotK = 16, kLkSlotScale = 24, kLkSlotWords = 48;
+constexpr uint32_t kLkIoWords = kLkIoSlot + 2 * kLkSlotWords;
 struct LookupJob {
   uint32_t st[8];             // transcript state after gamma, beta, alpha, u
   uint32_t gamma[8], beta[8], alpha[8], c1[8], c2[8];   // Montgomery (c1 = alpha^2 N / D', c2 = N / D')
@@ -343,7 +348,7 @@ hipError_t launch_lookup_mult(const LookupJob* jobs_dev, uint32_t n_jobs, uint32
 hipError_t launch_lookup_prep(const LookupJob* jobs_dev, uint32_t n_jobs, uint32_t n_blocks, hipStream_t s);
 hipError_t launch_lookup_start(const LookupJob* jobs_dev, uint32_t n_jobs, hipStream_t s);
 hipError_t launch_lookup_sweep(const LookupJob* jobs_dev, const LookupSweep* list_dev, uint32_t n_list,
-                               uint32_t n_blocks, uint32_t round, LookupSweepKind kind, hipStream_t s);
+                               uint32_t n_blocks, uint32_t round, LookupSweepKind kind, bool step, hipStream_t s);
 hipError_t launch_lookup_step(const LookupJob* jobs_dev, const LookupSweep* list_dev, uint32_t n_list,
                               uint32_t round, hipStream_t s);
 hipError_t launch_lookup_rounds(const LookupJob* jobs_dev, uint32_t n_jobs, hipStream_t s);

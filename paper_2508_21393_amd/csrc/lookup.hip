@@ -167,7 +167,9 @@ __device__ __forceinline__ Fr fr_minus_one() { return fr_neg(fr_R()); }
 
 // State of the rounds held by wave 0: lane 4 g + k (g < 3, k < 4) has group
 // g's running scalar, g = 0: alpha prod eq1(u_j, r_j) over the rounds so far,
-// 1: c1 prod over the low rounds, 2: one; and e = eq1(u_rd, k) times it.
+// 1: c1 prod over the low rounds, 2: one; and e = eq1(u_rd, k) times it.  The
+// scalars are canonical, so that they take the values, which are in Montgomery
+// form, to canonical ones.
 struct LkState {
   Fr sc, sce;
   Fr kc;       // the next high round's constant 2^(nH - rd - 1) K
@@ -178,13 +180,16 @@ __device__ __forceinline__ void lk_set_sce(const LookupJob& J, uint32_t rd, LkSt
 #pragma unroll
   for (int j = 0; j < 8; ++j) s.sce.w[j] = lane < 8 ? m.w[j] : s.sc.w[j];
 }
+// the state round rd starts from, left in io by round rd - 1 (or the start) in
+// the slot of its parity
+__device__ __forceinline__ uint32_t* lk_slot(const LookupJob& J, uint32_t rd) { return J.io + kLkIoSlot + kLkSlotWords * (~rd & 1u); }
 __device__ __forceinline__ void lk_load_state(const LookupJob& J, uint32_t rd, LkState& s, RoundLds& T, uint32_t lane) {
-  const uint32_t g = lane >> 2;
-  s.sc = lds_or_global_fr(J.io + kLkIoScale + 8 * min(g, 2u));
-  s.kc = lds_or_global_fr(J.io + kLkIoK);
+  const uint32_t g = lane >> 2, *io = lk_slot(J, rd);
+  s.sc = lds_or_global_fr(io + kLkSlotScale + 8 * min(g, 2u));
+  s.kc = lds_or_global_fr(io + kLkSlotK);
   if (lane < 8) {
-    T.st[lane] = J.io[kLkIoState + lane];
-    T.r[lane] = J.io[kLkIoR + lane];
+    T.st[lane] = io[lane];
+    T.r[lane] = io[kLkSlotR + lane];
   }
   if (rd < J.nH + J.nL) lk_set_sce(J, rd, s, lane);
 }
@@ -196,7 +201,7 @@ __device__ __forceinline__ void lk_load_state(const LookupJob& J, uint32_t rd, L
 // Round 0 checks the guard g(0) + g(1) = alpha + alpha^2 (false in every lane
 // if it fails).
 __device__ __forceinline__ bool lk_step(const LookupJob& J, uint32_t rd, const unsigned long long* acc, LkState& s,
-                                        RoundLds& T, uint32_t lane) {
+                                        RoundLds& T, uint32_t lane, bool write = true) {
   const uint32_t g = min(lane >> 2, 2u), k = lane & 3u;
   Fr v = acc_point(acc, 3 * g, k);
   if (rd == 0 && J.gather && g == 0) {   // A Sb = 1 at every entry, and the weights add up to 1
@@ -206,11 +211,10 @@ __device__ __forceinline__ bool lk_step(const LookupJob& J, uint32_t rd, const u
   v = fr_mul(v, s.sce);
   v = fr_add(v, fr_add(fr_row_shl<4>(v), fr_row_shl<8>(v)));   // lanes 0 .. 3
   if (rd < J.nH) v = fr_add(v, s.kc);
-  if (rd == 0 && !fr_eq(fr_add(readlane_fr(v, 0), readlane_fr(v, 1)), lk_fr(J.claim))) return false;
-  const Fr gm = fr_from_mont(v);
+  if (rd == 0 && !fr_eq(fr_add(readlane_fr(v, 0), readlane_fr(v, 1)), fr_from_mont(lk_fr(J.claim)))) return false;
   if (lane < 4) {
-    put_canon(J.proof + 128ull * rd + 32 * lane, gm);
-    lds_put(T.v + 8 * lane, gm);
+    if (write) put_canon(J.proof + 128ull * rd + 32 * lane, v);
+    lds_put(T.v + 8 * lane, v);
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   tr_round(T, 4);
@@ -432,14 +436,16 @@ __global__ void __launch_bounds__(64) lookup_start_kernel(const LookupJob* __res
   if (lane == 0) {
     Fr K = fr_sub(lk_fr(J.c1), s[0]);
     for (uint32_t i = 0; i + 1 < J.nH; ++i) K = fr_double(K);
-    const Fr alpha = lk_fr(J.alpha), c1 = lk_fr(J.c1), one = fr_R();
+    const Fr alpha = fr_from_mont(lk_fr(J.alpha)), c1 = fr_from_mont(lk_fr(J.c1)), one = fr_one_raw();
+    K = fr_from_mont(K);
+    uint32_t* io = lk_slot(J, 0);
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      J.io[kLkIoK + i] = K.w[i];
-      J.io[kLkIoState + i] = J.st[i];
-      J.io[kLkIoScale + i] = alpha.w[i];
-      J.io[kLkIoScale + 8 + i] = c1.w[i];
-      J.io[kLkIoScale + 16 + i] = one.w[i];
+      io[kLkSlotK + i] = K.w[i];
+      io[i] = J.st[i];
+      io[kLkSlotScale + i] = alpha.w[i];
+      io[kLkSlotScale + 8 + i] = c1.w[i];
+      io[kLkSlotScale + 16 + i] = one.w[i];
     }
     J.io[0] = (uint32_t)VL_OK;
   }
@@ -473,7 +479,7 @@ __global__ void __launch_bounds__(256) lookup_sweep_kernel(const LookupJob* __re
   Fr v[5];
 #pragma unroll
   for (int k = 0; k < 5; ++k) v[k] = fr_zero();
-  const Fr r = MODE == kSecond || MODE == kFold ? lds_or_global_fr(J.io + kLkIoR) : fr_zero();
+  const Fr r = MODE == kSecond || MODE == kFold ? lds_or_global_fr(lk_slot(J, rd) + kLkSlotR) : fr_zero();
 #pragma unroll 1
   for (uint64_t t = base + threadIdx.x; t < h && t < base + span; t += 256) {
     const Fr w = m > nlo ? lk_weight(J, nlo, t & ((1ull << nlo) - 1)) : lk_weight(J, m, t);
@@ -519,16 +525,64 @@ __global__ void __launch_bounds__(256) lookup_sweep_kernel(const LookupJob* __re
   lk_block_out(v, m > nlo ? &hi : nullptr, J.part + (uint64_t)(blk - L.block_begin) * kLookupPartWords);
 }
 
+// block b's sums of wide round rd: in part, in low rounds after the first in the
+// row records that this block, and no other, folds away in that round
+__device__ __forceinline__ uint32_t* lk_part(const LookupJob& J, uint32_t rd, uint64_t b) {
+  if (rd <= J.nH) return J.part + kLookupPartWords * b;
+  return J.rec + 16 * ((2ull << (J.nH + J.nL - 1 - rd)) + kLookupLowPairs * b);
+}
+// round rd's nine sums into acc (zeroed), one wave each
+__device__ __forceinline__ void lk_sum_parts(const LookupJob& J, uint32_t rd, unsigned long long* acc) {
+  const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
+  const uint32_t nblocks = lk_round_blocks(J.nH + J.nL, J.nH, rd);
+  Fr v = fr_zero();
+  for (uint32_t i = lane; i < nblocks; i += 64) v = fr_add(v, ld_rec(lk_part(J, rd, i) + 8 * wave));
+  acc_add(acc, wave, v);
+}
+// the step of wide round rd by wave 0; write: by the one workgroup that stores
+// proof bytes and io
+__device__ __forceinline__ bool lk_wide_step(const LookupJob& J, uint32_t rd, const unsigned long long* acc, LkState& s,
+                                             RoundLds& T, uint32_t lane, bool write) {
+  if (!lk_step(J, rd, acc, s, T, lane, write)) {
+    if (write && lane == 0) {
+      J.io[0] = (uint32_t)VL_ERR_FALSE_STATEMENT;
+      *J.status = VL_ERR_FALSE_STATEMENT;
+    }
+    return false;
+  }
+  if (write) {
+    uint32_t* io = lk_slot(J, rd + 1);
+    if (lane < 8) {
+      io[lane] = T.st[lane];
+      io[kLkSlotR + lane] = T.r[lane];
+    }
+    lk_advance(J, rd, s, T, lane);
+    if ((lane & 3u) == 0 && lane < 12)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) io[kLkSlotScale + 2 * lane + i] = s.sc.w[i];
+    if (lane == 0)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) io[kLkSlotK + i] = s.kc.w[i];
+  }
+  return true;
+}
+
 // One wide round in which a low index bit is bound, every table: 64 pairs a
 // block, one wave per term (lk_term).  Few pairs: bound by a thread's chain of
 // five products and by fetching the kernel's code, so the code is small.  The
 // tables fold in place: every wave has read the block's entries before any
 // wave writes.
+// step: every block first takes round rd - 1's transcript step itself, from the
+// previous launch's sums (its first block stores it), so that a round is one
+// launch: 26 us instead of 11.5 and 16.5, while the launch has no more
+// blocks than CUs (kLookupMergeBlocks).
 __global__ void __launch_bounds__(64 * kLkTerms) lookup_sweep_low_kernel(const LookupJob* __restrict__ jobs,
                                                                          const LookupSweep* __restrict__ list,
                                                                          uint32_t n_list, uint32_t n_blocks,
-                                                                         uint32_t rd) {
+                                                                         uint32_t rd, uint32_t step) {
   __shared__ unsigned long long acc[110];   // nine values; acc_point reads two past its base
+  __shared__ RoundLds T;
+  __shared__ uint32_t dead_s;
   const uint32_t blk = blockIdx.x;
   if (blk >= n_blocks) return;
   const LookupSweep& L = list[lk_find([&](uint32_t k) { return list[k].block_begin; }, n_list, blk)];
@@ -541,7 +595,6 @@ __global__ void __launch_bounds__(64 * kLkTerms) lookup_sweep_low_kernel(const L
   const uint64_t t = (uint64_t)(blk - L.block_begin) * kLookupLowPairs + lane;   // h is a multiple of 64 here
   const uint64_t ldA = J.gather ? 1ull << (n - 1) : 1ull << n, ldN = 1ull << J.nL;
   const bool fold = role == 0 ? rd > 0 : rd > J.nH;
-  const Fr r = lds_or_global_fr(J.io + kLkIoR);
   auto get = [&](uint32_t k, uint64_t i) {   // table k: A, Sb, B, T + beta, M'
     if (k == 2 || k == 3) return ld_rec(J.rec + 16 * i + (k == 3 ? 8 : 0));
     return load_sol(k == 0 ? J.A : (k == 1 ? J.S : J.M), k == 4 ? ldN : ldA, i);
@@ -568,7 +621,23 @@ __global__ void __launch_bounds__(64 * kLkTerms) lookup_sweep_low_kernel(const L
     }
   }
   if (threadIdx.x < 110) acc[threadIdx.x] = 0;
+  if (threadIdx.x == 0) dead_s = 0;
   __syncthreads();   // everything read (and acc zeroed)
+  if (step) {
+    LkState s;
+    if (wave == 0) lk_load_state(J, rd - 1, s, T, lane);
+    lk_sum_parts(J, rd - 1, acc);
+    __syncthreads();
+    if (wave == 0) {
+      const bool ok = lk_wide_step(J, rd - 1, acc, s, T, lane, blk == L.block_begin);
+      acc[lane] = 0;
+      if (lane < 46) acc[64 + lane] = 0;
+      if (lane == 0 && !ok) dead_s = 1;
+    }
+    __syncthreads();
+    if (dead_s) return;
+  }
+  const Fr r = step ? lds_get(T.r) : lds_or_global_fr(lk_slot(J, rd) + kLkSlotR);
   const Fr w = role == 2 ? fr_minus_one() : m > nlo ? fr_mul(lk_weight(J, nlo, t & ((1ull << nlo) - 1)),
                                 load_sol(J.EH + 8 * ((1ull << (m - nlo)) - 1), 1ull << (m - nlo), t >> nlo))
                        : lk_weight(J, m, t);
@@ -582,47 +651,26 @@ __global__ void __launch_bounds__(64 * kLkTerms) lookup_sweep_low_kernel(const L
   __syncthreads();
   if (wave == 0) {
     const Fr v = acc_point(acc, min(lane, 8u), 0);
-    if (lane < 9) st_rec(J.part + (uint64_t)(blk - L.block_begin) * kLookupPartWords + 8 * lane, v);
+    if (lane < 9) st_rec(lk_part(J, rd, blk - L.block_begin) + 8 * lane, v);
   }
 }
 
-// The transcript step after a wide round, one workgroup per job: wave k adds
-// the blocks' value k, wave 0 then runs the round's step.
+// The transcript step after a wide round, one workgroup per job, where the next
+// sweep does not take it.
 __global__ void __launch_bounds__(64 * 9) lookup_step_kernel(const LookupJob* __restrict__ jobs,
                                                              const LookupSweep* __restrict__ list, uint32_t rd) {
   __shared__ unsigned long long acc[110];   // nine values; acc_point reads two past its base
   __shared__ RoundLds T;
   const LookupJob& J = jobs[list[blockIdx.x].job];
-  const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = tid & 63u;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u;
   if (lk_io_status(J) != VL_OK) return;
-  const uint32_t nblocks = lk_round_blocks(J.nH + J.nL, J.nH, rd);
   if (tid < 110) acc[tid] = 0;
   LkState s;
-  if (wave == 0) lk_load_state(J, rd, s, T, lane);
-  Fr v = fr_zero();
-  for (uint32_t i = lane; i < nblocks; i += 64) v = fr_add(v, ld_rec(J.part + (uint64_t)kLookupPartWords * i + 8 * wave));
+  if (tid < 64) lk_load_state(J, rd, s, T, lane);
   __syncthreads();
-  acc_add(acc, wave, v);
+  lk_sum_parts(J, rd, acc);
   __syncthreads();
-  if (wave != 0) return;
-  if (!lk_step(J, rd, acc, s, T, lane)) {
-    if (lane == 0) {
-      J.io[0] = (uint32_t)VL_ERR_FALSE_STATEMENT;
-      *J.status = VL_ERR_FALSE_STATEMENT;
-    }
-    return;
-  }
-  if (lane < 8) {
-    J.io[kLkIoState + lane] = T.st[lane];
-    J.io[kLkIoR + lane] = T.r[lane];
-  }
-  lk_advance(J, rd, s, T, lane);
-  if ((lane & 3u) == 0 && lane < 12)
-#pragma unroll
-    for (int i = 0; i < 8; ++i) J.io[kLkIoScale + 2 * lane + i] = s.sc.w[i];
-  if (lane == 0)
-#pragma unroll
-    for (int i = 0; i < 8; ++i) J.io[kLkIoK + i] = s.kc.w[i];
+  if (tid < 64) lk_wide_step(J, rd, acc, s, T, lane, true);
 }
 
 // The remaining rounds in one workgroup, then the final values.  The tables
@@ -630,15 +678,16 @@ __global__ void __launch_bounds__(64 * 9) lookup_step_kernel(const LookupJob* __
 // entries then) and live in LDS after it, folded from one buffer into the
 // other.  The rows of 16 lanes of waves 1 .. 11 take the terms
 // (lk_term) of 16 pairs at a time, so that short rounds leave no wave with
-// idle lanes beside another on its SIMD; wave 0
+// idle lanes beside another on its SIMD (with a wave per term the last rounds
+// took 25 us instead of 20); wave 0
 // runs the transcript and moves the running scalars on while the others work.
-// A round is a chain of one term (about 1700 instructions), the values (1000)
-// and the hashes (6000), 4 cycles each.
+// A round is a chain of one term (about 1700 instructions), the values (900)
+// and the hash (4700), 4 cycles each.
 constexpr uint32_t kTailWaves = 12;
 __global__ void __launch_bounds__(64 * kTailWaves) lookup_rounds_kernel(const LookupJob* __restrict__ jobs) {
   const LookupJob& J = jobs[blockIdx.x];
   constexpr uint32_t kLen = 1u << (kLookupTailVars - 1);   // entries of the first LDS buffer
-  __shared__ uint32_t buf[5][8 * (kLen + kLen / 2)];       // A, Sb, B, T, M': two buffers each
+  __shared__ alignas(16) uint32_t buf[5][8 * (kLen + kLen / 2)];   // A, Sb, B, T, M': two buffers each
   __shared__ unsigned long long acc[110];   // nine values; acc_point reads two past its base
   __shared__ RoundLds T;
   __shared__ uint32_t dead_s;
@@ -657,16 +706,19 @@ __global__ void __launch_bounds__(64 * kTailWaves) lookup_rounds_kernel(const Lo
   int atA = -1, atB = -1;
   auto get = [&](uint32_t k, uint32_t i) {
     const int w = k < 2 ? atA : atB;
-    if (w >= 0) return load_sol(buf[k] + (w ? 8 * kLen : 0), w ? kLen / 2 : kLen, i);
+    if (w >= 0) return ld_rec(buf[k] + (w ? 8 * kLen : 0) + 8 * i);
     if (k == 2 || k == 3) return ld_rec(gR + 16 * (uint64_t)i + (k == 3 ? 8 : 0));
     return load_sol(k == 0 ? gA : (k == 1 ? gS : gM), k == 4 ? ldN : ldA, i);
   };
   auto put = [&](uint32_t k, uint32_t i, const Fr& x) {
     const bool w = (k < 2 ? atA : atB) == 0;
-    store_sol(buf[k] + (w ? 8 * kLen : 0), w ? kLen / 2 : kLen, i, x);
+    st_rec(buf[k] + (w ? 8 * kLen : 0) + 8 * i, x);
   };
   LkState s;
-  if (wave == 0) lk_load_state(J, wide, s, T, lane);
+  if (wave == 0) {
+    __builtin_amdgcn_s_setprio(3);   // the transcript's wave goes before those it shares its SIMD with
+    lk_load_state(J, wide, s, T, lane);
+  }
   if (tid < 110) acc[tid] = 0;
   if (tid == 0) dead_s = 0;
   __syncthreads();
@@ -802,7 +854,7 @@ hipError_t launch_lookup_start(const LookupJob* jobs, uint32_t n_jobs, hipStream
 }
 
 hipError_t launch_lookup_sweep(const LookupJob* jobs, const LookupSweep* list, uint32_t n_list, uint32_t n_blocks,
-                               uint32_t round, LookupSweepKind kind, hipStream_t s) {
+                               uint32_t round, LookupSweepKind kind, bool step, hipStream_t s) {
   if (n_blocks == 0) return hipSuccess;
   const dim3 g(n_blocks), b(256);
   switch (kind) {
@@ -811,7 +863,8 @@ hipError_t launch_lookup_sweep(const LookupJob* jobs, const LookupSweep* list, u
     case LK_FOLD: hipLaunchKernelGGL(lookup_sweep_kernel<kFold>, g, b, 0, s, jobs, list, n_list, n_blocks, round); break;
     case LK_PLAIN: hipLaunchKernelGGL(lookup_sweep_kernel<kPlain>, g, b, 0, s, jobs, list, n_list, n_blocks, round); break;
     default:
-      hipLaunchKernelGGL(lookup_sweep_low_kernel, g, dim3(64 * kLkTerms), 0, s, jobs, list, n_list, n_blocks, round);
+      hipLaunchKernelGGL(lookup_sweep_low_kernel, g, dim3(64 * kLkTerms), 0, s, jobs, list, n_list, n_blocks, round,
+                         step ? 1u : 0u);
       break;
   }
   return hipGetLastError();
