@@ -1104,8 +1104,10 @@ hipError_t enqueue_plan(const Plan& P, const BlobLayout& L, uint8_t* dblob, hipS
     for (size_t k = 0; k < P.red_wide.size(); ++k) {
       const MatSweep* lst = reinterpret_cast<const MatSweep*>(dblob + L.red_wide[k]);
       const uint32_t nl = (uint32_t)P.red_wide[k].size();
-      VL_STAGE(ev, VL_STAGE_ROUNDS, s, launch_reduce_sweep(rj, lst, nl, P.red_wide_blocks[k], (uint32_t)k, s));
-      VL_STAGE(ev, VL_STAGE_ROUNDS, s, launch_reduce_step(rj, lst, nl, (uint32_t)k, s));
+      // round k - 1's step, for the jobs that stay wide
+      const bool merge = k > 0 && P.red_wide_blocks[k] <= kRedMergeBlocks;
+      if (k > 0 && !merge) VL_STAGE(ev, VL_STAGE_ROUNDS, s, launch_reduce_step(rj, lst, nl, (uint32_t)k - 1, s));
+      VL_STAGE(ev, VL_STAGE_ROUNDS, s, launch_reduce_sweep(rj, lst, nl, P.red_wide_blocks[k], (uint32_t)k, merge, s));
     }
     VL_STAGE(ev, VL_STAGE_ROUNDS, s, launch_reduce(rj, (uint32_t)P.reduces.size(), s));
   }

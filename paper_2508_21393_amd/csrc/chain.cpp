@@ -507,6 +507,7 @@ static vl_status chain_run(const vl_lora_layer& L, uint64_t seed, uint8_t* ws, u
       rj.ld = LR;
       rbufs[j].io = B.dev<uint32_t>(B.take(4ull * reduce_io_words(nR)));
       rj.io = rbufs[j].io;
+      rj.slot = reduce_io_slot(nR);
       for (uint32_t k = 0; k < K; ++k) {
         const Claim& c = claims[j][k];
         const Fr rm = fr_to_mont(rho[j][k]);
@@ -541,6 +542,7 @@ static vl_status chain_run(const vl_lora_layer& L, uint64_t seed, uint8_t* ws, u
       rj.n = nC;
       rj.ld = LC;
       rj.io = rbufs[j].io;
+      rj.slot = reduce_io_slot(nR);
       uint32_t* packR = B.dev<uint32_t>(B.take((uint64_t)m.rows * 32));
       rj.a[0] = B.dev<uint32_t>(B.take(8 * LC * 4));
       for (uint32_t k = 0; k < K; ++k) rj.w[k] = rbufs[j].ey[k];
@@ -567,8 +569,8 @@ static vl_status chain_run(const vl_lora_layer& L, uint64_t seed, uint8_t* ws, u
       return fail(VL_ERR_WORKSPACE, "workspace of %llu bytes, %llu needed", (unsigned long long)ws_bytes,
                   (unsigned long long)align_up(s4, 256));
     const BlobLayout LA = blob_layout(PA), LB = blob_layout(PB);
-    // phase 1's sweep partials (at most kRedPartWords words per 256 rows, of
-    // the at least 512 there are) go where plan B's eq job later writes the
+    // the sums of phase 1's first round (at most kRedPartWords words per 256
+    // rows, of the more than 256 there are) go where plan B's eq job later writes the
     // digits of eq(r, .) (8 words a row)
     for (int j = 0; j < kTensors; ++j) PA.reduces[j].part = packs[j];
     // the points are the eq jobs'; fill_blob gives them their addresses

@@ -141,13 +141,17 @@ struct EvalJob {
 //           sum_j M~(r, j) sum_k sigma_k eq(y_k, j),
 //           weights w[k] = eq(y_k, .) (canonical), table a[0] = M~(r, .)
 //           (Montgomery); then M~(r, s) is sent
-// The first `wide` rounds run as GPU-wide sweeps and a one-workgroup step.
+// The first `wide` rounds run as GPU-wide sweeps; a round's step is taken by the
+// next sweep's blocks, by a launch of its own before larger sweeps, and for the
+// last of them by the workgroup that runs the rest.
 constexpr int kMaxClaims = 3;
 constexpr uint32_t kMaxReduceClaims = kMaxClaims;
 constexpr uint32_t kRedSweepPairs = 128;     // pairs per sweep block (two threads per claim each)
-// rounds with at least this many pairs run wide: a sweep and a step take about
-// 28 us, 512 pairs of three claims in one workgroup about 40
-constexpr uint32_t kRedWidePairs = 512;
+// rounds with at least this many pairs run wide (shorter ones are summed ahead
+// in the workgroup, where one of 256 pairs of three claims would outlast the
+// hash)
+constexpr uint32_t kRedWidePairs = 256;
+constexpr uint32_t kRedMergeBlocks = 256;
 constexpr uint32_t kRedPartWords = 16 * kMaxReduceClaims;
 struct ReduceJob {
   uint32_t st[8];             // phase 1: transcript state after the rho squeezes
@@ -156,21 +160,26 @@ struct ReduceJob {
   uint32_t K;                 // claims
   uint32_t n;                 // rounds (row or column variables)
   uint32_t wide;
+  uint32_t slot;              // io words before the second slot
+  uint32_t pad_;
   uint64_t ld;                // table stride, 2^n
   uint32_t* a[1];
   uint32_t* b[kMaxClaims];
   uint32_t* w[kMaxClaims];
   const uint32_t* pt[kMaxClaims];   // the points x_k or y_k, Montgomery (their eq jobs')
-  uint32_t* part;             // sweep partials, 2 K elements per block
-  uint32_t* io;               // [state: 8][running scalars, then sigma: kMaxClaims x 8][r: n_rows x 8] words
+  uint32_t* part;             // round 0's sums, 2 K elements per block
+  uint32_t* io;               // two slots (below)
   uint8_t* proof;             // this phase's proof bytes
   uint8_t* digest;            // phase 2: final state of the reduction's branch
   int32_t* status;            // phase 2: VL_OK when done
 };
-// phase 2 keeps the pending challenge of its wide rounds in the first r slot
-// (phase 1's r has been read by then)
+// io: [state: 8][running scalars, then sigma: kMaxClaims x 8][r: n_rows x 8],
+// then a second slot [state][running scalars][r: 8]; wide round rd leaves its
+// state and scalars in the first for odd rd, in the second for even rd, and phase
+// 2 its challenge too (phase 1's r have been read by then)
 constexpr uint32_t kReduceIoSigma = 8, kReduceIoR = 8 + 8 * kMaxClaims;
-constexpr uint32_t reduce_io_words(uint32_t n_rows) { return kReduceIoR + 8 * (n_rows ? n_rows : 1); }
+constexpr uint32_t reduce_io_slot(uint32_t n_rows) { return kReduceIoR + 8 * (n_rows ? n_rows : 1); }
+constexpr uint32_t reduce_io_words(uint32_t n_rows) { return reduce_io_slot(n_rows) + kReduceIoR + 8; }
 
 // One per-head batched product (vl_bmm_prove): C_h = A_h B_h for h < H as
 // one sumcheck over (head, inner) variables of
@@ -315,7 +324,7 @@ struct LookupSweep {
 hipError_t launch_eval(const EvalJob* jobs_dev, uint32_t n_jobs, hipStream_t s);
 hipError_t launch_reduce(const ReduceJob* jobs_dev, uint32_t n_jobs, hipStream_t s);
 hipError_t launch_reduce_sweep(const ReduceJob* jobs_dev, const MatSweep* list_dev, uint32_t n_list, uint32_t n_blocks,
-                               uint32_t round, hipStream_t s);
+                               uint32_t round, bool step, hipStream_t s);
 hipError_t launch_reduce_step(const ReduceJob* jobs_dev, const MatSweep* list_dev, uint32_t n_list, uint32_t round,
                               hipStream_t s);
 hipError_t launch_eq(const EqJob* jobs_dev, uint32_t n_jobs, uint32_t n_blocks, hipStream_t s);

@@ -644,17 +644,25 @@ __device__ __forceinline__ RedTerm red_term(const Fr (&e)[2], bool fold, const F
   o.val = fr_mul(o.B, o.w);
   return o;
 }
-// Wave 0's state: lane 4 k + x has claim k's running scalar and that times
-// eq1(p_{k,rd}, x).
+// Wave 0's state: lane 4 k + x of each row of 16 has claim k's running scalar
+// and that times eq1(p_{k,rd}, x) (row 2 later on, see red_next).
 struct RedState {
   Fr sc, sce;
 };
-__device__ __forceinline__ uint32_t red_claim(const ReduceJob& J, uint32_t lane) { return min(lane >> 2, J.K - 1); }
+__device__ __forceinline__ uint32_t red_claim(const ReduceJob& J, uint32_t lane) { return min((lane & 15u) >> 2, J.K - 1); }
 __device__ __forceinline__ void red_set_sce(const ReduceJob& J, uint32_t rd, RedState& s, uint32_t lane) {
   if (rd >= J.n) return;
   Fr om, slope;
   s.sce = fr_mul(s.sc, fr_eq1(lds_or_global_fr(J.pt[red_claim(J, lane)] + 8 * rd), lane & 3u, om, slope));
-  if (lane >= 4 * J.K) s.sce = fr_zero();
+  if ((lane & 15u) >= 4 * J.K) s.sce = fr_zero();
+}
+// what round rd starts from (state and running scalars), left by round rd - 1
+// in the slot of its parity, and where round rd leaves its challenge: phase 1
+// keeps them all
+__device__ __forceinline__ uint32_t* red_slot(const ReduceJob& J, uint32_t rd) { return J.io + (rd & 1u ? J.slot : 0u); }
+__device__ __forceinline__ uint32_t* red_r(const ReduceJob& J, uint32_t rd) {
+  if (J.phase == 1) return J.io + kReduceIoR + 8 * rd;
+  return J.io + (rd & 1u ? kReduceIoR : J.slot + kReduceIoR);
 }
 __device__ __forceinline__ void red_load_state(const ReduceJob& J, uint32_t rd, RedState& s, RoundLds& T, uint32_t lane) {
   const uint32_t k = red_claim(J, lane);
@@ -662,41 +670,78 @@ __device__ __forceinline__ void red_load_state(const ReduceJob& J, uint32_t rd, 
 #pragma unroll
     for (int j = 0; j < 8; ++j) s.sc.w[j] = J.coef[k][j];
   } else {
-    s.sc = lds_or_global_fr(J.io + kReduceIoSigma + 8 * k);
+    s.sc = lds_or_global_fr(red_slot(J, rd) + kReduceIoSigma + 8 * k);
   }
-  if (lane < 8) {
-    T.st[lane] = J.phase == 1 && rd == 0 ? J.st[lane] : J.io[lane];
-    T.r[lane] = rd ? J.io[kReduceIoR + 8 * (J.phase == 1 ? rd - 1 : 0) + lane] : 0u;
-  }
+  if (lane < 8) T.st[lane] = J.phase == 1 && rd == 0 ? J.st[lane] : red_slot(J, rd)[lane];
   red_set_sce(J, rd, s, lane);
 }
 __device__ __forceinline__ void red_advance(const ReduceJob& J, uint32_t rd, RedState& s, const RoundLds& T, uint32_t lane) {
   Fr om, slope;
   fr_eq1(lds_or_global_fr(J.pt[red_claim(J, lane)] + 8 * rd), 0, om, slope);
   s.sc = fr_mul(s.sc, fr_add(om, fr_mul(slope, fr_vgpr(lds_get(T.r)))));
-  red_set_sce(J, rd + 1, s, lane);
 }
-// Round rd by wave 0: acc holds the limb sums of the lines at 0 and 1 of every
-// claim.  Lanes 0 .. 2 write g(0), g(1), g(2); absorbed, r squeezed into T.
-__device__ __forceinline__ void red_step(const ReduceJob& J, uint32_t rd, const unsigned long long* acc,
-                                         const RedState& s, RoundLds& T, uint32_t lane) {
-  Fr v = fr_mul(acc_line(acc, 2 * red_claim(J, lane), min(lane & 3u, 2u)), s.sce);
+// lane 4 k + x: claim k's line at x, from its sums at 0 and 1
+__device__ __forceinline__ Fr red_line(const ReduceJob& J, const unsigned long long* acc, uint32_t lane) {
+  return acc_line(acc, 2 * red_claim(J, lane), min(lane & 3u, 2u));
+}
+// Round rd by wave 0, v its lines' values.  Lanes 0 .. 2 write g(0), g(1), g(2);
+// absorbed, r squeezed into T.
+__device__ __forceinline__ void red_step(const ReduceJob& J, uint32_t rd, Fr v, const RedState& s, RoundLds& T,
+                                         uint32_t lane, bool write = true) {
+  v = fr_mul(v, s.sce);
   v = fr_add(fr_add(v, fr_row_shl<4>(v)), fr_add(fr_row_shl<8>(v), fr_row_shl<12>(v)));
   if (lane < 3) {
-    put_canon(J.proof + 96ull * rd + 32 * lane, v);
+    if (write) put_canon(J.proof + 96ull * rd + 32 * lane, v);
     lds_put(T.v + 8 * lane, v);
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   tr_round(T, 3);
 }
+// block b's sums of wide round rd: in part, later in the entries of the first
+// table's first plane that this block, and no other, folds away in that round
+__device__ __forceinline__ uint32_t* red_part(const ReduceJob& J, uint32_t rd, uint32_t b) {
+  if (rd == 0) return J.part + kRedPartWords * b;
+  return (J.phase == 1 ? J.b[0] : J.a[0]) + (2u << (J.n - 1 - rd)) + kRedSweepPairs * b;
+}
+static_assert(kRedPartWords <= kRedSweepPairs, "a block's sums fit its folded entries");
+// round rd's sums into acc (zeroed), one wave each
+__device__ __forceinline__ void red_sum_parts(const ReduceJob& J, uint32_t rd, unsigned long long* acc) {
+  const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
+  const uint32_t nblocks = (1u << (J.n - 1 - rd)) / kRedSweepPairs;
+  if (wave >= 2 * J.K) return;
+  Fr v = fr_zero();
+  for (uint32_t i = lane; i < nblocks; i += 64) v = fr_add(v, ld_rec(red_part(J, rd, i) + 8 * wave));
+  acc_add(acc, wave, v);
+}
+// the step of wide round rd by wave 0; write: by the one workgroup that stores
+// proof bytes and io
+__device__ __forceinline__ void red_wide_step(const ReduceJob& J, uint32_t rd, const unsigned long long* acc, RedState& s,
+                                              RoundLds& T, uint32_t lane, bool write) {
+  red_step(J, rd, red_line(J, acc, lane), s, T, lane, write);
+  if (!write) return;
+  red_advance(J, rd, s, T, lane);
+  uint32_t* io = red_slot(J, rd + 1);
+  if (lane < 8) {
+    io[lane] = T.st[lane];
+    red_r(J, rd)[lane] = T.r[lane];
+  }
+  if ((lane & 3u) == 0 && lane < 4 * J.K)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) io[kReduceIoSigma + 2 * lane + j] = s.sc.w[j];
+}
 
 // One wide round: the listed jobs, kRedSweepPairs pairs per block; the
 // waves take the terms (claim, point) of the pairs in turn.  Tables fold in
 // place: every wave reads its terms' entries before any wave writes.
+// step: every block first takes round rd - 1's transcript step itself, from the
+// previous launch's sums (its first block stores it), so that a round is one
+// launch: 22 us instead of 8.3 and 16.2 for a sweep and a step, while
+// the launch has no more blocks than CUs (kRedMergeBlocks).
 __global__ void __launch_bounds__(2 * kRedSweepPairs * kMaxReduceClaims) reduce_sweep_kernel(
     const ReduceJob* __restrict__ jobs, const MatSweep* __restrict__ list, uint32_t n_list, uint32_t n_blocks,
-    uint32_t rd) {
+    uint32_t rd, uint32_t step) {
   __shared__ unsigned long long acc[20 * kMaxReduceClaims + 10];
+  __shared__ RoundLds T;
   const uint32_t blk = blockIdx.x;
   if (blk >= n_blocks) return;
   uint32_t lo = 0, hi = n_list;
@@ -706,7 +751,7 @@ __global__ void __launch_bounds__(2 * kRedSweepPairs * kMaxReduceClaims) reduce_
   }
   const MatSweep& S = list[lo];
   const ReduceJob& J = jobs[S.job];
-  const uint32_t tid = threadIdx.x, term = tid / kRedSweepPairs, k = term >> 1, pt = term & 1u;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, term = tid / kRedSweepPairs, k = term >> 1, pt = term & 1u;
   const uint64_t ld = J.ld, h = 1ull << (J.n - 1 - rd);   // a multiple of kRedSweepPairs
   const uint64_t t = (uint64_t)(blk - S.block_begin) * kRedSweepPairs + tid % kRedSweepPairs;
   const uint64_t i0 = pt ? t + h : t;
@@ -717,15 +762,24 @@ __global__ void __launch_bounds__(2 * kRedSweepPairs * kMaxReduceClaims) reduce_
   if (mine) {
     tab = J.phase == 1 ? J.b[k] : J.a[0];
     e[0] = load_sol(tab, ld, i0);
-    if (fold) {
-      e[1] = load_sol(tab, ld, i0 + 2 * h);
-      r = lds_or_global_fr(J.io + kReduceIoR + 8 * (J.phase == 1 ? rd - 1 : 0));
-    }
+    if (fold) e[1] = load_sol(tab, ld, i0 + 2 * h);
     w0 = load_sol(J.w[k], ld, t);
     w1 = load_sol(J.w[k], ld, t + h);
   }
   if (tid < 20 * kMaxReduceClaims + 10) acc[tid] = 0;
   __syncthreads();   // everything read (and acc zeroed)
+  if (step) {
+    RedState s;
+    if (tid < 64) red_load_state(J, rd - 1, s, T, lane);
+    red_sum_parts(J, rd - 1, acc);
+    __syncthreads();
+    if (tid < 64) {
+      red_wide_step(J, rd - 1, acc, s, T, lane, blk == S.block_begin);
+      if (lane < 20 * kMaxReduceClaims) acc[lane] = 0;
+    }
+    __syncthreads();
+  }
+  if (fold) r = step ? lds_get(T.r) : lds_or_global_fr(red_r(J, rd - 1));
   if (mine) {
     const RedTerm o = red_term(e, fold, r, w0, w1);
     if (fold && (J.phase == 1 || k == 0)) store_sol(tab, ld, i0, o.B);
@@ -734,126 +788,173 @@ __global__ void __launch_bounds__(2 * kRedSweepPairs * kMaxReduceClaims) reduce_
   }
   __syncthreads();
   if (tid < 64) {
-    const Fr v = acc_line(acc, min(tid, 2 * kMaxReduceClaims - 1), 0);
-    if (tid < 2 * J.K) st_rec(J.part + (uint64_t)(blk - S.block_begin) * kRedPartWords + 8 * tid, v);
+    const Fr v = acc_value(acc, min(tid, 2 * kMaxReduceClaims - 1));
+    if (tid < 2 * J.K) st_rec(red_part(J, rd, blk - S.block_begin) + 8 * tid, v);
   }
 }
 
-// The transcript step after a wide round, one workgroup per job: wave q adds
-// the blocks' value q, wave 0 runs the round's step.
+// The transcript step after a wide round, one workgroup per job, where the next
+// sweep does not take it.
 __global__ void __launch_bounds__(128 * kMaxReduceClaims) reduce_step_kernel(const ReduceJob* __restrict__ jobs,
                                                                             const MatSweep* __restrict__ list,
                                                                             uint32_t rd) {
   __shared__ unsigned long long acc[20 * kMaxReduceClaims + 10];
   __shared__ RoundLds T;
   const ReduceJob& J = jobs[list[blockIdx.x].job];
-  const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = tid & 63u;
-  const uint32_t nblocks = (1u << (J.n - 1 - rd)) / kRedSweepPairs;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u;
   if (tid < 20 * kMaxReduceClaims + 10) acc[tid] = 0;
   RedState s;
-  if (wave == 0) red_load_state(J, rd, s, T, lane);
+  if (tid < 64) red_load_state(J, rd, s, T, lane);
   __syncthreads();
-  if (wave < 2 * J.K) {
-    Fr v = fr_zero();
-    for (uint32_t i = lane; i < nblocks; i += 64) v = fr_add(v, ld_rec(J.part + (uint64_t)kRedPartWords * i + 8 * wave));
-    acc_add(acc, wave, v);
-  }
+  red_sum_parts(J, rd, acc);
   __syncthreads();
-  if (wave != 0) return;
-  red_step(J, rd, acc, s, T, lane);
-  red_advance(J, rd, s, T, lane);
-  if (lane < 8) {
-    J.io[lane] = T.st[lane];
-    J.io[kReduceIoR + 8 * (J.phase == 1 ? rd : 0) + lane] = T.r[lane];
-  }
-  if ((lane & 3u) == 0 && lane < 4 * J.K)
+  if (tid < 64) red_wide_step(J, rd, acc, s, T, lane, true);
+}
+
+// The lines of a later round rd by wave 0 from sums that are linear in
+// r_{rd-1}, T.r (acc: a round's sums with the tables folded by 0, then by 1),
+// and the scalars' next values, side by side: rows 0 and 1 of 16 lanes have the
+// two values, row 2 the scalars.  pts: the claims' points, in LDS.
+constexpr uint32_t kRedAccWords = 20 * kMaxReduceClaims;
+__device__ __forceinline__ Fr fr_lane(const Fr& x, uint32_t l) {
+  Fr r;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) J.io[kReduceIoSigma + 2 * lane + j] = s.sc.w[j];
+  for (int j = 0; j < 8; ++j) r.w[j] = __shfl(x.w[j], (int)l, kWave);
+  return r;
+}
+__device__ __forceinline__ Fr red_next(const ReduceJob& J, const uint32_t (*pts)[32 * 8], uint32_t rd,
+                                       const unsigned long long* acc, RedState& s, const RoundLds& T, uint32_t lane) {
+  const bool scalar = lane >= 32;
+  const Fr v = red_line(J, acc + (lane & 16u ? kRedAccWords : 0), lane);
+  const Fr d = fr_sub(fr_lane(v, lane + 16), v), r = fr_vgpr(lds_get(T.r));
+  const uint32_t k = red_claim(J, lane);
+  Fr om, slope, om2, slope2;
+  fr_eq1(lds_get(pts[k] + 8 * (rd - 1)), 0, om, slope);
+  const Fr e = fr_eq1(lds_get(pts[k] + 8 * rd), lane & 3u, om2, slope2);
+  const Fr m1 = fr_mul(r, fr_pick(scalar, slope, d));
+  s.sc = fr_mul(s.sc, fr_add(om, m1));   // (row 2)
+  s.sce = fr_mul(s.sc, e);
+  if ((lane & 15u) >= 4 * J.K) s.sce = fr_zero();
+  s.sce = fr_lane(s.sce, (lane & 15u) + 32);
+  return fr_add(v, m1);
 }
 
 // The rounds left after the wide ones, one workgroup per job, and the phase's
-// end.  The tables come from global memory until their first fold (at most
-// 2 kRedWidePairs entries then), the weights until their first sums, and live
-// in LDS after that.  The rows of 16 lanes of waves 1 .. 11 take the terms of
-// 16 pairs at a time; wave 0 runs the transcript.  With all rounds in this
-// workgroup, both tables folded and three products a pair, the 7 tensors of
-// the FFN-up layer took 603 and 664 us in the two phases.
-constexpr uint32_t kRedTailWaves = 12;
-static_assert(20 * kMaxReduceClaims <= 64, "one wave zeroes the sums");
+// end.  As in the matmul rounds, waves 1 .. 7 sum round rd + 1, as lines in
+// r_rd, while wave 0 hashes round rd; a job without wide rounds sums its first
+// round before.  Wave 1 + q, 1 + q + 2 K, .. take term q (claim, point), a row
+// of 16 lanes 16 pairs.  The tables come from global memory until their first
+// fold (at most kLen entries then), the weights until their first sums, and
+// live in LDS after that.  With all rounds in this workgroup, both tables
+// folded and three products a pair, the 7 tensors of the FFN-up layer took 603
+// and 664 us in the two phases; with the sums after the hash the rounds from
+// 256 pairs on 160 and 137 us, now 151 and 125.
+constexpr uint32_t kRedTailWaves = 8;
 __global__ void __launch_bounds__(64 * kRedTailWaves) reduce_kernel(const ReduceJob* __restrict__ jobs) {
   const ReduceJob& J = jobs[blockIdx.x];
-  constexpr uint32_t kLen = kRedWidePairs;                                  // entries of the first table buffer
-  __shared__ uint32_t buf[kMaxReduceClaims][8 * (kLen + kLen / 2)];         // tables: two buffers each
-  __shared__ uint32_t wbuf[kMaxReduceClaims][8 * (kLen / 2 + kLen / 4)];    // weights: two buffers each
-  __shared__ unsigned long long acc[20 * kMaxReduceClaims + 10];
+  constexpr uint32_t kLen = kRedWidePairs;                                            // entries of the first table buffer
+  __shared__ alignas(16) uint32_t buf[kMaxReduceClaims][8 * (kLen + kLen / 2)];       // tables: two buffers each
+  __shared__ alignas(16) uint32_t wbuf[kMaxReduceClaims][8 * (kLen / 2 + kLen / 4)];  // weights: two buffers each
+  __shared__ unsigned long long acc_s[2][2 * kRedAccWords];                           // a round's sums, by parity
+  __shared__ uint32_t rbuf[2][8], fin[kMaxReduceClaims][2][8];                        // r_rd by parity; the last pairs
+  __shared__ uint32_t pts[kMaxReduceClaims][32 * 8];
   __shared__ RoundLds T;
   const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = tid & 63u;
   const uint32_t n = J.n, K = J.K, wide = J.wide, phase = J.phase, ntab = phase == 1 ? K : 1;
+  const uint32_t rd0 = wide ? wide - 1 : 0;   // the first round to hash: the last wide one's sums are in its parts
   const uint64_t ld = J.ld;
-  bool pending = wide > 0;
   int at = -1, wat = -1;   // the tables' and the weights' place: -1 global, else buffer 0 or 1
   auto get = [&](uint32_t k, uint32_t i) {
-    if (at >= 0) return load_sol(buf[k] + (at ? 8 * kLen : 0), at ? kLen / 2 : kLen, i);
+    if (at >= 0) return ld_rec(buf[k] + (at ? 8 * kLen : 0) + 8 * i);
     return load_sol(phase == 1 ? J.b[k] : J.a[0], ld, i);
   };
   RedState s;
-  if (wave == 0) red_load_state(J, wide, s, T, lane);
-  if (tid < 20 * kMaxReduceClaims + 10) acc[tid] = 0;
-  __syncthreads();
-#pragma unroll 1
-  for (uint32_t rd = wide; rd < n; ++rd) {
-    const uint32_t h = 1u << (n - 1 - rd);
-    if (wave == 0) {
-      if (rd > wide) red_advance(J, rd - 1, s, T, lane);
-    } else {
-      const uint32_t chunks = (h + 15) / 16, units = 2 * K * chunks;
-      const Fr r = lds_get(T.r);
-#pragma unroll 1
-      for (uint32_t q0 = 4 * (wave - 1); q0 < units; q0 += 4 * (kRedTailWaves - 1)) {
-        const uint32_t q = q0 + (lane >> 4), term = q / chunks, k = term >> 1, pt = term & 1u;
-        const uint32_t t = (q % chunks) * 16 + (lane & 15u), tab = phase == 1 ? k : 0;
-        const bool take = q < units;
-        RedTerm o;
-        o.val = fr_zero();
-        if (take && t < h) {
-          const uint32_t i0 = pt ? t + h : t;
-          Fr e[2], w0, w1;
-          e[0] = get(tab, i0);
-          e[1] = fr_zero();
-          if (pending) e[1] = get(tab, i0 + 2 * h);
-          if (wat >= 0) {
-            const uint32_t* w = wbuf[k] + (wat ? 4 * kLen : 0);
-            w0 = load_sol(w, wat ? kLen / 4 : kLen / 2, t);
-            w1 = load_sol(w, wat ? kLen / 4 : kLen / 2, t + h);
-          } else {
-            w0 = load_sol(J.w[k], ld, t);
-            w1 = load_sol(J.w[k], ld, t + h);
-          }
-          o = red_term(e, pending, r, w0, w1);
-          if (pending && (phase == 1 || k == 0))
-            store_sol(buf[tab] + (at == 0 ? 8 * kLen : 0), at == 0 ? kLen / 2 : kLen, i0, o.B);
-          if (pt == 0)
-            store_sol(wbuf[k] + (wat == 0 ? 4 * kLen : 0), wat == 0 ? kLen / 4 : kLen / 2, t, o.w);
-        }
-        acc_add(acc, term, o.val, take);
-      }
-    }
-    if (pending) at = at == 0 ? 1 : 0;
-    wat = wat == 0 ? 1 : 0;
-    __syncthreads();   // the sums, the folded entries and the next weights
-    if (wave == 0) {
-      red_step(J, rd, acc, s, T, lane);
-      if (lane < 20 * kMaxReduceClaims) acc[lane] = 0;
-      if (phase == 1 && lane < 8) J.io[kReduceIoR + 8 * rd + lane] = T.r[lane];   // Montgomery, for eq(r, .)
-    }
-    __syncthreads();   // r and the zeroed sums
-    pending = true;
+  if (wave == 0) {
+    __builtin_amdgcn_s_setprio(3);   // the transcript's wave goes before those it shares its SIMD with
+    red_load_state(J, rd0, s, T, lane);
   }
-  const Fr r = lds_get(T.r);
+  for (uint32_t i = tid; i < 4 * kRedAccWords; i += 64 * kRedTailWaves) acc_s[i / (2 * kRedAccWords)][i % (2 * kRedAccWords)] = 0;
+  for (uint32_t i = tid; i < 8 * n * K; i += 64 * kRedTailWaves) pts[i / (8 * n)][i % (8 * n)] = J.pt[i / (8 * n)][i % (8 * n)];
+  __syncthreads();
+  if (wide) red_sum_parts(J, rd0, acc_s[rd0 & 1]);
+  __syncthreads();
+  // rd: the round to hash; tl: the tables' round so far; ready: rd's sums are there
+  uint32_t rd = rd0, tl = rd0;
+  bool ready = wide > 0;
+#pragma unroll 1
+  while (rd < n) {
+    const bool poly = ready;   // sums of round nx in the challenge r_{nx-1} of the hash at hand
+    const uint32_t nx = ready ? rd + 1 : rd, to = ready ? rd : nx;
+    const bool fold = tl < to;
+    if (wave == 0) {
+      if (ready) {
+        unsigned long long* const cur = acc_s[rd & 1];
+        const Fr v = rd > rd0 ? red_next(J, pts, rd, cur, s, T, lane) : red_line(J, cur, lane);
+        red_step(J, rd, v, s, T, lane);
+#pragma unroll
+        for (uint32_t i = lane; i < 2 * kRedAccWords; i += kWave) cur[i] = 0;
+        if (lane < 8) {
+          rbuf[rd & 1][lane] = T.r[lane];
+          if (phase == 1) J.io[kReduceIoR + 8 * rd + lane] = T.r[lane];   // Montgomery, for eq(r, .)
+        }
+      }
+    } else if (nx < n) {
+      const uint32_t h = 1u << (n - 1 - nx), far = poly ? 4 * h : 2 * h;
+      const uint32_t groups = (kRedTailWaves - 1) / (2 * K), g = (wave - 1) / (2 * K), term = (wave - 1) % (2 * K);
+      const uint32_t k = term >> 1, pt = term & 1u, tab = phase == 1 ? k : 0, chunks = (h + 15) / 16;
+      const Fr r = lds_get(rbuf[~to & 1]);
+      Fr sum[2];
+      sum[0] = sum[1] = fr_zero();
+#pragma unroll 1
+      for (uint32_t ch = 4 * g + (lane >> 4); g < groups && ch < chunks; ch += 4 * groups) {
+        const uint32_t t = ch * 16 + (lane & 15u), i0 = pt ? t + h : t;
+        if (t >= h) continue;
+        auto entry = [&](uint32_t off) {
+          Fr x = get(tab, i0 + off);
+          if (fold) {
+            x = fr_fold(r, x, get(tab, i0 + off + far));
+            if (phase == 1 || k == 0) st_rec(buf[tab] + (at == 0 ? 8 * kLen : 0) + 8 * (i0 + off), x);
+          }
+          return x;
+        };
+        const Fr e0 = entry(0);
+        Fr w0, w1;
+        if (wat >= 0) {
+          const uint32_t* w = wbuf[k] + (wat ? 4 * kLen : 0);
+          w0 = ld_rec(w + 8 * t);
+          w1 = ld_rec(w + 8 * (t + h));
+        } else {
+          w0 = load_sol(J.w[k], ld, t);
+          w1 = load_sol(J.w[k], ld, t + h);
+        }
+        const Fr w = fr_add(w0, w1), v0 = fr_mul(e0, w);
+        if (pt == 0) st_rec(wbuf[k] + (wat == 0 ? 4 * kLen : 0) + 8 * t, w);
+        sum[0] = fr_add(sum[0], v0);
+        sum[1] = fr_add(sum[1], poly ? fr_mul(entry(2 * h), w) : v0);
+      }
+      if (g < groups && 4 * g < chunks) {
+        acc_add(acc_s[nx & 1], term, sum[0]);
+        acc_add(acc_s[nx & 1] + kRedAccWords, term, sum[1]);
+      }
+    } else if (fold && tid < kWave + 2 * ntab) {   // the last pair of each table
+      const uint32_t k = lane >> 1, i = lane & 1u;
+      lds_put(fin[k][i], fr_fold(lds_get(rbuf[~to & 1]), get(k, i), get(k, i + 2)));
+    }
+    if (nx < n) {
+      if (fold) at = at == 0 ? 1 : 0;
+      tl = to;
+      wat = wat == 0 ? 1 : 0;
+    }
+    rd += ready ? 1 : 0;
+    ready = true;
+    __syncthreads();   // r, the sums, the folded entries and the next weights
+  }
   if (wave != 0) return;
   // lane k < ntab: the last challenge folds the remaining pair of table k
-  Fr mine = get(min(lane, ntab - 1), 0);
-  if (pending) mine = fr_fold(r, mine, get(min(lane, ntab - 1), 1));
+  const uint32_t k1 = min(lane, ntab - 1);
+  const bool two = n > 0 && tl + 1 < n;   // the last fold is in fin
+  Fr mine = two ? lds_get(fin[k1][0]) : get(k1, 0);
+  if (n) mine = fr_fold(lds_get(T.r), mine, two ? lds_get(fin[k1][1]) : get(k1, 1));
   if (phase == 2) mine = fr_from_mont(mine);
   if (lane < ntab) {
     put_canon(J.proof + 96ull * n + 32 * lane, mine);
@@ -989,10 +1090,10 @@ hipError_t launch_reduce(const ReduceJob* jobs, uint32_t n_jobs, hipStream_t s) 
 }
 
 hipError_t launch_reduce_sweep(const ReduceJob* jobs, const MatSweep* list, uint32_t n_list, uint32_t n_blocks,
-                               uint32_t round, hipStream_t s) {
+                               uint32_t round, bool step, hipStream_t s) {
   if (n_blocks == 0) return hipSuccess;
   hipLaunchKernelGGL(reduce_sweep_kernel, dim3(n_blocks), dim3(2 * kRedSweepPairs * kMaxReduceClaims), 0, s, jobs, list,
-                     n_list, n_blocks, round);
+                     n_list, n_blocks, round, step ? 1u : 0u);
   return hipGetLastError();
 }
 

@@ -1,5 +1,6 @@
 """Chained layers whose claim reductions change route (row and column tables
-around 2^9 and 2^10 entries, tables of one entry), byte for byte against the
+around 2^8 to 2^10 entries, tables of one entry, and 2^16 entries, whose steps
+are launches of their own), byte for byte against the
 oracle."""
 import pytest
 
@@ -17,7 +18,8 @@ class _Dev:
         self.F, self.eta = w.F, w.eta
 
 
-@pytest.mark.parametrize("T,d_in,d_out,r", [(1, 1, 1, 1), (2, 512, 3, 1), (513, 3, 2, 2), (5, 2, 1025, 3)])
+@pytest.mark.parametrize("T,d_in,d_out,r", [(1, 1, 1, 1), (2, 512, 3, 1), (513, 3, 2, 2), (5, 2, 1025, 3), (257, 2, 256, 1),
+                                           (1, 1, 65535, 1)])
 def test_routes_match_oracle(T, d_in, d_out, r):
     from paper_2508_21393_amd import binding as B
     w = workloads.tiny_layer(T + d_in, T, d_in, d_out, r)
