@@ -133,13 +133,14 @@ __device__ __forceinline__ const uint32_t* lk_row(const LookupJob& J, uint64_t i
   return J.rec + 16 * (uint64_t)j;
 }
 
-// v += {h(0), h(1), h2} of one product of lines, weighted: w x0 y0, w x1 y1,
-// w (x1 - x0)(y1 - y0)
+// v += {h(0), h(1), h2} of one product of lines, weighted: (w x0) y0, (w x1) y1,
+// (w x1 - w x0)(y1 - y0), five products
 __device__ __forceinline__ void lk_weighted(const Fr& w, const Fr& x0, const Fr& x1, const Fr& y0, const Fr& y1,
                                             Fr (&v)[5]) {
-  v[0] = fr_add(v[0], fr_mul(w, fr_mul(x0, y0)));
-  v[1] = fr_add(v[1], fr_mul(w, fr_mul(x1, y1)));
-  v[2] = fr_add(v[2], fr_mul(w, fr_mul(fr_sub(x1, x0), fr_sub(y1, y0))));
+  const Fr w0 = fr_mul(w, x0), w1 = fr_mul(w, x1);
+  v[0] = fr_add(v[0], fr_mul(w0, y0));
+  v[1] = fr_add(v[1], fr_mul(w1, y1));
+  v[2] = fr_add(v[2], fr_mul(fr_sub(w1, w0), fr_sub(y1, y0)));
 }
 
 // One of the nine terms of a pair in a low round: product `role` (0: A Sb,
@@ -460,7 +461,9 @@ __global__ void __launch_bounds__(64) lookup_start_kernel(const LookupJob* __res
 //             h(0) = h(1) = 1 because A Sb = 1 at every entry: 2 products a pair
 //   kSecond   round 1: the four entries looked up, folded by r_0 and stored
 //   kFold     later rounds: folded in place (each thread reads and writes
-//             only its own entries): 10 products a pair
+//             only its own entries): 9 products a pair (262 and 149 us for the
+//             largest kSecond and kFold sweeps of 2^23 entries with 10, now 243 and
+//             145)
 //   kPlain    round 0 of stored tables
 enum { kFirst = 0, kSecond = 1, kFold = 2, kPlain = 3 };
 template <int MODE>
