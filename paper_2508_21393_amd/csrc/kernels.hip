@@ -611,16 +611,6 @@ __global__ void __launch_bounds__(256) eval_kernel(const EvalJob* __restrict__ j
   }
 }
 
-// absorb(label, x_0 .. x_{K-1}) for a run-time K <= kMaxReduceClaims
-template <int LN>
-__device__ __forceinline__ void absorb_k(Transcript& tr, const char (&label)[LN], const Fr* xs, uint32_t K) {
-  switch (K) {
-    case 1: { const Fr a[1] = {xs[0]}; tr_absorb_frs(tr, label, a); break; }
-    case 2: { const Fr a[2] = {xs[0], xs[1]}; tr_absorb_frs(tr, label, a); break; }
-    default: { const Fr a[3] = {xs[0], xs[1], xs[2]}; tr_absorb_frs(tr, label, a); break; }
-  }
-}
-
 // Claim reductions (ReduceJob).  Both phases are sumchecks of
 //     sum_k s_k sum_t eq(p_k, t) B_k(t),
 // B_k = t_k in phase 1 and the one table M~(r, .) in phase 2.  The challenges
@@ -848,7 +838,7 @@ __device__ __forceinline__ Fr red_next(const ReduceJob& J, const uint32_t (*pts)
 // live in LDS after that.  With all rounds in this workgroup, both tables
 // folded and three products a pair, the 7 tensors of the FFN-up layer took 603
 // and 664 us in the two phases; with the sums after the hash the rounds from
-// 256 pairs on 160 and 137 us, now 151 and 125.
+// 256 pairs on 160 and 137 us, now 140 and 124.
 constexpr uint32_t kRedTailWaves = 8;
 __global__ void __launch_bounds__(64 * kRedTailWaves) reduce_kernel(const ReduceJob* __restrict__ jobs) {
   const ReduceJob& J = jobs[blockIdx.x];
@@ -963,23 +953,13 @@ __global__ void __launch_bounds__(64 * kRedTailWaves) reduce_kernel(const Reduce
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   if (phase == 1) {
     // t_k(r) sent and absorbed ("rfinal"); sigma_1 .. sigma_K squeezed for phase 2
-    if (lane == 0) {
-      Transcript tr;
-      Fr fin[kMaxReduceClaims];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) tr.h[j] = T.st[j];
-#pragma unroll
-      for (uint32_t k = 0; k < kMaxReduceClaims; ++k) fin[k] = lds_get(T.v + 8 * k);
-      absorb_k(tr, VL_LBL_RFINAL, fin, K);
+    tr_absorb_lanes(T, kLblRfinal4, kLblRfinal2, (int)K);
 #pragma unroll 1
-      for (uint32_t k = 0; k < K; ++k) {
-        const Fr sg = fr_to_mont(tr_squeeze_fixed(tr, VL_LBL_SIGMA));
-#pragma unroll
-        for (int j = 0; j < 8; ++j) J.io[kReduceIoSigma + 8 * k + j] = sg.w[j];
-      }
-#pragma unroll
-      for (int j = 0; j < 8; ++j) J.io[j] = tr.h[j];
+    for (uint32_t k = 0; k < K; ++k) {
+      tr_squeeze_lanes(T, kLblSigma4, kLblSigma1);
+      if (lane < 8) J.io[kReduceIoSigma + 8 * k + lane] = T.r[lane];
     }
+    if (lane < 8) J.io[lane] = T.st[lane];
     return;
   }
   tr_absorb_lanes(T, kLblFinal4, kLblFinal1, 1);

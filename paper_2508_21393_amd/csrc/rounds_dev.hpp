@@ -281,19 +281,21 @@ __device__ __forceinline__ uint32_t sha_s0(uint32_t x) { return xor3v(rotv(x, 7)
 __device__ __forceinline__ uint32_t sha_s1(uint32_t x) { return xor3v(rotv(x, 17), rotv(x, 19), x >> 10); }
 #define VL_SHA_IV {0x6a09e667u, 0xbb67ae85u, 0x3c6ef372u, 0xa54ff53au, 0x510e527fu, 0x9b05688cu, 0x1f83d9abu, 0x5be0cd19u}
 
-// Word `lane` of the padded message state || five-letter label || K values,
-// written to T.w by each lane (K <= 5: at most four blocks): the label's first
-// four letters are word 8, its last one the top byte of word 9, so word i >= 9
-// holds the last byte of value word i - 10 and the first three of i - 9.  A
-// four-letter label (label1 = 0) leaves whole words.
+// Word `lane` of the padded message state || label || K values, written to T.w by
+// each lane (K <= 5: at most four blocks).  The label's first four letters are
+// word 8; up to two more (label2, below 256 for one) begin word 9, so word i >=
+// 9 holds the last bytes of value word i - 10 and the first ones of i - 9.
 // Returns the number of blocks.
-__device__ __forceinline__ uint32_t tr_message(RoundLds& T, uint32_t label4, uint32_t label1, int K) {
-  const int N = 32 + (label1 ? 5 : 4) + 32 * K, NB = (N + 9 + 63) / 64;
-  auto word = [&](int d) -> uint32_t { return d < 8 * K ? T.v[d < 0 ? 0 : d] : (d == 8 * K ? 0x80u : 0u); };
+__device__ __forceinline__ uint32_t tr_message(RoundLds& T, uint32_t label4, uint32_t label2, int K) {
+  const int n = label2 == 0 ? 0 : (label2 < 256 ? 1 : 2);
+  const int N = 32 + 4 + n + 32 * K, NB = (N + 9 + 63) / 64;
+  auto word = [&](int d) -> uint32_t {
+    const uint32_t x = d < 8 * K ? T.v[d < 0 ? 0 : d] : (d == 8 * K ? 0x80u : 0u);
+    return __builtin_amdgcn_perm(x, x, 0x00010203u);
+  };
   const int i = (int)(threadIdx.x & 63u);
-  const uint32_t lo = word(i - 9), hi = i >= 10 ? word(i - 10) : label1 << 24;
-  uint32_t m = (hi & 0xff000000u) | ((lo & 0xffu) << 16) | (lo & 0xff00u) | ((lo >> 16) & 0xffu);
-  if (!label1) m = __builtin_amdgcn_perm(lo, lo, 0x00010203u);   // a four-letter label: no shift
+  const uint32_t lo = word(i - 9), hi = i >= 10 ? word(i - 10) : label2;
+  uint32_t m = __builtin_amdgcn_alignbit(hi, lo, 8 * n);
   if (i < 8) m = T.st[i & 7];
   if (i == 8) m = label4;
   if (i == 16 * NB - 1) m = N * 8;
@@ -364,64 +366,132 @@ __device__ __forceinline__ void sha_next_pair(uint32_t (&p)[8], uint32_t (&q)[8]
   q[i] = sha_to_even(0u, p[i]);   // its odd lanes: with the pair after
 }
 
-// absorb(label, x_0 .. x_{K-1}) for a label of four or five letters by all 64 lanes of one
+// One block on the lanes' own schedules (small code: 16 rounds and 16 words in a
+// loop): w0, p and q as for sha_next_pair, h the chaining value.
+__device__ __forceinline__ void sha_block_lanes(const ShaLane& L, uint32_t w0, uint32_t (&p)[8], uint32_t (&q)[8],
+                                                uint32_t (&h)[4]) {
+  const uint32_t* KK = sha256_k();
+  uint32_t s[4], kk[16];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) s[j] = h[j];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) kk[i] = KK[i];
+#pragma unroll 1
+  for (int it = 0; it < 4; ++it) {
+    uint32_t w[16], u;
+    w[0] = w0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      w[2 * k + 1] = p[k];
+      if (k < 7) w[2 * k + 2] = q[k];
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) w[i] += kk[i];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) kk[i] = KK[(16 * it + 16 + i) & 63];   // on their way during the rounds
+    __builtin_amdgcn_sched_barrier(0);
+    u = L.odd ? s[3] + w[0] : 0u;
+#pragma unroll
+    for (int i = 0; i < 16; i += 4) sha_four(s, u, L, w[i + 1], w[i + 2], w[i + 3], w[(i + 4) & 15]);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      sha_next_pair(p, q, i);
+      if (i == 0) w0 = q[7];
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) h[j] += s[j];
+}
+
+// absorb(label, x_0 .. x_{K-1}) for a label of four to six letters by all 64 lanes of one
 // wave, the K <= 5 canonical values in T.v: one block after the other, every
 // lane pair the same (once or twice per proof, so small code counts: it is
 // fetched for one pass)
-constexpr uint32_t kLblFinal4 = 0x66696e61u, kLblFinal1 = 0x6cu;   // "fina", "l"
-constexpr uint32_t kLblPart4 = 0x70617274u;                        // "part"
-constexpr uint32_t kLblClaim4 = 0x636c6169u, kLblClaim1 = 0x6du;   // "clai", "m"
-__device__ __forceinline__ void tr_absorb_lanes(RoundLds& T, uint32_t label4, uint32_t label1, int K) {
+constexpr uint32_t kLblFinal4 = 0x66696e61u, kLblFinal1 = 0x6cu;     // "fina", "l"
+constexpr uint32_t kLblPart4 = 0x70617274u;                          // "part"
+constexpr uint32_t kLblClaim4 = 0x636c6169u, kLblClaim1 = 0x6du;     // "clai", "m"
+constexpr uint32_t kLblRfinal4 = 0x7266696eu, kLblRfinal2 = 0x616cu; // "rfin", "al"
+constexpr uint32_t kLblSigma4 = 0x7369676du, kLblSigma1 = 0x61u;     // "sigm", "a"
+__device__ __forceinline__ void tr_absorb_lanes(RoundLds& T, uint32_t label4, uint32_t label2, int K) {
   const uint32_t lane = threadIdx.x & 63u;
-  const uint32_t NB = tr_message(T, label4, label1, K);
+  const uint32_t NB = tr_message(T, label4, label2, K);
   const ShaLane L = sha_lane(lane);
   constexpr uint32_t iv[8] = VL_SHA_IV;
   uint32_t h[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) h[j] = L.odd ? iv[4 + j] : iv[j];
-  const uint32_t* KK = sha256_k();
 #pragma unroll 1
   for (uint32_t b = 0; b < NB; ++b) {
-    uint32_t w0 = T.w[16 * b], p[8], q[8], s[4];
+    uint32_t p[8], q[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
       p[k] = T.w[16 * b + 2 * k + L.odd];
-      q[k] = T.w[(16 * b + 2 * k + 1 + L.odd) & 63];   // (word 16 of the last one follows below)
+      q[k] = T.w[(16 * b + 2 * k + 1 + L.odd) & 63];   // (word 16 of the last one follows in the block)
     }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) s[j] = h[j];
-    uint32_t kk[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) kk[i] = KK[i];
-#pragma unroll 1
-    for (int it = 0; it < 4; ++it) {
-      uint32_t w[16], u;
-      w[0] = w0;
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        w[2 * k + 1] = p[k];
-        if (k < 7) w[2 * k + 2] = q[k];
-      }
-#pragma unroll
-      for (int i = 0; i < 16; ++i) w[i] += kk[i];
-#pragma unroll
-      for (int i = 0; i < 16; ++i) kk[i] = KK[(16 * it + 16 + i) & 63];   // on their way during the rounds
-      __builtin_amdgcn_sched_barrier(0);
-      u = L.odd ? s[3] + w[0] : 0u;
-#pragma unroll
-      for (int i = 0; i < 16; i += 4) sha_four(s, u, L, w[i + 1], w[i + 2], w[i + 3], w[(i + 4) & 15]);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        sha_next_pair(p, q, i);
-        if (i == 0) w0 = q[7];
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) h[j] += s[j];
+    sha_block_lanes(L, T.w[16 * b], p, q, h);
   }
   if ((lane & ~4u) == 0)
 #pragma unroll
     for (int j = 0; j < 4; ++j) T.st[lane + j] = h[j];
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+// the eight words of a pair's digest in its odd lane, read as a candidate
+__device__ __forceinline__ Fr sha_candidate(const uint32_t (&h)[4], uint32_t (&g)[8]) {
+  Fr x;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    g[j] = sha_to_odd(0u, h[j]);
+    g[4 + j] = h[j];
+  }
+#pragma unroll
+  for (int j = 0; j < 8; ++j) x.w[j] = __builtin_amdgcn_perm(g[j], g[j], 0x00010203u);
+  x.w[7] &= 0x7fffffffu;
+  return x;
+}
+// the counter that a lane's pair squeezes with
+__device__ __forceinline__ uint32_t sha_counter(uint32_t lane) {
+  return (lane >> 4) * 8 + ((lane >> 3) & 1u) * 4 + (lane & 3u);
+}
+// squeeze(label) for a five-letter label by all 64 lanes of one wave: the new
+// state in T.st, the element in Montgomery form in T.r; 32 counters at a time,
+// of which one in ten is rejected
+__device__ __forceinline__ void tr_squeeze_lanes(RoundLds& T, uint32_t label4, uint32_t label1) {
+  const uint32_t lane = threadIdx.x & 63u;
+  const ShaLane L = sha_lane(lane);
+  constexpr uint32_t iv[8] = VL_SHA_IV;
+  uint64_t ok = 0;
+  uint32_t g[8];
+  Fr x;
+#pragma unroll 1
+  for (uint32_t base = 0; ok == 0; base += 32) {
+    const uint32_t c = base + sha_counter(lane);
+    // word 8: label4, 9: the last letter and the counter's low bytes (below 2^16), 10: padding
+    const uint32_t w9 = (label1 << 24) | ((c & 0xffu) << 16) | (c & 0xff00u), bits = 41 * 8;
+    uint32_t p[8], q[8], h[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      p[k] = T.st[2 * k + L.odd];
+      q[k] = k < 3 ? T.st[2 * k + 1 + L.odd] : (L.odd ? label4 : T.st[7]);
+    }
+    p[4] = L.odd ? w9 : label4;
+    q[4] = L.odd ? 0x00800000u : w9;
+    p[5] = L.odd ? 0u : 0x00800000u;
+    q[5] = p[6] = q[6] = 0u;
+    p[7] = L.odd ? bits : 0u;
+    q[7] = bits;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) h[j] = L.odd ? iv[4 + j] : iv[j];
+    sha_block_lanes(L, T.st[0], p, q, h);
+    x = sha_candidate(h, g);
+    ok = __ballot(L.odd && fr_lt_p(x));
+  }
+  const Fr xm = fr_to_mont(x);
+  if (lane == (uint32_t)__builtin_ctzll(ok))
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      T.st[j] = g[j];
+      T.r[j] = xm.w[j];
+    }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 }
 // the state as 32 digest bytes, by one lane
@@ -505,17 +575,8 @@ __device__ __forceinline__ void tr_round(RoundLds& T, int K) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) T.st[j] = d[j];
     } else {
-      // the candidate's eight words to the odd lane
       uint32_t g[8];
-      Fr x;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        g[j] = sha_to_odd(0u, h[j]);
-        g[4 + j] = h[j];
-      }
-#pragma unroll
-      for (int j = 0; j < 8; ++j) x.w[j] = __builtin_amdgcn_perm(g[j], g[j], 0x00010203u);
-      x.w[7] &= 0x7fffffffu;
+      const Fr x = sha_candidate(h, g);
       const uint64_t ok = __ballot(L.odd && fr_lt_p(x));
       if (ok) {
         const Fr xm = fr_to_mont(x);
@@ -533,7 +594,7 @@ __device__ __forceinline__ void tr_round(RoundLds& T, int K) {
       for (int j = 0; j < 8; ++j) d[j] = T.st[j];
     }
     // state || "r", the counter (below 2^16) || padding
-    const uint32_t c = base + (lane >> 4) * 8 + ((lane >> 3) & 1u) * 4 + (lane & 3u);
+    const uint32_t c = base + sha_counter(lane);
     d[8] = 0x72000000u | ((c & 0xffu) << 16) | (c & 0xff00u);
     w0 = d[0];
 #pragma unroll
