@@ -301,10 +301,9 @@ __device__ __forceinline__ Fq fq_mul_dev(const Fq& a, const Fq& b) {
   return fq_reduce_once(fl_pack(fl_mul(fl_split<8>(a.w), fl_split<0>(b.w))));
 }
 
-// one out-of-line copy for the code outside the commitment loop (setup,
-// reductions, normalisation): inlining every product there makes the kernels
-// many times larger and slow to compile; the loop's mixed addition inlines
-// its products (g1_add_affine_inl)
+// one out-of-line copy for the code outside the commitment kernels (generators
+// and tables): inlining every product there makes the kernels many times larger
+// and slow to compile
 __device__ __noinline__ Fq fq_mul_call(const Fq& a, const Fq& b) { return fq_mul_dev(a, b); }
 #else
 // host: CIOS on 6 64-bit limbs
