@@ -163,11 +163,6 @@ __global__ void __launch_bounds__(256) bmm_start_kernel(const BmmJob* __restrict
   }
 }
 
-// block b's three sums of wide round rd: in part, later in the entries of a's
-// first plane that this block, and no other, folds away in that round
-__device__ __forceinline__ uint32_t* bmm_part(const BmmJob& J, uint32_t rd, uint64_t b) {
-  return rd == 0 ? J.part + 24 * b : J.a + (2ull << (J.nh + J.n1 - 1 - rd)) + kBmmSweepPairs * b;
-}
 // round rd's sums into acc (zeroed), by waves 0 .. 2
 __device__ __forceinline__ void bmm_sum_parts(const BmmJob& J, uint32_t rd, unsigned long long* acc) {
   const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;

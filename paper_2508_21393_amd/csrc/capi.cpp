@@ -958,6 +958,14 @@ bool plan_forks(const Plan& P) {
   return false;
 }
 
+static size_t lookups_at(const Plan& P, int kd, size_t k) { return k < P.lk_wide[kd].size() ? P.lk_wide[kd][k].size() : 0; }
+
+bool lookup_merged(const Plan& P, size_t k) {
+  size_t before = 0;
+  for (int kd = 0; kd < LK_KINDS; ++kd) before += k ? lookups_at(P, kd, k - 1) : 0;
+  return before && lookups_at(P, LK_LOW, k) == before && P.lk_wide_blocks[LK_LOW][k] <= kLookupMergeBlocks;
+}
+
 // whether a plan holds lookups alone
 static bool lookups_only(const Plan& P) {
   if (P.lookups.empty() || !P.bmms.empty() || !P.evals.empty() || !P.reduces.empty()) return false;
@@ -1167,20 +1175,12 @@ hipError_t enqueue_plan(const Plan& P, const BlobLayout& L, uint8_t* dblob, hipS
     }
     size_t nk = 0;
     for (const auto& w : P.lk_wide) nk = std::max(nk, w.size());
-    auto jobs_at = [&](int kd, size_t k) { return k < P.lk_wide[kd].size() ? P.lk_wide[kd][k].size() : 0; };
-    // whether round k's low sweep takes round k - 1's step: for all of that
-    // round's jobs or none
-    auto merged = [&](size_t k) {
-      size_t before = 0;
-      for (int kd = 0; kd < LK_KINDS; ++kd) before += k ? jobs_at(kd, k - 1) : 0;
-      return k > 0 && jobs_at(LK_LOW, k) == before && before && P.lk_wide_blocks[LK_LOW][k] <= kLookupMergeBlocks;
-    };
     for (size_t k = 0; k < nk; ++k)
       for (int kd = 0; kd < LK_KINDS; ++kd) {
-        if (jobs_at(kd, k) == 0) continue;
-        const bool step = kd == LK_LOW && merged(k);
+        if (lookups_at(P, kd, k) == 0) continue;
+        const bool step = kd == LK_LOW && lookup_merged(P, k);
         if (kd != LK_FIRST) VL_STAGE(ev, step ? VL_STAGE_ROUNDS : VL_STAGE_PASS1, s, sweep(kd, k, step));
-        if (!merged(k + 1))
+        if (!lookup_merged(P, k + 1))
           VL_STAGE(ev, VL_STAGE_ROUNDS, s,
                    launch_lookup_step(lj, reinterpret_cast<const LookupSweep*>(dblob + L.lk_wide[kd][k]),
                                       (uint32_t)P.lk_wide[kd][k].size(), (uint32_t)k, s));

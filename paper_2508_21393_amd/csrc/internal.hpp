@@ -320,6 +320,33 @@ struct LookupSweep {
   uint32_t block_begin;
 };
 
+// Where block b of wide round rd leaves its sums.  A sweep that takes the step
+// of round rd - 1 itself has every block read that round's sums while others
+// may already be storing their own, so the two rounds' places are apart: from
+// the first fold on, a round's sums lie in the entries of a table's first
+// plane (or records) that its block b, and no other, folds away in it, which
+// the next round leaves alone.
+inline __host__ __device__ uint32_t* mat_part(const RoundsJob& J, uint32_t rd, uint32_t b) {   // rd >= 1
+  return J.prods[0].a + (2ull << (J.prods[0].n1 - 1 - rd)) + (uint64_t)kMatSweepPairs * b;
+}
+inline __host__ __device__ uint32_t* red_part(const ReduceJob& J, uint32_t rd, uint32_t b) {
+  if (rd == 0) return J.part + kRedPartWords * b;
+  return (J.phase == 1 ? J.b[0] : J.a[0]) + (2u << (J.n - 1 - rd)) + kRedSweepPairs * b;
+}
+static_assert(kRedPartWords <= kRedSweepPairs, "a block's sums fit its folded entries");
+inline __host__ __device__ uint32_t* bmm_part(const BmmJob& J, uint32_t rd, uint64_t b) {
+  return rd == 0 ? J.part + 24 * b : J.a + (2ull << (J.nh + J.n1 - 1 - rd)) + kBmmSweepPairs * b;
+}
+// (a lookup's first low round folds no records: its sums go behind those of the
+// last high round, which its sweep reads)
+inline __host__ __device__ uint64_t lk_part_block(uint32_t n, uint32_t nH, uint32_t rd, uint64_t b) {   // rd <= nH
+  return b + (rd == nH && rd > 0 ? lk_round_blocks(n, nH, rd - 1) : 0u);
+}
+inline __host__ __device__ uint32_t* lk_part(const LookupJob& J, uint32_t rd, uint64_t b) {
+  if (rd <= J.nH) return J.part + kLookupPartWords * lk_part_block(J.nH + J.nL, J.nH, rd, b);
+  return J.rec + 16 * ((2ull << (J.nH + J.nL - 1 - rd)) + kLookupLowPairs * b);
+}
+
 // host launchers (kernels.hip)
 hipError_t launch_eval(const EvalJob* jobs_dev, uint32_t n_jobs, hipStream_t s);
 hipError_t launch_reduce(const ReduceJob* jobs_dev, uint32_t n_jobs, hipStream_t s);

@@ -173,11 +173,6 @@ __device__ __forceinline__ void mat_sum_first(const RoundsJob& J, unsigned long 
     acc_add(acc, v, x);
   }
 }
-// partials of wide round rd: block b's three sums lie in the entries of a~'s
-// first plane that this block, and no other, folds away in that round
-__device__ __forceinline__ uint32_t* mat_part(const RoundsJob& J, uint32_t rd, uint32_t b) {
-  return J.prods[0].a + (2ull << (J.prods[0].n1 - 1 - rd)) + (uint64_t)kMatSweepPairs * b;
-}
 // sums of wide round rd >= 1 into acc's round values, by waves 0 .. 2
 __device__ __forceinline__ void mat_sum_wide(const RoundsJob& J, uint32_t rd, unsigned long long* acc) {
   const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
@@ -687,13 +682,6 @@ __device__ __forceinline__ void red_step(const ReduceJob& J, uint32_t rd, Fr v, 
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   tr_round(T, 3);
 }
-// block b's sums of wide round rd: in part, later in the entries of the first
-// table's first plane that this block, and no other, folds away in that round
-__device__ __forceinline__ uint32_t* red_part(const ReduceJob& J, uint32_t rd, uint32_t b) {
-  if (rd == 0) return J.part + kRedPartWords * b;
-  return (J.phase == 1 ? J.b[0] : J.a[0]) + (2u << (J.n - 1 - rd)) + kRedSweepPairs * b;
-}
-static_assert(kRedPartWords <= kRedSweepPairs, "a block's sums fit its folded entries");
 // round rd's sums into acc (zeroed), one wave each
 __device__ __forceinline__ void red_sum_parts(const ReduceJob& J, uint32_t rd, unsigned long long* acc) {
   const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;

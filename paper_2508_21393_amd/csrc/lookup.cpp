@@ -172,8 +172,8 @@ void plan_lookup(Builder& B, const vl_lookup& L, const LookupChallenges& ch, uin
   j.mult_begin = B.P.lk_mult_blocks;
   B.P.lk_mult_blocks += j.nkparts;
   if (wide) {
-    uint32_t nb = 0;
-    for (uint32_t k = 0; k < wide; ++k) nb = std::max(nb, lk_round_blocks(n, nH, k));
+    uint64_t nb = 0;
+    for (uint32_t k = 0; k < wide && k <= nH; ++k) nb = std::max(nb, lk_part_block(n, nH, k, lk_round_blocks(n, nH, k)));
     j.part = B.dev<uint32_t>(B.take(4ull * kLookupPartWords * nb));
   }
   const uint32_t idx = (uint32_t)B.P.lookups.size();

@@ -525,15 +525,9 @@ __global__ void __launch_bounds__(256) lookup_sweep_kernel(const LookupJob* __re
   }
   Fr hi = fr_R();
   if (m > nlo) hi = load_sol(J.EH + 8 * ((1ull << (m - nlo)) - 1), 1ull << (m - nlo), base >> nlo);
-  lk_block_out(v, m > nlo ? &hi : nullptr, J.part + (uint64_t)(blk - L.block_begin) * kLookupPartWords);
+  lk_block_out(v, m > nlo ? &hi : nullptr, lk_part(J, rd, blk - L.block_begin));
 }
 
-// block b's sums of wide round rd: in part, in low rounds after the first in the
-// row records that this block, and no other, folds away in that round
-__device__ __forceinline__ uint32_t* lk_part(const LookupJob& J, uint32_t rd, uint64_t b) {
-  if (rd <= J.nH) return J.part + kLookupPartWords * b;
-  return J.rec + 16 * ((2ull << (J.nH + J.nL - 1 - rd)) + kLookupLowPairs * b);
-}
 // round rd's nine sums into acc (zeroed), one wave each
 __device__ __forceinline__ void lk_sum_parts(const LookupJob& J, uint32_t rd, unsigned long long* acc) {
   const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;

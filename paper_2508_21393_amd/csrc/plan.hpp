@@ -155,6 +155,9 @@ BlobLayout blob_layout(const Plan& P);
 uint64_t blob_bound(const vl_group* groups, uint64_t n);
 void fill_blob(Plan& P, const BlobLayout& L, uint8_t* dblob);
 void set_eq_points(Plan& P, const BlobLayout& L, uint8_t* dblob);
+// whether the lookups' low sweep of round k takes round k - 1's step: for all
+// of that round's jobs or none
+bool lookup_merged(const Plan& P, size_t k);
 // HIP events around every launch (blocking mode timing); one pair per
 // launch, summed per stage after the call's streams are synchronised.
 struct StageEvents {
