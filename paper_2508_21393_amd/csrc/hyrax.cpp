@@ -41,6 +41,7 @@ vl_status check_setup(uint32_t m, uint32_t W) {
 
 struct Split {
   uint32_t n_split, chunk;
+  uint32_t lanes;   // lanes that share a slice (1, or a power of two in 4 .. 64)
 };
 
 // the slices' sums and, for more than kHyraxMaxFinal of them, the runs' sums
@@ -51,22 +52,33 @@ uint64_t partial_bytes(uint32_t R, const Split& s) {
 
 // split given: that many slices of a multiple of 64 columns.  Otherwise
 // enough slices of at least kMinSlice columns to fill the GPU with one lane
-// per (row, slice), as far as `room` bytes of workspace hold them.
+// per (row, slice), as far as `room` bytes of workspace hold their sums.
 Split plan_split(uint32_t R, uint32_t m, uint32_t split, uint64_t room = UINT64_MAX) {
-  Split s;
-  if (split) {
-    const uint64_t n = std::min<uint64_t>(split, (m + 63) / 64);
-    s.chunk = (uint32_t)align_up((m + n - 1) / n, 64);
+  auto cut = [&](uint64_t n, uint64_t unit) {
+    Split s;
+    s.chunk = (uint32_t)align_up((m + n - 1) / n, unit);
     s.n_split = (uint32_t)((m + s.chunk - 1) / s.chunk);
+    s.lanes = 1;
     return s;
-  }
+  };
   uint64_t n = std::min<uint64_t>((kTargetLanes + R - 1) / R, (m + kMinSlice - 1) / kMinSlice);
-  for (;; n = n * 7 / 8) {
-    n = std::max<uint64_t>(n, 1);
-    s.chunk = (uint32_t)((m + n - 1) / n);
-    s.n_split = (uint32_t)((m + s.chunk - 1) / s.chunk);
-    if (n == 1 || partial_bytes(R, s) <= room) return s;
+  const Split full = cut(n, 1);
+  Split s = full;
+  if (split) {
+    s = cut(std::min<uint64_t>(split, (m + 63) / 64), 64);
+  } else {
+    while (n > 1 && partial_bytes(R, s) > room) s = cut(n = std::max<uint64_t>(1, n * 7 / 8), 1);
   }
+  // Far fewer slices than the full plan: as many lanes in all as it has, those
+  // of a slice added within their workgroup.  4096 x 4096 int16 in one slice 46
+  // ms on one lane each and 3.0 on 32, in 8 slices 6.1 and 3.0; with half the
+  // slices of the full plan the additions within the workgroup cost more than
+  // the shorter chains give (2048 x 1000: 0.65 ms on one lane, 0.75 on four).
+  if (3 * s.n_split < full.n_split) {
+    s.lanes = 4;   // a quad adds the sums of four lanes at the least
+    while (s.lanes < 64 && (uint64_t)s.n_split * s.lanes < full.n_split) s.lanes *= 2;
+  }
+  return s;
 }
 
 // the least workspace a call is accepted with: slices of 256 columns, as
@@ -229,8 +241,9 @@ vl_status vl_hyrax_commit(const void* M, int32_t dtype, uint32_t R, uint32_t m, 
                 (unsigned long long)workspace_bytes, (unsigned long long)need);
   const Split s = plan_split(R, m, split, workspace_bytes);
   hipError_t e = launch_hyrax_commit(M, dtype, ld, R, m, windows, reinterpret_cast<const uint32_t*>(table), s.n_split,
-                                     s.chunk, reinterpret_cast<uint32_t*>(workspace),
-                                     partial_bytes(R, s) <= workspace_bytes, reinterpret_cast<uint32_t*>(commits), reinterpret_cast<hipStream_t>(stream));
+                                     s.chunk, s.lanes, reinterpret_cast<uint32_t*>(workspace),
+                                     partial_bytes(R, s) <= workspace_bytes, reinterpret_cast<uint32_t*>(commits),
+                                     reinterpret_cast<hipStream_t>(stream));
   if (e != hipSuccess) return fail(VL_ERR_HIP, "hyrax commit: %s", hipGetErrorString(e));
   return VL_OK;
 }

@@ -344,7 +344,7 @@ struct NonzeroTerms {
   T vn;                   // entry t + 1
 
   __device__ __forceinline__ T load(uint32_t k) const {
-    return row[j0 + min(k, cnt - 1)];   // clamped: always in the slice
+    return row[j0 + min(k, max(cnt, 1u) - 1)];   // clamped: always in the slice
   }
   __device__ __forceinline__ void init(const T* r, uint32_t j0_, uint32_t cnt_) {
     row = r; j0 = j0_; cnt = cnt_; t = 0; w = 0; c = 0;
@@ -387,21 +387,13 @@ struct NonzeroTerms {
 // cross-lane step.  With a wave per (row, slice), 32-bit limbs and carries
 // (about 7900 instructions an addition and a butterfly over the lanes) a
 // 4096 x 4096 int16 commitment took 4.82 ms, with this 2.99 ms.
-template <typename T>
-__global__ void __launch_bounds__(256, 2) hyrax_commit_kernel(const T* __restrict__ M, uint64_t ld, uint32_t R,
-                                                              uint32_t m, uint32_t W,
-                                                              const uint32_t* __restrict__ table, uint32_t n_split,
-                                                              uint32_t chunk, uint32_t* partials) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  const uint64_t task = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-  if (task >= (uint64_t)R * n_split) return;
-  const uint32_t sl = (uint32_t)(task / R), i = (uint32_t)(task % R);
-  const uint32_t jb = sl * chunk;
-  const uint32_t cnt = min(chunk, m - jb);
+template <typename T>
+__device__ __forceinline__ G1l slice_sum(const T* row, uint32_t jb, uint32_t cnt, uint32_t W,
+                                         const uint32_t* __restrict__ table) {
   const uint32_t* safe = table + table_index(jb, W, 0, 1);
-
   NonzeroTerms<T> ts;
-  ts.init(M + (uint64_t)i * ld, jb, cnt);
+  ts.init(row, jb, cnt);
   int dn = 0;
   uint32_t jn = 0, wn = 0;
   bool have = ts.next(dn, jn, wn);
@@ -421,7 +413,51 @@ __global__ void __launch_bounds__(256, 2) hyrax_commit_kernel(const T* __restric
       g1l_madd(acc, x, y);
     }
   }
-  store_l(partials + task * kZWords, acc);
+  return acc;
+}
+#endif
+
+template <typename T>
+__global__ void __launch_bounds__(256, 2) hyrax_commit_kernel(const T* __restrict__ M, uint64_t ld, uint32_t R,
+                                                              uint32_t m, uint32_t W,
+                                                              const uint32_t* __restrict__ table, uint32_t n_split,
+                                                              uint32_t chunk, uint32_t* partials) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const uint64_t task = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+  if (task >= (uint64_t)R * n_split) return;
+  const uint32_t sl = (uint32_t)(task / R), i = (uint32_t)(task % R);
+  const uint32_t jb = sl * chunk;
+  store_l(partials + task * kZWords, slice_sum(M + (uint64_t)i * ld, jb, min(chunk, m - jb), W, table));
+#endif
+}
+
+// The same for slices shared by `lanes` lanes (a power of two in 4 .. 64),
+// where the caller's split or workspace gives too few slices to fill the GPU: a
+// workgroup has 256 / lanes rows, whose lanes' sums it adds by quads through
+// LDS (64 lanes: three additions a quad, then four levels over the quads).
+// Bound like the kernel above: 16 x 11008 in one slice 2.2 ms, 119 on one lane
+// each; 4096 x 4096 in a workspace for one slice 3.3 ms, 46 on one lane each.
+template <typename T>
+__global__ void __launch_bounds__(256, 2) hyrax_commit_cut_kernel(const T* __restrict__ M, uint64_t ld, uint32_t R,
+                                                                  uint32_t m, uint32_t W,
+                                                                  const uint32_t* __restrict__ table, uint32_t chunk,
+                                                                  uint32_t lanes, uint32_t* partials) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __shared__ alignas(16) uint32_t sums[256 * kZWords];
+  const uint32_t rows = 256 / lanes, groups = (R + rows - 1) / rows;
+  const uint32_t sl = blockIdx.x / groups, i0 = blockIdx.x % groups * rows;
+  const uint32_t jb = sl * chunk, len = min(chunk, m - jb), per = (len + lanes - 1) / lanes;
+  const uint32_t part = threadIdx.x / rows, i = i0 + threadIdx.x % rows;   // neighbouring lanes: rows
+  const uint32_t j0 = part * per, cnt = i < R && j0 < len ? min(per, len - j0) : 0;
+  // (a lane without entries is given the slice's first one, of which it takes none)
+  const G1l acc = slice_sum(M + (uint64_t)min(i, R - 1) * ld, cnt ? jb + j0 : jb, cnt, W, table);
+  store_l(sums + threadIdx.x * kZWords, acc);
+  __syncthreads();
+  const uint32_t G = lanes / 4, wrows = 16 / G;   // quads per row, rows per wave
+  const uint32_t wave = threadIdx.x >> 6, qd = (threadIdx.x >> 2) & 15u, q = threadIdx.x & 3u, gl = qd / wrows;
+  const uint32_t row = wave * wrows + qd % wrows;
+  const Fl sum = sum_slices(sums, rows, row, 0, lanes, gl, G, 4 * wrows);
+  if (gl == 0 && i0 + row < R) store_fl(partials + ((uint64_t)sl * R + i0 + row) * kZWords + 12 * q, sum);
 #endif
 }
 
@@ -486,23 +522,23 @@ hipError_t launch_hyrax_setup(uint32_t m, uint32_t W, uint32_t* table, hipStream
 }
 
 hipError_t launch_hyrax_commit(const void* M, int dtype, uint64_t ld, uint32_t R, uint32_t m, uint32_t W,
-                               const uint32_t* table, uint32_t n_split, uint32_t chunk, uint32_t* partials,
-                               bool with_runs, uint32_t* commits, hipStream_t s) {
-  const uint64_t tasks = (uint64_t)R * n_split;
-  const uint32_t blocks = (uint32_t)((tasks + 255) / 256);
+                               const uint32_t* table, uint32_t n_split, uint32_t chunk, uint32_t lanes,
+                               uint32_t* partials, bool with_runs, uint32_t* commits, hipStream_t s) {
+  auto commit = [&](auto* src) {
+    using T = std::remove_const_t<std::remove_pointer_t<decltype(src)>>;
+    if (lanes == 1) {
+      const uint64_t tasks = (uint64_t)R * n_split;
+      hipLaunchKernelGGL(hyrax_commit_kernel<T>, dim3((uint32_t)((tasks + 255) / 256)), dim3(256), 0, s, src, ld, R, m, W,
+                         table, n_split, chunk, partials);
+    } else {
+      hipLaunchKernelGGL(hyrax_commit_cut_kernel<T>, dim3(blocks_for(R, 256 / lanes) * n_split), dim3(256), 0, s, src, ld,
+                         R, m, W, table, chunk, lanes, partials);
+    }
+  };
   switch (dtype) {
-    case VL_I16:
-      hipLaunchKernelGGL(hyrax_commit_kernel<int16_t>, dim3(blocks), dim3(256), 0, s,
-                         reinterpret_cast<const int16_t*>(M), ld, R, m, W, table, n_split, chunk, partials);
-      break;
-    case VL_I32:
-      hipLaunchKernelGGL(hyrax_commit_kernel<int32_t>, dim3(blocks), dim3(256), 0, s,
-                         reinterpret_cast<const int32_t*>(M), ld, R, m, W, table, n_split, chunk, partials);
-      break;
-    default:
-      hipLaunchKernelGGL(hyrax_commit_kernel<int64_t>, dim3(blocks), dim3(256), 0, s,
-                         reinterpret_cast<const int64_t*>(M), ld, R, m, W, table, n_split, chunk, partials);
-      break;
+    case VL_I16: commit(reinterpret_cast<const int16_t*>(M)); break;
+    case VL_I32: commit(reinterpret_cast<const int32_t*>(M)); break;
+    default: commit(reinterpret_cast<const int64_t*>(M)); break;
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

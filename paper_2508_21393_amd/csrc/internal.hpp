@@ -397,8 +397,8 @@ hipError_t launch_lookup_rounds(const LookupJob* jobs_dev, uint32_t n_jobs, hipS
 constexpr uint32_t kHyraxRun = 128, kHyraxMaxFinal = 256;
 hipError_t launch_hyrax_setup(uint32_t m, uint32_t W, uint32_t* table, hipStream_t s);
 hipError_t launch_hyrax_commit(const void* M, int dtype, uint64_t ld, uint32_t R, uint32_t m, uint32_t W,
-                               const uint32_t* table, uint32_t n_split, uint32_t chunk, uint32_t* partials,
-                               bool with_runs, uint32_t* commits, hipStream_t s);
+                               const uint32_t* table, uint32_t n_split, uint32_t chunk, uint32_t lanes,
+                               uint32_t* partials, bool with_runs, uint32_t* commits, hipStream_t s);
 // bytes (a multiple of 16, both pointers 16-byte aligned) from pinned host
 // memory, given by its device-side address
 hipError_t launch_copy_in(void* dst, const void* src_dev, uint64_t bytes, hipStream_t s);
