@@ -282,6 +282,43 @@ VL_HD Fr fr_mul(const Fr& a, const Fr& b) {
 VL_HD Fr fr_to_mont(const Fr& a) { return fr_mul(a, fr_R2()); }
 VL_HD Fr fr_from_mont(const Fr& a) { return fr_mul(a, fr_one_raw()); }
 
+// limb sums t_i (i < 10, weight 2^(26 i), signed, total in [0, 2^272)) mod p
+VL_HD Fr fr_of_limb_sums(const uint64_t (&t)[10]) {
+  uint32_t l[11];
+  int64_t c = 0;
+#pragma unroll
+  for (int i = 0; i < 10; ++i) {
+    c += (int64_t)t[i];
+    l[i] = (uint32_t)c & 0x3ffffffu;
+    c >>= 26;
+  }
+  l[10] = (uint32_t)c;
+  uint32_t w[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    const int bit = 32 * k, i = bit / 26, sh = bit - 26 * i;
+    uint32_t v = l[i] >> sh;
+    if (i + 1 < 11) v |= l[i + 1] << (26 - sh);
+    if (i + 2 < 11 && 52 - sh < 32) v |= l[i + 2] << (52 - sh);
+    w[k] = v;
+  }
+  // T = floor(total / 2^240) below 2^32 times floor(2^286 / p), over 2^46:
+  // total / p less T 2^240 / p is below 2^240 / p < 2^-14, and the rounded
+  // constant takes at most T / 2^46 < 2^-14 more, so the quotient is exact or
+  // one too small
+  const uint32_t q = (uint32_t)(((uint64_t)((w[8] << 16) | (w[7] >> 16)) * 2371102011u) >> 46);
+  Fr r;
+  uint64_t m = 0;
+  uint32_t borrow = 0;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    m += (uint64_t)q * p_limb(k);
+    r.w[k] = sbb32(w[k], (uint32_t)m, borrow, borrow);
+    m >>= 32;
+  }
+  return fr_reduce_once(r);
+}
+
 // canonical little-endian 32-byte encoding
 VL_HD void fr_to_bytes(const Fr& a, uint8_t* out) {
 #pragma unroll

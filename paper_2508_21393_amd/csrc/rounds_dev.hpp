@@ -48,40 +48,6 @@ __device__ __forceinline__ void wave_add10(uint32_t (&x)[10]) {   // the wave's 
   VL_DPP_LEVEL(0x143, 0xc, false)
 }
 #undef VL_DPP_LEVEL
-// limb sums t_i (i < 10, weight 2^(26 i), signed, total in [0, 2^272)) mod p
-__device__ __forceinline__ Fr fr_of_limb_sums(const uint64_t (&t)[10]) {
-  uint32_t l[11];
-  int64_t c = 0;
-#pragma unroll
-  for (int i = 0; i < 10; ++i) {
-    c += (int64_t)t[i];
-    l[i] = (uint32_t)c & 0x3ffffffu;
-    c >>= 26;
-  }
-  l[10] = (uint32_t)c;
-  uint32_t w[9];
-#pragma unroll
-  for (int k = 0; k < 9; ++k) {
-    const int bit = 32 * k, i = bit / 26, sh = bit - 26 * i;
-    uint32_t v = l[i] >> sh;
-    if (i + 1 < 11) v |= l[i + 1] << (26 - sh);
-    if (i + 2 < 11 && 52 - sh < 32) v |= l[i + 2] << (52 - sh);
-    w[k] = v;
-  }
-  // p / 2^240 is between 29677 and 29678: the quotient by the top words is
-  // exact or one too small
-  const uint32_t q = ((w[8] << 16) | (w[7] >> 16)) / 29678u;
-  Fr r;
-  uint64_t m = 0;
-  uint32_t borrow = 0;
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    m += (uint64_t)q * p_limb(k);
-    r.w[k] = sbb32(w[k], (uint32_t)m, borrow, borrow);
-    m >>= 32;
-  }
-  return fr_reduce_once(r);
-}
 // Value sums of a workgroup whose rows of 16 lanes each hold one value: acc
 // holds ten 64-bit limb sums per value (zeroed and read between barriers).
 // acc_add adds the row's 16 elements to value k (the same in the row's lanes)
