@@ -62,11 +62,62 @@ VL_HD void divsteps30(int32_t& delta, uint32_t f, uint32_t g, int32_t (&t)[4]) {
   t[3] = (int32_t)r;
 }
 
+// The multiple k of M that makes 2^30 divide u d + v e + k M and keeps the
+// quotient short: first M towards zero for d and for e (by their signs neg_d,
+// neg_e), which takes values in [-3 M / 2, 3 M / 2] into [-M, M], then a
+// centred multiple in [-2^29, 2^29).  As |u| + |v| <= 2^30, the quotient is in
+// [-3 M / 2, 3 M / 2] again.  low: limb 0 of u d + v e.
+template <typename Mod>
+VL_HD int64_t modinv_multiple(int32_t u, int32_t v, bool neg_d, bool neg_e, uint32_t low) {
+  const int32_t back = (neg_d ? u : -u) + (neg_e ? v : -v);   // at most 2^30
+  low += (uint32_t)back * Mod::limb(0);
+  return (int64_t)back + ((int32_t)((0u - low * Mod::inv30) << 2) >> 2);
+}
+
+// A batch's matrix applied to f, g (divided by 2^30, exactly for the batch's own
+// matrix) and to d, e (divided by 2^30 mod M)
+template <typename Mod>
+VL_HD void modinv_apply(const int32_t (&t)[4], int32_t (&f)[Mod::L], int32_t (&g)[Mod::L], int32_t (&d)[Mod::L],
+                        int32_t (&e)[Mod::L]) {
+  constexpr int L = Mod::L;
+  constexpr int32_t kM = 0x3fffffff;
+  const int64_t u = t[0], v = t[1], q = t[2], r = t[3];
+  int64_t cf = u * f[0] + v * g[0], cg = q * f[0] + r * g[0];
+  int64_t cd = u * d[0] + v * e[0], ce = q * d[0] + r * e[0];
+  const bool nd = d[L - 1] < 0, ne = e[L - 1] < 0;
+  const int64_t kd = modinv_multiple<Mod>(t[0], t[1], nd, ne, (uint32_t)cd);
+  const int64_t ke = modinv_multiple<Mod>(t[2], t[3], nd, ne, (uint32_t)ce);
+  cd += kd * (int32_t)Mod::limb(0);
+  ce += ke * (int32_t)Mod::limb(0);
+  cf >>= 30;
+  cg >>= 30;
+  cd >>= 30;
+  ce >>= 30;
+#pragma unroll
+  for (int i = 1; i < L; ++i) {   // below 5 2^59 + a carry: at most 2^60 of each pair of products, 3 2^59 of k m
+    const int64_t m = (int32_t)Mod::limb(i);
+    cf += u * f[i] + v * g[i];
+    cg += q * f[i] + r * g[i];
+    cd += u * d[i] + v * e[i] + kd * m;
+    ce += q * d[i] + r * e[i] + ke * m;
+    f[i - 1] = (int32_t)cf & kM;
+    g[i - 1] = (int32_t)cg & kM;
+    d[i - 1] = (int32_t)cd & kM;
+    e[i - 1] = (int32_t)ce & kM;
+    cf >>= 30;
+    cg >>= 30;
+    cd >>= 30;
+    ce >>= 30;
+  }
+  f[L - 1] = (int32_t)cf;
+  g[L - 1] = (int32_t)cg;
+  d[L - 1] = (int32_t)cd;
+  e[L - 1] = (int32_t)ce;
+}
+
 // Mod: L 30-bit limbs, limb(i), inv30 = M^-1 mod 2^30, kBatches (the bound
 // above).  x: limbs of a value in (0, 2 M) prime to M.  Returns d = x^-1 mod M
-// in (-2 M, 2 M) as 30-bit limbs with a signed top limb (d stays below M after
-// every batch in a model run of random and extreme inputs, and |d| grows by at
-// most M / 2 a batch in any case, far below 2^(30 L)).  x = 0 gives 0.
+// in [-3 M / 2, 3 M / 2] as 30-bit limbs with a signed top limb.  x = 0 gives 0.
 template <typename Mod>
 VL_HD void modinv30(const int32_t (&x)[Mod::L], int32_t (&out)[Mod::L]) {
   constexpr int L = Mod::L;
@@ -89,38 +140,7 @@ VL_HD void modinv30(const int32_t (&x)[Mod::L], int32_t (&out)[Mod::L]) {
     int32_t t[4];
     // 32-bit low words: limb 0 and the low bits of limb 1
     divsteps30(delta, (uint32_t)f[0] | ((uint32_t)f[1] << 30), (uint32_t)g[0] | ((uint32_t)g[1] << 30), t);
-    const int64_t u = t[0], v = t[1], q = t[2], r = t[3];
-    int64_t cf = u * f[0] + v * g[0], cg = q * f[0] + r * g[0];
-    int64_t cd = u * d[0] + v * e[0], ce = q * d[0] + r * e[0];
-    // the multiples of M, in [-2^29, 2^29), that make 2^30 divide
-    const int64_t kd = (int32_t)((0u - (uint32_t)cd * Mod::inv30) << 2) >> 2;
-    const int64_t ke = (int32_t)((0u - (uint32_t)ce * Mod::inv30) << 2) >> 2;
-    cd += kd * (int32_t)Mod::limb(0);
-    ce += ke * (int32_t)Mod::limb(0);
-    cf >>= 30;
-    cg >>= 30;
-    cd >>= 30;
-    ce >>= 30;
-#pragma unroll
-    for (int i = 1; i < L; ++i) {
-      const int64_t m = (int32_t)Mod::limb(i);
-      cf += u * f[i] + v * g[i];
-      cg += q * f[i] + r * g[i];
-      cd += u * d[i] + v * e[i] + kd * m;
-      ce += q * d[i] + r * e[i] + ke * m;
-      f[i - 1] = (int32_t)cf & kM;
-      g[i - 1] = (int32_t)cg & kM;
-      d[i - 1] = (int32_t)cd & kM;
-      e[i - 1] = (int32_t)ce & kM;
-      cf >>= 30;
-      cg >>= 30;
-      cd >>= 30;
-      ce >>= 30;
-    }
-    f[L - 1] = (int32_t)cf;
-    g[L - 1] = (int32_t)cg;
-    d[L - 1] = (int32_t)cd;
-    e[L - 1] = (int32_t)ce;
+    modinv_apply<Mod>(t, f, g, d, e);
   }
   // f = +-1: the inverse is d or -d
   const bool neg = f[L - 1] < 0;
@@ -156,7 +176,7 @@ VL_HD void limbs30_to_words(const int32_t (&l)[L], uint32_t (&w)[W]) {
   }
 }
 
-// x + 2 M with carries passed on: brings an inverse into (0, 4 M)
+// x + 2 M with carries passed on: brings an inverse into [M / 2, 7 M / 2]
 template <typename Mod>
 VL_HD void add_2m30(int32_t (&x)[Mod::L]) {
   uint32_t carry = 0;
