@@ -86,6 +86,10 @@ constexpr uint32_t kMatSweepPairs = 128;
 // (a wide round of 512 pairs takes 20 us, in one workgroup about 23; one of
 // 256 there 17 to 19)
 constexpr uint32_t kMatWidePairs = 512;
+// rounds of at most this many pairs are summed ahead of their challenge in the
+// rounds workgroup (of two products of 4096 inner entries the second takes 150
+// us with 256 here and 175 with 512; longer rounds three times as long ahead)
+constexpr uint32_t kMatAhead = 256;
 constexpr uint32_t kMatLds = 512;             // entries of the rounds workgroup's LDS tables
 constexpr uint32_t kMatMaxWide = 16;          // n1 <= 20 needs at most 11
 constexpr uint32_t kMatIoState = 8, kMatIoR = 24, kMatIoWords = 48;

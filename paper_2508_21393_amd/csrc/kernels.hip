@@ -383,6 +383,10 @@ __global__ void __launch_bounds__(kPass1Block) pass1_kernel(const Pass1Job* __re
 // values in one thread (the leading one first, which reads all entries);
 // shorter ones are folded from one LDS buffer into the other and a pair's
 // values go to different waves.
+// That is 21 products a pair of round rd + 1.  Rounds of more than kMatAhead
+// pairs (persistent mode, and the later products of a sum) would outlast the
+// hash with it: their tables fold after the hash of round rd, 7 products a
+// pair on all waves (2^18 inner entries in one workgroup: 2.8 ms, all ahead 7.4).
 // Bound by the hash (7.9 of about 10.7 us a round).  With the sums after
 // the hash a round took 13 us, before that, with sums by lane shuffles, the
 // squeeze and claims on one lane and 183 KB of code, 18, and 30 with 42 groups
@@ -475,22 +479,24 @@ __global__ void __launch_bounds__(kRoundsBlock) rounds_kernel(const RoundsJob* _
       if (at >= 0) return ld_rec(buf[k] + (at ? 8 * kMatLds : 0) + 8 * i);
       return load_sol(k ? gb : ga, ld, i);
     };
+    bool fold = false;   // the sums of the round at hand are quadratics; the tables are a round behind
 #pragma unroll 1
     for (uint32_t rd = rd0; rd < n1; ++rd) {
+      const uint32_t h = rd + 1 < n1 ? 1u << (n1 - 2 - rd) : 0;   // pairs of round rd + 1
+      const bool ahead = h <= kMatAhead;
       unsigned long long* const cur = acc + 10 * (kMatAccNext + kMatAccNextLen * (rd & 1));
       unsigned long long* const nxt = acc + 10 * (kMatAccNext + kMatAccNextLen * (~rd & 1));
-      const bool fold = rd > rd0;
       // the last round's tables are one pair each, in fin
-      const bool lds = fold && rd + 1 < n1 && (2u << (n1 - 1 - rd)) <= kMatLds;
+      const bool lds = fold && h && 4 * h <= kMatLds;
       if (wave == 0) {
         // (one call: its code is large)
         mat_round(fold ? cur : acc, fold ? 0 : (rd == 0 ? kMatAccProd + 3 * p : kMatAccRound), out + 96ull * rd, T, true,
                   fold);
 #pragma unroll
         for (uint32_t i = lane; i < 10 * kMatAccNextLen; i += kWave) cur[i] = 0;
+        if (!ahead && lane < 30) acc[10 * kMatAccRound + lane] = 0;
         if (lane < 8) rbuf[rd & 1][lane] = T.r[lane];
-      } else if (rd + 1 < n1) {
-        const uint32_t h = 1u << (n1 - 2 - rd);   // pairs of round rd + 1
+      } else if (h && ahead) {
         const Fr r = lds_get(rbuf[~rd & 1]);
         const bool split = lds || !fold;   // a pair's values on different waves
         constexpr uint32_t kWaves = kRoundsBlock / kWave - 1, kPtWaves = kWaves / 3;
@@ -549,6 +555,35 @@ __global__ void __launch_bounds__(kRoundsBlock) rounds_kernel(const RoundsJob* _
       }
       if (lds) at = at == 0 ? 1 : 0;
       __syncthreads();   // r_rd, round rd + 1's sums, the folded entries
+      if (!ahead) {
+        const Fr r = lds_get(rbuf[rd & 1]);
+        // the values at 0 and 1 of all pairs, then the leading coefficients from
+        // the folded entries (small code: three products)
+#pragma unroll 1
+        for (uint32_t pt = 0; pt < 3; ++pt) {
+          Fr sum = fr_zero();
+#pragma unroll 1
+          for (uint32_t t = tid; t < h; t += kRoundsBlock) {
+            const uint32_t i = pt ? t + h : t, i2 = pt < 2 ? i + 2 * h : t;
+            Fr A = load_sol(ga, ld, i), B = load_sol(gb, ld, i);
+            const Fr dA = fr_sub(load_sol(ga, ld, i2), A), dB = fr_sub(load_sol(gb, ld, i2), B);
+            if (pt < 2) {
+              A = fr_add(A, fr_mul(r, dA));
+              B = fr_add(B, fr_mul(r, dB));
+              store_sol(ga, ld, i, A);
+              store_sol(gb, ld, i, B);
+            } else {
+              A = dA;   // (both differences negated)
+              B = dB;
+            }
+            sum = fr_add(sum, fr_mul(A, B));
+          }
+          acc_add(acc, kMatAccRound + pt, sum);
+        }
+        __threadfence_block();
+        __syncthreads();   // round rd + 1's sums and tables
+      }
+      fold = ahead;
     }
     // lane k < 2 of wave 0: the final value of table k, the last challenge
     // folding the remaining pair; a~ out of Montgomery form
