@@ -697,7 +697,7 @@ void Builder::group(const vl_group& g, const Challenges& ch, uint8_t* proof_dev,
       m.block_begin = G.wide_blocks[rd];
       G.wide[rd].push_back(m);
       if (rd > 0)
-        G.wide_blocks[rd] += (uint32_t)((1ull << (n1w - 1 - rd)) / kMatSweepPairs);
+        G.wide_blocks[rd] += (1u << (n1w - 1 - rd)) / mat_span(1u << (n1w - 1 - rd));
     }
   }
   // persistent mode: one resident launch for every group (segment 0's list)

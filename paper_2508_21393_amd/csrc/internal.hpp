@@ -82,13 +82,21 @@ struct RoundsProd {
 // zeros): [0] status, [8..23] transcript state after round k in slot k & 1,
 // [24..39] r_k in slot k & 1 (Montgomery).  The partials lie in entries of the
 // a~ table that the round folds away (mat_part).
-constexpr uint32_t kMatSweepPairs = 128;
+constexpr uint32_t kMatSweepPairs = 128;      // pairs that a sweep block takes at a time
+// blocks of a wide round at the most: every block takes the transcript step, so
+// beyond one per CU they take more pairs each (2^20 inner entries: the first
+// sweeps with 2048, 1024 and 512 blocks 224, 105 and 49 us, so 71, 38 and 28)
+constexpr uint32_t kMatSweepBlocks = 256;
+inline __host__ __device__ uint32_t mat_span(uint32_t pairs) {   // pairs per block (pairs: a power of two)
+  const uint32_t s = pairs / kMatSweepBlocks;
+  return s < kMatSweepPairs ? kMatSweepPairs : s;
+}
 // (a wide round of 512 pairs takes 20 us, in one workgroup about 23; one of
 // 256 there 17 to 19)
 constexpr uint32_t kMatWidePairs = 512;
 // rounds of at most this many pairs are summed ahead of their challenge in the
-// rounds workgroup (of two products of 4096 inner entries the second takes 150
-// us with 256 here and 175 with 512; longer rounds three times as long ahead)
+// rounds workgroup (two products of 4096 inner entries: 415 us with 256 here,
+// 441 with 512; much longer rounds three times as long ahead)
 constexpr uint32_t kMatAhead = 256;
 constexpr uint32_t kMatLds = 512;             // entries of the rounds workgroup's LDS tables
 constexpr uint32_t kMatMaxWide = 16;          // n1 <= 20 needs at most 11
@@ -331,7 +339,8 @@ struct LookupSweep {
 // plane (or records) that its block b, and no other, folds away in it, which
 // the next round leaves alone.
 inline __host__ __device__ uint32_t* mat_part(const RoundsJob& J, uint32_t rd, uint32_t b) {   // rd >= 1
-  return J.prods[0].a + (2ull << (J.prods[0].n1 - 1 - rd)) + (uint64_t)kMatSweepPairs * b;
+  const uint32_t h = 1u << (J.prods[0].n1 - 1 - rd);
+  return J.prods[0].a + 2ull * h + (uint64_t)mat_span(h) * b;
 }
 inline __host__ __device__ uint32_t* red_part(const ReduceJob& J, uint32_t rd, uint32_t b) {
   if (rd == 0) return J.part + kRedPartWords * b;

@@ -177,7 +177,7 @@ __device__ __forceinline__ void mat_sum_first(const RoundsJob& J, unsigned long 
 __device__ __forceinline__ void mat_sum_wide(const RoundsJob& J, uint32_t rd, unsigned long long* acc) {
   const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
   if (wave >= 3) return;
-  const uint32_t nb = (1u << (J.prods[0].n1 - 1 - rd)) / kMatSweepPairs;
+  const uint32_t h = 1u << (J.prods[0].n1 - 1 - rd), nb = h / mat_span(h);
   Fr x = fr_zero();
   for (uint32_t i = lane; i < nb; i += kWave) x = fr_add(x, ld_rec(mat_part(J, rd, i) + 8 * wave));
   acc_add(acc, kMatAccRound + wave, x);
@@ -229,8 +229,8 @@ __device__ __forceinline__ void mat_round(const unsigned long long* acc, uint32_
   tr_round(T, 3);
 }
 
-// Wide round rd >= 1 of product 0 across the GPU, kMatSweepPairs pairs per
-// block.  Wave 0 of every block first takes round rd - 1's transcript step
+// Wide round rd >= 1 of product 0 across the GPU, mat_span pairs per block,
+// kMatSweepPairs at a time.  Wave 0 of every block first takes round rd - 1's transcript step
 // (round 0: also the statement) from the previous launch's sums, so no block
 // waits for another and a round is one launch; only the job's first block
 // stores proof bytes and io.  Then each thread folds by r_{rd-1} and takes the
@@ -266,19 +266,23 @@ __global__ void __launch_bounds__(3 * kMatSweepPairs) mat_sweep_kernel(const Rou
   }
   const RoundsProd& P = J.prods[0];
   const uint64_t ld = P.ld;
-  const uint32_t h = 1u << (P.n1 - 1 - rd);   // a multiple of kMatSweepPairs
-  const uint32_t t = (blk - S.block_begin) * kMatSweepPairs + tid % kMatSweepPairs;
-  const uint32_t i0 = pt == 1 ? t + h : t;
+  const uint32_t h = 1u << (P.n1 - 1 - rd), span = mat_span(h);   // h is a multiple of span, span of kMatSweepPairs
+  uint32_t t = (blk - S.block_begin) * span + tid % kMatSweepPairs;
+  const uint32_t end = (blk - S.block_begin + 1) * span;
   Fr ea[2], eb[2];
+  auto load = [&]() {
+    const uint32_t i0 = pt == 1 ? t + h : t;
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    ea[q] = load_sol(P.a, ld, i0 + 2 * q * h);
-    eb[q] = load_sol(P.b, ld, i0 + 2 * q * h);
-    if (pt == 2) {
-      ea[q] = fr_sub(load_sol(P.a, ld, t + h + 2 * q * h), ea[q]);
-      eb[q] = fr_sub(load_sol(P.b, ld, t + h + 2 * q * h), eb[q]);
+    for (int q = 0; q < 2; ++q) {
+      ea[q] = load_sol(P.a, ld, i0 + 2 * q * h);
+      eb[q] = load_sol(P.b, ld, i0 + 2 * q * h);
+      if (pt == 2) {
+        ea[q] = fr_sub(load_sol(P.a, ld, t + h + 2 * q * h), ea[q]);
+        eb[q] = fr_sub(load_sol(P.b, ld, t + h + 2 * q * h), eb[q]);
+      }
     }
-  }
+  };
+  load();
   for (uint32_t i = tid; i < kMatAccWords; i += 3 * kMatSweepPairs) acc[i] = 0;
   __syncthreads();
   if (rd == 1) {
@@ -305,12 +309,22 @@ __global__ void __launch_bounds__(3 * kMatSweepPairs) mat_sweep_kernel(const Rou
   }
   __syncthreads();
   if (!verdict) return;
-  const MatTerm o = mat_term(ea, eb, lds_get(T.r));
-  if (pt < 2) {
-    store_sol(P.a, ld, i0, o.A);
-    store_sol(P.b, ld, i0, o.B);
+  Fr sum = fr_zero();
+#pragma unroll 1
+  for (;;) {
+    const MatTerm o = mat_term(ea, eb, lds_get(T.r));
+    if (pt < 2) {
+      const uint32_t i0 = pt == 1 ? t + h : t;
+      store_sol(P.a, ld, i0, o.A);
+      store_sol(P.b, ld, i0, o.B);
+    }
+    sum = fr_add(sum, o.val);
+    t += kMatSweepPairs;
+    if (t >= end) break;   // the same for all threads
+    load();                // (other pairs than those stored)
+    __syncthreads();       // read by all points before any is stored over
   }
-  acc_add(acc, kMatAccRound + pt, o.val);
+  acc_add(acc, kMatAccRound + pt, sum);
   __syncthreads();
   if (tid < 64) {
     const Fr v = acc_value(acc, kMatAccRound + min(tid, 2u));
@@ -366,6 +380,35 @@ __global__ void __launch_bounds__(kPass1Block) pass1_kernel(const Pass1Job* __re
     // workgroup (release: the partials, and everything the earlier
     // kernels of the stream wrote, are visible to whoever sees the count)
     if (J.ready) __hip_atomic_fetch_add(J.ready, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+// A long round's tables folded by r in place and its sums added to acc, by all
+// threads: the values at 0 and 1 of all pairs t < h, then the leading
+// coefficients from the folded entries (small code: three products).
+__device__ __noinline__ void mat_fold_long(uint32_t* ga, uint32_t* gb, uint64_t ld, uint32_t h, const uint32_t* rp,
+                                           unsigned long long* acc) {
+  const Fr r = lds_get(rp);
+#pragma unroll 1
+  for (uint32_t pt = 0; pt < 3; ++pt) {
+    Fr sum = fr_zero();
+#pragma unroll 1
+    for (uint32_t t = threadIdx.x; t < h; t += kRoundsBlock) {
+      const uint32_t i = pt ? t + h : t, i2 = pt < 2 ? i + 2 * h : t;
+      Fr A = load_sol(ga, ld, i), B = load_sol(gb, ld, i);
+      const Fr dA = fr_sub(load_sol(ga, ld, i2), A), dB = fr_sub(load_sol(gb, ld, i2), B);
+      if (pt < 2) {
+        A = fr_add(A, fr_mul(r, dA));
+        B = fr_add(B, fr_mul(r, dB));
+        store_sol(ga, ld, i, A);
+        store_sol(gb, ld, i, B);
+      } else {
+        A = dA;   // (both differences negated)
+        B = dB;
+      }
+      sum = fr_add(sum, fr_mul(A, B));
+    }
+    acc_add(acc, kMatAccRound + pt, sum);
   }
 }
 
@@ -556,30 +599,7 @@ __global__ void __launch_bounds__(kRoundsBlock) rounds_kernel(const RoundsJob* _
       if (lds) at = at == 0 ? 1 : 0;
       __syncthreads();   // r_rd, round rd + 1's sums, the folded entries
       if (!ahead) {
-        const Fr r = lds_get(rbuf[rd & 1]);
-        // the values at 0 and 1 of all pairs, then the leading coefficients from
-        // the folded entries (small code: three products)
-#pragma unroll 1
-        for (uint32_t pt = 0; pt < 3; ++pt) {
-          Fr sum = fr_zero();
-#pragma unroll 1
-          for (uint32_t t = tid; t < h; t += kRoundsBlock) {
-            const uint32_t i = pt ? t + h : t, i2 = pt < 2 ? i + 2 * h : t;
-            Fr A = load_sol(ga, ld, i), B = load_sol(gb, ld, i);
-            const Fr dA = fr_sub(load_sol(ga, ld, i2), A), dB = fr_sub(load_sol(gb, ld, i2), B);
-            if (pt < 2) {
-              A = fr_add(A, fr_mul(r, dA));
-              B = fr_add(B, fr_mul(r, dB));
-              store_sol(ga, ld, i, A);
-              store_sol(gb, ld, i, B);
-            } else {
-              A = dA;   // (both differences negated)
-              B = dB;
-            }
-            sum = fr_add(sum, fr_mul(A, B));
-          }
-          acc_add(acc, kMatAccRound + pt, sum);
-        }
+        mat_fold_long(ga, gb, ld, h, rbuf[rd & 1], acc);
         __threadfence_block();
         __syncthreads();   // round rd + 1's sums and tables
       }
