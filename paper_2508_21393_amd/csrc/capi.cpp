@@ -675,31 +675,6 @@ void Builder::group(const vl_group& g, const Challenges& ch, uint8_t* proof_dev,
                             : pass1(a, L1, b, L1, 1, true, rj.prods[k].g_nparts, ready);
     rj.ready_target += rj.prods[k].g_nparts;
   }
-  // wide rounds for product 0 while its half-table has >= kMatWidePairs pairs;
-  // not in persistent mode, whose rounds workgroups are resident before the
-  // contractions run
-  const uint32_t n1w = rj.prods[0].n1;
-  if (!T.persistent && n1w >= 2 && (1ull << (n1w - 2)) >= kMatWidePairs) {
-    uint32_t W = 1;
-    while (W < kMatMaxWide && W + 1 < n1w && (1ull << (n1w - 1 - W)) >= kMatWidePairs) ++W;
-    rj.wide = W;
-    rj.io = nullptr;   // a slot of the descriptor blob, set when the blob is filled
-    Segment& G = S();
-    const uint32_t idx = (uint32_t)G.rounds.size();
-    P.n_wide += 1;
-    if (G.wide.size() < W) {
-      G.wide.resize(W);
-      G.wide_blocks.resize(W, 0);
-    }
-    for (uint32_t rd = 0; rd < W; ++rd) {
-      MatSweep m{};
-      m.job = idx;
-      m.block_begin = G.wide_blocks[rd];
-      G.wide[rd].push_back(m);
-      if (rd > 0)
-        G.wide_blocks[rd] += (1u << (n1w - 1 - rd)) / mat_span(1u << (n1w - 1 - rd));
-    }
-  }
   // persistent mode: one resident launch for every group (segment 0's list)
   (T.persistent ? P.seg[0] : S()).rounds.push_back(rj);
 }
@@ -1330,6 +1305,45 @@ static double group_bytes(const vl_group& g) {
   return b;
 }
 
+// Wide rounds of a segment's groups, for product 0 while its half-table has at
+// least `least` pairs: kMatWidePairs, or as many more as it takes for the
+// segment's first sweep to have no more blocks than the GPU has CUs.  Beyond
+// that the groups' own workgroups fill the GPU, and a sweep only repeats the
+// step (100 / 200 groups of 8192 inner entries: 782 / 1193 us wide, 592 / 756 in
+// their workgroups).
+static void wide_rounds(Plan& P, Segment& G) {
+  auto goes_wide = [](const RoundsJob& J, uint32_t least) {
+    return J.prods[0].n1 >= 2 && (1u << (J.prods[0].n1 - 2)) >= least;
+  };
+  uint32_t least = kMatWidePairs;
+  for (;; least *= 2) {
+    uint64_t blocks = 0;
+    for (const RoundsJob& J : G.rounds)
+      if (goes_wide(J, least)) blocks += (1u << (J.prods[0].n1 - 2)) / mat_span(1u << (J.prods[0].n1 - 2));
+    if (blocks <= kMatSweepBlocks) break;
+  }
+  for (uint32_t idx = 0; idx < G.rounds.size(); ++idx) {
+    RoundsJob& J = G.rounds[idx];
+    if (!goes_wide(J, least)) continue;
+    const uint32_t n1 = J.prods[0].n1;
+    uint32_t W = 1;
+    while (W < kMatMaxWide && W + 1 < n1 && (1u << (n1 - 1 - W)) >= least) ++W;
+    J.wide = W;   // (io: a slot of the descriptor blob, set when the blob is filled)
+    P.n_wide += 1;
+    if (G.wide.size() < W) {
+      G.wide.resize(W);
+      G.wide_blocks.resize(W, 0);
+    }
+    for (uint32_t rd = 0; rd < W; ++rd) {
+      MatSweep m{};
+      m.job = idx;
+      m.block_begin = G.wide_blocks[rd];
+      G.wide[rd].push_back(m);
+      if (rd > 0) G.wide_blocks[rd] += (1u << (n1 - 1 - rd)) / mat_span(1u << (n1 - 1 - rd));
+    }
+  }
+}
+
 void plan_groups(Plan& P, const Tuning& T, const vl_group* groups, uint64_t g0, uint64_t g1,
                  uint64_t seed, uint8_t* ws, bool async, uint8_t* proofs_dev, const uint64_t* offsets,
                  int32_t* status_dev, uint8_t* digests_dev, uint8_t* out, const Challenges* given) {
@@ -1419,6 +1433,10 @@ void plan_groups(Plan& P, const Tuning& T, const vl_group* groups, uint64_t g0, 
       build(li);
     }
   }
+  // not in persistent mode, whose rounds workgroups are resident before the
+  // contractions run
+  if (!T.persistent)
+    for (Segment& G : P.seg) wide_rounds(P, G);
   P.data_end = B.off;
 }
 
