@@ -416,7 +416,7 @@ def hyrax_leg(B, reps, seed=4, hidden=4096, ffn=11008):
     ref = [o.cpu() for o in outs]
     # per matrix on one stream (its own time); then the block with the
     # matrices alternating between two streams, so that one matrix's final
-    # kernel (one inversion per 64 rows, a few waves) overlaps the next one's
+    # kernel (a chain of additions and one inversion) overlaps the next one's
     # commit kernel
     per = [[] for _ in mats]
     totals = []

@@ -204,7 +204,7 @@ __device__ __forceinline__ bool bmm_wide_step(const BmmJob& J, uint32_t rd, cons
 // step: every block first takes round rd - 1's transcript step itself, from the
 // previous launch's sums (its first block stores it), so that a round is one
 // launch.  That pays while the launch has no more blocks than CUs
-// (kBmmMergeBlocks): 21 to 26 us instead of 12 and 15.5 for a sweep and a step.
+// (kBmmMergeBlocks): 21 to 30 us instead of 12 and 15.5 for a sweep and a step.
 // Bound by the chain of a thread (four products) and of the step.
 __global__ void __launch_bounds__(3 * kBmmSweepPairs) bmm_sweep_kernel(const BmmJob* __restrict__ jobs,
                                                                        const BmmSweep* __restrict__ list,
@@ -320,14 +320,15 @@ __device__ __forceinline__ Fr bmm_next(const BmmJob& J, const uint32_t* rho, uin
 }
 
 // The rounds left after the wide ones, one workgroup per job, then the final
-// values.  As in the matmul rounds (kernels.hip), waves 1 .. 11 sum round rd +
-// 1 while wave 0 hashes round rd, as quadratics in r_rd, once that has at most
+// values.  As in the matmul rounds (kernels.hip), waves 1 .. 6 sum round rd + 1
+// while wave 0 hashes round rd, as quadratics in r_rd, once that has at most
 // kBmmAhead pairs: it takes up to nine products a pair's value, after the hash
-// at most four, and those of 256 pairs (28 us to 18) would outlast the hash.
-// The first round's sums and the larger ones' come before their hash.  The tables come from global memory until their first
-// fold (at most kBmmLds entries then) and live in LDS after it.  With
-// the pairs' points on one thread and 183 KB of code a round took 30 us, with
-// the sums after the hash 16, now 11.4.
+// at most four, and the sums of 256 pairs would outlast the hash.  The first
+// round's sums and the larger ones' come before their hash.  The tables come
+// from global memory until their first fold (at most kBmmLds entries then) and
+// live in LDS after it.  With the pairs' points on one thread and 183 KB of code
+// a round took 30 us, with the sums after the hash 16, now 11.4 (the last nine
+// rounds and the end of a product 116 to 119 us).
 constexpr uint32_t kBmmTailWaves = 8;
 __global__ void __launch_bounds__(64 * kBmmTailWaves) bmm_rounds_kernel(const BmmJob* __restrict__ jobs) {
   const BmmJob& J = jobs[blockIdx.x];

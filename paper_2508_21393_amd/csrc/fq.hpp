@@ -7,11 +7,11 @@
 //       fffeb153ffffb9feffffffffaaab   (381 bits, q = 3 mod 4)
 // Elements are 12 little-endian 32-bit limbs, in Montgomery form x*R mod q
 // with R = 2^384 inside the library and canonical on the wire.  On the device
-// the Montgomery product is the finely integrated product scanning of fr.hpp
-// with 12 limbs; -q^-1 mod 2^32 = 0xfffcfffd, so the quotient digit of a
-// column is a 32-bit multiply.  The host uses 6 64-bit limbs (the same bytes:
+// the Montgomery product works on 14 limbs of 28 bits in 64-bit columns (Fl
+// below); -q^-1 mod 2^32 = 0xfffcfffd, so the quotient digit of a column is a
+// 32-bit multiply.  The host uses 6 64-bit limbs (the same bytes:
 // little-endian 32-bit limbs pair into 64-bit limbs) with CIOS.  The top limb
-// of q is below 2^29, so every running value fits in the limbs plus one
+// of q is below 2^29, so every running value there fits in the limbs plus one
 // carry word and a product of two reduced values is below 2q.
 //
 // Points of G1 are kept in XYZZ coordinates (X, Y, ZZ, ZZZ) with

@@ -91,8 +91,8 @@ inline __host__ __device__ uint32_t mat_span(uint32_t pairs) {   // pairs per bl
   const uint32_t s = pairs / kMatSweepBlocks;
   return s < kMatSweepPairs ? kMatSweepPairs : s;
 }
-// (a wide round of 512 pairs takes 20 us, in one workgroup about 23; one of
-// 256 there 17 to 19)
+// a group goes wide from this many pairs of its second round on, in calls of few
+// groups (wide_rounds): a wide round takes 18 to 20 us, the first 25 to 31
 constexpr uint32_t kMatWidePairs = 512;
 // rounds of at most this many pairs are summed ahead of their challenge in the
 // rounds workgroup (two products of 4096 inner entries: 415 us with 256 here,
@@ -255,8 +255,9 @@ struct BmmSweep {
 // Rounds bind the high index bits first (only A and Sb depend on them; the
 // rows' terms add a constant per round), then the low bits.  The first `wide`
 // rounds run as GPU-wide sweeps and a one-block transcript step.
-// rounds with at least this many pairs run wide: a wide round of 256 pairs
-// takes about 30 us, in one workgroup 45; one of 128 about 27 there
+// rounds with at least this many pairs run wide: a wide round of 256 pairs takes
+// 26 us with its step, the eight rounds of 128 pairs and fewer in one workgroup
+// 160 to 170 together
 constexpr uint32_t kLookupWidePairs = 256;
 constexpr uint32_t kLookupTailVars = 9;       // log2 of the entries the one-workgroup rounds start from, at most
 constexpr uint32_t kLookupLowPairs = 64;       // pairs per block of a low round's sweep
@@ -404,8 +405,8 @@ hipError_t launch_lookup_rounds(const LookupJob* jobs_dev, uint32_t n_jobs, hipS
 // Hyrax: generators and fixed-base tables of windows W for m generators;
 // commitments of R rows of an int16/int32/int64 matrix in n_split column
 // slices of chunk columns (partials: R n_split XYZZ points)
-// slices of a row that one wave sums (two per lane), and the most slices the
-// final kernel takes without a pass of runs before it; the runs' sums take
+// slices of a row that one wave sums (eight per quad of lanes), and the most
+// slices the final kernel takes without a pass of runs before it; the runs' sums take
 // R ceil(n_split / kHyraxRun) points behind the slices
 constexpr uint32_t kHyraxRun = 128, kHyraxMaxFinal = 256;
 hipError_t launch_hyrax_setup(uint32_t m, uint32_t W, uint32_t* table, hipStream_t s);

@@ -235,9 +235,9 @@ __device__ __forceinline__ void mat_round(const unsigned long long* acc, uint32_
 // waits for another and a round is one launch; only the job's first block
 // stores proof bytes and io.  Then each thread folds by r_{rd-1} and takes the
 // product at one point of a pair; the entries are loaded before the step.
-// Bound by the step (about 13 us of 20, 28 the first); with the sums by lane
-// shuffles, the squeeze and the statement on one lane it was 30 us, 43 the
-// first.  256 pairs per block: 22 us.
+// Bound by the step (about 13 us of 18; the first sweep 25 to 31); with the sums
+// by lane shuffles, the squeeze and the statement on one lane it was 30 us, 43
+// the first.  256 pairs per block: 22 us.
 __global__ void __launch_bounds__(3 * kMatSweepPairs) mat_sweep_kernel(const RoundsJob* __restrict__ jobs,
                                                                        const MatSweep* __restrict__ list,
                                                                        uint32_t n_list, uint32_t n_blocks,

@@ -268,8 +268,8 @@ __device__ __forceinline__ uint32_t lk_find(Get begin_of, uint32_t n, uint32_t b
 // columns, whose second value differs from the table's) sets the job's flag.
 // Tables of up to 2^kLookupLdsVars rows: a block of 1024 threads counts
 // J.hist_chunk entries (below 2^16) in 16-bit counters in LDS and writes them
-// to its slice of J.hist; the multiplicity kernel adds the slices.  (One
-// global atomic per entry: 8.4 M activations took 400 us, this 40 us.)
+// to its slice of J.hist; the multiplicity kernel adds the slices.  (One global
+// atomic per entry: 8.4 M activations took 400 us, this 61 beside the tables.)
 // Larger tables: 32-bit global atomics on J.hist, zeroed before.
 __global__ void __launch_bounds__(1024) lookup_hist_kernel(const LookupJob* __restrict__ jobs, uint32_t n_jobs,
                                                            uint32_t n_blocks) {
@@ -462,8 +462,8 @@ __global__ void __launch_bounds__(64) lookup_start_kernel(const LookupJob* __res
 //   kSecond   round 1: the four entries looked up, folded by r_0 and stored
 //   kFold     later rounds: folded in place (each thread reads and writes
 //             only its own entries): 9 products a pair (262 and 149 us for the
-//             largest kSecond and kFold sweeps of 2^23 entries with 10, now 243 and
-//             145)
+//             largest kSecond and kFold sweeps of 2^23 entries with 10, now 245 and
+//             143)
 //   kPlain    round 0 of stored tables
 enum { kFirst = 0, kSecond = 1, kFold = 2, kPlain = 3 };
 template <int MODE>

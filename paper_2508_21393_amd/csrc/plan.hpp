@@ -77,7 +77,7 @@ struct Plan {
   std::vector<EqJob> eq;
   uint32_t eq_blocks = 0;
   std::vector<Segment> seg;
-  std::vector<std::vector<uint32_t>> points;  // per eq job: (x_j, 1 - x_j) Montgomery
+  std::vector<std::vector<uint32_t>> points;  // per eq job: x_j, Montgomery
   std::vector<const uint32_t*> point_dev;     // per eq job: a point already in device memory, or null
   uint32_t n_err = 0;
   uint32_t n_wide = 0;            // groups with wide rounds (one io slot each in the blob)

@@ -1,5 +1,6 @@
-// Device helpers of the sumcheck kernels (kernels.hip, bmm.hip): wave and
-// workgroup sums of field elements, proof-byte stores, LDS element access.
+// Device helpers of the sumcheck kernels (kernels.hip, bmm.hip, lookup.hip): wave
+// and workgroup sums of field elements, proof-byte stores, LDS element access,
+// the transcript's hashing.
 #pragma once
 #include "device.hpp"
 #include "sha256.hpp"
