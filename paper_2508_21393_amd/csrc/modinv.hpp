@@ -66,12 +66,13 @@ VL_HD void divsteps30(int32_t& delta, uint32_t f, uint32_t g, int32_t (&t)[4]) {
 // quotient short: first M towards zero for d and for e (by their signs neg_d,
 // neg_e), which takes values in [-3 M / 2, 3 M / 2] into [-M, M], then a
 // centred multiple in [-2^29, 2^29).  As |u| + |v| <= 2^30, the quotient is in
-// [-3 M / 2, 3 M / 2] again.  low: limb 0 of u d + v e.
+// [-3 M / 2, 3 M / 2] again; the multiple is below 3 2^29.  low: limb 0 of
+// u d + v e.
 template <typename Mod>
-VL_HD int64_t modinv_multiple(int32_t u, int32_t v, bool neg_d, bool neg_e, uint32_t low) {
+VL_HD int32_t modinv_multiple(int32_t u, int32_t v, bool neg_d, bool neg_e, uint32_t low) {
   const int32_t back = (neg_d ? u : -u) + (neg_e ? v : -v);   // at most 2^30
   low += (uint32_t)back * Mod::limb(0);
-  return (int64_t)back + ((int32_t)((0u - low * Mod::inv30) << 2) >> 2);
+  return back + ((int32_t)((0u - low * Mod::inv30) << 2) >> 2);
 }
 
 // A batch's matrix applied to f, g (divided by 2^30, exactly for the batch's own
